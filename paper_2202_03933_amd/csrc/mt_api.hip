@@ -88,6 +88,11 @@ KParams kparams(const mt_params& p) {
   k.dual = p.lm_basis == MT_BASIS_DUAL ? 1 : 0;
   k.rule = p.rule;
   k.elem = p.element_rule;
+  // the closed form is exact to a few units of rounding: it stands for
+  // Newton's method where that would be run to convergence (the default step
+  // limit or more, no tolerance below the default); tighter limits and
+  // tolerances keep the iteration and its non-convergence report
+  k.direct = p.newton_maxit >= 30 && p.newton_tol >= 1e-14 ? 1 : 0;
   return k;
 }
 

@@ -34,19 +34,6 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
   return x;
 }
 
-// Inverse bilinear map of p on one quad by Newton's method from xi = 0 (the
-// first step from the precomputed Jacobian at 0); at most maxit steps.
-__device__ __forceinline__ void inverse1(const QMap& B, double pu, double pv, double tol, int maxit, double& b1,
-                                         double& b2, unsigned& noconv) {
-#pragma clang fp contract(fast)
-  const double dbu = pu - B.cu, dbv = pv - B.cv;
-  b1 = (B.e2v * dbu - B.e2u * dbv) * B.r0;
-  b2 = (B.e1u * dbv - B.e1v * dbu) * B.r0;
-  bool cb = false;
-  for (int it = 1; it < maxit && !cb; ++it) newton_step(B, dbu, dbv, tol, b1, b2, cb);
-  noconv += cb ? 0u : 1u;
-}
-
 // Rule point of the auxiliary plane at (x1, x2): the bilinear map of the
 // projected slave quad in monomial form ((c + e1 x1) + e2 x2) + f (x1 x2),
 // evaluated in this order without fused multiply-add (P decides which
@@ -129,7 +116,8 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
   const int64_t p = base + threadIdx.x;
   const bool valid = p < n_pairs;
   const int s = valid ? pair_s[p] : 0;
-  QMap ms, mm;
+  QMap ms;
+  IMap mm;
   V2 Mo[4];
   if (valid) {
     double Xs[4][3], f[12];
@@ -140,7 +128,7 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
     slave_setup(Xs, f, Sp, hs, As, hmax);
     ms = qmap(Sp);
     master_quad(M, pair_m[p], f, Mo, Mn);
-    mm = qmap(Mn);
+    mm = imap(Mn);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       sq[2 * k][threadIdx.x] = Mo[k].u;
@@ -160,11 +148,11 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
       d1 = ms.e1u * ms.fv - ms.fu * ms.e1v;
       d2 = ms.fu * ms.e2v - ms.e2u * ms.fv;
     }
-    double mu[9], Mm[16];
+    double mu[9], Mx[12];
 #pragma unroll
     for (int k = 0; k < 9; ++k) mu[k] = 0.0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) Mm[k] = 0.0;
+    for (int k = 0; k < 12; ++k) Mx[k] = 0.0;
     const int ng = kp.elem, nq = ng * ng;
     // points inside the own master (a loop uniform over the wave)
     unsigned long long mine = 0ull;
@@ -203,7 +191,7 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
       if (earlier) continue;
       double y1, y2;
-      inverse1(mm, P.u, P.v, kp.newton_tol, kp.newton_maxit, y1, y2, noconv);
+      inverse1(mm, P.u, P.v, kp, y1, y2, noconv);
       {
 #pragma clang fp contract(fast)
         const double wJ = (sw[a] * sw[b]) * (d0 + d1 * x1 + d2 * x2);
@@ -220,10 +208,9 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
         const double y12 = y1 * y2;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          Mm[4 * r] += t[r];
-          Mm[4 * r + 1] += t[r] * y1;
-          Mm[4 * r + 2] += t[r] * y2;
-          Mm[4 * r + 3] += t[r] * y12;
+          Mx[3 * r] += t[r] * y1;
+          Mx[3 * r + 1] += t[r] * y2;
+          Mx[3 * r + 2] += t[r] * y12;
         }
       }
     }
@@ -240,7 +227,7 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
       V2 S2[4], M2[4];
       double hs[4], hm[4];
       pair_project(Xs2, Xm2, f2, S2, M2, hs, hm);
-      moments_to_blocks<DUAL>(qmap(S2), mu, Mm, hs, hm, D, Mv, g);
+      moments_to_blocks<DUAL>(S2, mu, Mx, hs, hm, D, Mv, g);
     }
 #pragma unroll
     for (int k = 0; k < 16; ++k) blk[(int64_t)k * stride + p] = D[k];

@@ -475,39 +475,6 @@ __device__ __forceinline__ void shape4(double x1, double x2, double N[4]) {
   N[3] = 0.25 * a0 * b1;
 }
 
-// Inverse of the bilinear map xi -> sum_k N_k(xi) X_k by Newton's method
-// from xi = 0; stops when max |dxi| <= tol.  Returns false when it did not
-// converge in maxit iterations.  The map is written as
-// x(xi) = c + e1 xi1 + e2 xi2 + e12 xi1 xi2.
-__device__ __forceinline__ bool inverse_bilinear(const V2 X[4], double pu, double pv, double tol, int maxit,
-                                                 double& x1, double& x2) {
-#pragma clang fp contract(fast)
-  const double cu = 0.25 * ((X[0].u + X[1].u) + (X[2].u + X[3].u));
-  const double cv = 0.25 * ((X[0].v + X[1].v) + (X[2].v + X[3].v));
-  const double e1u = 0.25 * ((X[1].u - X[0].u) + (X[2].u - X[3].u));
-  const double e1v = 0.25 * ((X[1].v - X[0].v) + (X[2].v - X[3].v));
-  const double e2u = 0.25 * ((X[2].u - X[1].u) + (X[3].u - X[0].u));
-  const double e2v = 0.25 * ((X[2].v - X[1].v) + (X[3].v - X[0].v));
-  const double fu = 0.25 * ((X[0].u - X[1].u) + (X[2].u - X[3].u));
-  const double fv = 0.25 * ((X[0].v - X[1].v) + (X[2].v - X[3].v));
-  x1 = 0.0;
-  x2 = 0.0;
-  const double ru0 = cu - pu, rv0 = cv - pv;
-  for (int it = 0; it < maxit; ++it) {
-    const double ru = ru0 + e1u * x1 + e2u * x2 + fu * x1 * x2;
-    const double rv = rv0 + e1v * x1 + e2v * x2 + fv * x1 * x2;
-    const double j00 = e1u + fu * x2, j01 = e2u + fu * x1;
-    const double j10 = e1v + fv * x2, j11 = e2v + fv * x1;
-    const double rdet = 1.0 / (j00 * j11 - j01 * j10);
-    const double s1 = (j11 * ru - j01 * rv) * rdet;
-    const double s2 = (j00 * rv - j10 * ru) * rdet;
-    x1 -= s1;
-    x2 -= s2;
-    if (fmax(fabs(s1), fabs(s2)) <= tol) return true;
-  }
-  return false;
-}
-
 // Dual basis coefficients A = De Me^-1 of one slave element from its
 // projected nodes (2x2 Gauss; De = diag int N_j, Me = int N N^T).
 __device__ __forceinline__ void dual_coefficients(const V2 S[4], double A[16]) {

@@ -130,6 +130,7 @@ struct KParams {
   int32_t dual;
   int32_t rule;
   int32_t elem;  // 0: segment-based integration; n: element-based, n x n Gauss points
+  int32_t direct;  // inverse maps in closed form (else Newton's method throughout)
 };
 
 }  // namespace mt
