@@ -68,6 +68,7 @@ __global__ __launch_bounds__(BSC) __attribute__((amdgpu_waves_per_eu(2))) void k
                                                    const double* __restrict__ W_D, const double* __restrict__ W_M,
                                                    const double* __restrict__ w_g, double* __restrict__ gpair,
                                                    double* __restrict__ gn0, int64_t stride, Counters* cnt) {
+  __shared__ double stash[BWD_STASH * BSC];
   const int64_t n_pairs = *n_dev;
   const int64_t tile = dyn_tile(blockIdx.x, n_pairs, BSC);
   if (tile < 0) return;
@@ -79,8 +80,8 @@ __global__ __launch_bounds__(BSC) __attribute__((amdgpu_waves_per_eu(2))) void k
     double WD[16], WM[16], wg[4];
     gather_weights(s, p, csn, posD, n_s, posM, stride, W_D, W_M, w_g, WD, WM, wg);
     double Xsb[4][3], Xmb[4][3], n0b[3];
-    pair_backward<NQ, DUAL, NODAL>(S, s, csn, M, load_conn(M.conn, pair_m[p]), gpoly(poly, p), gpoly_nf(poly, p), kp, WD, WM, wg,
-                            Xsb, Xmb, n0b, noconv);
+    pair_backward<NQ, DUAL, NODAL>(S, s, csn, M, load_conn(M.conn, pair_m[p]), gpoly(poly, p), gpoly_nf(poly, p), kp,
+                                   Stash{stash + threadIdx.x, BSC}, WD, WM, wg, Xsb, Xmb, n0b, noconv);
     if (NODAL)
 #pragma unroll
       for (int d = 0; d < 3; ++d) {

@@ -129,6 +129,7 @@ template <int BSZ, int NQ, bool DUAL>
 __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(3))) void k_batch_fwd(const BatchInst* __restrict__ inst,
                                                     const WorkItem* __restrict__ items,
                                                     const int32_t* __restrict__ qbeg, int32_t* qnext, Counters* cnt) {
+  __shared__ double stash[FWD_STASH * BSZ];
   unsigned noconv = 0;
   int qi = 0;
   for (int it = next_item(qbeg, qnext, qi); it >= 0; it = next_item(qbeg, qnext, qi)) {
@@ -138,7 +139,7 @@ __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(3))) void k
       double D[16], Mv[16], g[4];
       const int s = I.pair_s[p];
       pair_forward<NQ, DUAL>(I.S, s, load_conn(I.S.conn, s), I.M, load_conn(I.M.conn, I.pair_m[p]),
-                             gpoly(I.poly, p), gpoly_nf(I.poly, p), I.kp, D, Mv, g, noconv);
+                             gpoly(I.poly, p), gpoly_nf(I.poly, p), I.kp, Stash{stash + threadIdx.x, BSZ}, D, Mv, g, noconv);
       const int64_t st = I.stride;
 #pragma unroll
       for (int k = 0; k < 16; ++k) I.blk[(int64_t)k * st + p] = D[k];
@@ -191,6 +192,7 @@ template <int BSZ, int NQ, bool DUAL, bool NODAL>
 __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(2))) void k_batch_bwd(const BatchInst* __restrict__ inst,
                                                     const WorkItem* __restrict__ items,
                                                     const int32_t* __restrict__ qbeg, int32_t* qnext, Counters* cnt) {
+  __shared__ double stash[BWD_STASH * BSZ];
   unsigned noconv = 0;
   int qi = 0;
   for (int it = next_item(qbeg, qnext, qi); it >= 0; it = next_item(qbeg, qnext, qi)) {
@@ -204,7 +206,8 @@ __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(2))) void k
       batch_weights(I, s, csn, p, WD, WM, wg);
       double Xsb[4][3], Xmb[4][3], n0b[3];
       pair_backward<NQ, DUAL, NODAL>(I.S, s, csn, I.M, load_conn(I.M.conn, I.pair_m[p]), gpoly(I.poly, p),
-                                     gpoly_nf(I.poly, p), I.kp, WD, WM, wg, Xsb, Xmb, n0b, noconv);
+                                     gpoly_nf(I.poly, p), I.kp, Stash{stash + threadIdx.x, BSZ}, WD, WM, wg, Xsb, Xmb, n0b,
+                                     noconv);
       if (NODAL)
 #pragma unroll
         for (int d = 0; d < 3; ++d) {

@@ -79,11 +79,10 @@ __device__ __forceinline__ bool in_edges(const V2 Mo[4], V2 P) {
   return in;
 }
 
-// Oriented (counter-clockwise) projected master quad of master element m on
-// the slave plane f; Mn keeps the node order.
-__device__ __forceinline__ void master_quad(const MeshPtrs& M, int m, const double f[12], V2 Mo[4], V2 Mn[4]) {
-  double Xm[4][3], hm[4];
-  load_nodes(M.x, M.y, M.z, load_conn(M.conn, m), Xm);
+// Oriented (counter-clockwise) projected master quad on the slave plane f.
+__device__ __forceinline__ void master_quad(const double Xm[4][3], const double f[12], V2 Mo[4]) {
+  V2 Mn[4];
+  double hm[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) project(Xm[k], f, Mn[k], hm[k]);
   const bool flip = quad_fan_area(Mn) < 0.0;
@@ -105,6 +104,8 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
     double* __restrict__ blk, int64_t stride, Counters* cnt) {
   __shared__ double sq[8][BSE];
   __shared__ double sg[8], sw[8];
+  __shared__ double stash[15 * BSE];  // heights' coefficients and slave map, for the blocks
+  const Stash st{stash + threadIdx.x, BSE};
   const int64_t n_pairs = *n_dev;
   const int64_t tile = dyn_tile(blockIdx.x, n_pairs, BSE);
   if (tile < 0) return;  // the whole block
@@ -119,16 +120,27 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
   QMap ms;
   IMap mm;
   V2 Mo[4];
+  double ou = 0.0, ov = 0.0;
   if (valid) {
-    double Xs[4][3], f[12];
+    double Xs[4][3], Xm[4][3], f[12];
     load_nodes(S.x, S.y, S.z, load_conn(S.conn, s), Xs);
+    load_nodes(M.x, M.y, M.z, load_conn(M.conn, pair_m[p]), Xm);
     slave_frame_p(Xs, elem_nrm(S, s), f);
-    V2 Sp[4], Mn[4];
+    V2 Sp[4];
     double hs[4], As, hmax;
     slave_setup(Xs, f, Sp, hs, As, hmax);
     ms = qmap(Sp);
-    master_quad(M, pair_m[p], f, Mo, Mn);
-    mm = imap(Mn);
+    master_quad(Xm, f, Mo);
+    double R[3][3], hc[3], hm[4];
+    SMap sm;
+    pair_setup(Xs, Xm, elem_nrm(S, s), R, sm, mm, hc, hm, ou, ov);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) st[k] = hc[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) st[3 + k] = hm[k];
+    const double sv[8] = {sm.e1u, sm.e1v, sm.e2u, sm.e2v, sm.fu, sm.fv, sm.a2, sm.j0};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) st[7 + k] = sv[k];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       sq[2 * k][threadIdx.x] = Mo[k].u;
@@ -180,18 +192,18 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
           for (int k = 0; k < 4; ++k) Eo[k] = V2{sq[2 * k][t], sq[2 * k + 1][t]};
         } else {
           // earlier pair outside the block: its quad from reloaded nodes
-          double Xs2[4][3], f2[12];
+          double Xs2[4][3], Xm2[4][3], f2[12];
           const int s2 = launder(s);
           load_nodes(S.x, S.y, S.z, load_conn(S.conn, s2), Xs2);
           slave_frame_p(Xs2, elem_nrm(S, s2), f2);
-          V2 En[4];
-          master_quad(M, pair_m[pp], f2, Eo, En);
+          load_nodes(M.x, M.y, M.z, load_conn(M.conn, pair_m[pp]), Xm2);
+          master_quad(Xm2, f2, Eo);
         }
         earlier = in_box(oquad(Eo), P) && in_edges(Eo, P);
       }
       if (earlier) continue;
       double y1, y2;
-      inverse1(mm, P.u, P.v, kp, y1, y2, noconv);
+      inverse1(mm, P.u - ou, P.v - ov, kp, y1, y2, noconv);
       {
 #pragma clang fp contract(fast)
         const double wJ = (sw[a] * sw[b]) * (d0 + d1 * x1 + d2 * x2);
@@ -214,20 +226,12 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
         }
       }
     }
-    // heights from reloaded nodes rather than kept through the loop
     double D[16], Mv[16], g[4];
     {
-      const int s2 = launder(s);
-      const int4 cs = load_conn(S.conn, s2);
-      const int4 cm = load_conn(M.conn, launder(pair_m[p]));
-      double Xs2[4][3], Xm2[4][3], f2[12];
-      load_nodes(S.x, S.y, S.z, cs, Xs2);
-      load_nodes(M.x, M.y, M.z, cm, Xm2);
-      slave_frame_p(Xs2, elem_nrm(S, s2), f2);
-      V2 S2[4], M2[4];
-      double hs[4], hm[4];
-      pair_project(Xs2, Xm2, f2, S2, M2, hs, hm);
-      moments_to_blocks<DUAL>(S2, mu, Mx, hs, hm, D, Mv, g);
+      const Stash sb = st.back();
+      const double hc[3] = {sb[0], sb[1], sb[2]}, hm[4] = {sb[3], sb[4], sb[5], sb[6]};
+      const SMap sm{sb[7], sb[8], sb[9], sb[10], sb[11], sb[12], sb[13], sb[14]};
+      moments_to_blocks<DUAL>(sm, mu, Mx, hc, hm, D, Mv, g);
     }
 #pragma unroll
     for (int k = 0; k < 16; ++k) blk[(int64_t)k * stride + p] = D[k];

@@ -91,16 +91,6 @@ __device__ __forceinline__ int store_pair_polygon(const double Xs[4][3], const d
   return st | (n >= 3 ? 0 : PS_LOST);
 }
 
-// Projected nodes and heights of both elements on the slave plane f.
-__device__ __forceinline__ void pair_project(const double Xs[4][3], const double Xm[4][3], const double f[12],
-                                             V2 S[4], V2 Mn[4], double hs[4], double hm[4]) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    project(Xs[k], f, S[k], hs[k]);
-    project(Xm[k], f, Mn[k], hm[k]);
-  }
-}
-
 // ---- monomial basis helpers ------------------------------------------------------
 
 // y = H x
@@ -214,26 +204,13 @@ struct IMap {
   double j0;                                  // J0
 };
 
-__device__ __forceinline__ IMap imap(const V2 X[4]) {
-#pragma clang fp contract(fast)
-  const QMap q = qmap(X);
-  const double r = 2.0 * q.r0;
-  IMap m;
-  m.cu = q.cu;
-  m.cv = q.cv;
-  m.e1u = q.e1u * r;
-  m.e1v = q.e1v * r;
-  m.e2u = q.e2u * r;
-  m.e2v = q.e2v * r;
-  m.fu = q.fu * r;
-  m.fv = q.fv * r;
-  m.a2 = q.e1u * m.fv - q.e1v * m.fu;
-  m.j0 = q.e1u * q.e2v - q.e2u * q.e1v;
-  return m;
-}
+// The slave quad's map, with its centre as the origin (c = 0).
+struct SMap {
+  double e1u, e1v, e2u, e2v, fu, fv, a2, j0;
+};
 
 // Node k of a quad from its scaled map.
-__device__ __forceinline__ V2 imap_node(const IMap& m, int k) {
+__device__ __forceinline__ V2 map_node(const IMap& m, int k) {
 #pragma clang fp contract(fast)
   const double h = 0.5 * m.j0;
   const double h1 = (k == 1 || k == 2) ? h : -h;
@@ -241,14 +218,18 @@ __device__ __forceinline__ V2 imap_node(const IMap& m, int k) {
   const double h12 = (k & 1) ? -h : h;
   return V2{m.cu + h1 * m.e1u + h2 * m.e2u + h12 * m.fu, m.cv + h1 * m.e1v + h2 * m.e2v + h12 * m.fv};
 }
+__device__ __forceinline__ IMap widen(const SMap& m) {
+  return IMap{0.0, 0.0, m.e1u, m.e1v, m.e2u, m.e2v, m.fu, m.fv, m.a2, m.j0};
+}
 
 // The scalars of one point's two quadratic equations (t1, t2 doubled).
 struct IPoint {
   double t1, t2, b1, b2;
 };
 
-__device__ __forceinline__ IPoint ipoint(const IMap& m, double du, double dv) {
+__device__ __forceinline__ IPoint ipoint(const IMap& m, double pu, double pv) {
 #pragma clang fp contract(fast)
+  const double du = pu - m.cu, dv = pv - m.cv;
   IPoint p;
   p.t1 = du * m.e2v - dv * m.e2u;
   p.t2 = dv * m.e1u - du * m.e1v;
@@ -257,11 +238,22 @@ __device__ __forceinline__ IPoint ipoint(const IMap& m, double du, double dv) {
   p.b2 = 1.0 + 0.5 * q;
   return p;
 }
+__device__ __forceinline__ IPoint ipoint(const SMap& m, double pu, double pv) {
+#pragma clang fp contract(fast)
+  IPoint p;
+  p.t1 = pu * m.e2v - pv * m.e2u;
+  p.t2 = pv * m.e1u - pu * m.e1v;
+  const double q = pu * m.fv - pv * m.fu;
+  p.b1 = 1.0 - 0.5 * q;
+  p.b2 = 1.0 + 0.5 * q;
+  return p;
+}
 
 // Newton's method from xi = 0 on the same scalars: at most maxit steps, the
 // first with the Jacobian at 0; stops once the next step is at most tol in
 // both components, tested without the division.  rd = J0 / det J.
-__device__ __forceinline__ void inverse_newton(const IMap& m, const IPoint& p, double tol, int maxit, double& x1,
+template <class Map>
+__device__ __forceinline__ void inverse_newton(const Map& m, const IPoint& p, double tol, int maxit, double& x1,
                                                double& x2, double& rd, unsigned& noconv) {
 #pragma clang fp contract(fast)
   const double al = 0.5 * m.a2, be = 0.25 * m.j0 * (m.e2u * m.fv - m.e2v * m.fu);
@@ -319,11 +311,11 @@ constexpr double INV_MIN = 0x1p-10;
 // 0.95 -> 0.76 ms; 64 batched interfaces (13M pairs): forward and backward
 // 9.35 -> 6.79 ms.  Newton's method for tighter settings and for points near
 // a fold of the map.  Maps that do not converge are counted in noconv.
-__device__ __forceinline__ void inverse2(const IMap& A, const IMap& B, double pu, double pv, const KParams& kp,
+__device__ __forceinline__ void inverse2(const SMap& A, const IMap& B, double pu, double pv, const KParams& kp,
                                          double& a1, double& a2, double& b1, double& b2, double& rda, double& rdb,
                                          unsigned& noconv) {
 #pragma clang fp contract(fast)
-  const IPoint pa = ipoint(A, pu - A.cu, pv - A.cv), pb = ipoint(B, pu - B.cu, pv - B.cv);
+  const IPoint pa = ipoint(A, pu, pv), pb = ipoint(B, pu, pv);
   const double sa = pa.b1 * pa.b1 + A.a2 * pa.t1, sb = pb.b1 * pb.b1 + B.a2 * pb.t1;
   double da, db;
   sqrt_rsqrt(sa, da, rda);
@@ -347,7 +339,7 @@ __device__ __forceinline__ void inverse2(const IMap& A, const IMap& B, double pu
 __device__ __forceinline__ void inverse1(const IMap& B, double pu, double pv, const KParams& kp, double& b1,
                                          double& b2, unsigned& noconv) {
 #pragma clang fp contract(fast)
-  const IPoint pb = ipoint(B, pu - B.cu, pv - B.cv);
+  const IPoint pb = ipoint(B, pu, pv);
   const double sb = pb.b1 * pb.b1 + B.a2 * pb.t1;
   double db, rdb;
   sqrt_rsqrt(sb, db, rdb);
@@ -360,16 +352,152 @@ __device__ __forceinline__ void inverse1(const IMap& B, double pu, double pv, co
     inverse_newton(B, pb, kp.newton_tol, kp.newton_maxit, b1, b2, rdb, noconv);
 }
 
+// ---- plane and maps of one pair ---------------------------------------------------
+// The axes are the search's, evaluated in its order: the stored polygons are
+// in them, at small elements far from the origin its g1 and g2 (sums of
+// coordinates) are rounded well above an element's own rounding, and the
+// heights of distant surfaces feel a tilt of the normal.  The lengths and
+// quotients come from a refined reciprocal square root instead of IEEE
+// square roots and divisions (about 60 instructions against 200), and each
+// quad is projected through its four map coefficients.
+
+// a = v / |v|: the reciprocal square root's root and each quotient corrected
+// by its residual (the rounded values of the IEEE operations, up to rare ties).
+__device__ __forceinline__ void unit3(const double v[3], double a[3]) {
+  const double q = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
+  double l, rl;
+  sqrt_rsqrt(q, l, rl);
+  l = fma(fma(-l, l, q), 0.5 * rl, l);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double t = v[d] * rl;
+    a[d] = fma(fma(-t, l, v[d]), rl, t);
+  }
+}
+
+// The axes R = (t1, t2, n0) of the slave plane; ns: the plane normal of the
+// continuous field, else null.
+__device__ __forceinline__ void plane_axes(const double X[4][3], const double* ns, double R[3][3]) {
+  double g1[3], g2[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    g1[d] = 0.25 * (((X[1][d] - X[0][d]) + X[2][d]) - X[3][d]);
+    g2[d] = 0.25 * (((X[2][d] + X[3][d]) - X[0][d]) - X[1][d]);
+  }
+  if (ns) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) R[2][d] = ns[d];
+    const double gn = (g1[0] * ns[0] + g1[1] * ns[1]) + g1[2] * ns[2];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) g1[d] = g1[d] - gn * ns[d];
+  } else {
+    const double n[3] = {g1[1] * g2[2] - g1[2] * g2[1], g1[2] * g2[0] - g1[0] * g2[2], g1[0] * g2[1] - g1[1] * g2[0]};
+    unit3(n, R[2]);
+  }
+  unit3(g1, R[0]);
+  R[1][0] = R[2][1] * R[0][2] - R[2][2] * R[0][1];
+  R[1][1] = R[2][2] * R[0][0] - R[2][0] * R[0][2];
+  R[1][2] = R[2][0] * R[0][1] - R[2][1] * R[0][0];
+}
+
+// Map coefficients (c, e1, e2, f) of a quad in space, relative to the point
+// o.  The nodes are taken relative to it first: these differences are exact
+// to rounding of an element's size, sums of the coordinates are not.
+__device__ __forceinline__ void coefficients(const double X[4][3], const double o[3], double C[4][3]) {
+#pragma clang fp contract(fast)
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double x0 = X[0][d] - o[d], x1 = X[1][d] - o[d], x2 = X[2][d] - o[d], x3 = X[3][d] - o[d];
+    C[0][d] = 0.25 * ((x0 + x1) + (x2 + x3));
+    C[1][d] = 0.25 * ((x1 - x0) + (x2 - x3));
+    C[2][d] = 0.25 * ((x2 - x1) + (x3 - x0));
+    C[3][d] = 0.25 * ((x0 - x1) + (x2 - x3));
+  }
+}
+
+__device__ __forceinline__ double dot3(const double a[3], const double b[3]) {
+#pragma clang fp contract(fast)
+  return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+}
+// The slave plane's axes R = (t1, t2, n0), the maps of the projected quads
+// and the heights' coefficients (slave: of e1, e2, f; its centre has height
+// 0).  ns: the plane normal of the continuous field, else null.  The stored
+// polygons are relative to the rounded centre x0 of the search; the maps are
+// relative to the centre itself, (ou, ov) in the polygons' coordinates.
+__device__ __forceinline__ void pair_setup(const double Xs[4][3], const double Xm[4][3], const double* ns,
+                                           double R[3][3], SMap& ms, IMap& mm, double hs[3], double hm[4], double& ou,
+                                           double& ov) {
+#pragma clang fp contract(fast)
+  double C[4][3], B[4][3], x0[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) x0[d] = 0.25 * (((Xs[0][d] + Xs[1][d]) + Xs[2][d]) + Xs[3][d]);
+  coefficients(Xs, x0, C);
+  coefficients(Xm, x0, B);
+  plane_axes(Xs, ns, R);
+  {
+    const double e1u = dot3(C[1], R[0]), e1v = dot3(C[1], R[1]), e2u = dot3(C[2], R[0]), e2v = dot3(C[2], R[1]);
+    const double fu = dot3(C[3], R[0]), fv = dot3(C[3], R[1]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) hs[k] = dot3(C[k + 1], R[2]);
+    ms.j0 = e1u * e2v - e2u * e1v;
+    const double r = 2.0 * rcp3(ms.j0);
+    ms.e1u = e1u * r;
+    ms.e1v = e1v * r;
+    ms.e2u = e2u * r;
+    ms.e2v = e2v * r;
+    ms.fu = fu * r;
+    ms.fv = fv * r;
+    ms.a2 = e1u * ms.fv - e1v * ms.fu;
+  }
+  ou = dot3(C[0], R[0]);
+  ov = dot3(C[0], R[1]);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) B[0][d] -= C[0][d];
+  double u[4], v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    u[k] = dot3(B[k], R[0]);
+    v[k] = dot3(B[k], R[1]);
+    hm[k] = dot3(B[k], R[2]);
+  }
+  mm.cu = u[0];
+  mm.cv = v[0];
+  mm.j0 = u[1] * v[2] - u[2] * v[1];
+  const double r = 2.0 * rcp3(mm.j0);
+  mm.e1u = u[1] * r;
+  mm.e1v = v[1] * r;
+  mm.e2u = u[2] * r;
+  mm.e2v = v[2] * r;
+  mm.fu = u[3] * r;
+  mm.fv = v[3] * r;
+  mm.a2 = u[1] * mm.fv - v[1] * mm.fu;
+}
+
+// Values a lane needs again after the quadrature, kept in LDS meanwhile
+// instead of in registers (or instead of gathering the nodes and rebuilding
+// the plane a second time, about 600 instructions of the reverse sweep's
+// 5,100); lane-interleaved, no bank conflicts.
+struct Stash {
+  double* p;
+  int stride;
+  __device__ __forceinline__ double& operator[](int i) const { return p[i * stride]; }
+  // for reading back: the laundered offset keeps the compiler from holding
+  // the stored values in registers after all
+  __device__ __forceinline__ Stash back() const { return Stash{p + launder(0), stride}; }
+};
+constexpr int FWD_STASH = 7;   // heights' coefficients
+constexpr int BWD_STASH = 16;  // the same and R
+
 // ---- forward -------------------------------------------------------------------
 // Blocks from the monomial moments of a quadrature: mu_ij = sum w xi1^i
 // xi2^j (i, j <= 2) and Mm[p][r] = sum w m_p(xi) m_r(eta) (Mx: its columns
-// r = 1..3; column 0 is mu's first four), with the projected slave nodes and
-// the nodal heights: D = C Dm C^T (Dm[p][r] the moment of m_p m_r), M = C Mm C^T,
-// g = C (Mm ht_m - Dm ht_s), ht = C^T h; for the dual basis Phi = A N:
-// D, M, g <- A D, A M, A g.
+// r = 1..3; column 0 is mu's first four), with the slave map (its nodes, for
+// the dual basis) and the heights' coefficients ht:
+// D = C Dm C^T (Dm[p][r] the moment of m_p m_r), M = C Mm C^T,
+// g = C (Mm ht_m - Dm ht_s); for the dual basis Phi = A N: D, M, g <- A D, A M, A g.
 template <bool DUAL>
-__device__ __forceinline__ void moments_to_blocks(const V2 S[4], const double mu[9], const double Mx[12],
-                                                  const double hs[4], const double hm[4], double D[16],
+__device__ __forceinline__ void moments_to_blocks(const SMap& ms, const double mu[9], const double Mx[12],
+                                                  const double hs[3], const double hm[4], double D[16],
                                                   double M[16], double g[4]) {
 #pragma clang fp contract(fast)
   // Dm[p][r]: monomial exponents (0,0), (1,0), (0,1), (1,1) added
@@ -377,21 +505,19 @@ __device__ __forceinline__ void moments_to_blocks(const V2 S[4], const double mu
                          mu[2], mu[3], mu[5], mu[7], mu[3], mu[6], mu[7], mu[8]};
   const double Mm[16] = {mu[0], Mx[0], Mx[1], Mx[2], mu[1], Mx[3], Mx[4], Mx[5],
                          mu[2], Mx[6], Mx[7], Mx[8], mu[3], Mx[9], Mx[10], Mx[11]};
-  double hts[4], htm[4];
-  ht_apply(hs, hts);
-  ht_apply(hm, htm);
   double gm[4];
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    gm[p] = 0.25 * ((Mm[4 * p] * htm[0] + Mm[4 * p + 1] * htm[1] + Mm[4 * p + 2] * htm[2] + Mm[4 * p + 3] * htm[3]) -
-                    (Dm[4 * p] * hts[0] + Dm[4 * p + 1] * hts[1] + Dm[4 * p + 2] * hts[2] + Dm[4 * p + 3] * hts[3]));
-  }
+  for (int p = 0; p < 4; ++p)
+    gm[p] = (Mm[4 * p] * hm[0] + Mm[4 * p + 1] * hm[1] + Mm[4 * p + 2] * hm[2] + Mm[4 * p + 3] * hm[3]) -
+            (Dm[4 * p + 1] * hs[0] + Dm[4 * p + 2] * hs[1] + Dm[4 * p + 3] * hs[2]);
   double gs[4];
   h_apply(gm, gs);
   double Ds[16], Ms[16];
   h_sandwich(Dm, 0.0625, Ds);
   h_sandwich(Mm, 0.0625, Ms);
   if (DUAL) {
+    const IMap w = widen(ms);
+    const V2 S[4] = {map_node(w, 0), map_node(w, 1), map_node(w, 2), map_node(w, 3)};
     double A[16];
     dual_coefficients(S, A);
 #pragma unroll
@@ -414,29 +540,56 @@ __device__ __forceinline__ void moments_to_blocks(const V2 S[4], const double mu
   }
 }
 
-// Local blocks of one pair from its stored polygon (n vertices):
+// Local blocks of pair p of slave element s from its stored polygon
+// (nf = count | flip << 7):
 //   D[j][k] = sum w A_t Phi_j N_k(xi),  M[j][l] = sum w A_t Phi_j N_l(eta),
 //   g[j]    = sum w A_t Phi_j (sum_l N_l(eta) hm_l - sum_k N_k(xi) hs_k),
-// over the fan triangles from vertex 0 and the rule points.  Accumulates the
-// moments mu_ij = sum w A_t xi1^i xi2^j (i, j <= 2) and
-// Mm[p][r] = sum w A_t m_p(xi) m_r(eta); then D = C Dm C^T (Dm[p][r] the
-// moment of m_p m_r), M = C Mm C^T, g = C (Mm ht_m - Dm ht_s) with
-// ht = C^T h, and for the dual basis Phi = A N: D, M, g <- A D, A M, A g.
-template <int NQ, bool DUAL, class Heights>
-__device__ __forceinline__ void pair_integrate(const IMap& ms, const IMap& mm, const Heights& heights,
-                                               const GPoly& P, int n, const KParams& kp, double D[16], double M[16],
-                                               double g[4], unsigned& noconv) {
+// over the fan triangles from vertex 0 and the rule points, through the
+// moments (moments_to_blocks).  The vertex of the next triangle is loaded
+// before the points of this one.
+template <int NQ, bool DUAL>
+__device__ __forceinline__ void pair_forward(const MeshPtrs& SM, int s, int4 cs, const MeshPtrs& MM, int4 cm,
+                                             const GPoly& P, int nf, const KParams& kp, const Stash& st,
+                                             double D[16], double M[16], double g[4], unsigned& noconv) {
+  const int n = nf & 0x7f;
+  if (n < 3) {
+    // no segment (a pair lost after a coordinate update): no contribution, and
+    // no dual coefficients of a possibly degenerate slave element
+#pragma unroll
+    for (int k = 0; k < 16; ++k) D[k] = M[k] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) g[k] = 0.0;
+    return;
+  }
+  SMap ms;
+  IMap mm;
+  double ou, ov;
+  {
+    double Xs[4][3], Xm[4][3], R[3][3], hs[3], hm[4];
+    load_nodes(SM.x, SM.y, SM.z, cs, Xs);
+    load_nodes(MM.x, MM.y, MM.z, cm, Xm);
+    pair_setup(Xs, Xm, elem_nrm(SM, s), R, ms, mm, hs, hm, ou, ov);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) st[k] = hs[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) st[3 + k] = hm[k];
+  }
   double mu[9], Mx[12];
 #pragma unroll
   for (int k = 0; k < 9; ++k) mu[k] = 0.0;
 #pragma unroll
   for (int k = 0; k < 12; ++k) Mx[k] = 0.0;
-  if (n >= 3) {
+  {
 #pragma clang fp contract(fast)
-    const double u0 = P.U(0), v0 = P.V(0);
-    double u1 = P.U(1) - u0, v1 = P.V(1) - v0;
+    const double u0 = P.U(0) - ou, v0 = P.V(0) - ov;
+    double u1 = P.U(1) - ou - u0, v1 = P.V(1) - ov - v0;
+    double un = P.U(2), vn = P.V(2);
     for (int i = 1; i + 1 < n; ++i) {
-      const double u2 = P.U(i + 1) - u0, v2 = P.V(i + 1) - v0;
+      const double u2 = un - ou - u0, v2 = vn - ov - v0;
+      if (i + 2 < n) {
+        un = P.U(i + 2);
+        vn = P.V(i + 2);
+      }
       const double At = 0.5 * (u1 * v2 - v1 * u2);
 #pragma unroll 1
       for (int q = 0; q < NQ; ++q) {
@@ -466,107 +619,123 @@ __device__ __forceinline__ void pair_integrate(const IMap& ms, const IMap& mm, c
       v1 = v2;
     }
   }
-  if (n < 3) {
-    // no segment (a pair lost after a coordinate update): no contribution, and
-    // no dual coefficients of a possibly degenerate slave element
-#pragma unroll
-    for (int k = 0; k < 16; ++k) D[k] = M[k] = 0.0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) g[k] = 0.0;
-    return;
-  }
-  V2 S[4];
-  double hs[4], hm[4];
-  heights(S, hs, hm);
-  moments_to_blocks<DUAL>(S, mu, Mx, hs, hm, D, M, g);
+  const Stash sb = st.back();
+  const double hs[3] = {sb[0], sb[1], sb[2]}, hm[4] = {sb[3], sb[4], sb[5], sb[6]};
+  moments_to_blocks<DUAL>(ms, mu, Mx, hs, hm, D, M, g);
 }
 
 // ---- backward ------------------------------------------------------------------
 
-// Adjoint of the intersection X of line A (A1 -> A2) and line B (B1 -> B2):
-// X = A1 + s (A2 - A1), s = cross(B1 - A1, dB) / cross(dA, dB).  Parallel
-// lines (no defined intersection) contribute nothing.
-__device__ __forceinline__ void intersect_adjoint(V2 A1, V2 A2, V2 B1, V2 B2, double xu, double xv, V2& a1, V2& a2,
-                                                  V2& b1, V2& b2) {
+// The line of edge k (node k to node k + 1) of a quad, in the parameters of
+// its map: direction D (scaled as the map), a point M0 on it, and the
+// parameter that is constant along it, sg = -1 or 1 (xi2 on even edges, xi1
+// on odd ones).
+struct EdgeLine {
+  double du, dv, mu, mv, sg;
+  bool odd;
+};
+
+__device__ __forceinline__ EdgeLine edge_line(const IMap& m, int k) {
 #pragma clang fp contract(fast)
-  const double dAu = A2.u - A1.u, dAv = A2.v - A1.v;
-  const double dBu = B2.u - B1.u, dBv = B2.v - B1.v;
-  const double wu = B1.u - A1.u, wv = B1.v - A1.v;
-  const double den = dAu * dBv - dAv * dBu;
-  const double scale = (fabs(dAu) + fabs(dAv)) * (fabs(dBu) + fabs(dBv));
-  a1 = a2 = b1 = b2 = V2{0.0, 0.0};
-  if (!(fabs(den) > 1e-14 * scale)) return;
-  const double rden = rcp_nr(den);
-  const double num = wu * dBv - wv * dBu;
-  const double s = num * rden;
-  double dAbu = s * xu, dAbv = s * xv;
-  const double sb = xu * dAu + xv * dAv;
-  const double numb = sb * rden;
-  const double denb = -numb * s;
-  const double wbu = numb * dBv, wbv = -numb * dBu;
-  double dBbu = -numb * wv, dBbv = numb * wu;
-  dAbu += denb * dBv;
-  dAbv += -denb * dBu;
-  dBbu += -denb * dAv;
-  dBbv += denb * dAu;
-  b1.u = wbu - dBbu;
-  b1.v = wbv - dBbv;
-  a1.u = xu - wbu - dAbu;
-  a1.v = xv - wbv - dAbv;
-  a2.u = dAbu;
-  a2.v = dAbv;
-  b2.u = dBbu;
-  b2.v = dBbv;
+  EdgeLine e;
+  e.odd = k & 1;
+  e.sg = (k == 1 || k == 2) ? 1.0 : -1.0;
+  const double h = 0.5 * m.j0 * e.sg;
+  e.du = (e.odd ? m.e2u : m.e1u) + e.sg * m.fu;
+  e.dv = (e.odd ? m.e2v : m.e1v) + e.sg * m.fv;
+  e.mu = m.cu + h * (e.odd ? m.e1u : m.e2u);
+  e.mv = m.cv + h * (e.odd ? m.e1v : m.e2v);
+  return e;
 }
 
-// Adjoint of node k of a quad, added in map-coefficient form:
-// (c, e1, e2, f)-bar += H[k][.] d (the node adjoint is then C times it).
-__device__ __forceinline__ void add_node_adj(double cb[8], int k, double du, double dv) {
+// Adjoint (xu, xv) of the intersection X of edge lines A and B.  X moves with
+// line A's normal displacement at X and with line B's: with normals nA, nB,
+// (xu, xv) = pA + pB, pA along nA and pB along nB, acts on the points of the
+// two lines at X, i.e. on the maps at the parameters xa, xb of X there.
+// Parallel lines (no defined intersection) contribute nothing.
+__device__ __forceinline__ void cross_adjoint(const EdgeLine& A, double ja, const EdgeLine& B, double jb, double X,
+                                              double Y, double xu, double xv, double xa[2], double pa[2],
+                                              double xb[2], double pb[2]) {
 #pragma clang fp contract(fast)
-  const double s1 = (k == 1 || k == 2) ? 1.0 : -1.0;
-  const double s2 = k >= 2 ? 1.0 : -1.0;
-  const double s12 = s1 * s2;
-  cb[0] += du;
-  cb[1] += dv;
-  cb[2] += s1 * du;
-  cb[3] += s1 * dv;
-  cb[4] += s2 * du;
-  cb[5] += s2 * dv;
-  cb[6] += s12 * du;
-  cb[7] += s12 * dv;
+  const double den = A.du * B.dv - A.dv * B.du;
+  const double scale = (fabs(A.du) + fabs(A.dv)) * (fabs(B.du) + fabs(B.dv));
+  const bool ok = fabs(den) > 1e-14 * scale;
+  const double rden = ok ? rcp3(den) : 0.0;
+  const double al = (xu * B.du + xv * B.dv) * rden, be = -(xu * A.du + xv * A.dv) * rden;
+  pa[0] = -al * A.dv;
+  pa[1] = al * A.du;
+  pb[0] = -be * B.dv;
+  pb[1] = be * B.du;
+  // X = M0 + t (J0 / 2) D on each line: t along the line itself, so that it
+  // is as accurate on nearly parallel lines
+  const double la = 0.5 * ja * (A.du * A.du + A.dv * A.dv), lb = 0.5 * jb * (B.du * B.du + B.dv * B.dv);
+  const double r = rcp3(la * lb);
+  const double ta = ((X - A.mu) * A.du + (Y - A.mv) * A.dv) * (r * lb);
+  const double tb = ((X - B.mu) * B.du + (Y - B.mv) * B.dv) * (r * la);
+  xa[0] = A.odd ? A.sg : ta;
+  xa[1] = A.odd ? ta : A.sg;
+  xb[0] = B.odd ? B.sg : tb;
+  xb[1] = B.odd ? tb : B.sg;
 }
 
-// Pull the adjoint (xu, xv) of one clip vertex back to the projected nodes
-// through its provenance: a slave node directly; otherwise the intersection
-// of its two lines (the second always a master clip edge).  Master clip edge
-// l runs Mo[l] -> Mo[l+1] with Mo[j] = Mn[(4 - j) % 4] when flipped.
-__device__ __forceinline__ void vertex_adjoint(uint8_t lab, double xu, double xv, const IMap& ms, const IMap& mm,
-                                               bool flip, double cbs[8], double cbm[8]) {
+// Pull the adjoint (xu, xv) of clip vertex (X, Y) back to the coefficients
+// of the two maps through its provenance: a slave node; a master node (two
+// neighbouring master edges meet there); otherwise the intersection of two
+// edge lines.  Clip edge l of a flipped master is its edge 3 - l.  The
+// adjoint of a map's point at x adds m(x) times it to (c, e1, e2, f)-bar
+// (the slave's c-bar is not needed: its plane moves with it).
+__device__ __forceinline__ void vertex_adjoint(uint8_t lab, double X, double Y, double xu, double xv, const SMap& ms,
+                                               const IMap& mm, bool flip, double cbs[6], double cbm[8]) {
+#pragma clang fp contract(fast)
+  double xa[2], pa[2] = {0.0, 0.0}, xb[2] = {0.0, 0.0}, pb[2] = {0.0, 0.0};
+  const int la = lab >> 4, lb = flip ? 3 - (lab & 3) : lab & 3;
   if (lab & 0x80) {
-    add_node_adj(cbs, lab & 3, xu, xv);
-    return;
-  }
-  const int la = lab >> 4, lb = lab & 15;
-  const bool ma = la >= 4;
-  const int la4 = la & 3, lb4 = lb & 3;
-  const int ia0 = ma && flip ? (4 - la4) & 3 : la4;
-  const int ia1 = ma && flip ? (3 - la4) & 3 : (la4 + 1) & 3;
-  const int ib0 = flip ? (4 - lb4) & 3 : lb4;
-  const int ib1 = flip ? (3 - lb4) & 3 : (lb4 + 1) & 3;
-  const IMap& mA = ma ? mm : ms;
-  const V2 A1 = imap_node(mA, ia0), A2 = imap_node(mA, ia1);
-  const V2 B1 = imap_node(mm, ib0), B2 = imap_node(mm, ib1);
-  V2 a1, a2, b1, b2;
-  intersect_adjoint(A1, A2, B1, B2, xu, xv, a1, a2, b1, b2);
-  if (ma) {
-    add_node_adj(cbm, ia0, a1.u, a1.v);
-    add_node_adj(cbm, ia1, a2.u, a2.v);
+    const int k = lab & 3;
+    xa[0] = (k == 1 || k == 2) ? 1.0 : -1.0;
+    xa[1] = k >= 2 ? 1.0 : -1.0;
+    pa[0] = xu;
+    pa[1] = xv;
+  } else if (la < 4) {
+    cross_adjoint(edge_line(widen(ms), la), ms.j0, edge_line(mm, lb), mm.j0, X, Y, xu, xv, xa, pa, xb, pb);
   } else {
-    add_node_adj(cbs, ia0, a1.u, a1.v);
-    add_node_adj(cbs, ia1, a2.u, a2.v);
+    const int ka = flip ? 3 - (la & 3) : la & 3;
+    xa[0] = xa[1] = 0.0;
+    if (((ka ^ lb) & 1) == 0) {
+      // opposite master edges
+      double x2[2], p2[2];
+      cross_adjoint(edge_line(mm, ka), mm.j0, edge_line(mm, lb), mm.j0, X, Y, xu, xv, x2, p2, xb, pb);
+      const double x12 = x2[0] * x2[1];
+      cbm[0] += p2[0];
+      cbm[1] += p2[1];
+      cbm[2] += x2[0] * p2[0];
+      cbm[3] += x2[0] * p2[1];
+      cbm[4] += x2[1] * p2[0];
+      cbm[5] += x2[1] * p2[1];
+      cbm[6] += x12 * p2[0];
+      cbm[7] += x12 * p2[1];
+    } else {
+      const int k = lb == ((ka + 1) & 3) ? lb : ka;
+      xb[0] = (k == 1 || k == 2) ? 1.0 : -1.0;
+      xb[1] = k >= 2 ? 1.0 : -1.0;
+      pb[0] = xu;
+      pb[1] = xv;
+    }
   }
-  add_node_adj(cbm, ib0, b1.u, b1.v);
-  add_node_adj(cbm, ib1, b2.u, b2.v);
+  const double xa12 = xa[0] * xa[1], xb12 = xb[0] * xb[1];
+  cbs[0] += xa[0] * pa[0];
+  cbs[1] += xa[0] * pa[1];
+  cbs[2] += xa[1] * pa[0];
+  cbs[3] += xa[1] * pa[1];
+  cbs[4] += xa12 * pa[0];
+  cbs[5] += xa12 * pa[1];
+  cbm[0] += pb[0];
+  cbm[1] += pb[1];
+  cbm[2] += xb[0] * pb[0];
+  cbm[3] += xb[0] * pb[1];
+  cbm[4] += xb[1] * pb[0];
+  cbm[5] += xb[1] * pb[1];
+  cbm[6] += xb12 * pb[0];
+  cbm[7] += xb12 * pb[1];
 }
 
 // Adjoint of the projection (u, v, h) = ((X - x0).t1, (X - x0).t2,
@@ -676,35 +845,65 @@ __device__ __forceinline__ void projection_adjoint(const double Xs[4][3], const 
 // the stored polygon (nf = count | flip << 7).  Per rule point the
 // integrand is F = 1/2 ma^T Q ma + ma^T W mb (ma = m(xi), mb = m(eta)), with
 // Q = C^T (WD + WD^T) C - (wt ht_s^T + ht_s wt^T), W = C^T WM C + wt ht_m^T,
-// wt = C^T wg, ht = C^T h; reverse mode runs through the quadrature, the
-// inverse maps (implicit-function derivative), the clip vertices (line
-// intersections, each vertex once: the fan's pending vertex is carried to the
-// next triangle), the projection and the slave frame.
+// wt = C^T wg, ht the heights' coefficients; reverse mode runs through the
+// quadrature, the inverse maps (implicit-function derivative), the clip
+// vertices (line intersections, each vertex once: the fan's pending vertex is
+// carried to the next triangle) to the coefficients (u, v, height) of the two
+// maps in the plane's axes R = (t1, t2, n0), and from there to the nodes:
+//  - a rotation of the axes by the small vector w (components along t1, t2,
+//    n0) turns every coefficient p into p - w x p, so wb = -sum p x pb;
+//  - element normals: w follows g1 = (a, 0, 0), g2 = (b, c, 0) (components in
+//    R): wz = dg1_v / a, wy = -dg1_h / a, wx = (dg2_h - dg1_h b / a) / c;
+//    continuous field: wy = dn_u, wx = -dn_v, wz = (dg1_v - g1_h dn_v) / a
+//    with the plane normal n, whose gradient is n0b (along n it is left out:
+//    n is normalised);
+//  - the maps' origin is the slave's centre.
+// a, b, c are the slave map's: 2 / a = e2v, 2 / c = e1u, 2 b / (a c) = e2u.
+// Bound by VALU issue and, at two waves per SIMD (256 registers), by the
+// latency of its gathers.  The coefficient form of the vertex and axes
+// adjoints (two map points per vertex, one 3-vector per pair) against four
+// line end points and nine axis components took it from 0.76 to 0.57 ms on
+// the wavy interface of 3.24M pairs, the forward from 0.38 to 0.31 ms.
 template <int NQ, bool DUAL, bool NODAL = false>
 __device__ __forceinline__ void pair_backward(const MeshPtrs& SM, int s, int4 cs, const MeshPtrs& MM, int4 cm,
-                                              const GPoly& P, int nf, const KParams& kp, const double WD_in[16],
-                                              const double WM_in[16], const double wg_in[4], double Xsb[4][3],
-                                              double Xmb[4][3], double n0b[3], unsigned& noconv) {
+                                              const GPoly& P, int nf, const KParams& kp, const Stash& st,
+                                              const double WD_in[16], const double WM_in[16], const double wg_in[4],
+                                              double Xsb[4][3], double Xmb[4][3], double n0b[3], unsigned& noconv) {
   const int n = nf & 0x7f;
   const bool flip = (nf & 0x80) != 0;
-  IMap ms, mm;
-  double Qs[10], W[16], wt[4];
+  if (n < 3) {  // no segment (a pair lost after a coordinate update)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) Xsb[k][d] = Xmb[k][d] = 0.0;
+      n0b[d] = 0.0;
+    }
+    return;
+  }
+  SMap ms;
+  IMap mm;
+  double Qs[10], W[16], wt[4], ou, ov;
   {
 #pragma clang fp contract(fast)
-    double Xs[4][3], Xm[4][3], f[12];
+    double Xs[4][3], Xm[4][3], R[3][3], hs[3], hm[4];
     load_nodes(SM.x, SM.y, SM.z, cs, Xs);
     load_nodes(MM.x, MM.y, MM.z, cm, Xm);
-    slave_frame_p(Xs, NODAL ? elem_nrm(SM, s) : nullptr, f);
-    V2 S[4], Mn[4];
-    double hs[4], hm[4];
-    pair_project(Xs, Xm, f, S, Mn, hs, hm);
-    ms = imap(S);
-    mm = imap(Mn);
+    pair_setup(Xs, Xm, NODAL ? elem_nrm(SM, s) : nullptr, R, ms, mm, hs, hm, ou, ov);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      st[k] = hs[k];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) st[7 + 3 * k + d] = R[k][d];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) st[3 + k] = hm[k];
     // dual basis: the blocks are A times the standard ones, so the standard
     // sweep runs on the weights A^T W (the dependence of A on the slave
     // nodes is added by dual_adjoint)
     double WD[16], WM[16], wg[4];
     if (DUAL) {
+      const IMap w = widen(ms);
+      const V2 S[4] = {map_node(w, 0), map_node(w, 1), map_node(w, 2), map_node(w, 3)};
       double A[16];
       dual_coefficients(S, A);
 #pragma unroll
@@ -725,16 +924,9 @@ __device__ __forceinline__ void pair_backward(const MeshPtrs& SM, int s, int4 cs
 #pragma unroll
       for (int k = 0; k < 4; ++k) wg[k] = wg_in[k];
     }
-    double hts[4], htm[4];
-    ht_apply(hs, hts);
-    ht_apply(hm, htm);
     ht_apply(wg, wt);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      hts[k] *= 0.25;
-      htm[k] *= 0.25;
-      wt[k] *= 0.25;
-    }
+    for (int k = 0; k < 4; ++k) wt[k] *= 0.25;
     double WDs[16], Q[16];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -742,6 +934,7 @@ __device__ __forceinline__ void pair_backward(const MeshPtrs& SM, int s, int4 cs
       for (int k = 0; k < 4; ++k) WDs[4 * j + k] = WD[4 * j + k] + WD[4 * k + j];
     ht_sandwich(WDs, 0.0625, Q);
     ht_sandwich(WM, 0.0625, W);
+    const double hts[4] = {0.0, hs[0], hs[1], hs[2]};
     int z = 0;
 #pragma unroll
     for (int p = 0; p < 4; ++p)
@@ -750,38 +943,41 @@ __device__ __forceinline__ void pair_backward(const MeshPtrs& SM, int s, int4 cs
 #pragma unroll
     for (int p = 0; p < 4; ++p)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) W[4 * p + r] += wt[p] * htm[r];
+      for (int r = 0; r < 4; ++r) W[4 * p + r] += wt[p] * hm[r];
   }
   // Qs: q00 q01 q02 q03 q11 q12 q13 q22 q23 q33
-  double cbs[8], cbm[8], htsb[4], htmb[4];
+  // adjoints of the maps' coefficients: cbs of the slave's (e1, e2, f), cbm
+  // of the master's (c, e1, e2, f), hsb and hmb of their heights
+  double cbs[6], cbm[8], hsb[3], hmb[4];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    cbs[k] = 0.0;
-    cbm[k] = 0.0;
-  }
+  for (int k = 0; k < 6; ++k) cbs[k] = 0.0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    htsb[k] = 0.0;
-    htmb[k] = 0.0;
-  }
-  if (n >= 3) {
+  for (int k = 0; k < 8; ++k) cbm[k] = 0.0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) hsb[k] = 0.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) hmb[k] = 0.0;
+  {
 #pragma clang fp contract(fast)
-    const double u0 = P.U(0), v0 = P.V(0);
-    double u1 = P.U(1), v1 = P.V(1);
+    const double u0 = P.U(0) - ou, v0 = P.V(0) - ov;
+    double u1 = P.U(1) - ou - u0, v1 = P.V(1) - ov - v0;
+    double un = P.U(2), vn = P.V(2);
     double x0bu = 0.0, x0bv = 0.0, pendu = 0.0, pendv = 0.0;
     for (int i = 1; i + 1 < n; ++i) {
-      const double u2 = P.U(i + 1), v2 = P.V(i + 1);
-      const double At = 0.5 * ((u1 - u0) * (v2 - v0) - (v1 - v0) * (u2 - u0));
+      const double u2 = un - ou - u0, v2 = vn - ov - v0;
+      if (i + 2 < n) {
+        un = P.U(i + 2);
+        vn = P.V(i + 2);
+      }
+      const double At = 0.5 * (u1 * v2 - v1 * u2);
       double Atb = 0.0;
-      double pb0u = 0.0, pb0v = 0.0, pb1u = 0.0, pb1v = 0.0, pb2u = 0.0, pb2v = 0.0;
+      double pb1u = 0.0, pb1v = 0.0, pb2u = 0.0, pb2v = 0.0;
 #pragma unroll 1
       for (int q = 0; q < NQ; ++q) {
         double l0, l1, l2, w;
         rule_point<NQ>(q, l0, l1, l2, w);
-        const double pu = l0 * u0 + l1 * u1 + l2 * u2;
-        const double pv = l0 * v0 + l1 * v1 + l2 * v2;
         double a1, a2, b1, b2, rda, rdb;
-        inverse2(ms, mm, pu, pv, kp, a1, a2, b1, b2, rda, rdb, noconv);
+        inverse2(ms, mm, u0 + l1 * u1 + l2 * u2, v0 + l1 * v1 + l2 * v2, kp, a1, a2, b1, b2, rda, rdb, noconv);
         const double a12 = a1 * a2, b12 = b1 * b2;
         const double qa0 = Qs[0] + Qs[1] * a1 + Qs[2] * a2 + Qs[3] * a12;
         const double qa1 = Qs[1] + Qs[4] * a1 + Qs[5] * a2 + Qs[6] * a12;
@@ -799,33 +995,29 @@ __device__ __forceinline__ void pair_backward(const MeshPtrs& SM, int s, int4 cs
         const double wA = w * At;
         Atb += w * F;
         const double ga3 = qa3 + wb3;
-        const double xa1 = wA * ((qa1 + wb1) + a2 * ga3), xa2 = wA * ((qa2 + wb2) + a1 * ga3);
-        const double xb1 = wA * (wa1 + b2 * wa3), xb2 = wA * (wa2 + b1 * wa3);
-        const double wAG = wA * G;
-        htsb[0] -= wAG;
-        htsb[1] -= wAG * a1;
-        htsb[2] -= wAG * a2;
-        htsb[3] -= wAG * a12;
-        htmb[0] += wAG;
-        htmb[1] += wAG * b1;
-        htmb[2] += wAG * b2;
-        htmb[3] += wAG * b12;
         // implicit-function adjoint: lambda = J^-T xibar at the solution (the
         // scaled Jacobian times J0 / (2 det J))
-        const double ra = 0.5 * rda, rb = 0.5 * rdb;
-        const double ya1 = xa1 * ra, ya2 = xa2 * ra, yb1 = xb1 * rb, yb2 = xb2 * rb;
+        const double ra = 0.5 * wA * rda, rb = 0.5 * wA * rdb;
+        const double ya1 = ra * ((qa1 + wb1) + a2 * ga3), ya2 = ra * ((qa2 + wb2) + a1 * ga3);
+        const double yb1 = rb * (wa1 + b2 * wa3), yb2 = rb * (wa2 + b1 * wa3);
         const double lau = (ms.e2v + ms.fv * a1) * ya1 - (ms.e1v + ms.fv * a2) * ya2;
         const double lav = (ms.e1u + ms.fu * a2) * ya2 - (ms.e2u + ms.fu * a1) * ya1;
         const double lbu = (mm.e2v + mm.fv * b1) * yb1 - (mm.e1v + mm.fv * b2) * yb2;
         const double lbv = (mm.e1u + mm.fu * b2) * yb2 - (mm.e2u + mm.fu * b1) * yb1;
-        cbs[0] -= lau;
-        cbs[1] -= lav;
-        cbs[2] -= a1 * lau;
-        cbs[3] -= a1 * lav;
-        cbs[4] -= a2 * lau;
-        cbs[5] -= a2 * lav;
-        cbs[6] -= a12 * lau;
-        cbs[7] -= a12 * lav;
+        const double wAG = wA * G;
+        hsb[0] -= wAG * a1;
+        hsb[1] -= wAG * a2;
+        hsb[2] -= wAG * a12;
+        hmb[0] += wAG;
+        hmb[1] += wAG * b1;
+        hmb[2] += wAG * b2;
+        hmb[3] += wAG * b12;
+        cbs[0] -= a1 * lau;
+        cbs[1] -= a1 * lav;
+        cbs[2] -= a2 * lau;
+        cbs[3] -= a2 * lav;
+        cbs[4] -= a12 * lau;
+        cbs[5] -= a12 * lav;
         cbm[0] -= lbu;
         cbm[1] -= lbv;
         cbm[2] -= b1 * lbu;
@@ -835,8 +1027,8 @@ __device__ __forceinline__ void pair_backward(const MeshPtrs& SM, int s, int4 cs
         cbm[6] -= b12 * lbu;
         cbm[7] -= b12 * lbv;
         const double pbu = lau + lbu, pbv = lav + lbv;
-        pb0u += l0 * pbu;
-        pb0v += l0 * pbv;
+        x0bu += l0 * pbu;
+        x0bv += l0 * pbv;
         pb1u += l1 * pbu;
         pb1v += l1 * pbv;
         pb2u += l2 * pbu;
@@ -844,93 +1036,68 @@ __device__ __forceinline__ void pair_backward(const MeshPtrs& SM, int s, int4 cs
       }
       // triangle area, then vertex i is complete
       const double hA = 0.5 * Atb;
-      x0bu += pb0u + hA * (v1 - v2);
-      x0bv += pb0v + hA * (u2 - u1);
-      vertex_adjoint(P.L(i), pendu + pb1u + hA * (v2 - v0), pendv + pb1v - hA * (u2 - u0), ms, mm, flip, cbs, cbm);
-      pendu = pb2u - hA * (v1 - v0);
-      pendv = pb2v + hA * (u1 - u0);
+      x0bu += hA * (v1 - v2);
+      x0bv += hA * (u2 - u1);
+      vertex_adjoint(P.L(i), u0 + u1, v0 + v1, pendu + pb1u + hA * v2, pendv + pb1v - hA * u2, ms, mm, flip, cbs, cbm);
+      pendu = pb2u - hA * v1;
+      pendv = pb2v + hA * u1;
       u1 = u2;
       v1 = v2;
     }
-    vertex_adjoint(P.L(n - 1), pendu, pendv, ms, mm, flip, cbs, cbm);
-    vertex_adjoint(P.L(0), x0bu, x0bv, ms, mm, flip, cbs, cbm);
+    vertex_adjoint(P.L(n - 1), u0 + u1, v0 + v1, pendu, pendv, ms, mm, flip, cbs, cbm);
+    vertex_adjoint(P.L(0), u0, v0, x0bu, x0bv, ms, mm, flip, cbs, cbm);
   }
-
-  // node adjoints: Xbar = C (coefficient adjoint), hbar = C htbar (the 1/4
-  // of C is applied in projection_adjoint)
   {
-    double nb[8][3];
-    {
-      const double cu[4] = {cbs[0], cbs[2], cbs[4], cbs[6]}, cv[4] = {cbs[1], cbs[3], cbs[5], cbs[7]};
-      double u[4], v[4], h[4];
-      h_apply(cu, u);
-      h_apply(cv, v);
-      h_apply(htsb, h);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        nb[k][0] = 0.25 * u[k];
-        nb[k][1] = 0.25 * v[k];
-        nb[k][2] = 0.25 * h[k];
-      }
+#pragma clang fp contract(fast)
+    const Stash back = st.back();
+    // adjoints of the coefficients, components (t1, t2, n0)
+    double Sb[4][3] = {{0, 0, 0}, {cbs[0], cbs[1], hsb[0]}, {cbs[2], cbs[3], hsb[1]}, {cbs[4], cbs[5], hsb[2]}};
+    const double Mb[4][3] = {{cbm[0], cbm[1], hmb[0]}, {cbm[2], cbm[3], hmb[1]}, {cbm[4], cbm[5], hmb[2]},
+                             {cbm[6], cbm[7], hmb[3]}};
+    double wx = 0.0, wy = 0.0, wz = 0.0;  // minus the sum of p x pb
+    auto add = [&](double u, double v, double h, const double b[3]) {
+      wx -= v * b[2] - h * b[1];
+      wy -= h * b[0] - u * b[2];
+      wz -= u * b[1] - v * b[0];
+    };
+    const double js = 0.5 * ms.j0, jm = 0.5 * mm.j0;
+    add(js * ms.e1u, js * ms.e1v, back[0], Sb[1]);
+    add(js * ms.e2u, js * ms.e2v, back[1], Sb[2]);
+    add(js * ms.fu, js * ms.fv, back[2], Sb[3]);
+    add(mm.cu, mm.cv, back[3], Mb[0]);
+    add(jm * mm.e1u, jm * mm.e1v, back[4], Mb[1]);
+    add(jm * mm.e2u, jm * mm.e2v, back[5], Mb[2]);
+    add(jm * mm.fu, jm * mm.fv, back[6], Mb[3]);
+    const double ra = 0.5 * ms.e2v;  // 1 / a
+    Sb[1][1] += wz * ra;
+    double nu = 0.0, nv = 0.0;
+    if (NODAL) {
+      nu = wy;
+      nv = -wx - wz * ra * back[0];
+    } else {
+      Sb[1][2] -= wy * ra + wx * (0.5 * ms.e2u);
+      Sb[2][2] += wx * (0.5 * ms.e1u);
     }
-    {
-      const double cu[4] = {cbm[0], cbm[2], cbm[4], cbm[6]}, cv[4] = {cbm[1], cbm[3], cbm[5], cbm[7]};
-      double u[4], v[4], h[4];
-      h_apply(cu, u);
-      h_apply(cv, v);
-      h_apply(htmb, h);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        nb[4 + k][0] = 0.25 * u[k];
-        nb[4 + k][1] = 0.25 * v[k];
-        nb[4 + k][2] = 0.25 * h[k];
-      }
+    for (int k = 0; k < 3; ++k) Sb[0][k] = -Mb[0][k];
+    // to space, coefficients to nodes (C = H / 4)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const double r0 = back[7 + d], r1 = back[10 + d], r2 = back[13 + d];
+      double c[4], x[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c[k] = 0.25 * (Sb[k][0] * r0 + Sb[k][1] * r1 + Sb[k][2] * r2);
+      h_apply(c, x);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) Xsb[k][d] = x[k];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c[k] = 0.25 * (Mb[k][0] * r0 + Mb[k][1] * r1 + Mb[k][2] * r2);
+      h_apply(c, x);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) Xmb[k][d] = x[k];
+      n0b[d] = NODAL ? nu * r0 + nv * r1 : 0.0;
     }
-    // on reloaded nodes and a recomputed frame
-    const int4 cs2{launder(cs.x), launder(cs.y), launder(cs.z), launder(cs.w)};
-    const int4 cm2{launder(cm.x), launder(cm.y), launder(cm.z), launder(cm.w)};
-    double Xs[4][3], Xm[4][3];
-    load_nodes(SM.x, SM.y, SM.z, cs2, Xs);
-    load_nodes(MM.x, MM.y, MM.z, cm2, Xm);
-    n0b[0] = n0b[1] = n0b[2] = 0.0;
-    projection_adjoint(Xs, Xm, NODAL ? elem_nrm(SM, launder(s)) : nullptr, nb, Xsb, Xmb, n0b);
   }
-}
-
-}  // namespace mt
-
-namespace mt {
-
-// Forward of pair p from its stored polygon: nodes, slave frame, projection,
-// then the quadrature of pair_integrate.  The heights are recomputed after
-// the quadrature from reloaded nodes rather than kept in registers.
-template <int NQ, bool DUAL>
-__device__ __forceinline__ void pair_forward(const MeshPtrs& SM, int s, int4 cs, const MeshPtrs& MM, int4 cm,
-                                             const GPoly& P, int nf, const KParams& kp, double D[16], double M[16],
-                                             double g[4], unsigned& noconv) {
-  IMap ms, mm;
-  {
-    double Xs[4][3], Xm[4][3], f[12];
-    load_nodes(SM.x, SM.y, SM.z, cs, Xs);
-    load_nodes(MM.x, MM.y, MM.z, cm, Xm);
-    slave_frame_p(Xs, elem_nrm(SM, s), f);
-    V2 S[4], Mn[4];
-    double hs[4], hm[4];
-    pair_project(Xs, Xm, f, S, Mn, hs, hm);
-    ms = imap(S);
-    mm = imap(Mn);
-  }
-  auto heights = [&](V2 S[4], double hs[4], double hm[4]) {
-    const int4 cs2{launder(cs.x), launder(cs.y), launder(cs.z), launder(cs.w)};
-    const int4 cm2{launder(cm.x), launder(cm.y), launder(cm.z), launder(cm.w)};
-    double Xs[4][3], Xm[4][3], f[12];
-    load_nodes(SM.x, SM.y, SM.z, cs2, Xs);
-    load_nodes(MM.x, MM.y, MM.z, cm2, Xm);
-    slave_frame_p(Xs, elem_nrm(SM, launder(s)), f);
-    V2 Mn[4];
-    pair_project(Xs, Xm, f, S, Mn, hs, hm);
-  };
-  pair_integrate<NQ, DUAL>(ms, mm, heights, P, nf & 0x7f, kp, D, M, g, noconv);
 }
 
 }  // namespace mt

@@ -209,6 +209,7 @@ __global__ __launch_bounds__(BSC) __attribute__((amdgpu_waves_per_eu(3))) void k
                                                    const int32_t* __restrict__ pair_m,
                                                    const int32_t* __restrict__ n_dev, PolyBuf poly,
                                                    double* __restrict__ blk, int64_t stride, Counters* cnt) {
+  __shared__ double stash[FWD_STASH * BSC];
   const int64_t n_pairs = *n_dev;
   const int64_t tile = dyn_tile(blockIdx.x, n_pairs, BSC);
   if (tile < 0) return;
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(BSC) __attribute__((amdgpu_waves_per_eu(3))) void k
     double D[16], Mv[16], g[4];
     const int s = pair_s[p];
     pair_forward<NQ, DUAL>(S, s, load_conn(S.conn, s), M, load_conn(M.conn, pair_m[p]), gpoly(poly, p),
-                           gpoly_nf(poly, p), kp, D, Mv, g, noconv);
+                           gpoly_nf(poly, p), kp, Stash{stash + threadIdx.x, BSC}, D, Mv, g, noconv);
 #pragma unroll
     for (int k = 0; k < 16; ++k) blk[(int64_t)k * stride + p] = D[k];
 #pragma unroll
