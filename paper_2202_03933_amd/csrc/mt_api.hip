@@ -106,11 +106,8 @@ constexpr size_t PIN_BYTES = 1024;
 constexpr int64_t CAP_MAX = (int64_t(1) << 31) - 1;
 
 int64_t scan_max(const mt_ctx* c, const mt_capacity& cap) {
-  const int64_t nm = c->side[1].n_el;
-  const int64_t sortn = std::max<int64_t>(nm, cap.pairs);
-  const int64_t hist = radix_hist_elems(sortn);
   int64_t m = std::max<int64_t>({(int64_t)c->side[0].n_el, (int64_t)c->side[0].n_nodes, (int64_t)c->side[1].n_nodes,
-                                 nm, cap.screened, hist});
+                                 (int64_t)c->side[1].n_el, cap.screened, cap.cells});
   return m + 1;
 }
 
@@ -122,10 +119,7 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   const size_t ns = (size_t)S.n_el, nm = (size_t)M.n_el, nsn = (size_t)S.n_nodes, nmn = (size_t)M.n_nodes;
   const size_t C = (size_t)cap.candidates, SC = (size_t)cap.screened, P = (size_t)cap.pairs, G = (size_t)cap.cells;
   const bool nodal = c->params.normals == MT_NORMALS_NODAL;
-  const size_t sortn = std::max(nm, P);
-  const size_t hist = sizeof(int32_t) * (size_t)radix_hist_elems((int64_t)sortn);
   const size_t scan = sizeof(int32_t) * (size_t)scan_tmp_elems(scan_max(c, cap));
-  A.take(c->reduce, sizeof(PrepReduce));
   A.take(c->counters, sizeof(Counters));
   A.take(c->state, sizeof(DevState));
   A.take(c->box_s, 48 * ns);
@@ -133,11 +127,11 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   A.take(c->sdata, 8 * SD_N * ns);
   A.take(c->mdata, 96 * nm);
   A.take(c->prep_part, 72 * (size_t)(prep_blocks(S.n_el) + prep_blocks(M.n_el)));
-  for (Buf* b : {&c->keys, &c->vals, &c->keys_tmp, &c->vals_tmp}) A.take(*b, 4 * sortn);
-  A.take(c->cell_range, 8 * G);
+  for (Buf* b : {&c->mcell, &c->mrank, &c->vals}) A.take(*b, 4 * nm);
+  A.take(c->cell_cnt, 4 * G);
+  A.take(c->cell_start, 4 * (G + 1));
   A.take(c->sbox, 48 * nm);
   A.take(c->qbox, 16 * nm);
-  A.take(c->sort_hist, hist);
   A.take(c->scan_tmp, scan);
   A.take(c->aux_scan, scan);
   A.take(c->cand_cnt, 4 * (ns + 1));
@@ -624,39 +618,31 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
   }
   DevState* dst = c->state.as<DevState>();
   Counters* cnt = c->counters.as<Counters>();
-  PrepReduce* red = c->reduce.as<PrepReduce>();
   const KParams kp = kparams(c->params);
   const int nb_s = prep_blocks(ns), nb_m = prep_blocks(nm);
   {
     PhaseTimer t(c, MT_T_PREP, st);
-    // counters and state start at zero (a fill kernel: no memset node)
-    static_assert(sizeof(Counters) % 4 == 0 && sizeof(DevState) % 4 == 0, "word fills");
-    MT_HIP(fill_i32(c->counters.as<int32_t>(), 0, sizeof(Counters) / 4, st));
-    MT_HIP(fill_i32(c->state.as<int32_t>(), 0, sizeof(DevState) / 4, st));
     // the continuous normal field first: the slave frames use it
     int rc = normals_for_coords(c, st);
     if (rc) return rc;
     double* part = c->prep_part.as<double>();
     MT_HIP(launch_prep(S, M, c->box_s.as<double>(), c->sdata.as<double>(), c->box_m.as<double>(),
                        c->mdata.as<double>(), part, st));
-    MT_HIP(launch_prep_reduce(part, nb_s, nb_m, red, c->params.delta, c->params.bin_size, cap.cells, dst, st));
+    MT_HIP(launch_prep_reduce(part, nb_s, nb_m, c->params.delta, c->params.bin_size, cap.cells, dst, cnt,
+                              c->cell_cnt.as<int32_t>(), st));
   }
   const Grid* g = &dst->grid;
   {
-    // master elements sorted by cell, cell ranges from segment heads
+    // master elements by cell
     PhaseTimer t(c, MT_T_BIN_SORT, st);
-    int bits = 1;
-    while ((int64_t(1) << bits) < cap.cells) ++bits;
-    // keys written where an odd number of sort passes starts, so that the
-    // sorted pairs end in (keys, vals) without a copy
-    const bool in_tmp = radix_passes(bits) % 2 == 1;
-    MT_HIP(launch_master_keys(c->box_m.as<double>(), nm, g, cap.cells,
-                              (in_tmp ? c->keys_tmp : c->keys).as<uint32_t>(),
-                              (in_tmp ? c->vals_tmp : c->vals).as<uint32_t>(), c->cell_range.as<int2>(), st));
-    MT_HIP(radix_sort_pairs(c->keys.as<uint32_t>(), c->vals.as<uint32_t>(), c->keys_tmp.as<uint32_t>(),
-                            c->vals_tmp.as<uint32_t>(), nm, nullptr, bits, c->sort_hist, c->scan_tmp, st, in_tmp));
-    MT_HIP(launch_cell_ranges(c->keys.as<uint32_t>(), c->vals.as<uint32_t>(), nm, c->box_m.as<double>(), g,
-                              c->cell_range.as<int2>(), c->sbox.as<double>(), c->qbox.as<uint64_t>(), st));
+    MT_HIP(launch_cell_count(c->box_m.as<double>(), nm, g, c->cell_cnt.as<int32_t>(), c->mcell.as<uint32_t>(),
+                             c->mrank.as<uint32_t>(), st));
+    // (the cell count as an int32 is the low word of the grid's, < 2^31)
+    MT_HIP(scan_exclusive_dev(c->cell_cnt.as<int32_t>(), c->cell_start.as<int32_t>(),
+                              reinterpret_cast<const int32_t*>(&g->ncells), cap.cells, c->scan_tmp, st));
+    MT_HIP(launch_cell_place(c->mcell.as<uint32_t>(), c->mrank.as<uint32_t>(), nm, c->box_m.as<double>(), g,
+                             c->cell_start.as<int32_t>(), c->vals.as<uint32_t>(), c->sbox.as<double>(),
+                             c->qbox.as<uint64_t>(), st));
   }
   {
     // candidates: count, scan, fill (sorted by master within each slave),
@@ -664,12 +650,12 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
     // degeneracy checks, separating-line test)
     PhaseTimer t(c, MT_T_CAND, st);
     MT_HIP(launch_cand_count(c->box_s.as<double>(), ns, c->sbox.as<double>(), c->qbox.as<uint64_t>(),
-                             c->vals.as<uint32_t>(), c->cell_range.as<int2>(), g, c->params.delta,
+                             c->vals.as<uint32_t>(), c->cell_start.as<int32_t>(), g, c->params.delta,
                              c->cand_cnt.as<int32_t>(), c->cand_tmp.as<int32_t>(), st));
-    MT_HIP(scan_exclusive(c->cand_cnt.as<int32_t>(), c->cand_off.as<int32_t>(), ns, c->scan_tmp, st));
-    MT_HIP(launch_stage_totals(0, c->cand_off.as<int32_t>(), ns, cap.candidates, dst, st));
+    MT_HIP(scan_exclusive(c->cand_cnt.as<int32_t>(), c->cand_off.as<int32_t>(), ns, c->scan_tmp, st, 0,
+                          ScanStage{ScanStage::CANDIDATES, cap.candidates, dst}));
     MT_HIP(launch_cand_fill(c->box_s.as<double>(), ns, c->sbox.as<double>(), c->vals.as<uint32_t>(),
-                            c->cell_range.as<int2>(), g, c->params.delta, c->cand_tmp.as<int32_t>(),
+                            c->cell_start.as<int32_t>(), g, c->params.delta, c->cand_tmp.as<int32_t>(),
                             c->cand_off.as<int32_t>(), c->cand_s.as<int32_t>(), c->cand_m.as<int32_t>(),
                             c->sdata.as<double>(), c->mdata.as<double>(), kp.eps_a, c->cand_nv.as<uint8_t>(),
                             c->cand_flag.as<int32_t>(), c->scr_cnt.as<int32_t>(), cnt, cap.candidates, st));
@@ -680,8 +666,8 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
                       c->mpoly_nf.as<uint8_t>(), SC, nullptr};
   {
     PhaseTimer t(c, MT_T_COMPACT, st);
-    MT_HIP(scan_exclusive(c->scr_cnt.as<int32_t>(), c->scr_off.as<int32_t>(), ns, c->scan_tmp, st));
-    MT_HIP(launch_stage_totals(1, c->scr_off.as<int32_t>(), ns, SC, dst, st));
+    MT_HIP(scan_exclusive(c->scr_cnt.as<int32_t>(), c->scr_off.as<int32_t>(), ns, c->scan_tmp, st, 0,
+                          ScanStage{ScanStage::SCREENED, SC, dst}));
     MT_HIP(launch_maybe_list(c->cand_flag.as<int32_t>(), c->cand_off.as<int32_t>(), c->scr_off.as<int32_t>(), ns,
                              cap.candidates, SC, c->maybe_list.as<int32_t>(), st));
   }
@@ -694,8 +680,7 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
   {
     PhaseTimer t(c, MT_T_COMPACT, st);
     MT_HIP(scan_exclusive_dev(c->maybe_flag.as<int32_t>(), c->maybe_scan.as<int32_t>(), &dst->n_screened, SC,
-                              c->scan_tmp, st));
-    MT_HIP(launch_stage_totals(2, c->maybe_scan.as<int32_t>(), 0, cap.pairs, dst, st));
+                              c->scan_tmp, st, ScanStage{ScanStage::PAIRS, cap.pairs, dst}));
     MT_HIP(launch_compact_pairs(c->cand_s.as<int32_t>(), c->cand_m.as<int32_t>(), c->maybe_list.as<int32_t>(),
                                 c->maybe_flag.as<int32_t>(), c->maybe_scan.as<int32_t>(), &dst->n_screened, SC,
                                 c->mpoly_nf.as<uint8_t>(), c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(),

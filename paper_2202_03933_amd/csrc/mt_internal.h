@@ -170,13 +170,14 @@ struct mt_ctx {
   mt::Buf box_s, box_m;    // [6][n_el] lo xyz, hi xyz
   mt::Buf sdata;           // [SD_N][n_s_el] precomputed slave frame and polygon
   mt::Buf mdata;           // [n_m_el][12] master element node coordinates
-  mt::Buf reduce;          // PrepReduce
   mt::Buf prep_part;       // per-block partials of the element preparation
   mt::Buf counters;        // Counters
   mt::Buf state;           // DevState
   // binning
-  mt::Buf keys, vals, keys_tmp, vals_tmp;  // [max(n_m_el, pair capacity)]
-  mt::Buf cell_range;      // int2 [cell capacity]: sorted-master range of each cell
+  mt::Buf mcell, mrank;    // [n_m_el] each master's cell and its place there
+  mt::Buf vals;            // [n_m_el] masters in cell order
+  mt::Buf cell_cnt;        // [cell capacity] masters per cell
+  mt::Buf cell_start;      // [cell capacity + 1] first master of each cell in that order
   mt::Buf sbox;            // [n_m_el][6] master boxes in cell order
   mt::Buf qbox;            // uint64 [n_m_el][2] their bounds quantised (candidate prefilter)
   // candidates
@@ -237,45 +238,41 @@ struct mt_ctx {
   mt::Buf mp_vals;         // uint32 [pair capacity] pairs sorted by master element
   mt::Buf mp_tmp;          // uint32 [pair capacity] merge scratch of that sort
   mt::Buf mp_pos;          // int32 [pair capacity]: rank of each pair in that order
-  // scan / sort scratch
-  mt::Buf scan_tmp, sort_hist;
+  // scan scratch
+  mt::Buf scan_tmp;
   void* pin = nullptr;     // pinned host memory: read-backs and the connectivity check
 };
 
 namespace mt {
 
 // ---- primitives (mt_prims.hip) ------------------------------------------
+// What a scan's total is to the build (st null: nothing): the count of a
+// stage, written to the device state clamped to the stage's capacity `cap`,
+// an excess flagged.
+struct ScanStage {
+  enum { CANDIDATES, SCREENED, PAIRS };
+  int32_t stage = 0;
+  int64_t cap = 0;
+  DevState* st = nullptr;
+};
 // Scratch (int32 elements) of a scan of up to n values.
 int64_t scan_tmp_elems(int64_t n);
 // Exclusive prefix sum of n int32 values into out[0..n]; out[n] = total.
 // max_blocks > 0 caps the workgroups per launch (for a scan that runs beside
 // a long kernel on another stream).
 hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, const Buf& tmp, hipStream_t s,
-                          int64_t max_blocks = 0);
+                          int64_t max_blocks = 0, const ScanStage& stage = ScanStage{});
 // Two such scans of arrays of the same length (in into out, in2 into out2)
 // in the launches of one; the same scratch.
 hipError_t scan_exclusive2(const int32_t* in, int32_t* out, const int32_t* in2, int32_t* out2, int64_t n,
                            const Buf& tmp, hipStream_t s, int64_t max_blocks = 0);
 // Workgroup cap of scans that run beside the pair kernels.
 constexpr int64_t SCAN_BLOCKS_BESIDE = 256;
-// The same over a count the device holds (*n_dev <= cap): out[0..cap] with
-// the values from *n_dev on taken as zero, so out[*n_dev] = total.
+// The same over a count the device holds (*n_dev <= cap): out[0..*n_dev],
+// out[*n_dev] = total; what lies behind is not written.
 hipError_t scan_exclusive_dev(const int32_t* in, int32_t* out, const int32_t* n_dev, int64_t cap, const Buf& tmp,
-                              hipStream_t s);
-// Histogram scratch (int32 elements) of a radix sort of up to n keys.
-int64_t radix_hist_elems(int64_t n);
-// Stable LSD radix sort of (key, value) pairs on key bits [0, bits).
-// Results end in (keys, vals); (keys_tmp, vals_tmp) are scratch of size n.
-// With n_dev, only the first *n_dev <= n pairs are sorted.
-// in_tmp: the input is in (keys_tmp, vals_tmp) instead (then an odd number
-// of passes ends in (keys, vals) without a copy).
-hipError_t radix_sort_pairs(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp, int64_t n,
-                            const int32_t* n_dev, int bits, const Buf& hist, const Buf& scan_tmp, hipStream_t s,
-                            bool in_tmp = false);
-// Passes of radix_sort_pairs for `bits` key bits.
-inline int radix_passes(int bits) { return (bits + 7) / 8; }
+                              hipStream_t s, const ScanStage& stage = ScanStage{});
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
-hipError_t fill_f64(double* p, double v, int64_t n, hipStream_t s);
 
 // ---- search (mt_search.hip) ------------------------------------------------
 // Element preparation of both sides in one launch; per-block partial
@@ -285,34 +282,35 @@ int prep_blocks(int32_t n_el);
 hipError_t launch_prep(const DeviceMesh& S, const DeviceMesh& M, double* box_s, double* sd, double* box_m,
                        double* md, double* part, hipStream_t s);
 // The reductions of both sides, then the search grid (st->grid) from them,
-// at most max_cells cells; flags non-finite coordinates.
-hipError_t launch_prep_reduce(const double* part, int nb_s, int nb_m, PrepReduce* red, double delta,
-                              double bin_size, int64_t max_cells, DevState* st, hipStream_t s);
-// Master keys and values for the bin sort; the cell table cleared in the
-// same launch.
-hipError_t launch_master_keys(const double* box_m, int32_t n_m, const Grid* g, int64_t max_cells, uint32_t* keys,
-                              uint32_t* vals, int2* range, hipStream_t s);
-hipError_t launch_cell_ranges(const uint32_t* keys, const uint32_t* vals, int32_t n, const double* box_m,
-                              const Grid* g, int2* range, double* sbox, uint64_t* qbox, hipStream_t s);
+// at most max_cells cells; the rest of the state and the counters start at
+// zero, non-finite coordinates are flagged, and the counts of the grid's
+// cells (cell_cnt) are cleared.
+hipError_t launch_prep_reduce(const double* part, int nb_s, int nb_m, double delta, double bin_size,
+                              int64_t max_cells, DevState* st, Counters* cnt, int32_t* cell_cnt, hipStream_t s);
+// Counting sort of the master elements by cell: the cell of each box centre
+// and the element's place in it (arrival order), then, with the scanned
+// counts, the master index vals[i], box and quantised box of the i-th
+// element in cell order.
+hipError_t launch_cell_count(const double* box_m, int32_t n_m, const Grid* g, int32_t* cell_cnt, uint32_t* cell,
+                             uint32_t* rank, hipStream_t s);
+hipError_t launch_cell_place(const uint32_t* cell, const uint32_t* rank, int32_t n, const double* box_m,
+                             const Grid* g, const int32_t* cell_start, uint32_t* vals, double* sbox, uint64_t* qbox,
+                             hipStream_t s);
 hipError_t launch_cand_count(const double* box_s, int32_t n_s, const double* sbox, const uint64_t* qbox,
-                             const uint32_t* mvals, const int2* range, const Grid* g, double delta, int32_t* count,
+                             const uint32_t* mvals, const int32_t* cell_start, const Grid* g, double delta,
+                             int32_t* count,
                              int32_t* tmp, hipStream_t s);
 // Candidates of slave s go to [off[s], off[s + 1]) of cand_s / cand_m / nv /
 // flag, whose length is cap: a slave whose range ends beyond cap writes
 // nothing and gets scr_cnt[s] = 0 (the stage totals flag the excess).
 hipError_t launch_cand_fill(const double* box_s, int32_t n_s, const double* sbox, const uint32_t* mvals,
-                            const int2* range, const Grid* g, double delta, const int32_t* tmp, const int32_t* off,
-                            int32_t* cand_s, int32_t* cand_m, const double* sd, const double* md, double eps_a,
+                            const int32_t* cell_start, const Grid* g, double delta, const int32_t* tmp,
+                            const int32_t* off, int32_t* cand_s, int32_t* cand_m, const double* sd, const double* md, double eps_a,
                             uint8_t* nv, int32_t* flag, int32_t* scr_cnt, Counters* cnt, int64_t cap,
                             hipStream_t s);
 int cand_tmp_per_slave();
 
 // ---- pairs (mt_pairs.hip) ----------------------------------------------------
-// Stage totals into the device state: stage 0 candidates (vec[idx]), 1
-// screened candidates (vec[idx]), 2 pairs (vec[st->n_screened]); clamped to
-// cap, the excess flagged.
-hipError_t launch_stage_totals(int stage, const int32_t* vec, int64_t idx, int64_t cap, DevState* st,
-                               hipStream_t s);
 // Histogram of clip vertex counts nv[0..n) added to hist[17].
 hipError_t launch_nv_hist(const uint8_t* nv, int64_t n, unsigned long long* hist, hipStream_t s);
 hipError_t launch_maybe_list(const int32_t* flag, const int32_t* cand_off, const int32_t* scr_off, int32_t n_s,

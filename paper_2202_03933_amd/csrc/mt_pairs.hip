@@ -38,32 +38,6 @@ __device__ __forceinline__ void load_slave_data(const double* __restrict__ sd, i
   hmax = sd[(int64_t)21 * n_s + s];
 }
 
-// Totals of one stage of the build into the device state, clamped to the
-// stage's capacity (the flag records an excess):
-//  0 candidates: cand_off[n_s];
-//  1 screened candidates: scr_off[n_s];
-//  2 pairs: maybe_scan[n_screened].
-__global__ void k_stage_totals(int stage, const int32_t* __restrict__ vec, int64_t idx, int64_t cap,
-                               DevState* st) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  if (stage == 2) idx = st->n_screened;
-  const int64_t total = vec[idx];
-  const bool over = total < 0 || total > cap;  // negative: the int32 scan overflowed (more than 2^31)
-  const int32_t kept = (int32_t)(total < 0 ? 0 : (total < cap ? total : cap));
-  if (stage == 0) {
-    st->n_cand = (int32_t)(total < 0 ? 0x7fffffff : total);
-    if (over) st->flags |= DS_CAP_CAND;
-  } else if (stage == 1) {
-    st->need_screened = (int32_t)(total < 0 ? 0x7fffffff : total);
-    st->n_screened = kept;
-    if (over) st->flags |= DS_CAP_SCREENED;
-  } else {
-    st->need_pairs = (int32_t)(total < 0 ? 0x7fffffff : total);
-    st->n_pairs = kept;
-    if (over) st->flags |= DS_CAP_PAIRS;
-  }
-}
-
 // Screened candidates in candidate order: slave s writes its screened
 // candidates from mlist[scr_off[s]] on, in order; a slave whose candidates
 // were not stored (beyond their capacity) has none, and nothing is written
@@ -237,12 +211,6 @@ hipError_t launch_nv_hist(const uint8_t* nv, int64_t n, unsigned long long* hist
   if (n == 0) return hipSuccess;
   const unsigned nb = (unsigned)std::min<int64_t>(1024, (n + BS - 1) / BS);
   k_nv_hist<<<nb, BS, 0, s>>>(nv, n, hist);
-  return hipGetLastError();
-}
-
-hipError_t launch_stage_totals(int stage, const int32_t* vec, int64_t idx, int64_t cap, DevState* st,
-                               hipStream_t s) {
-  k_stage_totals<<<1, 64, 0, s>>>(stage, vec, idx, cap, st);
   return hipGetLastError();
 }
 

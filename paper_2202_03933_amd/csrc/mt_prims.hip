@@ -1,5 +1,5 @@
-// Device-wide primitives: exclusive scan and a stable LSD radix sort of
-// (uint32 key, uint32 value) pairs, written for 64-wide wavefronts.
+// Device-wide primitives: exclusive scan and fill, written for 64-wide
+// wavefronts.
 #include "mt_internal.h"
 
 namespace mt {
@@ -44,7 +44,7 @@ __device__ __forceinline__ T block_exclusive(T x, T* total) {
 }
 
 // n_dev (optional): a count the device holds, at most n; entries from it on
-// count as zero.
+// count as zero, and the outputs behind out[*n_dev] are left alone.
 template <class T>
 __device__ __forceinline__ int64_t live_count(int64_t n, const int32_t* n_dev) {
   if (!n_dev) return n;
@@ -53,9 +53,12 @@ __device__ __forceinline__ int64_t live_count(int64_t n, const int32_t* n_dev) {
 }
 
 // Exclusive scan: per-tile sums, then each tile's scan with its offset.
-// Up to SCAN_DIRECT tiles, every tile adds up the sums before it itself (no
-// third launch; the sums are a few KB, read from L2); beyond, the sums are
-// scanned recursively first.  No tile waits for another.
+// Up to SCAN_SELF workgroups there is one launch: each adds up the inputs
+// before its own itself (at most 64K values from L2, about 2 us, where the
+// launch of the sums costs 4-5 us).  Up to SCAN_DIRECT, every workgroup adds
+// up the sums before it (no third launch; the sums are a few KB); beyond, the
+// sums are scanned recursively first.  No tile waits for another.
+constexpr int64_t SCAN_SELF = 32;
 constexpr int64_t SCAN_DIRECT = 8192;
 
 // The SCAN_IPT values of thread's slot (zero past `live`): two 16-byte loads
@@ -86,6 +89,10 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_sums(const int32_t* __restrict
     sums += gridDim.x;
   }
   const int64_t live = live_count<int32_t>(n, n_dev);
+  if ((int64_t)blockIdx.x * per * SCAN_TILE >= live) {  // nothing here (the whole workgroup)
+    if (threadIdx.x == 0) sums[blockIdx.x] = 0;
+    return;
+  }
   int32_t s = 0;
   for (int q = 0; q < per; ++q) {
     const int64_t base = ((int64_t)blockIdx.x * per + q) * SCAN_TILE + (int64_t)threadIdx.x * SCAN_IPT;
@@ -99,26 +106,61 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_sums(const int32_t* __restrict
   if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
+// The total of a stage of the build into the device state, clamped to the
+// stage's capacity (the flag records an excess).
+__device__ void stage_total(const ScanStage& g, int64_t total) {
+  DevState* st = g.st;
+  const bool over = total < 0 || total > g.cap;  // negative: the int32 scan overflowed (more than 2^31)
+  const int32_t all = (int32_t)(total < 0 ? 0x7fffffff : total);
+  const int32_t kept = (int32_t)(total < 0 ? 0 : (total < g.cap ? total : g.cap));
+  if (g.stage == ScanStage::CANDIDATES) {
+    st->n_cand = all;
+    if (over) st->flags |= DS_CAP_CAND;
+  } else if (g.stage == ScanStage::SCREENED) {
+    st->need_screened = all;
+    st->n_screened = kept;
+    if (over) st->flags |= DS_CAP_SCREENED;
+  } else {
+    st->need_pairs = all;
+    st->n_pairs = kept;
+    if (over) st->flags |= DS_CAP_PAIRS;
+  }
+}
+
 // out[i] = offset of the workgroup + exclusive prefix of in within its
-// tiles; the last workgroup also writes out[n] = grand total.  Offset of
-// workgroup w: offs[w] (scanned), or with DIRECT the sum of sums[0..w) (raw
-// workgroup sums), or 0.
-template <bool VEC, bool DIRECT>
+// tiles; the workgroup that holds the end of the live values also writes the
+// total behind them, and with a stage to the device state.  Offset of
+// workgroup w: OFF_GIVEN offs[w] (scanned) or 0, OFF_SUMS the sum of
+// sums[0..w) (raw workgroup sums), OFF_SELF the sum of the inputs before it.
+enum { OFF_GIVEN, OFF_SUMS, OFF_SELF };
+
+template <bool VEC, int OFF>
 __global__ __launch_bounds__(SCAN_BS) void k_tile_scan(const int32_t* __restrict__ in, const int32_t* __restrict__ in2,
                                                        int64_t n, const int32_t* n_dev,
                                                        const int32_t* __restrict__ offs, int32_t* __restrict__ out,
-                                                       int32_t* __restrict__ out2, int per) {
+                                                       int32_t* __restrict__ out2, int per, ScanStage stage) {
   if (blockIdx.y) {  // (the raw workgroup sums of the second array follow the first's)
     in = in2;
     out = out2;
-    if (DIRECT) offs += gridDim.x;
+    if (OFF == OFF_SUMS) offs += gridDim.x;
   }
   const int64_t live = live_count<int32_t>(n, n_dev);
   const int64_t w = blockIdx.x;
+  const int64_t end = min(live / ((int64_t)per * SCAN_TILE), (int64_t)gridDim.x - 1);
+  if (w > end) return;
   int32_t off = 0;
-  if (DIRECT) {
+  if (OFF == OFF_SUMS) {
     int32_t part = 0;
     for (int64_t i = threadIdx.x; i < w; i += SCAN_BS) part += offs[i];
+    block_exclusive(part, &off);
+  } else if (OFF == OFF_SELF) {
+    int32_t part = 0;
+    for (int64_t t = 0; t < w * per; ++t) {
+      int32_t v[SCAN_IPT];
+      load_slot<VEC>(in, t * SCAN_TILE + (int64_t)threadIdx.x * SCAN_IPT, live, v);
+#pragma unroll
+      for (int i = 0; i < SCAN_IPT; ++i) part += v[i];
+    }
     block_exclusive(part, &off);
   } else if (offs) {
     off = offs[w];
@@ -148,17 +190,21 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_scan(const int32_t* __restrict
     }
     off += tot;
   }
-  if (w == (int64_t)gridDim.x - 1 && threadIdx.x == 0) out[n] = off;
+  if (w == end && threadIdx.x == 0) {
+    if (live == n) out[n] = off;  // (else written above: no value lies behind the live ones)
+    if (stage.st) stage_total(stage, off);
+  }
 }
 
-// Exclusive scan of n values (of the first *n_dev when given; the rest count
-// as zero) into out[0..n]; with in2, also of in2 into out2 (n_dev null) in
-// the same launches while the workgroup sums of both fit the direct scheme.
+// Exclusive scan of n values (of the first *n_dev when given) into
+// out[0..n]; with in2, also of in2 into out2 (n_dev null) in the same
+// launches while the workgroup sums of both fit the direct scheme.
 // max_blocks > 0 caps the workgroups of each launch (several tiles each): a
 // scan queued beside a long kernel on another stream then waits for few
 // dispatch slots.  No memset: the launches can be captured in a graph.
 hipError_t scan_impl(const int32_t* in, int32_t* out, int64_t n, const int32_t* n_dev, int32_t* tmp, hipStream_t s,
-                     const int32_t* in2 = nullptr, int32_t* out2 = nullptr, int64_t max_blocks = 0) {
+                     const int32_t* in2 = nullptr, int32_t* out2 = nullptr, int64_t max_blocks = 0,
+                     const ScanStage& stage = ScanStage{}) {
   const int64_t tiles = std::max<int64_t>(1, (n + SCAN_TILE - 1) / SCAN_TILE);
   const int per = max_blocks > 0 ? (int)((tiles + max_blocks - 1) / max_blocks) : 1;
   const int64_t blocks = (tiles + per - 1) / per;
@@ -170,9 +216,9 @@ hipError_t scan_impl(const int32_t* in, int32_t* out, int64_t n, const int32_t* 
     return e != hipSuccess ? e : scan_impl(in2, out2, n, nullptr, tmp, s, nullptr, nullptr, max_blocks);
   }
   const dim3 grid((unsigned)blocks, in2 ? 2u : 1u);
-  if (blocks == 1) {
-    auto* k = vec ? k_tile_scan<true, false> : k_tile_scan<false, false>;
-    k<<<grid, SCAN_BS, 0, s>>>(in, in2, n, n_dev, nullptr, out, out2, per);
+  if (blocks <= SCAN_SELF && per == 1) {
+    auto* k = vec ? k_tile_scan<true, OFF_SELF> : k_tile_scan<false, OFF_SELF>;
+    k<<<grid, SCAN_BS, 0, s>>>(in, in2, n, n_dev, nullptr, out, out2, per, stage);
     return hipGetLastError();
   }
   int32_t* sums = tmp;  // blocks (2 blocks with in2) entries
@@ -180,15 +226,15 @@ hipError_t scan_impl(const int32_t* in, int32_t* out, int64_t n, const int32_t* 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (blocks <= SCAN_DIRECT) {
-    auto* k = vec ? k_tile_scan<true, true> : k_tile_scan<false, true>;
-    k<<<grid, SCAN_BS, 0, s>>>(in, in2, n, n_dev, sums, out, out2, per);
+    auto* k = vec ? k_tile_scan<true, OFF_SUMS> : k_tile_scan<false, OFF_SUMS>;
+    k<<<grid, SCAN_BS, 0, s>>>(in, in2, n, n_dev, sums, out, out2, per, stage);
     return hipGetLastError();
   }
   int32_t* offs = tmp + blocks;  // blocks + 1 entries
   e = scan_impl(sums, offs, blocks, nullptr, offs + blocks + 1, s);
   if (e != hipSuccess) return e;
-  auto* k = vec ? k_tile_scan<true, false> : k_tile_scan<false, false>;
-  k<<<(unsigned)blocks, SCAN_BS, 0, s>>>(in, nullptr, n, n_dev, offs, out, nullptr, per);
+  auto* k = vec ? k_tile_scan<true, OFF_GIVEN> : k_tile_scan<false, OFF_GIVEN>;
+  k<<<(unsigned)blocks, SCAN_BS, 0, s>>>(in, nullptr, n, n_dev, offs, out, nullptr, per, stage);
   return hipGetLastError();
 }
 
@@ -209,92 +255,6 @@ int64_t scan_tmp_elems(int64_t n) {
 
 namespace {
 
-// ---- radix sort ------------------------------------------------------------
-
-constexpr int RS_BS = 256;
-constexpr int RS_IPT = 8;
-constexpr int RS_TILE = RS_BS * RS_IPT;
-constexpr int RS_RADIX = 256;
-
-// Per tile digit histogram, stored digit-major: hist[d * tiles + tile].
-__global__ __launch_bounds__(RS_BS) void k_rs_hist(const uint32_t* __restrict__ keys, int64_t n,
-                                                    const int32_t* n_dev, int shift, int32_t* __restrict__ hist,
-                                                    int64_t tiles) {
-  n = live_count<int32_t>(n, n_dev);
-  __shared__ int32_t h[RS_RADIX];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-#pragma unroll
-  for (int i = 0; i < RS_IPT; ++i) {
-    const int64_t idx = base + (int64_t)i * RS_BS + threadIdx.x;
-    if (idx < n) atomicAdd(&h[(keys[idx] >> shift) & 0xff], 1);
-  }
-  __syncthreads();
-  hist[(int64_t)threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
-}
-
-// Stable scatter: keys of a tile are taken in rounds of RS_BS consecutive
-// keys; a key's rank among equal digits is its rank within its wavefront
-// (ballot match over the 8 digit bits), plus the counts of lower waves in
-// the round, plus the count of earlier rounds.
-__global__ __launch_bounds__(RS_BS) void k_rs_scatter(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                       uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                       int64_t n, const int32_t* n_dev, int shift,
-                                                       const int32_t* __restrict__ offs, int64_t tiles) {
-  n = live_count<int32_t>(n, n_dev);
-  __shared__ int32_t run[RS_RADIX];
-  __shared__ int32_t wcnt[RS_BS / 64][RS_RADIX];
-  run[threadIdx.x] = offs[(int64_t)threadIdx.x * tiles + blockIdx.x];
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-  for (int r = 0; r < RS_IPT; ++r) {
-#pragma unroll
-    for (int i = 0; i < RS_BS / 64; ++i) wcnt[i][threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t idx = base + (int64_t)r * RS_BS + threadIdx.x;
-    const bool valid = idx < n;
-    uint32_t key = 0, val = 0;
-    int d = 0;
-    if (valid) {
-      key = kin[idx];
-      val = vin[idx];
-      d = (key >> shift) & 0xff;
-    }
-    uint64_t m = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (d >> b) & 1;
-      const uint64_t bb = __ballot(bit);
-      m &= bit ? bb : ~bb;
-    }
-    const int rank = __popcll(m & lt);
-    if (valid && rank == 0) wcnt[w][d] = __popcll(m);
-    __syncthreads();
-    // exclusive prefix over waves for digit threadIdx.x
-    {
-      int acc = 0;
-#pragma unroll
-      for (int i = 0; i < RS_BS / 64; ++i) {
-        const int c = wcnt[i][threadIdx.x];
-        wcnt[i][threadIdx.x] = acc;
-        acc += c;
-      }
-      __syncthreads();
-      if (valid) {
-        const int64_t pos = (int64_t)run[d] + wcnt[w][d] + rank;
-        kout[pos] = key;
-        vout[pos] = val;
-      }
-      __syncthreads();
-      run[threadIdx.x] += acc;
-    }
-    __syncthreads();
-  }
-}
-
 // Grid-stride fill: at most FILL_BLOCKS workgroups, so that a fill queued
 // beside a long kernel on another stream waits for few dispatch slots.
 constexpr int64_t FILL_BLOCKS = 1024;
@@ -302,23 +262,12 @@ __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
 }
-__global__ void k_fill_f64(double* p, double v, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-__global__ void k_copy_u32(const uint32_t* __restrict__ a, uint32_t* __restrict__ b, int64_t n,
-                           const int32_t* n_dev) {
-  n = live_count<int32_t>(n, n_dev);
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) b[i] = a[i];
-}
-
 }  // namespace
 
 hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, const Buf& tmp, hipStream_t s,
-                          int64_t max_blocks) {
+                          int64_t max_blocks, const ScanStage& stage) {
   if ((int64_t)(tmp.bytes / sizeof(int32_t)) < scan_tmp_elems(n)) return hipErrorInvalidValue;
-  return scan_impl(in, out, n, nullptr, tmp.as<int32_t>(), s, nullptr, nullptr, max_blocks);
+  return scan_impl(in, out, n, nullptr, tmp.as<int32_t>(), s, nullptr, nullptr, max_blocks, stage);
 }
 
 hipError_t scan_exclusive2(const int32_t* in, int32_t* out, const int32_t* in2, int32_t* out2, int64_t n,
@@ -328,68 +277,14 @@ hipError_t scan_exclusive2(const int32_t* in, int32_t* out, const int32_t* in2, 
 }
 
 hipError_t scan_exclusive_dev(const int32_t* in, int32_t* out, const int32_t* n_dev, int64_t cap, const Buf& tmp,
-                              hipStream_t s) {
+                              hipStream_t s, const ScanStage& stage) {
   if ((int64_t)(tmp.bytes / sizeof(int32_t)) < scan_tmp_elems(cap)) return hipErrorInvalidValue;
-  return scan_impl(in, out, cap, n_dev, tmp.as<int32_t>(), s);
-}
-
-int64_t radix_hist_elems(int64_t n) { return 2 * ((n + RS_TILE - 1) / RS_TILE) * RS_RADIX + 1; }
-
-hipError_t radix_sort_pairs(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp, int64_t n,
-                            const int32_t* n_dev, int bits, const Buf& hist, const Buf& scan_tmp, hipStream_t s,
-                            bool in_tmp) {
-  if (in_tmp) {
-    std::swap(keys, keys_tmp);
-    std::swap(vals, vals_tmp);
-  }
-  // from here the input is in (keys, vals); the result goes to (keys, vals)
-  // of the caller: the other pair when in_tmp
-  uint32_t* const out_k = in_tmp ? keys_tmp : keys;
-  uint32_t* const out_v = in_tmp ? vals_tmp : vals;
-  if (n <= 1 || bits <= 0) {  // no pass: the input is the result
-    if (in_tmp && n > 0) {
-      const unsigned nb = (unsigned)((n + 255) / 256);
-      k_copy_u32<<<nb, 256, 0, s>>>(keys, out_k, n, n_dev);
-      k_copy_u32<<<nb, 256, 0, s>>>(vals, out_v, n, n_dev);
-      return hipGetLastError();
-    }
-    return hipSuccess;
-  }
-  const int64_t tiles = (n + RS_TILE - 1) / RS_TILE;
-  const int64_t hn = tiles * RS_RADIX;
-  if ((int64_t)(hist.bytes / sizeof(int32_t)) < radix_hist_elems(n)) return hipErrorInvalidValue;
-  int32_t* h = hist.as<int32_t>();
-  int32_t* off = h + hn;
-  hipError_t e;
-  const int passes = radix_passes(bits);
-  uint32_t *ki = keys, *vi = vals, *ko = keys_tmp, *vo = vals_tmp;
-  for (int p = 0; p < passes; ++p) {
-    k_rs_hist<<<(unsigned)tiles, RS_BS, 0, s>>>(ki, n, n_dev, 8 * p, h, tiles);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = scan_exclusive(h, off, hn, scan_tmp, s)) != hipSuccess) return e;
-    k_rs_scatter<<<(unsigned)tiles, RS_BS, 0, s>>>(ki, vi, ko, vo, n, n_dev, 8 * p, off, tiles);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    std::swap(ki, ko);
-    std::swap(vi, vo);
-  }
-  if (ki != out_k) {
-    const unsigned nb = (unsigned)((n + 255) / 256);
-    k_copy_u32<<<nb, 256, 0, s>>>(ki, out_k, n, n_dev);
-    k_copy_u32<<<nb, 256, 0, s>>>(vi, out_v, n, n_dev);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return scan_impl(in, out, cap, n_dev, tmp.as<int32_t>(), s, nullptr, nullptr, 0, stage);
 }
 
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   k_fill_i32<<<(unsigned)std::min<int64_t>((n + 255) / 256, FILL_BLOCKS), 256, 0, s>>>(p, v, n);
-  return hipGetLastError();
-}
-
-hipError_t fill_f64(double* p, double v, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  k_fill_f64<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, v, n);
   return hipGetLastError();
 }
 

@@ -1,6 +1,5 @@
-// Contact search on the GPU: element preparation, Cartesian bins sorted by
-// radix sort with bin ranges from segment heads, and the candidate lists of
-// every slave element from its own bin and the 26 neighbouring bins
+// Contact search on the GPU: element preparation, master elements counted
+// into Cartesian bins, and the candidate lists of every slave element from its own bin and the 26 neighbouring bins
 // (Alg. 2 and its bin-sizing rule, Sec. "Distributed storage: going to large
 // problems").
 #include <cmath>
@@ -159,16 +158,20 @@ __global__ __launch_bounds__(BS) void k_prep(PrepSide s_side, PrepSide m_side) {
   if (threadIdx.x == 8) part[(int64_t)blockIdx.x * PREP_PART + 8] = (double)bad;
 }
 
-__device__ void grid_from(const PrepReduce* __restrict__ red, double delta, double bin_size, int64_t max_cells,
-                          DevState* st);
+__device__ Grid grid_from(const PrepReduce& red, double delta, double bin_size, int64_t max_cells);
 
 // Final reduction of the per-block partials of both sides (nb_s slave
-// blocks first, then nb_m master blocks) into the grid quantities, then the
-// search grid from them (grid_from, by the same thread).
+// blocks first, then nb_m master blocks) into the grid quantities and the
+// search grid from them (grid_from, one thread).  Every workgroup does this
+// for itself, so that all of them can clear their part of the grid's cell
+// counts without another launch; the first one also writes the state (zero
+// but for the grid and the flags) and zeroes the counters.  Bound by the
+// latency of the partials' loads and of grid_from.
 __global__ __launch_bounds__(BS) void k_prep_reduce(const double* __restrict__ part, int nb_s, int nb_m,
-                                                     PrepReduce* red, double delta, double bin_size,
-                                                     int64_t max_cells, DevState* st) {
+                                                     double delta, double bin_size, int64_t max_cells, DevState* st,
+                                                     Counters* cnt, int32_t* __restrict__ cell_cnt) {
   __shared__ double sh[BS / 64][PREP_PART];
+  __shared__ Grid sgrid;
   double v[PREP_PART];
 #pragma unroll
   for (int k = 0; k < PREP_PART; ++k) v[k] = k == 0 || k == 1 || k == 8 ? 0.0 : -INFINITY;
@@ -183,6 +186,11 @@ __global__ __launch_bounds__(BS) void k_prep_reduce(const double* __restrict__ p
   }
   __shared__ int sbits;
   if (threadIdx.x == 0) sbits = 0;
+  if (blockIdx.x == 0) {
+    static_assert(sizeof(Counters) % 4 == 0 && sizeof(DevState) % 4 == 0, "word fills");
+    for (unsigned i = threadIdx.x; i < sizeof(Counters) / 4; i += BS) reinterpret_cast<int32_t*>(cnt)[i] = 0;
+    for (unsigned i = threadIdx.x; i < sizeof(DevState) / 4; i += BS) reinterpret_cast<int32_t*>(st)[i] = 0;
+  }
   __syncthreads();
   if (bits) atomicOr(&sbits, bits);
 #pragma unroll
@@ -199,17 +207,23 @@ __global__ __launch_bounds__(BS) void k_prep_reduce(const double* __restrict__ p
 #pragma unroll
       for (int i = 1; i < BS / 64; ++i) r[k] = fmax(r[k], sh[i][k]);
     }
-    red->emax_bits = (unsigned long long)__double_as_longlong(r[0]);
-    red->edge_bits = (unsigned long long)__double_as_longlong(r[1]);
+    PrepReduce red;
+    red.emax_bits = (unsigned long long)__double_as_longlong(r[0]);
+    red.edge_bits = (unsigned long long)__double_as_longlong(r[1]);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      red->lo_key[d] = r[2 + d] > -INFINITY ? order_key(-r[2 + d]) : ~0ull;
-      red->hi_key[d] = r[5 + d] > -INFINITY ? order_key(r[5 + d]) : 0ull;
+      red.lo_key[d] = r[2 + d] > -INFINITY ? order_key(-r[2 + d]) : ~0ull;
+      red.hi_key[d] = r[5 + d] > -INFINITY ? order_key(r[5 + d]) : 0ull;
     }
-    red->bad_index = sbits;
-    red->pad = 0;
-    grid_from(red, delta, bin_size, max_cells, st);
+    sgrid = grid_from(red, delta, bin_size, max_cells);
+    if (blockIdx.x == 0) {
+      st->grid = sgrid;
+      st->flags = (sbits & 2) ? DS_NONFINITE : 0u;
+    }
   }
+  __syncthreads();
+  const int64_t nc = sgrid.ncells;
+  for (int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x; i < nc; i += (int64_t)gridDim.x * BS) cell_cnt[i] = 0;
 }
 
 // Cell index along one axis, clamped to [0, n); a NaN position (a
@@ -300,18 +314,17 @@ __device__ __forceinline__ QSlave q_slave(const Grid& g, const double lo[3], con
 // complete), the node bounding box expanded by beta_min, max(1, floor(L /
 // beta_min)) cells per axis, the dense cell table coarsened to at most
 // max_cells cells (coarser cells stay complete).
-__device__ void grid_from(const PrepReduce* __restrict__ red, double delta, double bin_size, int64_t max_cells,
-                          DevState* st) {
-  const double emax = __longlong_as_double((long long)red->emax_bits);
-  const double edge = __longlong_as_double((long long)red->edge_bits);
+__device__ Grid grid_from(const PrepReduce& red, double delta, double bin_size, int64_t max_cells) {
+  const double emax = __longlong_as_double((long long)red.emax_bits);
+  const double edge = __longlong_as_double((long long)red.edge_bits);
   double beta_min = fmax(fmax(edge, emax + delta), bin_size) * (1.0 + 0x1p-20);
   if (!(beta_min > 0.0) || !isfinite(beta_min)) beta_min = 1.0;
   Grid g;
   double L[3];
   int64_t n[3];
   for (int d = 0; d < 3; ++d) {
-    double lo = from_order_key(red->lo_key[d]);
-    double hi = from_order_key(red->hi_key[d]);
+    double lo = from_order_key(red.lo_key[d]);
+    double hi = from_order_key(red.hi_key[d]);
     if (!(lo <= hi) || !isfinite(lo) || !isfinite(hi)) { lo = 0.0; hi = 0.0; }
     g.lo[d] = lo - beta_min;
     L[d] = (hi + beta_min) - g.lo[d];
@@ -343,46 +356,42 @@ __device__ void grid_from(const PrepReduce* __restrict__ red, double delta, doub
   }
   // padded so that rounding in the box centres cannot move a centre across
   g.reach = (delta + 0.5 * emax) * (1.0 + 1e-9) + 1e-9 * beta_min;
-  st->grid = g;
-  if (red->bad_index & 2) st->flags |= DS_NONFINITE;
+  return g;
 }
 
 
-// Master keys (cell of each master box centre, master index as value); the
-// same launch clears the cell table over the grid's cells (grid-stride).
-__global__ __launch_bounds__(BS) void k_master_keys(const double* __restrict__ box, int32_t n,
-                                                     const Grid* __restrict__ gp, uint32_t* __restrict__ keys,
-                                                     uint32_t* __restrict__ vals, int2* __restrict__ range) {
-  const int64_t nc = gp->ncells;
-  for (int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x; i < nc; i += (int64_t)gridDim.x * BS)
-    range[i] = make_int2(0, 0);
+// Cell of each master box centre, and the master's place among those of its
+// cell in arrival order (the candidate lists are ordered by master index
+// afterwards, so it does not matter which order the atomics take).
+__global__ __launch_bounds__(BS) void k_cell_count(const double* __restrict__ box, int32_t n,
+                                                    const Grid* __restrict__ gp, int32_t* __restrict__ cell_cnt,
+                                                    uint32_t* __restrict__ cell, uint32_t* __restrict__ rank) {
   const int m = blockIdx.x * BS + threadIdx.x;
   if (m >= n) return;
-  const Grid g = *gp;
+  const Grid& g = *gp;
   int ix[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const double c = 0.5 * (box[(int64_t)d * n + m] + box[(int64_t)(3 + d) * n + m]);
     ix[d] = cell_coord(c, g.lo[d], g.inv_beta[d], g.n[d]);
   }
-  keys[m] = (uint32_t)(ix[0] + g.n[0] * (ix[1] + g.n[1] * ix[2]));
-  vals[m] = (uint32_t)m;
+  const uint32_t k = (uint32_t)(ix[0] + g.n[0] * (ix[1] + g.n[1] * ix[2]));
+  cell[m] = k;
+  rank[m] = (uint32_t)atomicAdd(&cell_cnt[k], 1);
 }
 
-// Cell ranges [x, y) of the cell-sorted master list from segment heads, and
-// the master boxes copied into cell order (sbox[i] = lo xyz, hi xyz of the
-// i-th sorted master) so that the candidate walks read them contiguously.
-__global__ __launch_bounds__(BS) void k_cell_ranges(const uint32_t* __restrict__ keys,
-                                                     const uint32_t* __restrict__ vals, int32_t n,
-                                                     const double* __restrict__ box_m, const Grid* __restrict__ gp,
-                                                     int2* __restrict__ range, double* __restrict__ sbox,
-                                                     uint64_t* __restrict__ qbox) {
-  const int i = blockIdx.x * BS + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t k = keys[i];
-  if (i == 0 || keys[i - 1] != k) range[k].x = i;
-  if (i == n - 1 || keys[i + 1] != k) range[k].y = i + 1;
-  const int m = (int)vals[i];
+// Masters in cell order: index vals[i] and box (sbox[i] = lo xyz, hi xyz) of
+// the i-th, so that the candidate walks read them contiguously.
+__global__ __launch_bounds__(BS) void k_cell_place(const uint32_t* __restrict__ cell,
+                                                    const uint32_t* __restrict__ rank, int32_t n,
+                                                    const double* __restrict__ box_m, const Grid* __restrict__ gp,
+                                                    const int32_t* __restrict__ cell_start,
+                                                    uint32_t* __restrict__ vals, double* __restrict__ sbox,
+                                                    uint64_t* __restrict__ qbox) {
+  const int m = blockIdx.x * BS + threadIdx.x;
+  if (m >= n) return;
+  const int64_t i = (int64_t)cell_start[cell[m]] + rank[m];
+  vals[i] = (uint32_t)m;
   double bx[6];
 #pragma unroll
   for (int j = 0; j < 6; ++j) bx[j] = box_m[(int64_t)j * n + m];
@@ -472,27 +481,19 @@ __device__ __forceinline__ void cell_window(const SlaveBox& b, const Grid& g, in
   }
 }
 
-// The cells c0[0] .. c1[0] of one (y, z) row have consecutive keys, so their
-// masters form one run [lo, hi) of the cell-sorted list (empty cells hold the
-// range (0, 0)); walking it visits them in the same order as cell by cell.
-__device__ __forceinline__ void row_run(const int2* __restrict__ range, int64_t row, int x0, int x1, int& lo,
+// The cells x0 .. x1 of one (y, z) row are consecutive, so their masters are
+// one run [lo, hi) of the cell-ordered list.
+__device__ __forceinline__ void row_run(const int32_t* __restrict__ cell_start, int64_t row, int x0, int x1, int& lo,
                                         int& hi) {
-  lo = 0x7fffffff;
-  hi = 0;
-  for (int xx = x0; xx <= x1; ++xx) {
-    const int2 r = range[row + xx];
-    if (r.y > r.x) {
-      lo = min(lo, r.x);
-      hi = max(hi, r.y);
-    }
-  }
+  lo = cell_start[row + x0];
+  hi = cell_start[row + x1 + 1];
 }
 
 // Candidates of one slave element: masters of its own and the 26 neighbouring
 // cells whose boxes touch its delta-enlarged box, in walk order; the first
 // vcap go to v[k * vs].  One lane per slave.
 __device__ __forceinline__ int walk_cells(const SlaveBox& b, const double* __restrict__ sbox,
-                                          const uint32_t* __restrict__ mvals, const int2* __restrict__ range,
+                                          const uint32_t* __restrict__ mvals, const int32_t* __restrict__ cell_start,
                                           const Grid& g, double delta, int32_t* v, int64_t vs, int vcap) {
   int c0[3], c1[3];
   cell_window(b, g, c0, c1);
@@ -500,7 +501,7 @@ __device__ __forceinline__ int walk_cells(const SlaveBox& b, const double* __res
   for (int zz = c0[2]; zz <= c1[2]; ++zz) {
     for (int yy = c0[1]; yy <= c1[1]; ++yy) {
       int lo, hi;
-      row_run(range, (int64_t)g.n[0] * (yy + (int64_t)g.n[1] * zz), c0[0], c1[0], lo, hi);
+      row_run(cell_start, (int64_t)g.n[0] * (yy + (int64_t)g.n[1] * zz), c0[0], c1[0], lo, hi);
       for (int i = lo; i < hi; ++i) {
         if (touch(b, sbox, i, delta)) {
           if (c < vcap) v[c * vs] = (int)mvals[i];
@@ -518,7 +519,7 @@ __device__ __forceinline__ int walk_cells(const SlaveBox& b, const double* __res
 // the one-lane walk, and the boxes a group reads in one step are adjacent.
 __device__ __forceinline__ int walk_cells_group(const SlaveBox& b, const double* __restrict__ sbox,
                                                 const uint64_t* __restrict__ qbox,
-                                                const uint32_t* __restrict__ mvals, const int2* __restrict__ range,
+                                                const uint32_t* __restrict__ mvals, const int32_t* __restrict__ cell_start,
                                                 const Grid& g, double delta, int32_t* v, int64_t vs, int vcap, int r,
                                                 int gshift) {
   int c0[3], c1[3];
@@ -528,22 +529,8 @@ __device__ __forceinline__ int walk_cells_group(const SlaveBox& b, const double*
   int c = 0;
   for (int zz = c0[2]; zz <= c1[2]; ++zz) {
     for (int yy = c0[1]; yy <= c1[1]; ++yy) {
-      // the run of the row's cells: the group's lanes read alternate cells
-      // and combine their bounds (the same run as row_run)
-      const int64_t row = (int64_t)g.n[0] * (yy + (int64_t)g.n[1] * zz);
-      int lo = 0x7fffffff, hi = 0;
-      for (int xx = c0[0] + r; xx <= c1[0]; xx += G) {
-        const int2 cr = range[row + xx];
-        if (cr.y > cr.x) {
-          lo = min(lo, cr.x);
-          hi = max(hi, cr.y);
-        }
-      }
-#pragma unroll
-      for (int d = 1; d < G; d <<= 1) {
-        lo = min(lo, __shfl_xor(lo, d, 64));
-        hi = max(hi, __shfl_xor(hi, d, 64));
-      }
+      int lo, hi;
+      row_run(cell_start, (int64_t)g.n[0] * (yy + (int64_t)g.n[1] * zz), c0[0], c1[0], lo, hi);
       for (int i0 = lo; i0 < hi; i0 += G) {
         const int i = i0 + r;
         const bool hit = i < hi && touch_q(b, qs, sbox, qbox, i, delta);
@@ -565,7 +552,7 @@ __global__ __launch_bounds__(BS) void k_cand_count(const double* __restrict__ bo
                                                     const double* __restrict__ sbox,
                                                     const uint64_t* __restrict__ qbox,
                                                     const uint32_t* __restrict__ mvals,
-                                                    const int2* __restrict__ range, const Grid* __restrict__ gp,
+                                                    const int32_t* __restrict__ cell_start, const Grid* __restrict__ gp,
                                                     double delta, int32_t* __restrict__ count,
                                                     int32_t* __restrict__ tmp) {
   const int64_t t = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * BS + threadIdx.x;
@@ -573,7 +560,7 @@ __global__ __launch_bounds__(BS) void k_cand_count(const double* __restrict__ bo
   if (s >= n_s) return;  // whole groups leave together
   const Grid g = *gp;
   const SlaveBox b = load_box(box_s, n_s, s);
-  const int c = walk_cells_group(b, sbox, qbox, mvals, range, g, delta, tmp + s, n_s, CTMP, r,
+  const int c = walk_cells_group(b, sbox, qbox, mvals, cell_start, g, delta, tmp + s, n_s, CTMP, r,
                                  (int)(__lane_id() & ~(G - 1)));
   if (r == 0) count[s] = c;
 }
@@ -694,12 +681,12 @@ __global__ __launch_bounds__(BS) void k_cand_fill(int32_t n_s, const int32_t* __
 // then the screening.
 __device__ __forceinline__ void fill_long(int s, int32_t n_s, int base, int c, int32_t* v, int vs,
                                           const double* __restrict__ box_s, const double* __restrict__ sbox,
-                                          const uint32_t* __restrict__ mvals, const int2* __restrict__ range,
+                                          const uint32_t* __restrict__ mvals, const int32_t* __restrict__ cell_start,
                                           const Grid& g, double delta, int32_t* __restrict__ cand_s,
                                           int32_t* __restrict__ cand_m, const double* __restrict__ sd,
                                           const double* __restrict__ md, double eps_a, uint8_t* __restrict__ nv_out,
                                           int32_t* __restrict__ flag, ScreenOut& so, int& nscr) {
-  walk_cells(load_box(box_s, n_s, s), sbox, mvals, range, g, delta, v, vs, c);
+  walk_cells(load_box(box_s, n_s, s), sbox, mvals, cell_start, g, delta, v, vs, c);
   for (int i = 1; i < c; ++i) {
     const int x = v[i * vs];
     int j = i - 1;
@@ -718,7 +705,7 @@ __device__ __forceinline__ void fill_long(int s, int32_t n_s, int base, int c, i
 __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict__ box_s, int32_t n_s,
                                                         const double* __restrict__ sbox,
                                                         const uint32_t* __restrict__ mvals,
-                                                        const int2* __restrict__ range, const Grid* __restrict__ gp,
+                                                        const int32_t* __restrict__ cell_start, const Grid* __restrict__ gp,
                                                         double delta,
                                                         const int32_t* __restrict__ off, int32_t* __restrict__ cand_s,
                                                         int32_t* __restrict__ cand_m, const double* __restrict__ sd,
@@ -740,10 +727,10 @@ __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict_
   ScreenOut so{0u, 0u};
   int nscr = 0;
   if (c <= CCAP)
-    fill_long(s, n_s, base, c, lds + threadIdx.x, BS, box_s, sbox, mvals, range, g, delta, cand_s, cand_m, sd,
+    fill_long(s, n_s, base, c, lds + threadIdx.x, BS, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd,
               md, eps_a, nv_out, flag, so, nscr);
   else
-    fill_long(s, n_s, base, c, cand_m + base, 1, box_s, sbox, mvals, range, g, delta, cand_s, cand_m, sd, md,
+    fill_long(s, n_s, base, c, cand_m + base, 1, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd, md,
               eps_a, nv_out, flag, so, nscr);
   count_degenerate(so, cnt);
   scr_cnt[s] = nscr;
@@ -751,7 +738,7 @@ __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict_
 
 }  // namespace
 
-int prep_blocks(int32_t n_el) { return n_el == 0 ? 0 : std::min(2048, (n_el + BS - 1) / BS); }
+int prep_blocks(int32_t n_el) { return n_el == 0 ? 0 : std::min(512, (n_el + BS - 1) / BS); }
 
 hipError_t launch_prep(const DeviceMesh& S, const DeviceMesh& M, double* box_s, double* sd, double* box_m,
                        double* md, double* part, hipStream_t s) {
@@ -764,23 +751,26 @@ hipError_t launch_prep(const DeviceMesh& S, const DeviceMesh& M, double* box_s, 
   return hipGetLastError();
 }
 
-hipError_t launch_prep_reduce(const double* part, int nb_s, int nb_m, PrepReduce* red, double delta,
-                              double bin_size, int64_t max_cells, DevState* st, hipStream_t s) {
-  k_prep_reduce<<<1, BS, 0, s>>>(part, nb_s, nb_m, red, delta, bin_size, max_cells, st);
+hipError_t launch_prep_reduce(const double* part, int nb_s, int nb_m, double delta, double bin_size,
+                              int64_t max_cells, DevState* st, Counters* cnt, int32_t* cell_cnt, hipStream_t s) {
+  // one workgroup per 16K cells of the capacity, at most one per compute unit
+  const unsigned nb = (unsigned)std::min<int64_t>(256, std::max<int64_t>(1, max_cells >> 14));
+  k_prep_reduce<<<nb, BS, 0, s>>>(part, nb_s, nb_m, delta, bin_size, max_cells, st, cnt, cell_cnt);
   return hipGetLastError();
 }
 
-hipError_t launch_master_keys(const double* box_m, int32_t n_m, const Grid* g, int64_t max_cells, uint32_t* keys,
-                              uint32_t* vals, int2* range, hipStream_t s) {
-  const int64_t nb = std::max<int64_t>((n_m + BS - 1) / BS, std::min<int64_t>(2048, (max_cells + BS - 1) / BS));
-  k_master_keys<<<(unsigned)std::max<int64_t>(nb, 1), BS, 0, s>>>(box_m, n_m, g, keys, vals, range);
+hipError_t launch_cell_count(const double* box_m, int32_t n_m, const Grid* g, int32_t* cell_cnt, uint32_t* cell,
+                             uint32_t* rank, hipStream_t s) {
+  if (n_m == 0) return hipSuccess;
+  k_cell_count<<<(n_m + BS - 1) / BS, BS, 0, s>>>(box_m, n_m, g, cell_cnt, cell, rank);
   return hipGetLastError();
 }
 
-hipError_t launch_cell_ranges(const uint32_t* keys, const uint32_t* vals, int32_t n, const double* box_m,
-                              const Grid* g, int2* range, double* sbox, uint64_t* qbox, hipStream_t s) {
+hipError_t launch_cell_place(const uint32_t* cell, const uint32_t* rank, int32_t n, const double* box_m,
+                             const Grid* g, const int32_t* cell_start, uint32_t* vals, double* sbox, uint64_t* qbox,
+                             hipStream_t s) {
   if (n == 0) return hipSuccess;
-  k_cell_ranges<<<(n + BS - 1) / BS, BS, 0, s>>>(keys, vals, n, box_m, g, range, sbox, qbox);
+  k_cell_place<<<(n + BS - 1) / BS, BS, 0, s>>>(cell, rank, n, box_m, g, cell_start, vals, sbox, qbox);
   return hipGetLastError();
 }
 
@@ -790,22 +780,22 @@ unsigned group_blocks(int32_t n_s) { return xcd_grid((unsigned)(((int64_t)n_s * 
 
 hipError_t launch_cand_count(const double* box_s, int32_t n_s, const double* sbox, const uint64_t* qbox,
                              const uint32_t* mvals,
-                             const int2* range, const Grid* g, double delta, int32_t* count, int32_t* tmp,
+                             const int32_t* cell_start, const Grid* g, double delta, int32_t* count, int32_t* tmp,
                              hipStream_t s) {
   if (n_s == 0) return hipSuccess;
-  k_cand_count<<<group_blocks(n_s), BS, 0, s>>>(box_s, n_s, sbox, qbox, mvals, range, g, delta, count, tmp);
+  k_cand_count<<<group_blocks(n_s), BS, 0, s>>>(box_s, n_s, sbox, qbox, mvals, cell_start, g, delta, count, tmp);
   return hipGetLastError();
 }
 
 hipError_t launch_cand_fill(const double* box_s, int32_t n_s, const double* sbox, const uint32_t* mvals,
-                            const int2* range, const Grid* g, double delta, const int32_t* tmp, const int32_t* off,
+                            const int32_t* cell_start, const Grid* g, double delta, const int32_t* tmp, const int32_t* off,
                             int32_t* cand_s, int32_t* cand_m, const double* sd, const double* md, double eps_a,
                             uint8_t* nv, int32_t* flag, int32_t* scr_cnt, Counters* cnt, int64_t cap,
                             hipStream_t s) {
   if (n_s == 0) return hipSuccess;
   k_cand_fill<<<group_blocks(n_s), BS, 0, s>>>(n_s, tmp, off, cand_s, cand_m, sd, md, eps_a, nv, flag, scr_cnt, cnt,
                                                cap);
-  k_cand_fill_long<<<xcd_grid((unsigned)((n_s + BS - 1) / BS)), BS, 0, s>>>(box_s, n_s, sbox, mvals, range, g, delta,
+  k_cand_fill_long<<<xcd_grid((unsigned)((n_s + BS - 1) / BS)), BS, 0, s>>>(box_s, n_s, sbox, mvals, cell_start, g, delta,
                                                                             off, cand_s, cand_m, sd, md, eps_a, nv,
                                                                             flag, scr_cnt, cnt, cap);
   return hipGetLastError();
