@@ -179,8 +179,7 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   }
   A.take(c->blk, 288 * P);
   A.take(c->gpair, 192 * P);
-  A.take(c->mp_cnt, 4 * (nm + 1));
-  A.take(c->mp_cur, 4 * (nm + 1));
+  A.take(c->mp_cnt, 8 * (nm + 1));
   A.take(c->mp_off, 4 * (nm + 1));
   A.take(c->mp_vals, 4 * P);
   A.take(c->mp_tmp, 4 * P);
@@ -406,11 +405,9 @@ int enqueue_backward(mt_ctx* c, const double* W_D, const double* W_M, const doub
                            c->counters.as<Counters>(), st));
   }
   PhaseTimer t(c, MT_T_GRAD_REDUCE, st);
-  MT_HIP(launch_grad_slave(c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), S.n_nodes, c->pair_off.as<int32_t>(),
-                           c->gpair.as<double>(), P, gXs, st));
-  const int32_t* mo = c->mp_off.as<int32_t>();
-  MT_HIP(launch_grad_master(c->minc_off.as<int32_t>(), c->minc_list.as<int32_t>(), M.n_nodes, mo, mo + 1,
-                            c->gpair.as<double>(), P, gXm, st));
+  MT_HIP(launch_grad_nodes(c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), S.n_nodes, c->pair_off.as<int32_t>(),
+                           c->minc_off.as<int32_t>(), c->minc_list.as<int32_t>(), M.n_nodes, c->mp_off.as<int32_t>(),
+                           c->gpair.as<double>(), P, gXs, gXm, st));
   if (nodal) {
     // through the element plane normals to the nodal normals and the
     // coordinates of the neighbouring elements
@@ -682,11 +679,10 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
     MT_HIP(scan_exclusive_dev(c->maybe_flag.as<int32_t>(), c->maybe_scan.as<int32_t>(), &dst->n_screened, SC,
                               c->scan_tmp, st, ScanStage{ScanStage::PAIRS, cap.pairs, dst}));
     MT_HIP(launch_compact_pairs(c->cand_s.as<int32_t>(), c->cand_m.as<int32_t>(), c->maybe_list.as<int32_t>(),
-                                c->maybe_flag.as<int32_t>(), c->maybe_scan.as<int32_t>(), &dst->n_screened, SC,
+                                c->maybe_flag.as<int32_t>(), c->maybe_scan.as<int32_t>(), dst, SC,
                                 c->mpoly_nf.as<uint8_t>(), c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(),
-                                c->pair_nv.as<uint8_t>(), c->pair_slot.as<int32_t>(), cap.pairs, st));
-    MT_HIP(launch_pair_off(c->scr_off.as<int32_t>(), c->maybe_scan.as<int32_t>(), ns, dst,
-                           c->pair_off.as<int32_t>(), st));
+                                c->pair_nv.as<uint8_t>(), c->pair_slot.as<int32_t>(), cap.pairs,
+                                c->scr_off.as<int32_t>(), ns, c->pair_off.as<int32_t>(), st));
   }
   c->poly_gen = c->coord_gen;
   c->have_pairs = true;
@@ -935,7 +931,7 @@ int mt::ensure_master_index(mt_ctx* c, hipStream_t st) {
 int mt::build_master_index(mt_ctx* c, hipStream_t st, const Buf& scan_tmp) {
   const DeviceMesh& M = c->side[1];
   MT_HIP(launch_master_index(c->pair_m.as<int32_t>(), dev_n_pairs(c), c->cap.pairs, M.n_el, c->mp_cnt.as<int32_t>(),
-                             c->mp_cur.as<int32_t>(), c->mp_off.as<int32_t>(), c->mp_vals.as<uint32_t>(),
+                             c->mp_off.as<int32_t>(), c->mp_vals.as<uint32_t>(),
                              c->mp_tmp.as<uint32_t>(), c->mp_pos.as<int32_t>(), scan_tmp, st));
   c->have_master_index = true;
   return MT_OK;

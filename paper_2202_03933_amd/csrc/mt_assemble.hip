@@ -304,20 +304,16 @@ __device__ __forceinline__ void lower_bound4(P v, int u, const int key[4], int p
 constexpr int POS_SPAN = 4096;
 
 template <bool MCOLS>
-__global__ __launch_bounds__(BS) void k_positions(int64_t n_items, const int32_t* __restrict__ n_dev,
-                                                   const int32_t* __restrict__ pair_s,
-                                                   const int32_t* __restrict__ pair_m,
-                                                   const int32_t* __restrict__ pair_off,
-                                                   const int32_t* __restrict__ conn_s,
-                                                   const int32_t* __restrict__ conn_m,
-                                                   const int32_t* __restrict__ rowptr,
-                                                   const int32_t* __restrict__ col, int32_t* __restrict__ pos,
-                                                   int64_t pstride) {
-  __shared__ int32_t span[POS_SPAN];
-  __shared__ int32_t red[2][BS / 64];
-  const int64_t n = MCOLS ? (int64_t)*n_dev : n_items;
+__device__ __forceinline__ void block_positions(unsigned block, int64_t n, int32_t* span, int32_t (*red)[BS / 64],
+                                                const int32_t* __restrict__ pair_s,
+                                                const int32_t* __restrict__ pair_m,
+                                                const int32_t* __restrict__ pair_off,
+                                                const int32_t* __restrict__ conn_s,
+                                                const int32_t* __restrict__ conn_m,
+                                                const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+                                                int32_t* __restrict__ pos, int64_t pstride) {
   // XCD-major tiles: neighbouring pairs (and the rows they stage) share an L2
-  const int64_t tile = dyn_tile(blockIdx.x, n, BS);
+  const int64_t tile = dyn_tile(block, n, BS);
   if (tile < 0) return;  // whole workgroups past the end
   const int64_t i = tile * BS + threadIdx.x;
   bool act = i < n;
@@ -369,6 +365,29 @@ __global__ __launch_bounds__(BS) void k_positions(int64_t n_items, const int32_t
   }
 }
 
+// Both in one launch: the first d_blocks workgroups (a multiple of 8) take
+// D, the others M.
+__global__ __launch_bounds__(BS) void k_positions(unsigned d_blocks, int32_t n_s_el, const int32_t* __restrict__ n_pairs,
+                                                   const int32_t* __restrict__ pair_s,
+                                                   const int32_t* __restrict__ pair_m,
+                                                   const int32_t* __restrict__ pair_off,
+                                                   const int32_t* __restrict__ conn_s,
+                                                   const int32_t* __restrict__ conn_m,
+                                                   const int32_t* __restrict__ D_rowptr,
+                                                   const int32_t* __restrict__ D_col,
+                                                   const int32_t* __restrict__ M_rowptr,
+                                                   const int32_t* __restrict__ M_col, int32_t* __restrict__ posD,
+                                                   int32_t* __restrict__ posM, int64_t pstride) {
+  __shared__ int32_t span[POS_SPAN];
+  __shared__ int32_t red[2][BS / 64];
+  if (blockIdx.x < d_blocks)
+    block_positions<false>(blockIdx.x, n_s_el, span, red, nullptr, nullptr, pair_off, conn_s, nullptr, D_rowptr,
+                           D_col, posD, n_s_el);
+  else
+    block_positions<true>(blockIdx.x - d_blocks, *n_pairs, span, red, pair_s, pair_m, nullptr, conn_s, conn_m,
+                          M_rowptr, M_col, posM, pstride);
+}
+
 // One thread per slave node (row): the row is accumulated in a per-thread
 // LDS segment (lane-interleaved) in a fixed order and written once.
 constexpr int AB = 128;   // block of the assembly kernel
@@ -390,25 +409,23 @@ __global__ __launch_bounds__(AB) void k_assemble(const int32_t* __restrict__ inc
                    M_val, gap, acc + threadIdx.x, AB, ACAP);
 }
 
-__global__ __launch_bounds__(BS) void k_grad_slave(const int32_t* __restrict__ inc_off,
-                                                    const int32_t* __restrict__ inc_list, int32_t n,
+// Nodal gradients of both sides in one launch: the first s_blocks workgroups
+// (a multiple of 8) take the slave nodes, the others the master nodes.
+__global__ __launch_bounds__(BS) void k_grad_nodes(unsigned s_blocks, const int32_t* __restrict__ inc_off,
+                                                    const int32_t* __restrict__ inc_list, int32_t n_s,
                                                     const int32_t* __restrict__ pair_off,
+                                                    const int32_t* __restrict__ minc_off,
+                                                    const int32_t* __restrict__ minc_list, int32_t n_m,
+                                                    const int32_t* __restrict__ mstart,
                                                     const double* __restrict__ gpair, int64_t stride,
-                                                    double* __restrict__ gX) {
-  const int a = xcd_tile(blockIdx.x, gridDim.x) * BS + threadIdx.x;
-  if (a >= n) return;
-  grad_slave_row(a, n, inc_off, inc_list, pair_off, gpair, stride, gX);
-}
-
-__global__ __launch_bounds__(BS) void k_grad_master(const int32_t* __restrict__ inc_off,
-                                                     const int32_t* __restrict__ inc_list, int32_t n,
-                                                     const int32_t* __restrict__ mstart,
-                                                     const int32_t* __restrict__ mend,
-                                                     const double* __restrict__ gpair, int64_t stride,
-                                                     double* __restrict__ gX) {
-  const int b = xcd_tile(blockIdx.x, gridDim.x) * BS + threadIdx.x;
-  if (b >= n) return;
-  grad_master_row(b, n, inc_off, inc_list, mstart, mend, gpair, stride, gX);
+                                                    double* __restrict__ gXs, double* __restrict__ gXm) {
+  if (blockIdx.x < s_blocks) {
+    const int a = xcd_tile(blockIdx.x, s_blocks) * BS + threadIdx.x;
+    if (a < n_s) grad_slave_row(a, n_s, inc_off, inc_list, pair_off, gpair, stride, gXs);
+  } else {
+    const int b = xcd_tile(blockIdx.x - s_blocks, gridDim.x - s_blocks) * BS + threadIdx.x;
+    if (b < n_m) grad_master_row(b, n_m, minc_off, minc_list, mstart, mstart + 1, gpair, stride, gXm);
+  }
 }
 
 // Pairs by master element (the order the master-node gradient sums read):
@@ -612,15 +629,10 @@ hipError_t launch_pattern_positions(const int32_t* pair_s, const int32_t* pair_m
                                     const int32_t* pair_off, const int32_t* D_rowptr, const int32_t* D_col,
                                     const int32_t* M_rowptr, const int32_t* M_col, int32_t* posD, int32_t* posM,
                                     hipStream_t s) {
-  if (n_s_el > 0) {
-    k_positions<false><<<xcd_grid(grid_of(n_s_el)), BS, 0, s>>>(n_s_el, nullptr, nullptr, nullptr, pair_off, conn_s, nullptr,
-                                                      D_rowptr, D_col, posD, n_s_el);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (cap > 0)
-    k_positions<true><<<xcd_grid(grid_of(cap)), BS, 0, s>>>(cap, n_pairs, pair_s, pair_m, nullptr, conn_s, conn_m, M_rowptr,
-                                                  M_col, posM, cap);
+  const unsigned nd = xcd_grid(grid_of(n_s_el)), nm = xcd_grid(grid_of(cap));
+  if (nd + nm == 0) return hipSuccess;
+  k_positions<<<nd + nm, BS, 0, s>>>(nd, n_s_el, n_pairs, pair_s, pair_m, pair_off, conn_s, conn_m, D_rowptr, D_col,
+                                     M_rowptr, M_col, posD, posM, cap);
   return hipGetLastError();
 }
 
@@ -644,21 +656,24 @@ hipError_t launch_assemble(const int32_t* inc_off, const int32_t* inc_list, int3
   return hipGetLastError();
 }
 
-hipError_t launch_grad_slave(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
-                             const int32_t* pair_off, const double* gpair, int64_t stride, double* gX,
-                             hipStream_t s) {
-  if (n_nodes == 0) return hipSuccess;
-  k_grad_slave<<<xcd_grid(grid_of(n_nodes)), BS, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, gpair, stride, gX);
+hipError_t launch_grad_nodes(const int32_t* inc_off, const int32_t* inc_list, int32_t n_s_nodes,
+                             const int32_t* pair_off, const int32_t* minc_off, const int32_t* minc_list,
+                             int32_t n_m_nodes, const int32_t* mstart, const double* gpair, int64_t stride,
+                             double* gXs, double* gXm, hipStream_t s) {
+  const unsigned ns = xcd_grid(grid_of(n_s_nodes)), nm = xcd_grid(grid_of(n_m_nodes));
+  if (ns + nm == 0) return hipSuccess;
+  k_grad_nodes<<<ns + nm, BS, 0, s>>>(ns, inc_off, inc_list, n_s_nodes, pair_off, minc_off, minc_list, n_m_nodes,
+                                      mstart, gpair, stride, gXs, gXm);
   return hipGetLastError();
 }
 
 hipError_t launch_master_index(const int32_t* pair_m, const int32_t* n_pairs, int64_t cap, int32_t n_m_el,
-                               int32_t* cnt, int32_t* cur, int32_t* off, uint32_t* vals, uint32_t* tmp, int32_t* mpos,
+                               int32_t* cnt, int32_t* off, uint32_t* vals, uint32_t* tmp, int32_t* mpos,
                                const Buf& scan_tmp, hipStream_t s) {
   if (n_m_el == 0) return hipSuccess;
   // cnt[n_m_el] counts the long ranges; cur, after the scatter, lists them
-  hipError_t e = fill_i32(cnt, 0, (int64_t)n_m_el + 1, s);
-  if (e == hipSuccess) e = fill_i32(cur, 0, (int64_t)n_m_el + 1, s);
+  int32_t* cur = cnt + n_m_el + 1;
+  hipError_t e = fill_i32(cnt, 0, 2 * ((int64_t)n_m_el + 1), s);
   if (e != hipSuccess) return e;
   if (cap > 0) {
     k_mcount<<<std::min<unsigned>(grid_of(cap), MS_GRID), BS, 0, s>>>(pair_m, n_pairs, cnt);
@@ -672,14 +687,6 @@ hipError_t launch_master_index(const int32_t* pair_m, const int32_t* n_pairs, in
   k_msort<<<grid_of(n_m_el), BS, 0, s>>>(off, n_m_el, vals, mpos, cur, cnt + n_m_el);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   k_msort_big<<<(unsigned)std::min<int64_t>(MS_BLOCKS, n_m_el), BS, 0, s>>>(off, cur, cnt + n_m_el, vals, tmp, mpos);
-  return hipGetLastError();
-}
-
-hipError_t launch_grad_master(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
-                              const int32_t* mstart, const int32_t* mend, const double* gpair, int64_t stride,
-                              double* gX, hipStream_t s) {
-  if (n_nodes == 0) return hipSuccess;
-  k_grad_master<<<xcd_grid(grid_of(n_nodes)), BS, 0, s>>>(inc_off, inc_list, n_nodes, mstart, mend, gpair, stride, gX);
   return hipGetLastError();
 }
 

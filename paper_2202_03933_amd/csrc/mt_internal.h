@@ -233,7 +233,7 @@ struct mt_ctx {
   int64_t blk_gen = -1;    // coord_gen of the blocks in blk (mt_integrate)
   bool blk_pending = false;  // blocks computed by mt_csr_pattern, not yet assembled
   mt::Buf gpair;           // [24][pair capacity]
-  mt::Buf mp_cnt, mp_cur;  // int32 [n_m_el + 1] counting-sort scratch of the pairs-by-master index
+  mt::Buf mp_cnt;          // int32 [2][n_m_el + 1] counting-sort scratch of the pairs-by-master index
   mt::Buf mp_off;          // int32 [n_m_el + 1] range of each master element in that order
   mt::Buf mp_vals;         // uint32 [pair capacity] pairs sorted by master element
   mt::Buf mp_tmp;          // uint32 [pair capacity] merge scratch of that sort
@@ -319,12 +319,13 @@ hipError_t launch_clip_screened(const double* mdata, const double* sdata, int32_
                                 const int32_t* cand_s, const int32_t* cand_m, const int32_t* mlist,
                                 const int32_t* n_maybe, int64_t cap, uint8_t* nv, int32_t* flag2, const PolyBuf& out,
                                 Counters* cnt, hipStream_t s);
+// The pair list from the screened candidates' flags and their scan, and the
+// first pair of each slave element (pair_off[n_s + 1]).
 hipError_t launch_compact_pairs(const int32_t* cand_s, const int32_t* cand_m, const int32_t* mlist,
-                                const int32_t* flag2, const int32_t* scan2, const int32_t* n_maybe, int64_t cap_maybe,
+                                const int32_t* flag2, const int32_t* scan2, const DevState* st, int64_t cap_maybe,
                                 const uint8_t* nf, int32_t* pair_s, int32_t* pair_m, uint8_t* pair_nv,
-                                int32_t* pair_slot, int64_t cap_pairs, hipStream_t s);
-hipError_t launch_pair_off(const int32_t* scr_off, const int32_t* scan2, int32_t n_s, const DevState* st,
-                           int32_t* pair_off, hipStream_t s);
+                                int32_t* pair_slot, int64_t cap_pairs, const int32_t* scr_off, int32_t n_s,
+                                int32_t* pair_off, hipStream_t s);
 // Kernels over the pairs take the device count n_pairs (<= cap, the stride
 // of the per-pair arrays).
 hipError_t launch_pair_poly(const DeviceMesh& S, const DeviceMesh& M, const KParams& kp, const int32_t* pair_s,
@@ -367,19 +368,18 @@ hipError_t launch_assemble(const int32_t* inc_off, const int32_t* inc_list, int3
                            const int32_t* pair_off, const int32_t* D_rowptr, const int32_t* M_rowptr,
                            const int32_t* posD, int32_t n_s_el, const int32_t* posM, const double* blk,
                            int64_t blk_stride, double* D_val, double* M_val, double* gap, hipStream_t s);
-hipError_t launch_grad_slave(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
-                             const int32_t* pair_off, const double* gpair, int64_t stride, double* gX,
-                             hipStream_t s);
+// Nodal gradients from the pairs' staged components; the pairs of master
+// element m are the positions mstart[m] .. mstart[m + 1].
+hipError_t launch_grad_nodes(const int32_t* inc_off, const int32_t* inc_list, int32_t n_s_nodes,
+                             const int32_t* pair_off, const int32_t* minc_off, const int32_t* minc_list,
+                             int32_t n_m_nodes, const int32_t* mstart, const double* gpair, int64_t stride,
+                             double* gXs, double* gXm, hipStream_t s);
 // Pairs by master element: off[m] .. off[m + 1] the range of master element
 // m in vals (pair indices, ascending within the range), mpos[p] the rank of
-// pair p in that order; cnt, cur scratch of n_m_el + 1, tmp of cap.
+// pair p in that order; cnt scratch of 2 (n_m_el + 1), tmp of cap.
 hipError_t launch_master_index(const int32_t* pair_m, const int32_t* n_pairs, int64_t cap, int32_t n_m_el,
-                               int32_t* cnt, int32_t* cur, int32_t* off, uint32_t* vals, uint32_t* tmp, int32_t* mpos,
+                               int32_t* cnt, int32_t* off, uint32_t* vals, uint32_t* tmp, int32_t* mpos,
                                const Buf& scan_tmp, hipStream_t s);
-hipError_t launch_grad_master(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
-                              const int32_t* mstart, const int32_t* mend, const double* gpair, int64_t stride,
-                              double* gX, hipStream_t s);
-
 // ---- backward (mt_backward.hip) ----------------------------------------------
 // Backward of every pair: slave gradient components at gpair[c * stride + p],
 // master components at gpair[(12 + c) * stride + mpos[p]].  With the dual

@@ -116,18 +116,30 @@ __global__ __launch_bounds__(BS) void k_nv_hist(const uint8_t* __restrict__ nv, 
 
 // Pair list from the screened candidates that are pairs; each pair's polygon
 // stays where the clip stored it (entry slot[p] of the screened-candidate
-// polygon buffer).  Pairs at or past the capacity are not stored.
-__global__ __launch_bounds__(BS) void k_compact_pairs(const int32_t* __restrict__ cand_s,
+// polygon buffer).  Pairs at or past the capacity are not stored.  The
+// workgroups from list_blocks on take the first pair of each slave element:
+// the pairs among the screened candidates before its first one (both clamped
+// to what was kept).
+__global__ __launch_bounds__(BS) void k_compact_pairs(unsigned list_blocks, const int32_t* __restrict__ cand_s,
                                                        const int32_t* __restrict__ cand_m,
                                                        const int32_t* __restrict__ mlist,
                                                        const int32_t* __restrict__ flag2,
                                                        const int32_t* __restrict__ scan2,
-                                                       const int32_t* __restrict__ n_dev, int64_t cap,
+                                                       const DevState* __restrict__ st, int64_t cap,
                                                        const uint8_t* __restrict__ nf, int32_t* __restrict__ ps,
                                                        int32_t* __restrict__ pm, uint8_t* __restrict__ pnv,
-                                                       int32_t* __restrict__ slot) {
+                                                       int32_t* __restrict__ slot, const int32_t* __restrict__ scr_off,
+                                                       int32_t n_s, int32_t* __restrict__ pair_off) {
+  const int32_t n = st->n_screened;
+  if (blockIdx.x >= list_blocks) {
+    const int64_t s = (int64_t)(blockIdx.x - list_blocks) * BS + threadIdx.x;
+    if (s > n_s) return;
+    const int32_t i = min(scr_off[s], n);
+    pair_off[s] = min(scan2[i < 0 ? 0 : i], st->n_pairs);
+    return;
+  }
   const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
-  if (i >= *n_dev || !flag2[i]) return;
+  if (i >= n || !flag2[i]) return;
   const int64_t p = scan2[i];
   if (p >= cap) return;
   const int c = mlist[i];
@@ -135,17 +147,6 @@ __global__ __launch_bounds__(BS) void k_compact_pairs(const int32_t* __restrict_
   pm[p] = cand_m[c];
   pnv[p] = (uint8_t)(nf[i] & 0x7f);
   slot[p] = (int32_t)i;
-}
-
-// First pair of each slave element: pairs among the screened candidates
-// before its first one (both clamped to what was kept).
-__global__ __launch_bounds__(BS) void k_pair_off(const int32_t* __restrict__ scr_off,
-                                                  const int32_t* __restrict__ scan2, int32_t n_s,
-                                                  const DevState* __restrict__ st, int32_t* __restrict__ pair_off) {
-  const int s = blockIdx.x * BS + threadIdx.x;
-  if (s > n_s) return;
-  const int32_t i = min(scr_off[s], st->n_screened);
-  pair_off[s] = min(scan2[i < 0 ? 0 : i], st->n_pairs);
 }
 
 // Clip polygon of every pair (projection, clip and cleanup in LDS), stored
@@ -232,19 +233,13 @@ hipError_t launch_clip_screened(const double* mdata, const double* sdata, int32_
 }
 
 hipError_t launch_compact_pairs(const int32_t* cand_s, const int32_t* cand_m, const int32_t* mlist,
-                                const int32_t* flag2, const int32_t* scan2, const int32_t* n_maybe, int64_t cap_maybe,
+                                const int32_t* flag2, const int32_t* scan2, const DevState* st, int64_t cap_maybe,
                                 const uint8_t* nf, int32_t* pair_s, int32_t* pair_m, uint8_t* pair_nv,
-                                int32_t* pair_slot, int64_t cap_pairs, hipStream_t s) {
-  if (cap_maybe == 0) return hipSuccess;
-  k_compact_pairs<<<(unsigned)((cap_maybe + BS - 1) / BS), BS, 0, s>>>(cand_s, cand_m, mlist, flag2, scan2, n_maybe,
-                                                                       cap_pairs, nf, pair_s, pair_m, pair_nv,
-                                                                       pair_slot);
-  return hipGetLastError();
-}
-
-hipError_t launch_pair_off(const int32_t* scr_off, const int32_t* scan2, int32_t n_s, const DevState* st,
-                           int32_t* pair_off, hipStream_t s) {
-  k_pair_off<<<(n_s + 1 + BS - 1) / BS, BS, 0, s>>>(scr_off, scan2, n_s, st, pair_off);
+                                int32_t* pair_slot, int64_t cap_pairs, const int32_t* scr_off, int32_t n_s,
+                                int32_t* pair_off, hipStream_t s) {
+  const unsigned nl = (unsigned)((cap_maybe + BS - 1) / BS), no = (unsigned)(((int64_t)n_s + BS) / BS);
+  k_compact_pairs<<<nl + no, BS, 0, s>>>(nl, cand_s, cand_m, mlist, flag2, scan2, st, cap_pairs, nf, pair_s, pair_m,
+                                         pair_nv, pair_slot, scr_off, n_s, pair_off);
   return hipGetLastError();
 }
 
