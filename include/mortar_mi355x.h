@@ -344,6 +344,13 @@ int mt_backward(mt_ctx* ctx, const double* W_D, const double* W_M, const double*
 int mt_integrate_backward(mt_ctx* ctx, double* D_val, double* M_val, double* gap, const double* W_D,
                           const double* W_M, const double* w_g, double* gXs, double* gXm, void* stream);
 
+/* Counts of the last build and pattern (host; NULL skips, nonzeros 0 before
+ * a pattern): candidates found, pairs kept, nonzeros of D and M.
+ * Synchronises the stream of the last call only when they have not been read
+ * back since (by mt_build_pairs or mt_csr_pattern with count pointers,
+ * mt_check, or a getter).  Errors: MT_ESTATE (no build). */
+int mt_get_counts(mt_ctx* ctx, int64_t* n_cand, int64_t* n_pairs, int64_t* nnz_D, int64_t* nnz_M);
+
 /* Copy the counters of the last calls into *st (host).  Synchronises the
  * stream of the last call. */
 int mt_get_stats(mt_ctx* ctx, mt_stats* st);

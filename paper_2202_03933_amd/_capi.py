@@ -81,6 +81,7 @@ SIGNATURES = {
     "mt_integrate": (_int, [_vp, _vp, _vp, _vp, _vp]),
     "mt_backward": (_int, [_vp, _vp, _vp, _vp, _vp, _vp, _vp]),
     "mt_integrate_backward": (_int, [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),
+    "mt_get_counts": (_int, [_vp, _pi64, _pi64, _pi64, _pi64]),
     "mt_get_stats": (_int, [_vp, ctypes.POINTER(mt_stats)]),
     "mt_last_error": (ctypes.c_char_p, []),
     "mt_set_timing": (_int, [_vp, _int]),

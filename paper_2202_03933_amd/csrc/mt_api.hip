@@ -278,6 +278,17 @@ int normals_for_coords(mt_ctx* c, hipStream_t st) {
   return MT_OK;
 }
 
+// The counts of a build (and the nonzeros of its pattern) as read back.
+void set_counts(mt_ctx* c, const DevState& hs, const int32_t nnz[2]) {
+  c->n_cand = hs.n_cand;
+  c->n_maybe = hs.n_screened;
+  c->n_pairs = hs.n_pairs;
+  c->nnz_D = nnz[0];
+  c->nnz_M = nnz[1];
+  c->grid = hs.grid;
+  c->counts_known = true;
+}
+
 }  // namespace
 
 int mt::host_counts(mt_ctx* c) {
@@ -293,13 +304,7 @@ int mt::host_counts(mt_ctx* c) {
   } else {
     MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}}, c->last_stream));
   }
-  c->n_cand = hs.n_cand;
-  c->n_maybe = hs.n_screened;
-  c->n_pairs = hs.n_pairs;
-  c->nnz_D = nnz[0];
-  c->nnz_M = nnz[1];
-  c->grid = hs.grid;
-  c->counts_known = true;
+  set_counts(c, hs, nnz);
   return MT_OK;
 }
 
@@ -721,8 +726,28 @@ int mt_check(mt_ctx* c) {
   DeviceScope ds(c->device);
   DevState hs;
   Counters hc;
-  MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}, {&hc, c->counters.p, sizeof(hc)}}, c->last_stream));
+  int32_t nnz[2] = {0, 0};
+  const int32_t n = c->side[0].n_nodes;
+  if (c->have_pattern) {
+    MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}, {&hc, c->counters.p, sizeof(hc)},
+                         {&nnz[0], c->D_rowptr.as<int32_t>() + n, 4}, {&nnz[1], c->M_rowptr.as<int32_t>() + n, 4}},
+                     c->last_stream));
+  } else {
+    MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}, {&hc, c->counters.p, sizeof(hc)}}, c->last_stream));
+  }
+  set_counts(c, hs, nnz);  // the same wait serves later reads of the counts
   return device_status(hs, hc, true);
+}
+
+int mt_get_counts(mt_ctx* c, int64_t* n_cand, int64_t* n_pairs, int64_t* nnz_D, int64_t* nnz_M) {
+  if (!c) return fail(MT_EINVAL, "mt_get_counts: null");
+  if (!c->have_pairs) return fail(MT_ESTATE, "mt_get_counts: no build");
+  if (int rc = host_counts(c)) return rc;
+  if (n_cand) *n_cand = c->n_cand;
+  if (n_pairs) *n_pairs = c->n_pairs;
+  if (nnz_D) *nnz_D = c->have_pattern ? c->nnz_D : 0;
+  if (nnz_M) *nnz_M = c->have_pattern ? c->nnz_M : 0;
+  return MT_OK;
 }
 
 int mt_get_pairs(mt_ctx* c, int32_t* s, int32_t* m, uint8_t* nv, void* stream) {

@@ -321,6 +321,7 @@ struct mt_batch {
   std::vector<mt::BatchInst> h_inst;
   std::vector<int64_t> pattern_gen;  // each instance's pattern generation at mt_batch_build
   mt::BatchInst* pinned = nullptr;
+  size_t pinned_bytes = 0;
   // regions of the caller's batch workspace
   mt::Buf d_inst, d_pitems, d_qbeg, d_qnext, d_ritems_s, d_ritems_sm, counters;
   int n_pitems = 0, n_ritems_s = 0, n_ritems_sm = 0;
@@ -680,9 +681,8 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
   std::vector<WorkItem> rs, rsm;
   for (size_t i = 0; i < b->ctxs.size(); ++i) {
     mt_ctx* c = b->ctxs[i];
-    {
-      int rc2 = ensure_master_index(c, st);
-      if (!rc2 && b->nodal) rc2 = ensure_normals(c, st);
+    if (b->nodal) {
+      int rc2 = ensure_normals(c, st);
       if (rc2) return rc2;
     }
     const DeviceMesh& S = c->side[0];
@@ -737,9 +737,13 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
     B_HIP(hipMemcpy(b->d_ritems_sm.p, rsm.data(), sizeof(WorkItem) * rsm.size(), hipMemcpyHostToDevice));
   const size_t ib = sizeof(BatchInst) * b->h_inst.size();
   B_HIP(fill_i32(b->counters.as<int32_t>(), 0, sizeof(Counters) / 4, st));
-  if (b->pinned) (void)hipHostFree(b->pinned);
-  b->pinned = nullptr;
-  B_HIP(hipHostMalloc((void**)&b->pinned, ib, hipHostMallocDefault));
+  if (ib > b->pinned_bytes) {  // (kept while it is large enough: a batch is built again after every search)
+    if (b->pinned) (void)hipHostFree(b->pinned);
+    b->pinned = nullptr;
+    b->pinned_bytes = 0;
+    B_HIP(hipHostMalloc((void**)&b->pinned, ib, hipHostMallocDefault));
+    b->pinned_bytes = ib;
+  }
   std::memcpy(b->pinned, b->h_inst.data(), ib);
   B_HIP(hipMemcpy(b->d_inst.p, b->pinned, ib, hipMemcpyHostToDevice));
   rc = build_items(b, st);
@@ -793,6 +797,18 @@ int mt_batch_backward(mt_batch* b, const double* const* W_D, const double* const
     b->h_inst[i].gXm = gXm[i];
   }
   int rc = sync_instances(b, st);
+  // the pairs-by-master index of every instance that has none yet (its pattern
+  // was built without the internal streams), outside any graph of this call
+  // (recorded in a capture of the caller's, it is there once that replays
+  // and not before: not taken as built)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  B_HIP(hipStreamIsCapturing(st, &cap));
+  for (size_t i = 0; i < b->ctxs.size() && rc == MT_OK; ++i) {
+    mt_ctx* c = b->ctxs[i];
+    if (c->have_master_index) continue;
+    rc = ensure_master_index(c, st);
+    if (cap != hipStreamCaptureStatusNone) c->have_master_index = false;
+  }
   if (rc) return rc;
   rc = upload_inst(b, st);
   if (rc) return rc;

@@ -164,9 +164,7 @@ class MortarInterface:
         """Read back the counts of the last search (waits for it) and raise
         MortarError for a device-side condition (mt_check)."""
         self.check()
-        st = self.stats()
-        self.n_cand, self.n_pairs = st["n_candidates"], st["n_pairs"]
-        self._nnz = (st["nnz_D"], st["nnz_M"])
+        self._read_counts()
         self._csr = None
 
     @property
@@ -234,6 +232,12 @@ class MortarInterface:
         non-converged inverse maps)."""
         C.check(C.lib().mt_check(self.h))
 
+    def _read_counts(self):
+        n = [ctypes.c_int64() for _ in range(4)]
+        C.check(C.lib().mt_get_counts(self.h, *(ctypes.byref(x) for x in n)))
+        self.n_cand, self.n_pairs = n[0].value, n[1].value
+        self._nnz = (n[2].value, n[3].value)
+
     def _counts(self):
         if self.n_pairs is None or self.n_cand is None:
             st = self.stats()
@@ -268,9 +272,7 @@ class MortarInterface:
             return None
         a, b = ctypes.c_int64(), ctypes.c_int64()
         C.check(C.lib().mt_csr_pattern(self.h, ctypes.byref(a), ctypes.byref(b), _stream(self.stream)))
-        self._nnz = (a.value, b.value)
-        st = self.stats()
-        self.n_cand, self.n_pairs = st["n_candidates"], st["n_pairs"]
+        self._read_counts()  # the pair counts came with the nonzeros: no further wait
         return self._nnz
 
     @property
