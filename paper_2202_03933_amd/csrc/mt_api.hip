@@ -170,15 +170,17 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   if (nodal) {
     A.take(c->nrm_node, 32 * nsn);
     A.take(c->nrm_el, 32 * ns);
-    A.take(c->gn0, 24 * P);
     A.take(c->nrm_sb, 32 * ns);
     A.take(c->nrm_ub, 32 * nsn);
     A.take(c->nrm_cg, 96 * ns);
   } else {
-    for (Buf* b : {&c->nrm_node, &c->nrm_el, &c->gn0, &c->nrm_sb, &c->nrm_ub, &c->nrm_cg}) *b = Buf{};
+    for (Buf* b : {&c->nrm_node, &c->nrm_el, &c->nrm_sb, &c->nrm_ub, &c->nrm_cg}) *b = Buf{};
   }
-  A.take(c->blk, 288 * P);
-  A.take(c->gpair, 192 * P);
+  const size_t sums = 8 * (size_t)elem_sums_stride((int64_t)ns, (int64_t)P);
+  A.take(c->blk, 128 * P);
+  A.take(c->eblk, FWD_SUMS * sums);
+  A.take(c->gpair, 96 * P);
+  A.take(c->egrad, (nodal ? BWD_SUMS_NODAL : BWD_SUMS) * sums);
   A.take(c->mp_cnt, 8 * (nm + 1));
   A.take(c->mp_off, 4 * (nm + 1));
   A.take(c->mp_vals, 4 * P);
@@ -369,13 +371,14 @@ int ensure_blocks(mt_ctx* c, hipStream_t st) {
     // element-based integration: no clip polygons
     PhaseTimer t(c, MT_T_PAIR_FWD, st);
     MT_HIP(launch_elem_fwd(S, M, kparams(c->params), c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(),
-                           c->pair_off.as<int32_t>(), dev_n_pairs(c), P, c->blk.as<double>(), P,
+                           c->pair_off.as<int32_t>(), dev_n_pairs(c), P, c->blk.as<double>(), fwd_sums(c),
                            c->counters.as<Counters>(), st));
     c->blk_gen = -1;
   } else if (!(c->blk_pending && c->blk_gen == c->coord_gen)) {
     PhaseTimer t(c, MT_T_PAIR_FWD, st);
     MT_HIP(launch_pair_fwd(S, M, kparams(c->params), c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(),
-                           dev_n_pairs(c), P, poly_buf(c), c->blk.as<double>(), P, c->counters.as<Counters>(), st));
+                           dev_n_pairs(c), P, poly_buf(c), c->blk.as<double>(), fwd_sums(c),
+                           c->counters.as<Counters>(), st));
     c->blk_gen = c->coord_gen;
   }
   c->blk_pending = false;
@@ -386,8 +389,9 @@ int enqueue_assemble(mt_ctx* c, double* D_val, double* M_val, double* gap, hipSt
   const DeviceMesh& S = c->side[0];
   PhaseTimer t(c, MT_T_ASSEMBLE, st);
   MT_HIP(launch_assemble(c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), S.n_nodes, c->pair_off.as<int32_t>(),
-                         c->D_rowptr.as<int32_t>(), c->M_rowptr.as<int32_t>(), c->posD.as<int32_t>(), S.n_el,
-                         c->posM.as<int32_t>(), c->blk.as<double>(), c->cap.pairs, D_val, M_val, gap, st));
+                         c->D_rowptr.as<int32_t>(), c->M_rowptr.as<int32_t>(), c->posD.as<int32_t>(),
+                         c->posM.as<int32_t>(), c->blk.as<double>(), c->cap.pairs, fwd_sums(c), D_val, M_val, gap,
+                         st));
   return MT_OK;
 }
 
@@ -403,21 +407,20 @@ int enqueue_backward(mt_ctx* c, const double* W_D, const double* W_M, const doub
   {
     PhaseTimer t(c, MT_T_PAIR_BWD, st);
     const KParams kp = kparams(c->params);
-    MT_HIP(launch_pair_bwd(S, M, kp, c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(), dev_n_pairs(c), P,
-                           poly_buf(c), c->mp_pos.as<int32_t>(), c->posD.as<int32_t>(), S.n_el,
-                           c->posM.as<int32_t>(), W_D, W_M, w_g, kp.dual ? c->blk.as<double>() : nullptr,
-                           c->gpair.as<double>(), nodal ? c->gn0.as<double>() : nullptr, P,
-                           c->counters.as<Counters>(), st));
+    MT_HIP(launch_pair_bwd(S, M, kp, c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(), c->pair_off.as<int32_t>(),
+                           dev_n_pairs(c), P, poly_buf(c), c->mp_pos.as<int32_t>(), c->posD.as<int32_t>(),
+                           c->posM.as<int32_t>(), W_D, W_M, w_g, c->blk.as<double>(), fwd_sums(c),
+                           c->gpair.as<double>(), bwd_sums(c), c->counters.as<Counters>(), st));
   }
   PhaseTimer t(c, MT_T_GRAD_REDUCE, st);
   MT_HIP(launch_grad_nodes(c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), S.n_nodes, c->pair_off.as<int32_t>(),
                            c->minc_off.as<int32_t>(), c->minc_list.as<int32_t>(), M.n_nodes, c->mp_off.as<int32_t>(),
-                           c->gpair.as<double>(), P, gXs, gXm, st));
+                           c->gpair.as<double>(), P, bwd_sums(c), gXs, gXm, st));
   if (nodal) {
     // through the element plane normals to the nodal normals and the
     // coordinates of the neighbouring elements
     MT_HIP(launch_normal_chain(S, c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), c->pair_off.as<int32_t>(),
-                               c->gn0.as<double>(), P, c->nrm_node.as<double>(), c->nrm_el.as<double>(),
+                               bwd_sums(c), c->nrm_node.as<double>(), c->nrm_el.as<double>(),
                                c->nrm_sb.as<double>(), c->nrm_ub.as<double>(), c->nrm_cg.as<double>(), gXs, nullptr,
                                nullptr, st));
   }
@@ -841,7 +844,7 @@ int mt::csr_pattern(mt_ctx* c, int64_t* nnz_D, int64_t* nnz_M, hipStream_t st, b
     if (aux && blocks) {
       PhaseTimer t(c, MT_T_PAIR_FWD, c->aux);
       MT_HIP(launch_pair_fwd(S, M, kparams(c->params), c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(), np_dev, P,
-                             poly_buf(c), c->blk.as<double>(), P, c->counters.as<Counters>(), c->aux));
+                             poly_buf(c), c->blk.as<double>(), fwd_sums(c), c->counters.as<Counters>(), c->aux));
     }
     MT_HIP(launch_pattern_rows(false, c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), n,
                                c->pair_off.as<int32_t>(), c->pair_m.as<int32_t>(), S.conn, M.conn,
@@ -937,6 +940,16 @@ int mt::ensure_poly(mt_ctx* c) {
   return MT_OK;
 }
 
+mt::ElemSums mt::fwd_sums(mt_ctx* c) {
+  const int32_t n = c->side[0].n_el;
+  return ElemSums{c->eblk.as<double>(), elem_sums_stride(n, c->cap.pairs), n};
+}
+
+mt::ElemSums mt::bwd_sums(mt_ctx* c) {
+  const int32_t n = c->side[0].n_el;
+  return ElemSums{c->egrad.as<double>(), elem_sums_stride(n, c->cap.pairs), n};
+}
+
 mt::PolyBuf mt::poly_buf(mt_ctx* c) {
   return PolyBuf{c->mpoly_u.as<double>(), c->mpoly_v.as<double>(), c->mpoly_lab.as<uint8_t>(),
                  c->mpoly_nf.as<uint8_t>(), c->mpoly_stride, c->pair_slot.as<int32_t>()};
@@ -981,7 +994,7 @@ int mt_backward(mt_ctx* c, const double* W_D, const double* W_M, const double* w
     PhaseTimer t(c, MT_T_PAIR_BWD, st);
     MT_HIP(launch_pair_fwd(c->side[0], c->side[1], kparams(c->params), c->pair_s.as<int32_t>(),
                            c->pair_m.as<int32_t>(), dev_n_pairs(c), c->cap.pairs, poly_buf(c), c->blk.as<double>(),
-                           c->cap.pairs, c->counters.as<Counters>(), st));
+                           fwd_sums(c), c->counters.as<Counters>(), st));
     c->blk_gen = c->coord_gen;
   }
   return enqueue_backward(c, W_D, W_M, w_g, gXs, gXm, st);

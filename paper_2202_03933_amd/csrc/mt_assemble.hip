@@ -398,15 +398,15 @@ __global__ __launch_bounds__(AB) void k_assemble(const int32_t* __restrict__ inc
                                                   const int32_t* __restrict__ pair_off,
                                                   const int32_t* __restrict__ D_rowptr,
                                                   const int32_t* __restrict__ M_rowptr,
-                                                  const int32_t* __restrict__ posD, int32_t n_s_el,
+                                                  const int32_t* __restrict__ posD,
                                                   const int32_t* __restrict__ posM, const double* __restrict__ blk,
-                                                  int64_t stride, double* __restrict__ D_val,
+                                                  int64_t stride, ElemSums eblk, double* __restrict__ D_val,
                                                   double* __restrict__ M_val, double* __restrict__ gap) {
   __shared__ double acc[ACAP * AB];
   const int a = xcd_tile(blockIdx.x, gridDim.x) * AB + threadIdx.x;
   if (a >= n) return;
-  assemble_row_acc(a, inc_off, inc_list, pair_off, D_rowptr, M_rowptr, posD, n_s_el, posM, blk, stride, D_val,
-                   M_val, gap, acc + threadIdx.x, AB, ACAP);
+  assemble_row_acc(a, inc_off, inc_list, pair_off, D_rowptr, M_rowptr, posD, posM, blk, stride, eblk, D_val, M_val,
+                   gap, acc + threadIdx.x, AB, ACAP);
 }
 
 // Nodal gradients of both sides in one launch: the first s_blocks workgroups
@@ -417,11 +417,11 @@ __global__ __launch_bounds__(BS) void k_grad_nodes(unsigned s_blocks, const int3
                                                     const int32_t* __restrict__ minc_off,
                                                     const int32_t* __restrict__ minc_list, int32_t n_m,
                                                     const int32_t* __restrict__ mstart,
-                                                    const double* __restrict__ gpair, int64_t stride,
+                                                    const double* __restrict__ gpair, int64_t stride, ElemSums egrad,
                                                     double* __restrict__ gXs, double* __restrict__ gXm) {
   if (blockIdx.x < s_blocks) {
     const int a = xcd_tile(blockIdx.x, s_blocks) * BS + threadIdx.x;
-    if (a < n_s) grad_slave_row(a, n_s, inc_off, inc_list, pair_off, gpair, stride, gXs);
+    if (a < n_s) grad_slave_row(a, n_s, inc_off, inc_list, pair_off, egrad, gXs);
   } else {
     const int b = xcd_tile(blockIdx.x - s_blocks, gridDim.x - s_blocks) * BS + threadIdx.x;
     if (b < n_m) grad_master_row(b, n_m, minc_off, minc_list, mstart, mstart + 1, gpair, stride, gXm);
@@ -647,23 +647,24 @@ int pattern_keep_per_row() { return KD + KM; }
 int pattern_elem_list() { return EL; }
 
 hipError_t launch_assemble(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes, const int32_t* pair_off,
-                           const int32_t* D_rowptr, const int32_t* M_rowptr, const int32_t* posD, int32_t n_s_el,
-                           const int32_t* posM, const double* blk, int64_t stride, double* D_val, double* M_val,
-                           double* gap, hipStream_t s) {
+                           const int32_t* D_rowptr, const int32_t* M_rowptr, const int32_t* posD,
+                           const int32_t* posM, const double* blk, int64_t stride, const ElemSums& eblk,
+                           double* D_val, double* M_val, double* gap, hipStream_t s) {
   if (n_nodes == 0) return hipSuccess;
-  k_assemble<<<xcd_grid((unsigned)((n_nodes + AB - 1) / AB)), AB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, D_rowptr, M_rowptr, posD, n_s_el,
-                                             posM, blk, stride, D_val, M_val, gap);
+  k_assemble<<<xcd_grid((unsigned)((n_nodes + AB - 1) / AB)), AB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off,
+                                                                          D_rowptr, M_rowptr, posD, posM, blk, stride,
+                                                                          eblk, D_val, M_val, gap);
   return hipGetLastError();
 }
 
 hipError_t launch_grad_nodes(const int32_t* inc_off, const int32_t* inc_list, int32_t n_s_nodes,
                              const int32_t* pair_off, const int32_t* minc_off, const int32_t* minc_list,
                              int32_t n_m_nodes, const int32_t* mstart, const double* gpair, int64_t stride,
-                             double* gXs, double* gXm, hipStream_t s) {
+                             const ElemSums& egrad, double* gXs, double* gXm, hipStream_t s) {
   const unsigned ns = xcd_grid(grid_of(n_s_nodes)), nm = xcd_grid(grid_of(n_m_nodes));
   if (ns + nm == 0) return hipSuccess;
   k_grad_nodes<<<ns + nm, BS, 0, s>>>(ns, inc_off, inc_list, n_s_nodes, pair_off, minc_off, minc_list, n_m_nodes,
-                                      mstart, gpair, stride, gXs, gXm);
+                                      mstart, gpair, stride, egrad, gXs, gXm);
   return hipGetLastError();
 }
 

@@ -4,8 +4,8 @@
 // dynamically evolving interfaces": work is distributed over all compute
 // units regardless of which interface it belongs to).
 //
-// Work items are buckets of consecutive pairs of one instance, each taken by
-// one wavefront.  They are split into 8 contiguous queues, one per XCD; the
+// Work items are buckets of consecutive pairs of one instance (whole tiles of
+// 64), each taken by one wavefront.  They are split into 8 contiguous queues, one per XCD; the
 // wavefronts of a block start on the queue of the block's XCD (blocks are
 // dispatched round-robin over XCDs, so block b runs on XCD b % 8) and then
 // take items from the other queues, so each XCD's L2 first sees one
@@ -47,7 +47,7 @@ struct BatchInst {
   const int32_t* mpos;
   double* blk;
   double* gpair;
-  double* gn0;  // [3][stride] dL/dn0 per pair (continuous normal field), else null
+  ElemSums eblk, egrad;
   PolyBuf poly;
   Counters* cnt;  // the instance's counters (pairs lost after a coordinate update)
   // per call
@@ -132,21 +132,24 @@ __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(3))) void k
   __shared__ double stash[FWD_STASH * BSZ];
   unsigned noconv = 0;
   int qi = 0;
+  const Stash st{stash + threadIdx.x, BSZ};
   for (int it = next_item(qbeg, qnext, qi); it >= 0; it = next_item(qbeg, qnext, qi)) {
     const WorkItem w = items[it];
     const BatchInst& I = inst[w.inst];
-    for (int64_t p = w.begin + (int)(threadIdx.x & 63); p < w.end; p += 64) {
-      double D[16], Mv[16], g[4];
-      const int s = I.pair_s[p];
-      pair_forward<NQ, DUAL>(I.S, s, load_conn(I.S.conn, s), I.M, load_conn(I.M.conn, I.pair_m[p]),
-                             gpoly(I.poly, p), gpoly_nf(I.poly, p), I.kp, Stash{stash + threadIdx.x, BSZ}, D, Mv, g, noconv);
-      const int64_t st = I.stride;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) I.blk[(int64_t)k * st + p] = D[k];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) I.blk[(int64_t)(16 + k) * st + p] = Mv[k];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) I.blk[(int64_t)(32 + k) * st + p] = g[k];
+    for (int64_t base = w.begin; base < w.end; base += TILE_PAIRS) {  // (items begin on a tile)
+      wave_lds_sync();  // (the sums of the tile before have been read)
+      const int64_t p = base + (int)(threadIdx.x & 63);
+      const bool valid = p < w.end;
+      SMap ms;
+      double mu[9], Mx[12], gm[4];
+      int s = -1, prev = -1;
+      if (valid) {
+        s = I.pair_s[p];
+        prev = p > 0 ? I.pair_s[p - 1] : -1;
+        pair_moments<NQ>(I.S, s, load_conn(I.S.conn, s), I.M, load_conn(I.M.conn, I.pair_m[p]), gpoly(I.poly, p),
+                         gpoly_nf(I.poly, p), I.kp, st, ms, mu, Mx, gm, noconv);
+      }
+      store_blocks<DUAL>(ms, mu, Mx, gm, valid, s, prev, p, st, I.blk, I.stride, I.eblk);
     }
   }
   const unsigned long long nc = wave_sum_u64(noconv);
@@ -166,28 +169,6 @@ __device__ __forceinline__ void batch_weights(const BatchInst& I, int s, int4 c,
   wg[3] = I.w_g[c.w];
 }
 
-// Dual basis: gradient through the dual coefficients of every pair, from its
-// dual blocks (computed by the forward launch that precedes this one), into
-// the slave slots of gpair before the sweep (a launch of its own, so that its
-// registers do not add to those of the sweep).
-template <int BSZ, bool NODAL>
-__global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(2))) void k_batch_dual_adj(
-    const BatchInst* __restrict__ inst, const WorkItem* __restrict__ items, const int32_t* __restrict__ qbeg,
-    int32_t* qnext, Counters* cnt) {
-  int qi = 0;
-  for (int it = next_item(qbeg, qnext, qi); it >= 0; it = next_item(qbeg, qnext, qi)) {
-    const WorkItem w = items[it];
-    const BatchInst& I = inst[w.inst];
-    for (int64_t p = w.begin + (int)(threadIdx.x & 63); p < w.end; p += 64) {
-      const int s = I.pair_s[p];
-      const int4 csn = load_conn(I.S.conn, s);
-      double WD[16], WM[16], wg[4];
-      batch_weights(I, s, csn, p, WD, WM, wg);
-      pair_dual_adjoint<NODAL>(I.S, s, csn, WD, WM, wg, I.blk, I.stride, p, I.gpair, I.gn0);
-    }
-  }
-}
-
 template <int BSZ, int NQ, bool DUAL, bool NODAL>
 __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(2))) void k_batch_bwd(const BatchInst* __restrict__ inst,
                                                     const WorkItem* __restrict__ items,
@@ -195,36 +176,30 @@ __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ double stash[BWD_STASH * BSZ];
   unsigned noconv = 0;
   int qi = 0;
+  const Stash st{stash + threadIdx.x, BSZ};
   for (int it = next_item(qbeg, qnext, qi); it >= 0; it = next_item(qbeg, qnext, qi)) {
     const WorkItem w = items[it];
     const BatchInst& I = inst[w.inst];
-    const int64_t st = I.stride;
-    for (int64_t p = w.begin + (int)(threadIdx.x & 63); p < w.end; p += 64) {
-      const int s = I.pair_s[p];
-      const int4 csn = load_conn(I.S.conn, s);
-      double WD[16], WM[16], wg[4];
-      batch_weights(I, s, csn, p, WD, WM, wg);
-      double Xsb[4][3], Xmb[4][3], n0b[3];
-      pair_backward<NQ, DUAL, NODAL>(I.S, s, csn, I.M, load_conn(I.M.conn, I.pair_m[p]), gpoly(I.poly, p),
-                                     gpoly_nf(I.poly, p), I.kp, Stash{stash + threadIdx.x, BSZ}, WD, WM, wg, Xsb, Xmb, n0b,
-                                     noconv);
-      if (NODAL)
+    for (int64_t base = w.begin; base < w.end; base += TILE_PAIRS) {
+      wave_lds_sync();  // (the sums of the tile before have been read)
+      const int64_t p = base + (int)(threadIdx.x & 63);
+      const bool valid = p < w.end;
+      int s = -1, prev = -1;
+      double Xsb[4][3], n0b[3];
+      if (valid) {
+        s = I.pair_s[p];
+        prev = p > 0 ? I.pair_s[p - 1] : -1;
+        const int4 csn = load_conn(I.S.conn, s);
+        double WD[16], WM[16], wg[4];
+        batch_weights(I, s, csn, p, WD, WM, wg);
+        double Xmb[4][3];
+        pair_backward<NQ, DUAL, NODAL>(I.S, s, csn, I.M, load_conn(I.M.conn, I.pair_m[p]), gpoly(I.poly, p),
+                                       gpoly_nf(I.poly, p), I.kp, st, WD, WM, wg, Xsb, Xmb, n0b, noconv);
+        const int64_t q = I.mpos[p];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          double v = n0b[d];
-          if (DUAL) v += I.gn0[(int64_t)d * st + p];
-          I.gn0[(int64_t)d * st + p] = v;
-        }
-      const int64_t q = I.mpos[p];
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          double v = Xsb[k][d];
-          if (DUAL) v += I.gpair[(int64_t)(3 * k + d) * st + p];
-          I.gpair[(int64_t)(3 * k + d) * st + p] = v;
-          I.gpair[(int64_t)(12 + 3 * k + d) * st + q] = Xmb[k][d];
-        }
+        for (int k = 0; k < 12; ++k) I.gpair[(int64_t)k * I.stride + q] = Xmb[k / 3][k % 3];
+      }
+      store_slave_gradient<NODAL>(Xsb, n0b, valid, s, prev, p, st, I.egrad);
     }
   }
   const unsigned long long nc = wave_sum_u64(noconv);
@@ -241,8 +216,8 @@ __global__ __launch_bounds__(ROWS_PER_ITEM) void k_batch_assemble(const BatchIns
   const int a = w.begin + threadIdx.x;
   if (a >= w.end) return;
   const BatchInst& I = inst[w.inst];
-  assemble_row_acc(a, I.inc_off, I.inc_list, I.pair_off, I.D_rowptr, I.M_rowptr, I.posD, I.n_s_el, I.posM, I.blk,
-                   I.stride, I.D_val, I.M_val, I.gap, acc + threadIdx.x, ROWS_PER_ITEM, BATCH_ACAP);
+  assemble_row_acc(a, I.inc_off, I.inc_list, I.pair_off, I.D_rowptr, I.M_rowptr, I.posD, I.posM, I.blk, I.stride,
+                   I.eblk, I.D_val, I.M_val, I.gap, acc + threadIdx.x, ROWS_PER_ITEM, BATCH_ACAP);
 }
 
 __global__ __launch_bounds__(ROWS_PER_ITEM) void k_batch_grad_rows(const BatchInst* __restrict__ inst,
@@ -252,9 +227,23 @@ __global__ __launch_bounds__(ROWS_PER_ITEM) void k_batch_grad_rows(const BatchIn
   if (a >= w.end) return;
   const BatchInst& I = inst[w.inst];
   if (w.pad == 0)
-    grad_slave_row(a, I.n_s_nodes, I.inc_off, I.inc_list, I.pair_off, I.gpair, I.stride, I.gXs);
+    grad_slave_row(a, I.n_s_nodes, I.inc_off, I.inc_list, I.pair_off, I.egrad, I.gXs);
   else
     grad_master_row(a, I.n_m_nodes, I.minc_off, I.minc_list, I.mstart, I.mend, I.gpair, I.stride, I.gXm);
+}
+
+// Dual basis: the dependence of the dual coefficients on the slave nodes, one
+// lane per slave element, after the sweep; an item is a range of elements.
+template <bool NODAL>
+__global__ __launch_bounds__(ROWS_PER_ITEM) __attribute__((amdgpu_waves_per_eu(2))) void k_batch_dual_adj(
+    const BatchInst* __restrict__ inst, const WorkItem* __restrict__ items) {
+  const WorkItem w = items[blockIdx.x];
+  const int e = w.begin + threadIdx.x;
+  if (e >= w.end) return;
+  const BatchInst& I = inst[w.inst];
+  const int p0 = I.pair_off[e], p1 = I.pair_off[e + 1];
+  if (p0 == p1) return;
+  elem_dual_adjoint<NODAL>(I.S, e, p0, p1, I.posD, I.posM, I.stride, I.W_D, I.W_M, I.w_g, I.blk, I.eblk, I.egrad);
 }
 
 using PolyFn = void (*)(const BatchInst*, const WorkItem*, const int32_t*, int32_t*);
@@ -281,11 +270,6 @@ FwdFn pick_fwd(int bsz, int nq, bool dual) {
   if (bsz == 256) return fwd_kernel<256>(nq, dual);
   if (bsz == 128) return fwd_kernel<128>(nq, dual);
   return fwd_kernel<64>(nq, dual);
-}
-BwdFn pick_dual(int bsz, bool nodal) {
-  if (bsz == 256) return nodal ? k_batch_dual_adj<256, true> : k_batch_dual_adj<256, false>;
-  if (bsz == 128) return nodal ? k_batch_dual_adj<128, true> : k_batch_dual_adj<128, false>;
-  return nodal ? k_batch_dual_adj<64, true> : k_batch_dual_adj<64, false>;
 }
 BwdFn pick_bwd(int bsz, int nq, bool dual, bool nodal) {
   if (nodal) {
@@ -323,8 +307,8 @@ struct mt_batch {
   mt::BatchInst* pinned = nullptr;
   size_t pinned_bytes = 0;
   // regions of the caller's batch workspace
-  mt::Buf d_inst, d_pitems, d_qbeg, d_qnext, d_ritems_s, d_ritems_sm, counters;
-  int n_pitems = 0, n_ritems_s = 0, n_ritems_sm = 0;
+  mt::Buf d_inst, d_pitems, d_qbeg, d_qnext, d_ritems_s, d_ritems_sm, d_eitems, counters;
+  int n_pitems = 0, n_ritems_s = 0, n_ritems_sm = 0, n_eitems = 0;
   int64_t max_pitems = 0;  // pair items the workspace holds (buckets of at least MIN_BUCKET pairs)
   hipGraphExec_t g_fwd = nullptr, g_bwd = nullptr;
   hipStream_t g_fwd_stream = nullptr, g_bwd_stream = nullptr;
@@ -466,15 +450,6 @@ int launch_bwd_all(mt_batch* b, hipStream_t st) {
     if (rc) return rc;
   }
   const int bsz = b->tune.block;
-  if (b->dual) {
-    BwdFn fd = pick_dual(bsz, b->nodal);
-    const int gd = b->num_cu * resident_blocks(reinterpret_cast<const void*>(fd), bsz);
-    k_reset_queues<<<1, 64, 0, st>>>(b->d_qnext.as<int32_t>());
-    B_HIP(hipGetLastError());
-    hipLaunchKernelGGL(fd, dim3(gd), dim3(bsz), 0, st, b->d_inst.as<BatchInst>(), b->d_pitems.as<WorkItem>(),
-                       b->d_qbeg.as<int32_t>(), b->d_qnext.as<int32_t>(), b->counters.as<Counters>());
-    B_HIP(hipGetLastError());
-  }
   BwdFn f = pick_bwd(bsz, b->nq, b->dual, b->nodal);
   const int grid = b->num_cu * resident_blocks(reinterpret_cast<const void*>(f), bsz);
   k_reset_queues<<<1, 64, 0, st>>>(b->d_qnext.as<int32_t>());
@@ -482,6 +457,12 @@ int launch_bwd_all(mt_batch* b, hipStream_t st) {
   hipLaunchKernelGGL(f, dim3(grid), dim3(bsz), 0, st, b->d_inst.as<BatchInst>(), b->d_pitems.as<WorkItem>(),
                      b->d_qbeg.as<int32_t>(), b->d_qnext.as<int32_t>(), b->counters.as<Counters>());
   B_HIP(hipGetLastError());
+  if (b->dual && b->n_eitems) {
+    auto* kd = b->nodal ? k_batch_dual_adj<true> : k_batch_dual_adj<false>;
+    hipLaunchKernelGGL(kd, dim3(b->n_eitems), dim3(ROWS_PER_ITEM), 0, st, b->d_inst.as<BatchInst>(),
+                       b->d_eitems.as<WorkItem>());
+    B_HIP(hipGetLastError());
+  }
   if (b->n_ritems_sm) {
     k_batch_grad_rows<<<b->n_ritems_sm, ROWS_PER_ITEM, 0, st>>>(b->d_inst.as<BatchInst>(),
                                                                  b->d_ritems_sm.as<WorkItem>());
@@ -497,7 +478,7 @@ int launch_bwd_all(mt_batch* b, hipStream_t st) {
       double* const* gx_at = reinterpret_cast<double* const*>(rec + offsetof(BatchInst, gXs));
       const MeshPtrs* s_at = reinterpret_cast<const MeshPtrs*>(rec + offsetof(BatchInst, S));
       B_HIP(launch_normal_chain(c->side[0], c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(),
-                                c->pair_off.as<int32_t>(), c->gn0.as<double>(), c->cap.pairs,
+                                c->pair_off.as<int32_t>(), bwd_sums(c),
                                 c->nrm_node.as<double>(), c->nrm_el.as<double>(), c->nrm_sb.as<double>(),
                                 c->nrm_ub.as<double>(), c->nrm_cg.as<double>(), nullptr, gx_at, s_at, st));
     }
@@ -613,14 +594,15 @@ static int batch_check(mt_batch* b, const char* who) {
 constexpr int MIN_BUCKET = 64;  // smallest pair bucket (the autotuner's)
 
 // Layout of the batch workspace for the current instances.
-static void batch_layout(mt_batch* b, Arena& A, int64_t& max_pitems, int64_t& n_rs, int64_t& n_rsm) {
+static void batch_layout(mt_batch* b, Arena& A, int64_t& max_pitems) {
   max_pitems = 0;
-  n_rs = n_rsm = 0;
+  int64_t n_rs = 0, n_rsm = 0, n_es = 0;
   for (mt_ctx* c : b->ctxs) {
     max_pitems += (c->n_pairs + MIN_BUCKET - 1) / MIN_BUCKET;
     const int64_t rs = (c->side[0].n_nodes + ROWS_PER_ITEM - 1) / ROWS_PER_ITEM;
     n_rs += rs;
     n_rsm += rs + (c->side[1].n_nodes + ROWS_PER_ITEM - 1) / ROWS_PER_ITEM;
+    n_es += (c->side[0].n_el + ROWS_PER_ITEM - 1) / ROWS_PER_ITEM;
   }
   A.take(b->d_inst, sizeof(BatchInst) * b->ctxs.size());
   A.take(b->d_pitems, sizeof(WorkItem) * (size_t)std::max<int64_t>(1, max_pitems));
@@ -628,6 +610,7 @@ static void batch_layout(mt_batch* b, Arena& A, int64_t& max_pitems, int64_t& n_
   A.take(b->d_qnext, sizeof(int32_t) * NQUEUE);
   A.take(b->d_ritems_s, sizeof(WorkItem) * (size_t)std::max<int64_t>(1, n_rs));
   A.take(b->d_ritems_sm, sizeof(WorkItem) * (size_t)std::max<int64_t>(1, n_rsm));
+  A.take(b->d_eitems, sizeof(WorkItem) * (size_t)std::max<int64_t>(1, n_es));
   A.take(b->counters, sizeof(Counters));
 }
 
@@ -638,8 +621,8 @@ int mt_batch_workspace_size(mt_batch* b, size_t* bytes) {
   mt_batch probe;
   probe.ctxs = b->ctxs;
   Arena A;
-  int64_t a, r1, r2;
-  batch_layout(&probe, A, a, r1, r2);
+  int64_t a;
+  batch_layout(&probe, A, a);
   *bytes = A.off;
   return MT_OK;
 }
@@ -655,8 +638,7 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
   {
     Arena A;
     A.base = static_cast<char*>(ws);
-    int64_t r1, r2;
-    batch_layout(b, A, b->max_pitems, r1, r2);
+    batch_layout(b, A, b->max_pitems);
     if (A.off > ws_bytes) {
       b->built = false;
       return bfail(MT_ECAPACITY, "mt_batch_build: workspace smaller than mt_batch_workspace_size");
@@ -673,12 +655,14 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
   if (t.blocks_per_cu <= 0) t.blocks_per_cu = resident;
   t.blocks_per_cu = std::min(t.blocks_per_cu, resident);
   if (t.bucket <= 0) t.bucket = 4 * 64;
-  t.bucket = std::max(t.bucket, MIN_BUCKET);
+  // whole tiles: the sums per slave element run tile by tile whatever the
+  // item, so the values do not depend on the tuning
+  t.bucket = (std::max(t.bucket, MIN_BUCKET) + TILE_PAIRS - 1) / TILE_PAIRS * TILE_PAIRS;
   b->tune = t;
 
   b->h_inst.assign(b->ctxs.size(), BatchInst{});
   b->pattern_gen.assign(b->ctxs.size(), 0);
-  std::vector<WorkItem> rs, rsm;
+  std::vector<WorkItem> rs, rsm, es;
   for (size_t i = 0; i < b->ctxs.size(); ++i) {
     mt_ctx* c = b->ctxs[i];
     if (b->nodal) {
@@ -713,7 +697,8 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
     I.mpos = c->mp_pos.as<int32_t>();
     I.blk = c->blk.as<double>();
     I.gpair = c->gpair.as<double>();
-    I.gn0 = b->nodal ? c->gn0.as<double>() : nullptr;
+    I.eblk = fwd_sums(c);
+    I.egrad = bwd_sums(c);
     {
       int rc2 = ensure_poly(c);
       if (rc2) return rc2;
@@ -728,13 +713,18 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
     }
     for (int r = 0; r < M.n_nodes; r += ROWS_PER_ITEM)
       rsm.push_back({(int32_t)i, r, std::min(M.n_nodes, r + ROWS_PER_ITEM), 1});
+    if (b->dual)
+      for (int r = 0; r < S.n_el; r += ROWS_PER_ITEM)
+        es.push_back({(int32_t)i, r, std::min(S.n_el, r + ROWS_PER_ITEM), 0});
   }
   b->n_ritems_s = (int)rs.size();
   b->n_ritems_sm = (int)rsm.size();
+  b->n_eitems = (int)es.size();
   B_HIP(hipStreamSynchronize(st));
   if (!rs.empty()) B_HIP(hipMemcpy(b->d_ritems_s.p, rs.data(), sizeof(WorkItem) * rs.size(), hipMemcpyHostToDevice));
   if (!rsm.empty())
     B_HIP(hipMemcpy(b->d_ritems_sm.p, rsm.data(), sizeof(WorkItem) * rsm.size(), hipMemcpyHostToDevice));
+  if (!es.empty()) B_HIP(hipMemcpy(b->d_eitems.p, es.data(), sizeof(WorkItem) * es.size(), hipMemcpyHostToDevice));
   const size_t ib = sizeof(BatchInst) * b->h_inst.size();
   B_HIP(fill_i32(b->counters.as<int32_t>(), 0, sizeof(Counters) / 4, st));
   if (ib > b->pinned_bytes) {  // (kept while it is large enough: a batch is built again after every search)

@@ -10,8 +10,8 @@
 // Integrands are those of the segment-based blocks.
 //
 // One thread per pair integrates the rule points of its slave element that
-// its master takes and writes its blocks blk[c * stride + p] for the
-// assembly.
+// its master takes; its blocks are staged for the assembly as those of the
+// segments (store_blocks).
 #include <cmath>
 #include <mutex>
 
@@ -101,7 +101,8 @@ template <bool DUAL>
 __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k_elem_fwd(
     MeshPtrs S, MeshPtrs M, KParams kp, GaussTab gt, const int32_t* __restrict__ pair_s,
     const int32_t* __restrict__ pair_m, const int32_t* __restrict__ pair_off, const int32_t* __restrict__ n_dev,
-    double* __restrict__ blk, int64_t stride, Counters* cnt) {
+    double* __restrict__ blk, int64_t stride, ElemSums eblk, Counters* cnt) {
+  static_assert(BSE == TILE_PAIRS, "one wavefront per tile");
   __shared__ double sq[8][BSE];
   __shared__ double sg[8], sw[8];
   __shared__ double stash[15 * BSE];  // heights' coefficients and slave map, for the blocks
@@ -132,13 +133,13 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
     ms = qmap(Sp);
     master_quad(Xm, f, Mo);
     double R[3][3], hc[3], hm[4];
-    SMap sm;
-    pair_setup(Xs, Xm, elem_nrm(S, s), R, sm, mm, hc, hm, ou, ov);
+    SMap so;
+    pair_setup(Xs, Xm, elem_nrm(S, s), R, so, mm, hc, hm, ou, ov);
 #pragma unroll
     for (int k = 0; k < 3; ++k) st[k] = hc[k];
 #pragma unroll
     for (int k = 0; k < 4; ++k) st[3 + k] = hm[k];
-    const double sv[8] = {sm.e1u, sm.e1v, sm.e2u, sm.e2v, sm.fu, sm.fv, sm.a2, sm.j0};
+    const double sv[8] = {so.e1u, so.e1v, so.e2u, so.e2v, so.fu, so.fv, so.a2, so.j0};
 #pragma unroll
     for (int k = 0; k < 8; ++k) st[7 + k] = sv[k];
 #pragma unroll
@@ -149,6 +150,9 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
   }
   __syncthreads();
   unsigned noconv = 0;
+  SMap sm;
+  double mu[9], Mx[12], gm[4];
+  const int prev = valid && p > 0 ? pair_s[p - 1] : -1;
   if (valid) {
     const int pfirst = pair_off[s];
     const OQuad own = oquad(Mo);
@@ -160,7 +164,6 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
       d1 = ms.e1u * ms.fv - ms.fu * ms.e1v;
       d2 = ms.fu * ms.e2v - ms.e2u * ms.fv;
     }
-    double mu[9], Mx[12];
 #pragma unroll
     for (int k = 0; k < 9; ++k) mu[k] = 0.0;
 #pragma unroll
@@ -226,20 +229,12 @@ __global__ __launch_bounds__(BSE) __attribute__((amdgpu_waves_per_eu(3))) void k
         }
       }
     }
-    double D[16], Mv[16], g[4];
-    {
-      const Stash sb = st.back();
-      const double hc[3] = {sb[0], sb[1], sb[2]}, hm[4] = {sb[3], sb[4], sb[5], sb[6]};
-      const SMap sm{sb[7], sb[8], sb[9], sb[10], sb[11], sb[12], sb[13], sb[14]};
-      moments_to_blocks<DUAL>(sm, mu, Mx, hc, hm, D, Mv, g);
-    }
-#pragma unroll
-    for (int k = 0; k < 16; ++k) blk[(int64_t)k * stride + p] = D[k];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) blk[(int64_t)(16 + k) * stride + p] = Mv[k];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) blk[(int64_t)(32 + k) * stride + p] = g[k];
+    const Stash sb = st.back();
+    const double hc[3] = {sb[0], sb[1], sb[2]}, hm[4] = {sb[3], sb[4], sb[5], sb[6]};
+    sm = SMap{sb[7], sb[8], sb[9], sb[10], sb[11], sb[12], sb[13], sb[14]};
+    gap_moments(mu, Mx, hc, hm, gm);
   }
+  store_blocks<DUAL>(sm, mu, Mx, gm, valid, s, prev, p, st, blk, stride, eblk);
   const unsigned long long nc = wave_sum_u64(noconv);
   if (threadIdx.x == 0 && nc) atomicAdd(&cnt->noconv, nc);
 }
@@ -291,7 +286,7 @@ void gauss_table(int n, GaussTab& t) {
 
 hipError_t launch_elem_fwd(const DeviceMesh& S, const DeviceMesh& M, const KParams& kp, const int32_t* pair_s,
                            const int32_t* pair_m, const int32_t* pair_off, const int32_t* n_pairs, int64_t cap,
-                           double* blk, int64_t stride, Counters* cnt, hipStream_t s) {
+                           double* blk, const ElemSums& eblk, Counters* cnt, hipStream_t s) {
   if (cap == 0) return hipSuccess;
   if (kp.elem < 1 || kp.elem > 8) return hipErrorInvalidValue;
   static GaussTab tabs[9];
@@ -302,9 +297,9 @@ hipError_t launch_elem_fwd(const DeviceMesh& S, const DeviceMesh& M, const KPara
   const MeshPtrs ms{S.x, S.y, S.z, S.conn, S.nrm}, mm{M.x, M.y, M.z, M.conn, nullptr};
   const unsigned nb = xcd_grid((unsigned)((cap + BSE - 1) / BSE));
   if (kp.dual)
-    k_elem_fwd<true><<<nb, BSE, 0, s>>>(ms, mm, kp, tabs[kp.elem], pair_s, pair_m, pair_off, n_pairs, blk, stride, cnt);
+    k_elem_fwd<true><<<nb, BSE, 0, s>>>(ms, mm, kp, tabs[kp.elem], pair_s, pair_m, pair_off, n_pairs, blk, cap, eblk, cnt);
   else
-    k_elem_fwd<false><<<nb, BSE, 0, s>>>(ms, mm, kp, tabs[kp.elem], pair_s, pair_m, pair_off, n_pairs, blk, stride,
+    k_elem_fwd<false><<<nb, BSE, 0, s>>>(ms, mm, kp, tabs[kp.elem], pair_s, pair_m, pair_off, n_pairs, blk, cap, eblk,
                                          cnt);
   return hipGetLastError();
 }

@@ -121,6 +121,23 @@ struct PolyBuf {
   __host__ __device__ __forceinline__ int64_t at(int64_t p) const { return slot ? (int64_t)slot[p] : p; }
 };
 
+// Quantities that a kernel over the pairs sums per slave element (the pairs
+// are sorted by slave element, each wavefront takes 64 consecutive ones, tile
+// t the pairs 64 t .. 64 t + 63): component k of element e at v[k * stride +
+// e], the sum over e's pairs in the tile of its first pair, and for each
+// later tile t that e reaches into a further part at v[k * stride + n_el + t].
+// Elements without pairs have no entry.
+struct ElemSums {
+  double* v = nullptr;
+  int64_t stride = 0;  // elem_sums_stride(n_el, pair capacity)
+  int32_t n_el = 0;
+};
+constexpr int TILE_PAIRS = 64;
+inline int64_t elem_sums_stride(int64_t n_el, int64_t cap) { return n_el + (cap + TILE_PAIRS - 1) / TILE_PAIRS; }
+constexpr int FWD_SUMS = 20;        // D (16), gap (4)
+constexpr int BWD_SUMS = 12;        // slave node gradients; with the continuous
+constexpr int BWD_SUMS_NODAL = 15;  // normal field also dL/d(plane normal)
+
 struct KParams {
   double delta;
   double eps_d;
@@ -218,7 +235,6 @@ struct mt_ctx {
   // forward / backward staging
   mt::Buf nrm_node;        // [n_s_nodes][4] nodal normals (continuous normal field)
   mt::Buf nrm_el;          // [n_s_el][4] element plane normals
-  mt::Buf gn0;             // [3][pair capacity] dL/dn0 per pair
   mt::Buf nrm_sb, nrm_ub, nrm_cg;
   int64_t nrm_gen = -1;    // coord_gen of nrm_node / nrm_el
   // internal streams on which mt_csr_pattern computes the pair blocks (aux)
@@ -229,10 +245,12 @@ struct mt_ctx {
   hipStream_t aux2 = nullptr;
   hipEvent_t aux2_join = nullptr;
   mt::Buf aux_scan;
-  mt::Buf blk;             // [36][pair capacity]
+  mt::Buf blk;             // [16][pair capacity] local M blocks
+  mt::Buf eblk;            // ElemSums [FWD_SUMS]: D blocks and gap of the slave elements
   int64_t blk_gen = -1;    // coord_gen of the blocks in blk (mt_integrate)
   bool blk_pending = false;  // blocks computed by mt_csr_pattern, not yet assembled
-  mt::Buf gpair;           // [24][pair capacity]
+  mt::Buf gpair;           // [12][pair capacity] master components, in pairs-by-master order
+  mt::Buf egrad;           // ElemSums [BWD_SUMS or BWD_SUMS_NODAL]: slave components
   mt::Buf mp_cnt;          // int32 [2][n_m_el + 1] counting-sort scratch of the pairs-by-master index
   mt::Buf mp_off;          // int32 [n_m_el + 1] range of each master element in that order
   mt::Buf mp_vals;         // uint32 [pair capacity] pairs sorted by master element
@@ -333,7 +351,7 @@ hipError_t launch_pair_poly(const DeviceMesh& S, const DeviceMesh& M, const KPar
                             Counters* cnt, hipStream_t s);
 hipError_t launch_pair_fwd(const DeviceMesh& S, const DeviceMesh& M, const KParams& kp, const int32_t* pair_s,
                            const int32_t* pair_m, const int32_t* n_pairs, int64_t cap, const PolyBuf& poly,
-                           double* blk, int64_t blk_stride, Counters* cnt, hipStream_t s);
+                           double* blk, const ElemSums& eblk, Counters* cnt, hipStream_t s);
 
 // ---- element-based integration (mt_elements.hip) -----------------------------
 // Blocks of every pair by the kp.elem x kp.elem Gauss rule on each slave
@@ -341,7 +359,7 @@ hipError_t launch_pair_fwd(const DeviceMesh& S, const DeviceMesh& M, const KPara
 // pair_off[e + 1]).
 hipError_t launch_elem_fwd(const DeviceMesh& S, const DeviceMesh& M, const KParams& kp, const int32_t* pair_s,
                            const int32_t* pair_m, const int32_t* pair_off, const int32_t* n_pairs, int64_t cap,
-                           double* blk, int64_t stride, Counters* cnt, hipStream_t s);
+                           double* blk, const ElemSums& eblk, Counters* cnt, hipStream_t s);
 
 // ---- assembly (mt_assemble.hip) ----------------------------------------------
 hipError_t launch_inc_count(const int32_t* conn, int32_t n_el, int32_t* cnt, hipStream_t s);
@@ -366,14 +384,14 @@ int pattern_keep_per_row();
 int pattern_elem_list();
 hipError_t launch_assemble(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
                            const int32_t* pair_off, const int32_t* D_rowptr, const int32_t* M_rowptr,
-                           const int32_t* posD, int32_t n_s_el, const int32_t* posM, const double* blk,
-                           int64_t blk_stride, double* D_val, double* M_val, double* gap, hipStream_t s);
-// Nodal gradients from the pairs' staged components; the pairs of master
+                           const int32_t* posD, const int32_t* posM, const double* blk, int64_t blk_stride,
+                           const ElemSums& eblk, double* D_val, double* M_val, double* gap, hipStream_t s);
+// Nodal gradients from the staged components; the pairs of master
 // element m are the positions mstart[m] .. mstart[m + 1].
 hipError_t launch_grad_nodes(const int32_t* inc_off, const int32_t* inc_list, int32_t n_s_nodes,
                              const int32_t* pair_off, const int32_t* minc_off, const int32_t* minc_list,
                              int32_t n_m_nodes, const int32_t* mstart, const double* gpair, int64_t stride,
-                             double* gXs, double* gXm, hipStream_t s);
+                             const ElemSums& egrad, double* gXs, double* gXm, hipStream_t s);
 // Pairs by master element: off[m] .. off[m + 1] the range of master element
 // m in vals (pair indices, ascending within the range), mpos[p] the rank of
 // pair p in that order; cnt scratch of 2 (n_m_el + 1), tmp of cap.
@@ -381,16 +399,16 @@ hipError_t launch_master_index(const int32_t* pair_m, const int32_t* n_pairs, in
                                int32_t* cnt, int32_t* off, uint32_t* vals, uint32_t* tmp, int32_t* mpos,
                                const Buf& scan_tmp, hipStream_t s);
 // ---- backward (mt_backward.hip) ----------------------------------------------
-// Backward of every pair: slave gradient components at gpair[c * stride + p],
-// master components at gpair[(12 + c) * stride + mpos[p]].  With the dual
-// basis, blk holds the pairs' dual blocks [36][stride] (the gradient through
-// the dual coefficients needs them); unused otherwise.  With the continuous
-// normal field (S.nrm), gn0[d * stride + p] receives the gradient with
-// respect to the slave element's plane normal; else gn0 is null.
-hipError_t launch_pair_bwd(const DeviceMesh& S, const DeviceMesh& M, const KParams& kp, const int32_t* pair_s, const int32_t* pair_m,
-                           const int32_t* n_pairs, int64_t cap, const PolyBuf& poly, const int32_t* mpos, const int32_t* posD, int32_t n_s_el, const int32_t* posM,
+// Backward of every pair: slave gradient components summed per slave element
+// into egrad (with the continuous normal field, S.nrm, also the gradient with
+// respect to the element's plane normal), master components at
+// gpair[c * cap + mpos[p]].  With the dual basis, blk and eblk hold the dual
+// blocks (the gradient through the dual coefficients needs them).
+hipError_t launch_pair_bwd(const DeviceMesh& S, const DeviceMesh& M, const KParams& kp, const int32_t* pair_s,
+                           const int32_t* pair_m, const int32_t* pair_off, const int32_t* n_pairs, int64_t cap,
+                           const PolyBuf& poly, const int32_t* mpos, const int32_t* posD, const int32_t* posM,
                            const double* W_D, const double* W_M, const double* w_g, const double* blk,
-                           double* gpair, double* gn0, int64_t stride, Counters* cnt, hipStream_t s);
+                           const ElemSums& eblk, double* gpair, const ElemSums& egrad, Counters* cnt, hipStream_t s);
 
 // ---- continuous normal field (mt_normals.hip) --------------------------------
 struct MeshPtrs;
@@ -402,13 +420,13 @@ int ensure_normals(mt_ctx* c, hipStream_t st);
 hipError_t launch_normals(const DeviceMesh& S, const int32_t* inc_off, const int32_t* inc_list, double* nn,
                           double* ne, hipStream_t s);
 // Adds to gX (SoA [3][n_nodes]) the gradient through the element plane
-// normals, from dL/dn0 per pair (gn0[d * stride + p]); sb, ub, cg scratch of
+// normals, from dL/dn0 of the elements (components 12 .. 14 of egrad); sb, ub, cg scratch of
 // 4 n_el, 4 n_nodes and 12 n_el doubles.  With gX_at / S_at (device memory
 // holding the output pointer / the slave coordinate pointers) those are read
 // there when the kernels run, so that launches recorded in a graph follow a
 // table updated per call.
 hipError_t launch_normal_chain(const DeviceMesh& S, const int32_t* inc_off, const int32_t* inc_list,
-                               const int32_t* pair_off, const double* gn0, int64_t stride, const double* nn,
+                               const int32_t* pair_off, const ElemSums& egrad, const double* nn,
                                const double* ne, double* sb, double* ub, double* cg, double* gX,
                                double* const* gX_at, const MeshPtrs* S_at, hipStream_t s);
 
@@ -419,6 +437,9 @@ int ensure_master_index(mt_ctx* c, hipStream_t st);
 // The same on a given stream with its own scan scratch (the master incidence
 // must exist already).
 int build_master_index(mt_ctx* c, hipStream_t st, const Buf& scan_tmp);
+// The per-element sums of the forward and of the backward.
+ElemSums fwd_sums(mt_ctx* c);
+ElemSums bwd_sums(mt_ctx* c);
 // Polygon buffers of the current pair list, and their view.
 int ensure_poly(mt_ctx* c);
 PolyBuf poly_buf(mt_ctx* c);

@@ -7,12 +7,13 @@
 // sum runs in that fixed order without fused multiply-add, so the planes, and
 // with them the clip topology, are reproducible bit for bit.
 //
-// Backward: the pair kernels leave dL/dn0 per pair; the chain runs
-// element (sum over its pairs, normalisation) -> node (sum over its elements,
+// Backward: the pair kernels leave dL/dn0 per element; the chain runs
+// element (normalisation) -> node (sum over its elements,
 // normalisation) -> element corners (cross product of the two edges) -> node
 // coordinates, each stage one thread per owner, summing in a fixed order.
 #include "mt_geometry.h"
 #include "mt_internal.h"
+#include "mt_rows.h"
 
 namespace mt {
 
@@ -81,19 +82,16 @@ __global__ __launch_bounds__(BSN) void k_elem_normals(const int32_t* __restrict_
   reinterpret_cast<double4*>(ne)[e] = make_double4(vx / l, vy / l, vz / l, l);
 }
 
-// dL/ds of s = sum of the element's four nodal normals, from dL/dn0 of its
-// pairs (pairs of element e: pair_off[e] .. pair_off[e + 1], in order).
+// dL/ds of s = sum of the element's four nodal normals, from dL/dn0 of the
+// element (components 12 .. 14 of egrad).
 __global__ __launch_bounds__(BSN) void k_elem_normal_adj(int32_t n_el, const int32_t* __restrict__ pair_off,
-                                                         const double* __restrict__ gn0, int64_t stride,
-                                                         const double* __restrict__ ne, double* __restrict__ sb) {
+                                                         ElemSums egrad, const double* __restrict__ ne,
+                                                         double* __restrict__ sb) {
   const int e = blockIdx.x * BSN + threadIdx.x;
   if (e >= n_el) return;
   double g[3] = {0.0, 0.0, 0.0};
-  for (int p = pair_off[e]; p < pair_off[e + 1]; ++p) {
-    g[0] += gn0[p];
-    g[1] += gn0[stride + p];
-    g[2] += gn0[2 * stride + p];
-  }
+  const int p0 = pair_off[e], p1 = pair_off[e + 1];
+  if (p1 > p0) elem_sums<3>(egrad, BWD_SUMS, e, p0, p1, g);
   const double4 n = reinterpret_cast<const double4*>(ne)[e];
   const double ng = n.x * g[0] + n.y * g[1] + n.z * g[2];
   const double r = 1.0 / n.w;
@@ -200,11 +198,11 @@ hipError_t launch_normals(const DeviceMesh& S, const int32_t* inc_off, const int
 }
 
 hipError_t launch_normal_chain(const DeviceMesh& S, const int32_t* inc_off, const int32_t* inc_list,
-                               const int32_t* pair_off, const double* gn0, int64_t stride, const double* nn,
+                               const int32_t* pair_off, const ElemSums& egrad, const double* nn,
                                const double* ne, double* sb, double* ub, double* cg, double* gX,
                                double* const* gX_at, const MeshPtrs* S_at, hipStream_t s) {
   if (S.n_el == 0) return hipSuccess;
-  k_elem_normal_adj<<<blocks(S.n_el), BSN, 0, s>>>(S.n_el, pair_off, gn0, stride, ne, sb);
+  k_elem_normal_adj<<<blocks(S.n_el), BSN, 0, s>>>(S.n_el, pair_off, egrad, ne, sb);
   k_node_normal_adj<<<blocks(S.n_nodes), BSN, 0, s>>>(S.n_nodes, inc_off, inc_list, sb, nn, ub);
   k_corner_adj<<<blocks(S.n_el), BSN, 0, s>>>(S.x, S.y, S.z, S.conn, S.n_el, ub, cg, S_at);
   k_corner_gather<<<blocks(S.n_nodes), BSN, 0, s>>>(S.n_nodes, inc_off, inc_list, S.n_el, cg, gX, gX_at);

@@ -485,83 +485,151 @@ struct Stash {
   // the stored values in registers after all
   __device__ __forceinline__ Stash back() const { return Stash{p + launder(0), stride}; }
 };
-constexpr int FWD_STASH = 7;   // heights' coefficients
-constexpr int BWD_STASH = 16;  // the same and R
+constexpr int FWD_STASH = 13;  // heights' coefficients; then the sums per slave element
+constexpr int BWD_STASH = 16;  // heights' coefficients and R; then the sums per slave element
 
 // ---- forward -------------------------------------------------------------------
-// Blocks from the monomial moments of a quadrature: mu_ij = sum w xi1^i
-// xi2^j (i, j <= 2) and Mm[p][r] = sum w m_p(xi) m_r(eta) (Mx: its columns
-// r = 1..3; column 0 is mu's first four), with the slave map (its nodes, for
-// the dual basis) and the heights' coefficients ht:
-// D = C Dm C^T (Dm[p][r] the moment of m_p m_r), M = C Mm C^T,
-// g = C (Mm ht_m - Dm ht_s); for the dual basis Phi = A N: D, M, g <- A D, A M, A g.
-template <bool DUAL>
-__device__ __forceinline__ void moments_to_blocks(const SMap& ms, const double mu[9], const double Mx[12],
-                                                  const double hs[3], const double hm[4], double D[16],
-                                                  double M[16], double g[4]) {
-#pragma clang fp contract(fast)
-  // Dm[p][r]: monomial exponents (0,0), (1,0), (0,1), (1,1) added
-  const double Dm[16] = {mu[0], mu[1], mu[2], mu[3], mu[1], mu[4], mu[3], mu[6],
-                         mu[2], mu[3], mu[5], mu[7], mu[3], mu[6], mu[7], mu[8]};
-  const double Mm[16] = {mu[0], Mx[0], Mx[1], Mx[2], mu[1], Mx[3], Mx[4], Mx[5],
-                         mu[2], Mx[6], Mx[7], Mx[8], mu[3], Mx[9], Mx[10], Mx[11]};
-  double gm[4];
+// Sums over the pairs of each slave element within a wavefront (the lanes
+// hold 64 consecutive pairs, sorted by slave element): every lane has put its
+// N values in its column of st; the lane of an element's first pair here adds
+// up the columns of its run, in pair order.  Returns whether this lane is
+// one; the whole wavefront calls it.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int N>
+__device__ __forceinline__ bool run_sums(const Stash& st, bool valid, bool head, double v[N]) {
+  wave_lds_sync();
+  const int lane = (int)(threadIdx.x & 63);
+  const uint64_t heads = __ballot(valid && head), live = __ballot(valid);
+  if (!(valid && head)) return false;
+  // the run ends before the next head, or behind the last valid lane
+  const uint64_t above = lane == 63 ? 0ull : ~0ull << (lane + 1);
+  const uint64_t stop = (heads | ~live) & above;
+  const int len = (stop ? __builtin_ctzll(stop) : 64) - lane;
 #pragma unroll
-  for (int p = 0; p < 4; ++p)
-    gm[p] = (Mm[4 * p] * hm[0] + Mm[4 * p + 1] * hm[1] + Mm[4 * p + 2] * hm[2] + Mm[4 * p + 3] * hm[3]) -
-            (Dm[4 * p + 1] * hs[0] + Dm[4 * p + 2] * hs[1] + Dm[4 * p + 3] * hs[2]);
-  double gs[4];
-  h_apply(gm, gs);
-  double Ds[16], Ms[16];
-  h_sandwich(Dm, 0.0625, Ds);
-  h_sandwich(Mm, 0.0625, Ms);
+  for (int k = 0; k < N; ++k) v[k] = st[k];
+  for (int r = 1; r < len; ++r)
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] += st.p[k * st.stride + r];
+  return true;
+}
+
+// Entry of the sums of slave element s in the tile of pair p: the element's
+// own, or the tile's when the element's pairs began in an earlier tile
+// (first: the lane of the tile's first pair, before which the element
+// already had pairs).
+__device__ __forceinline__ int64_t sums_entry(const ElemSums& E, int s, int64_t p, bool began_before) {
+  return began_before ? (int64_t)E.n_el + p / TILE_PAIRS : (int64_t)s;
+}
+
+// Blocks of one pair from the monomial moments of its quadrature: mu_ij =
+// sum w xi1^i xi2^j (i, j <= 2) and Mm[p][r] = sum w m_p(xi) m_r(eta) (Mx:
+// its columns r = 1..3; column 0 is mu's first four): M = C Mm C^T to
+// blk[c * stride + p], and, summed over the pairs of the slave element,
+// D = C Dm C^T (Dm[p][r] the moment of m_p m_r) and g = C gm with
+// gm = Mm ht_m - Dm ht_s (ht the heights' coefficients); for the dual basis
+// Phi = A N (ms: the slave map) D, M, g <- A D, A M, A g.  Staging D and g per
+// slave element instead of per pair cuts the values written from 36 to about
+// 22 per pair at three pairs per element.  The whole wavefront calls it
+// (valid: the lane has a pair; prev: the slave element of the pair before).
+template <bool DUAL>
+__device__ __forceinline__ void store_blocks(const SMap& ms, const double mu[9], const double Mx[12],
+                                             const double gm[4], bool valid, int s, int prev, int64_t p,
+                                             const Stash& st, double* __restrict__ blk, int64_t stride,
+                                             const ElemSums& E) {
+#pragma clang fp contract(fast)
+  double A[16];
+  if (valid) {
+    const double Mm[16] = {mu[0], Mx[0], Mx[1], Mx[2], mu[1], Mx[3], Mx[4], Mx[5],
+                           mu[2], Mx[6], Mx[7], Mx[8], mu[3], Mx[9], Mx[10], Mx[11]};
+    double M[16];
+    h_sandwich(Mm, 0.0625, M);
+    if (DUAL) {
+      const IMap w = widen(ms);
+      const V2 S[4] = {map_node(w, 0), map_node(w, 1), map_node(w, 2), map_node(w, 3)};
+      dual_coefficients(S, A);
+      double Ms[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) Ms[k] = M[k];
+      const bool some = mu[0] != 0.0;  // (no segment: possibly no coefficients either)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          M[4 * j + k] =
+              some ? A[4 * j] * Ms[k] + A[4 * j + 1] * Ms[4 + k] + A[4 * j + 2] * Ms[8 + k] + A[4 * j + 3] * Ms[12 + k]
+                   : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) blk[(int64_t)k * stride + p] = M[k];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) st[k] = mu[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) st[9 + k] = gm[k];
+  }
+  const bool first = (threadIdx.x & 63) == 0;
+  double v[13];
+  if (!run_sums<13>(st, valid, first || prev != s, v)) return;
+  const double Dm[16] = {v[0], v[1], v[2], v[3], v[1], v[4], v[3], v[6],
+                         v[2], v[3], v[5], v[7], v[3], v[6], v[7], v[8]};
+  const double gv[4] = {v[9], v[10], v[11], v[12]};
+  double D[16], g[4];
+  h_sandwich(Dm, 0.0625, D);
+  h_apply(gv, g);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) g[j] *= 0.25;
   if (DUAL) {
-    const IMap w = widen(ms);
-    const V2 S[4] = {map_node(w, 0), map_node(w, 1), map_node(w, 2), map_node(w, 3)};
-    double A[16];
-    dual_coefficients(S, A);
+    double Ds[16], gs[4];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) Ds[k] = D[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) gs[k] = g[k];
+    const bool some = v[0] != 0.0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        D[4 * j + k] = A[4 * j] * Ds[k] + A[4 * j + 1] * Ds[4 + k] + A[4 * j + 2] * Ds[8 + k] + A[4 * j + 3] * Ds[12 + k];
-        M[4 * j + k] = A[4 * j] * Ms[k] + A[4 * j + 1] * Ms[4 + k] + A[4 * j + 2] * Ms[8 + k] + A[4 * j + 3] * Ms[12 + k];
-      }
-      g[j] = 0.25 * (A[4 * j] * gs[0] + A[4 * j + 1] * gs[1] + A[4 * j + 2] * gs[2] + A[4 * j + 3] * gs[3]);
+      for (int k = 0; k < 4; ++k)
+        D[4 * j + k] =
+            some ? A[4 * j] * Ds[k] + A[4 * j + 1] * Ds[4 + k] + A[4 * j + 2] * Ds[8 + k] + A[4 * j + 3] * Ds[12 + k]
+                 : 0.0;
+      g[j] = some ? A[4 * j] * gs[0] + A[4 * j + 1] * gs[1] + A[4 * j + 2] * gs[2] + A[4 * j + 3] * gs[3] : 0.0;
     }
-  } else {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      D[k] = Ds[k];
-      M[k] = Ms[k];
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) g[j] = 0.25 * gs[j];
   }
+  const int64_t at = sums_entry(E, s, p, first && prev == s);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) E.v[(int64_t)k * E.stride + at] = D[k];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) E.v[(int64_t)(16 + k) * E.stride + at] = g[k];
 }
 
-// Local blocks of pair p of slave element s from its stored polygon
-// (nf = count | flip << 7):
+// gm of a pair from its moments and the heights' coefficients.
+__device__ __forceinline__ void gap_moments(const double mu[9], const double Mx[12], const double hs[3],
+                                            const double hm[4], double gm[4]) {
+#pragma clang fp contract(fast)
+  const double D1[4] = {mu[1], mu[4], mu[3], mu[6]}, D2[4] = {mu[2], mu[3], mu[5], mu[7]},
+               D3[4] = {mu[3], mu[6], mu[7], mu[8]};
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+    gm[p] = (mu[p] * hm[0] + Mx[3 * p] * hm[1] + Mx[3 * p + 1] * hm[2] + Mx[3 * p + 2] * hm[3]) -
+            (D1[p] * hs[0] + D2[p] * hs[1] + D3[p] * hs[2]);
+}
+
+// Moments of pair p of slave element s from its stored polygon
+// (nf = count | flip << 7), for
 //   D[j][k] = sum w A_t Phi_j N_k(xi),  M[j][l] = sum w A_t Phi_j N_l(eta),
-//   g[j]    = sum w A_t Phi_j (sum_l N_l(eta) hm_l - sum_k N_k(xi) hs_k),
-// over the fan triangles from vertex 0 and the rule points, through the
-// moments (moments_to_blocks).  The vertex of the next triangle is loaded
-// before the points of this one.
-template <int NQ, bool DUAL>
-__device__ __forceinline__ void pair_forward(const MeshPtrs& SM, int s, int4 cs, const MeshPtrs& MM, int4 cm,
-                                             const GPoly& P, int nf, const KParams& kp, const Stash& st,
-                                             double D[16], double M[16], double g[4], unsigned& noconv) {
+//   g[j]    = sum w A_t Phi_j (sum_l N_l(eta) hm_l - sum_k N_k(xi) hs_k)
+// (store_blocks), over the fan triangles from vertex 0 and the rule points.
+// The vertex of the next triangle is loaded before the points of this one.
+// A pair that is no segment (lost after a coordinate update) has none.
+template <int NQ>
+__device__ __forceinline__ void pair_moments(const MeshPtrs& SM, int s, int4 cs, const MeshPtrs& MM, int4 cm,
+                                             const GPoly& P, int nf, const KParams& kp, const Stash& st, SMap& ms,
+                                             double mu[9], double Mx[12], double gm[4], unsigned& noconv) {
   const int n = nf & 0x7f;
-  if (n < 3) {
-    // no segment (a pair lost after a coordinate update): no contribution, and
-    // no dual coefficients of a possibly degenerate slave element
-#pragma unroll
-    for (int k = 0; k < 16; ++k) D[k] = M[k] = 0.0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) g[k] = 0.0;
-    return;
-  }
-  SMap ms;
   IMap mm;
   double ou, ov;
   {
@@ -574,11 +642,13 @@ __device__ __forceinline__ void pair_forward(const MeshPtrs& SM, int s, int4 cs,
 #pragma unroll
     for (int k = 0; k < 4; ++k) st[3 + k] = hm[k];
   }
-  double mu[9], Mx[12];
 #pragma unroll
   for (int k = 0; k < 9; ++k) mu[k] = 0.0;
 #pragma unroll
   for (int k = 0; k < 12; ++k) Mx[k] = 0.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) gm[k] = 0.0;
+  if (n < 3) return;
   {
 #pragma clang fp contract(fast)
     const double u0 = P.U(0) - ou, v0 = P.V(0) - ov;
@@ -621,7 +691,7 @@ __device__ __forceinline__ void pair_forward(const MeshPtrs& SM, int s, int4 cs,
   }
   const Stash sb = st.back();
   const double hs[3] = {sb[0], sb[1], sb[2]}, hm[4] = {sb[3], sb[4], sb[5], sb[6]};
-  moments_to_blocks<DUAL>(ms, mu, Mx, hs, hm, D, M, g);
+  gap_moments(mu, Mx, hs, hm, gm);
 }
 
 // ---- backward ------------------------------------------------------------------
@@ -1098,6 +1168,30 @@ __device__ __forceinline__ void pair_backward(const MeshPtrs& SM, int s, int4 cs
       n0b[d] = NODAL ? nu * r0 + nv * r1 : 0.0;
     }
   }
+}
+
+// The slave components of a pair's gradient (and with the continuous normal
+// field the plane normal's), summed over the pairs of the slave element into
+// E.  The whole wavefront calls it (valid: the lane has a pair; prev: the
+// slave element of the pair before).
+template <bool NODAL>
+__device__ __forceinline__ void store_slave_gradient(const double Xsb[4][3], const double n0b[3], bool valid, int s,
+                                                     int prev, int64_t p, const Stash& st, const ElemSums& E) {
+  constexpr int N = NODAL ? BWD_SUMS_NODAL : BWD_SUMS;
+  static_assert(N <= BWD_STASH, "the sums fit the stash");
+  if (valid) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) st[k] = Xsb[k / 3][k % 3];
+    if (NODAL)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) st[12 + k] = n0b[k];
+  }
+  const bool first = (threadIdx.x & 63) == 0;
+  double v[N];
+  if (!run_sums<N>(st, valid, first || prev != s, v)) return;
+  const int64_t at = sums_entry(E, s, p, first && prev == s);
+#pragma unroll
+  for (int k = 0; k < N; ++k) E.v[(int64_t)k * E.stride + at] = v[k];
 }
 
 }  // namespace mt

@@ -3,9 +3,9 @@
 // segment-based integration of the local D, M and weighted-gap blocks.
 //
 // One lane owns one (slave, master) pair; its clip polygons live in LDS,
-// lane-interleaved.  Local blocks are staged structure-of-arrays,
-// blk[c * stride + p] for the 36 components c = [D 4x4 | M 4x4 | g 4], so
-// the stores of a wavefront are coalesced.
+// lane-interleaved.  Local M blocks are staged structure-of-arrays,
+// blk[c * stride + p], so the stores of a wavefront are coalesced; D and the
+// gap are summed per slave element first (ElemSums).
 #include <algorithm>
 
 #include "mt_pair_eval.h"
@@ -173,8 +173,8 @@ __global__ __launch_bounds__(BSC) void k_pair_poly(MeshPtrs S, MeshPtrs M, KPara
   if (st) atomicAdd(&cnt->degen_poly, 1ull);
 }
 
-// Segment-based integration of every pair from its stored polygon; local
-// blocks staged structure-of-arrays.  Blocks are mapped XCD-major:
+// Segment-based integration of every pair from its stored polygon
+// (pair_moments, store_blocks).  Blocks are mapped XCD-major:
 // consecutive blocks are dispatched to different XCDs, so block b works on
 // tile (b % 8) * ceil(nb / 8) + b / 8 and each XCD's L2 sees one contiguous
 // eighth of the pair list (neighbouring pairs share slave nodes).
@@ -183,25 +183,27 @@ __global__ __launch_bounds__(BSC) __attribute__((amdgpu_waves_per_eu(3))) void k
                                                    const int32_t* __restrict__ pair_s,
                                                    const int32_t* __restrict__ pair_m,
                                                    const int32_t* __restrict__ n_dev, PolyBuf poly,
-                                                   double* __restrict__ blk, int64_t stride, Counters* cnt) {
+                                                   double* __restrict__ blk, int64_t stride, ElemSums eblk,
+                                                   Counters* cnt) {
+  static_assert(BSC == TILE_PAIRS, "one wavefront per tile");
   __shared__ double stash[FWD_STASH * BSC];
+  const Stash st{stash + threadIdx.x, BSC};
   const int64_t n_pairs = *n_dev;
   const int64_t tile = dyn_tile(blockIdx.x, n_pairs, BSC);
   if (tile < 0) return;
   const int64_t p = tile * BSC + threadIdx.x;
+  const bool valid = p < n_pairs;
   unsigned noconv = 0;
-  if (p < n_pairs) {
-    double D[16], Mv[16], g[4];
-    const int s = pair_s[p];
-    pair_forward<NQ, DUAL>(S, s, load_conn(S.conn, s), M, load_conn(M.conn, pair_m[p]), gpoly(poly, p),
-                           gpoly_nf(poly, p), kp, Stash{stash + threadIdx.x, BSC}, D, Mv, g, noconv);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) blk[(int64_t)k * stride + p] = D[k];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) blk[(int64_t)(16 + k) * stride + p] = Mv[k];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) blk[(int64_t)(32 + k) * stride + p] = g[k];
+  SMap ms;
+  double mu[9], Mx[12], gm[4];
+  int s = -1, prev = -1;
+  if (valid) {
+    s = pair_s[p];
+    prev = p > 0 ? pair_s[p - 1] : -1;
+    pair_moments<NQ>(S, s, load_conn(S.conn, s), M, load_conn(M.conn, pair_m[p]), gpoly(poly, p), gpoly_nf(poly, p),
+                     kp, st, ms, mu, Mx, gm, noconv);
   }
+  store_blocks<DUAL>(ms, mu, Mx, gm, valid, s, prev, p, st, blk, stride, eblk);
   const unsigned long long nc = wave_sum_u64(noconv);
   if (threadIdx.x == 0 && nc) atomicAdd(&cnt->noconv, nc);
 }
@@ -255,16 +257,16 @@ hipError_t launch_pair_poly(const DeviceMesh& S, const DeviceMesh& M, const KPar
 
 hipError_t launch_pair_fwd(const DeviceMesh& S, const DeviceMesh& M, const KParams& kp, const int32_t* pair_s,
                            const int32_t* pair_m, const int32_t* n_pairs, int64_t cap, const PolyBuf& poly,
-                           double* blk, int64_t stride, Counters* cnt, hipStream_t s) {
+                           double* blk, const ElemSums& eblk, Counters* cnt, hipStream_t s) {
   if (cap == 0) return hipSuccess;
   const unsigned nb = xcd_grid((unsigned)((cap + BSC - 1) / BSC));
   const MeshPtrs ms{S.x, S.y, S.z, S.conn, S.nrm}, mm{M.x, M.y, M.z, M.conn, nullptr};
   if (kp.rule == 3) {
-    if (kp.dual) k_pair_fwd<3, true><<<nb, BSC, 0, s>>>(ms, mm, kp, pair_s, pair_m, n_pairs, poly, blk, stride, cnt);
-    else k_pair_fwd<3, false><<<nb, BSC, 0, s>>>(ms, mm, kp, pair_s, pair_m, n_pairs, poly, blk, stride, cnt);
+    if (kp.dual) k_pair_fwd<3, true><<<nb, BSC, 0, s>>>(ms, mm, kp, pair_s, pair_m, n_pairs, poly, blk, cap, eblk, cnt);
+    else k_pair_fwd<3, false><<<nb, BSC, 0, s>>>(ms, mm, kp, pair_s, pair_m, n_pairs, poly, blk, cap, eblk, cnt);
   } else {
-    if (kp.dual) k_pair_fwd<7, true><<<nb, BSC, 0, s>>>(ms, mm, kp, pair_s, pair_m, n_pairs, poly, blk, stride, cnt);
-    else k_pair_fwd<7, false><<<nb, BSC, 0, s>>>(ms, mm, kp, pair_s, pair_m, n_pairs, poly, blk, stride, cnt);
+    if (kp.dual) k_pair_fwd<7, true><<<nb, BSC, 0, s>>>(ms, mm, kp, pair_s, pair_m, n_pairs, poly, blk, cap, eblk, cnt);
+    else k_pair_fwd<7, false><<<nb, BSC, 0, s>>>(ms, mm, kp, pair_s, pair_m, n_pairs, poly, blk, cap, eblk, cnt);
   }
   return hipGetLastError();
 }

@@ -1,14 +1,29 @@
 // Row-owner device functions of the deterministic assembly: one thread owns
 // one output row (slave node) or one node's gradient and adds its
 // contributions in a fixed order (incident elements ascending, then pairs in
-// (slave, master) order).  Shared by the single-interface and batched kernels.
+// (slave, master) order; what depends on the slave element alone comes summed
+// over its pairs).  Shared by the single-interface and batched kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
+#include "mt_internal.h"
+
 namespace mt {
+
+// Components k0 .. k0 + N - 1 of element e, whose pairs are p0 .. p1 - 1
+// (p1 > p0): its first part, then the parts of later tiles in order (one
+// element in about 64 / pairs per element reaches into a second tile).
+template <int N>
+__device__ __forceinline__ void elem_sums(const ElemSums& E, int k0, int e, int p0, int p1, double v[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = E.v[(int64_t)(k0 + k) * E.stride + e];
+  for (int t = p0 / TILE_PAIRS + 1; t <= (p1 - 1) / TILE_PAIRS; ++t)
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] += E.v[(int64_t)(k0 + k) * E.stride + E.n_el + t];
+}
 
 // The pairs that one node's row gathers, as one flat sequence k = 0 .. n-1:
 // the pairs of its incident elements (ascending), each element's pairs in
@@ -65,15 +80,16 @@ __device__ __forceinline__ int run_at(const RowRuns& R, int k, int& j) {
 // pairs whose loads the gradient gathers issue together
 constexpr int ROW_BATCH = 8;
 
-// Row a of D, M and the gap from the staged local blocks blk[c * stride + p].
+// Row a of D, M and the gap from the slave elements' D blocks and gaps and
+// the pairs' M blocks blk[c * stride + p].
 __device__ __forceinline__ void assemble_row(int a, const int32_t* __restrict__ inc_off,
                                              const int32_t* __restrict__ inc_list,
                                              const int32_t* __restrict__ pair_off,
                                              const int32_t* __restrict__ D_rowptr,
                                              const int32_t* __restrict__ M_rowptr,
-                                             const int32_t* __restrict__ posD, int32_t n_s_el,
-                                             const int32_t* __restrict__ posM, const double* __restrict__ blk,
-                                             int64_t stride, double* __restrict__ D_val, double* __restrict__ M_val,
+                                             const int32_t* __restrict__ posD, const int32_t* __restrict__ posM,
+                                             const double* __restrict__ blk, int64_t stride, const ElemSums& E,
+                                             double* __restrict__ D_val, double* __restrict__ M_val,
                                              double* __restrict__ gap) {
   for (int i = D_rowptr[a]; i < D_rowptr[a + 1]; ++i) D_val[i] = 0.0;
   for (int i = M_rowptr[a]; i < M_rowptr[a + 1]; ++i) M_val[i] = 0.0;
@@ -82,58 +98,56 @@ __device__ __forceinline__ void assemble_row(int a, const int32_t* __restrict__ 
     const int e = inc_list[i] >> 2, j = inc_list[i] & 3;
     const int p0 = pair_off[e], p1 = pair_off[e + 1];
     if (p0 == p1) continue;
-    int pd[4];
+    double vd[4], vg[1];
+    elem_sums<4>(E, 4 * j, e, p0, p1, vd);
+    elem_sums<1>(E, 16 + j, e, p0, p1, vg);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) pd[k] = posD[(int64_t)(j * 4 + k) * n_s_el + e];
+    for (int k = 0; k < 4; ++k) D_val[posD[(int64_t)(j * 4 + k) * E.n_el + e]] += vd[k];
+    g += vg[0];
     for (int p = p0; p < p1; ++p) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) D_val[pd[k]] += blk[(int64_t)(j * 4 + k) * stride + p];
-#pragma unroll
       for (int l = 0; l < 4; ++l)
-        M_val[posM[(int64_t)(j * 4 + l) * stride + p]] += blk[(int64_t)(16 + j * 4 + l) * stride + p];
-      g += blk[(int64_t)(32 + j) * stride + p];
+        M_val[posM[(int64_t)(j * 4 + l) * stride + p]] += blk[(int64_t)(j * 4 + l) * stride + p];
     }
   }
   gap[a] = g;
 }
 
-// One sweep over the pairs of row a (incident elements ascending, then their
+// One sweep over the incident elements of row a (ascending, then their
 // pairs), adding the D part (DP: entry q at acc[(q - d0) * astride], and the
 // gap, returned) and/or the M part (MP: entry q at acc[(q + moff) * astride]).
 template <bool DP, bool MP>
 __device__ __forceinline__ double row_sweep(int a, const int32_t* __restrict__ inc_off,
                                             const int32_t* __restrict__ inc_list,
                                             const int32_t* __restrict__ pair_off, int d0, int moff,
-                                            const int32_t* __restrict__ posD, int32_t n_s_el,
-                                            const int32_t* __restrict__ posM, const double* __restrict__ blk,
-                                            int64_t stride, double* acc, int astride) {
+                                            const int32_t* __restrict__ posD, const int32_t* __restrict__ posM,
+                                            const double* __restrict__ blk, int64_t stride, const ElemSums& E,
+                                            double* acc, int astride) {
   double g = 0.0;
   for (int i = inc_off[a]; i < inc_off[a + 1]; ++i) {
     const int e = inc_list[i] >> 2, j = inc_list[i] & 3;
     const int p0 = pair_off[e], p1 = pair_off[e + 1];
     if (p0 == p1) continue;
-    int pd[4];
     if (DP) {
+      int pd[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) pd[k] = posD[(int64_t)(j * 4 + k) * n_s_el + e] - d0;
+      for (int k = 0; k < 4; ++k) pd[k] = posD[(int64_t)(j * 4 + k) * E.n_el + e] - d0;
+      double vd[4], vg[1];
+      elem_sums<4>(E, 4 * j, e, p0, p1, vd);
+      elem_sums<1>(E, 16 + j, e, p0, p1, vg);
+      g += vg[0];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[pd[k] * astride] += vd[k];
     }
-    for (int p = p0; p < p1; ++p) {
-      double vd[4], vm[4];
-      int pm[4];
+    if (MP) {
+      for (int p = p0; p < p1; ++p) {
+        double vm[4];
+        int pm[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (DP) vd[k] = blk[(int64_t)(j * 4 + k) * stride + p];
-        if (MP) {
-          vm[k] = blk[(int64_t)(16 + j * 4 + k) * stride + p];
+        for (int k = 0; k < 4; ++k) {
+          vm[k] = blk[(int64_t)(j * 4 + k) * stride + p];
           pm[k] = posM[(int64_t)(j * 4 + k) * stride + p] + moff;
         }
-      }
-      if (DP) g += blk[(int64_t)(32 + j) * stride + p];
-      if (DP) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[pd[k] * astride] += vd[k];
-      }
-      if (MP) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[pm[k] * astride] += vm[k];
       }
@@ -155,40 +169,36 @@ __device__ __forceinline__ void assemble_row_acc(int a, const int32_t* __restric
                                                  const int32_t* __restrict__ pair_off,
                                                  const int32_t* __restrict__ D_rowptr,
                                                  const int32_t* __restrict__ M_rowptr,
-                                                 const int32_t* __restrict__ posD, int32_t n_s_el,
-                                                 const int32_t* __restrict__ posM, const double* __restrict__ blk,
-                                                 int64_t stride, double* __restrict__ D_val,
-                                                 double* __restrict__ M_val, double* __restrict__ gap, double* acc,
-                                                 int astride, int cap) {
+                                                 const int32_t* __restrict__ posD, const int32_t* __restrict__ posM,
+                                                 const double* __restrict__ blk, int64_t stride, const ElemSums& E,
+                                                 double* __restrict__ D_val, double* __restrict__ M_val,
+                                                 double* __restrict__ gap, double* acc, int astride, int cap) {
   const int d0 = D_rowptr[a], d1 = D_rowptr[a + 1];
   const int m0 = M_rowptr[a], m1 = M_rowptr[a + 1];
   const int nd = d1 - d0, nm = m1 - m0;
   double g;
   if (nd + nm <= cap) {
     for (int i = 0; i < nd + nm; ++i) acc[i * astride] = 0.0;
-    g = row_sweep<true, true>(a, inc_off, inc_list, pair_off, d0, nd - m0, posD, n_s_el, posM, blk, stride, acc,
-                              astride);
+    g = row_sweep<true, true>(a, inc_off, inc_list, pair_off, d0, nd - m0, posD, posM, blk, stride, E, acc, astride);
     for (int i = 0; i < nd; ++i) D_val[d0 + i] = acc[i * astride];
     for (int i = 0; i < nm; ++i) M_val[m0 + i] = acc[(nd + i) * astride];
   } else if (nd <= cap && nm <= cap) {
     for (int i = 0; i < nd; ++i) acc[i * astride] = 0.0;
-    g = row_sweep<true, false>(a, inc_off, inc_list, pair_off, d0, 0, posD, n_s_el, posM, blk, stride, acc,
-                               astride);
+    g = row_sweep<true, false>(a, inc_off, inc_list, pair_off, d0, 0, posD, posM, blk, stride, E, acc, astride);
     for (int i = 0; i < nd; ++i) D_val[d0 + i] = acc[i * astride];
     for (int i = 0; i < nm; ++i) acc[i * astride] = 0.0;
-    row_sweep<false, true>(a, inc_off, inc_list, pair_off, d0, -m0, posD, n_s_el, posM, blk, stride, acc, astride);
+    row_sweep<false, true>(a, inc_off, inc_list, pair_off, d0, -m0, posD, posM, blk, stride, E, acc, astride);
     for (int i = 0; i < nm; ++i) M_val[m0 + i] = acc[i * astride];
   } else {
-    assemble_row(a, inc_off, inc_list, pair_off, D_rowptr, M_rowptr, posD, n_s_el, posM, blk, stride, D_val, M_val,
-                 gap);
+    assemble_row(a, inc_off, inc_list, pair_off, D_rowptr, M_rowptr, posD, posM, blk, stride, E, D_val, M_val, gap);
     return;
   }
   gap[a] = g;
 }
 
 // Sum over the flat pair sequence of R of the three components
-// gpair[(c0 + 3 j + d) * stride + p], d = 0, 1, 2, in sequence order.
-__device__ __forceinline__ void gather3(const RowRuns& R, int c0, const double* __restrict__ gpair, int64_t stride,
+// gpair[(3 j + d) * stride + p], d = 0, 1, 2, in sequence order.
+__device__ __forceinline__ void gather3(const RowRuns& R, const double* __restrict__ gpair, int64_t stride,
                                         double& g0, double& g1, double& g2) {
   constexpr int U = ROW_BATCH;
   for (int k0 = 0; k0 < R.n; k0 += U) {
@@ -199,7 +209,7 @@ __device__ __forceinline__ void gather3(const RowRuns& R, int c0, const double* 
       int j;
       const int p = run_at(R, min(k0 + u, R.n - 1), j);
 #pragma unroll
-      for (int d = 0; d < 3; ++d) v[u][d] = gpair[(int64_t)(c0 + 3 * j + d) * stride + p];
+      for (int d = 0; d < 3; ++d) v[u][d] = gpair[(int64_t)(3 * j + d) * stride + p];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -212,31 +222,24 @@ __device__ __forceinline__ void gather3(const RowRuns& R, int c0, const double* 
   }
 }
 
-// Gradient of slave node a (structure-of-arrays gX[3 * n]).
+// Gradient of slave node a (structure-of-arrays gX[3 * n]): the sum over its
+// incident elements, ascending.
 __device__ __forceinline__ void grad_slave_row(int a, int32_t n, const int32_t* __restrict__ inc_off,
                                                const int32_t* __restrict__ inc_list,
-                                               const int32_t* __restrict__ pair_off,
-                                               const double* __restrict__ gpair, int64_t stride,
+                                               const int32_t* __restrict__ pair_off, const ElemSums& E,
                                                double* __restrict__ gX) {
-  double g0 = 0.0, g1 = 0.0, g2 = 0.0;
-  const int i0 = inc_off[a], ni = inc_off[a + 1] - i0;
-  if (ni <= ROW_RUNS) {
-    RowRuns R;
-    load_runs(i0, ni, inc_list, pair_off, pair_off + 1, R);
-    gather3(R, 0, gpair, stride, g0, g1, g2);
-  } else {
-    for (int i = i0; i < i0 + ni; ++i) {
-      const int e = inc_list[i] >> 2, j = inc_list[i] & 3;
-      for (int p = pair_off[e]; p < pair_off[e + 1]; ++p) {
-        g0 += gpair[(int64_t)(3 * j + 0) * stride + p];
-        g1 += gpair[(int64_t)(3 * j + 1) * stride + p];
-        g2 += gpair[(int64_t)(3 * j + 2) * stride + p];
-      }
-    }
+  double g[3] = {0.0, 0.0, 0.0};
+  for (int i = inc_off[a]; i < inc_off[a + 1]; ++i) {
+    const int e = inc_list[i] >> 2, j = inc_list[i] & 3;
+    const int p0 = pair_off[e], p1 = pair_off[e + 1];
+    if (p0 == p1) continue;
+    double v[3];
+    elem_sums<3>(E, 3 * j, e, p0, p1, v);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) g[d] += v[d];
   }
-  gX[a] = g0;
-  gX[(int64_t)n + a] = g1;
-  gX[2 * (int64_t)n + a] = g2;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) gX[(int64_t)d * n + a] = g[d];
 }
 
 // Gradient of master node b: the master components of the pairs are staged
@@ -253,14 +256,14 @@ __device__ __forceinline__ void grad_master_row(int b, int32_t n, const int32_t*
   if (ni <= ROW_RUNS) {
     RowRuns R;
     load_runs(i0, ni, inc_list, mstart, mend, R);
-    gather3(R, 12, gpair, stride, g0, g1, g2);
+    gather3(R, gpair, stride, g0, g1, g2);
   } else {
     for (int i = i0; i < i0 + ni; ++i) {
       const int m = inc_list[i] >> 2, l = inc_list[i] & 3;
       for (int k = mstart[m]; k < mend[m]; ++k) {
-        g0 += gpair[(int64_t)(12 + 3 * l + 0) * stride + k];
-        g1 += gpair[(int64_t)(12 + 3 * l + 1) * stride + k];
-        g2 += gpair[(int64_t)(12 + 3 * l + 2) * stride + k];
+        g0 += gpair[(int64_t)(3 * l + 0) * stride + k];
+        g1 += gpair[(int64_t)(3 * l + 1) * stride + k];
+        g2 += gpair[(int64_t)(3 * l + 2) * stride + k];
       }
     }
   }
