@@ -109,9 +109,9 @@ __global__ __launch_bounds__(BSZ) void k_batch_poly(const BatchInst* __restrict_
                                                      const WorkItem* __restrict__ items,
                                                      const int32_t* __restrict__ qbeg, int32_t* qnext) {
   __shared__ double su[CAPT * BSZ], sv[CAPT * BSZ];
-  __shared__ uint8_t sl[CAPT * BSZ], se[CAPT * BSZ];
+  __shared__ uint16_t sl[CAPT * BSZ];
   int qi = 0;
-  const LdsPoly<true> P{su + threadIdx.x, sv + threadIdx.x, sl + threadIdx.x, se + threadIdx.x, BSZ};
+  const LdsPoly P{su + threadIdx.x, sv + threadIdx.x, sl + threadIdx.x, BSZ};
   for (int it = next_item(qbeg, qnext, qi); it >= 0; it = next_item(qbeg, qnext, qi)) {
     const WorkItem w = items[it];
     const BatchInst& I = inst[w.inst];

@@ -16,14 +16,14 @@
 
 namespace mt {
 
-// Working capacities of the two clip buffers (vertices): buffer 0 holds the
-// slave polygon and the outputs of clip stages 2 and 4, buffer 1 the outputs
-// of stages 1 and 3.  A convex quad clipped by k half planes has at most
-// 4 + k vertices; two vertices of headroom absorb near-duplicates from
-// rounding.  A stage exceeding its buffer marks the candidate degenerate.
+// Working capacities of the clip (vertices): the outputs of stages 1 and 3
+// hold CAP1, those of stages 2 and 4 CAP0.  A convex quad clipped by k half
+// planes has at most 4 + k vertices; two vertices of headroom absorb
+// near-duplicates from rounding.  A stage exceeding its capacity marks the
+// candidate degenerate.
 constexpr int CAP0 = 10;
 constexpr int CAP1 = 9;
-constexpr int CAPT = CAP0 + CAP1;  // LDS vertex slots per lane
+constexpr int CAPT = CAP0;  // LDS vertex slots per lane
 
 struct V2 {
   double u, v;
@@ -161,56 +161,66 @@ __device__ __forceinline__ double quad_fan_area(const V2 p[4]) {
 __device__ __forceinline__ double linf(double du, double dv) { return fmax(fabs(du), fabs(dv)); }
 
 // ---- per-lane polygon storage in LDS ---------------------------------------
-// Two ping-pong buffers (CAP0 + CAP1 vertices) per lane, lane-interleaved so that a
-// wavefront touching vertex i of its polygons hits consecutive addresses.
-// With labels, each vertex also carries its provenance (slave node k:
-// 0x80|k, else the two lines it lies on, (la << 4) | lb, line ids 0..3 =
-// slave edges k -> k+1, 4..7 = master clip edges) and the line id of the
-// edge leaving it.
-template <bool LAB>
+// One buffer of CAPT vertices per lane, lane-interleaved so that a wavefront
+// touching vertex i of its polygons hits consecutive addresses.  Each vertex
+// carries its provenance in the low byte of lab (slave node k: 0x80|k, else
+// the two lines it lies on, (la << 4) | lb, line ids 0..3 = slave edges
+// k -> k+1, 4..7 = master clip edges) and the line id of the edge leaving it
+// in the high byte.
 struct LdsPoly {
   double* u;
   double* v;
-  uint8_t* vl;
-  uint8_t* el;
+  uint16_t* lab;
   int bs;
-  __device__ __forceinline__ int at(int b, int i) const { return ((b ? CAP0 : 0) + i) * bs; }
+  __device__ __forceinline__ void set(int i, double x, double y, int l) const {
+    u[i * bs] = x;
+    v[i * bs] = y;
+    lab[i * bs] = (uint16_t)l;
+  }
+};
+
+// A lane's polygon in registers (static indices): vertices i < n.
+struct RegPoly {
+  double u[CAP0], v[CAP0];
+  uint16_t lab[CAP0];
+  __device__ __forceinline__ void load(const LdsPoly& P, int n) {
+#pragma unroll
+    for (int i = 0; i < CAP0; ++i) {
+      u[i] = 0.0;
+      v[i] = 0.0;
+      lab[i] = 0;
+      if (i < n) {
+        u[i] = P.u[i * P.bs];
+        v[i] = P.v[i * P.bs];
+        lab[i] = P.lab[i * P.bs];
+      }
+    }
+  }
 };
 
 // Clip the slave polygon S (counter-clockwise) by the master polygon Mo
 // (counter-clockwise) with Sutherland-Hodgman: per master edge a -> b keep
 // the closed left half plane, walking subject edges P -> E from vertex 0,
 // emitting P when inside and then the crossing when the sides differ.
-// Returns the vertex count; the polygon is in buffer `res`.  Sets *ovf on
-// capacity overflow (then returns 0).
+// Returns the vertex count; the polygon is in P.  Sets *ovf on capacity
+// overflow (then returns 0).
 //
-// The first stage reads the slave polygon from registers and writes buffer
-// 1; the later stages alternate between the LDS buffers, each first reading
-// its whole input polygon into registers (one round trip of independent LDS
-// reads instead of one per edge).
+// The first stage reads the slave polygon from registers; the later stages
+// first read their whole input polygon from LDS into registers (one round
+// trip of independent LDS reads instead of one per edge), so that they can
+// write their output over it: 11.5 KB of LDS per wavefront instead of the
+// 21.9 KB of two alternating buffers, i.e. three wavefronts per SIMD instead
+// of less than two to hide those round trips.
 
 // Side value of point (u, v) for the line a -> b (>= 0: inside).
 __device__ __forceinline__ double side_of(V2 a, double dbu, double dbv, double u, double v) {
   return dbu * (v - a.v) - dbv * (u - a.u);
 }
 
-template <bool LAB>
-__device__ __forceinline__ void emit_vertex(const LdsPoly<LAB>& P, int b, int k, double u, double v, uint8_t vl,
-                                            uint8_t el) {
-  P.u[P.at(b, k)] = u;
-  P.v[P.at(b, k)] = v;
-  if (LAB) {
-    P.vl[P.at(b, k)] = vl;
-    P.el[P.at(b, k)] = el;
-  }
-}
-
-template <bool LAB>
-__device__ __forceinline__ int clip_polygon(const V2 S[4], const V2 Mo[4], const LdsPoly<LAB>& P, int& res,
-                                            bool& ovf) {
+__device__ __forceinline__ int clip_polygon(const V2 S[4], const V2 Mo[4], const LdsPoly& P, bool& ovf) {
   ovf = false;
   int n;
-  // stage 1: slave polygon (registers) against master edge 0, into buffer 1
+  // stage 1: slave polygon (registers) against master edge 0
   {
     const V2 a = Mo[0], b = Mo[1];
     const double dbu = b.u - a.u, dbv = b.v - a.v;
@@ -223,120 +233,96 @@ __device__ __forceinline__ int clip_polygon(const V2 S[4], const V2 Mo[4], const
       const int e = (j + 1) & 3;
       const bool pin = c[j] >= 0.0, ein = c[e] >= 0.0;
       if (pin) {
-        emit_vertex<LAB>(P, 1, k, S[j].u, S[j].v, (uint8_t)(0x80 | j), (uint8_t)j);
+        P.set(k, S[j].u, S[j].v, 0x80 | j | (j << 8));
         ++k;
       }
       if (pin != ein) {
         const double t = c[j] / (c[j] - c[e]);
-        emit_vertex<LAB>(P, 1, k, S[j].u + t * (S[e].u - S[j].u), S[j].v + t * (S[e].v - S[j].v),
-                         (uint8_t)((j << 4) | 4), pin ? (uint8_t)4 : (uint8_t)j);
+        P.set(k, S[j].u + t * (S[e].u - S[j].u), S[j].v + t * (S[e].v - S[j].v), (j << 4) | 4 | ((pin ? 4 : j) << 8));
         ++k;
       }
     }
     n = k;
   }
-  int cur = 1;
-  constexpr int CIN = CAP0 > CAP1 ? CAP0 : CAP1;  // a stage's input fits its buffer
 #pragma unroll
   for (int l = 1; l < 4; ++l) {
     if (n == 0) break;
     const V2 a = Mo[l];
     const V2 b = Mo[(l + 1) & 3];
     const double dbu = b.u - a.u, dbv = b.v - a.v;
-    const int nxt = cur ^ 1;
-    const int cap = nxt ? CAP1 : CAP0;
-    // the stage's whole input polygon to registers first (independent LDS
-    // reads, one round trip), then the walk with static register indices
-    double qu[CIN], qv[CIN], qc[CIN];
-    uint8_t ql[CIN], qe[CIN];
+    const int cap = l == 2 ? CAP1 : CAP0;
+    RegPoly q;
+    q.load(P, n);
+    double qc[CAP0];
 #pragma unroll
-    for (int i = 0; i < CIN; ++i) {
-      qu[i] = 0.0;
-      qv[i] = 0.0;
-      ql[i] = 0;
-      qe[i] = 0;
-      if (i < n) {
-        qu[i] = P.u[P.at(cur, i)];
-        qv[i] = P.v[P.at(cur, i)];
-        if (LAB) { ql[i] = P.vl[P.at(cur, i)]; qe[i] = P.el[P.at(cur, i)]; }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < CIN; ++i) qc[i] = side_of(a, dbu, dbv, qu[i], qv[i]);
+    for (int i = 0; i < CAP0; ++i) qc[i] = side_of(a, dbu, dbv, q.u[i], q.v[i]);
     int k = 0;
 #pragma unroll
-    for (int j = 0; j < CIN; ++j) {
+    for (int j = 0; j < CAP0; ++j) {
       if (j < n) {
         // edge from vertex j to the next one (vertex 0 after the last)
-        const int jn = j + 1 < CIN ? j + 1 : 0;
+        const int jn = j + 1 < CAP0 ? j + 1 : 0;
         const bool wrap = j + 1 == n;
-        const double Eu = wrap ? qu[0] : qu[jn], Ev = wrap ? qv[0] : qv[jn];
+        const double Eu = wrap ? q.u[0] : q.u[jn], Ev = wrap ? q.v[0] : q.v[jn];
         const double cP = qc[j], cE = wrap ? qc[0] : qc[jn];
         const bool pin = cP >= 0.0;
         const bool ein = cE >= 0.0;
         if (pin) {
           if (k == cap) { ovf = true; return 0; }
-          emit_vertex<LAB>(P, nxt, k, qu[j], qv[j], ql[j], qe[j]);
+          P.set(k, q.u[j], q.v[j], q.lab[j]);
           ++k;
         }
         if (pin != ein) {
           if (k == cap) { ovf = true; return 0; }
           const double t = cP / (cP - cE);
-          emit_vertex<LAB>(P, nxt, k, qu[j] + t * (Eu - qu[j]), qv[j] + t * (Ev - qv[j]),
-                           (uint8_t)((qe[j] << 4) | (4 + l)), pin ? (uint8_t)(4 + l) : qe[j]);
+          const int el = q.lab[j] >> 8;
+          P.set(k, q.u[j] + t * (Eu - q.u[j]), q.v[j] + t * (Ev - q.v[j]),
+                (el << 4) | (4 + l) | ((pin ? 4 + l : el) << 8));
           ++k;
         }
       }
     }
     n = k;
-    cur = nxt;
   }
-  res = cur;
   return n;
 }
 
-template <bool LAB>
-__device__ __forceinline__ void poly_move(const LdsPoly<LAB>& P, int b, int dst, int src) {
-  P.u[P.at(b, dst)] = P.u[P.at(b, src)];
-  P.v[P.at(b, dst)] = P.v[P.at(b, src)];
-  if (LAB) {
-    P.vl[P.at(b, dst)] = P.vl[P.at(b, src)];
-    P.el[P.at(b, dst)] = P.el[P.at(b, src)];
-  }
+__device__ __forceinline__ void poly_move(const LdsPoly& P, int dst, int src) {
+  P.set(dst, P.u[src * P.bs], P.v[src * P.bs], P.lab[src * P.bs]);
 }
 
-// Cleanup of a raw clip polygon in buffer b: (i) one pass dropping vertices
+// Cleanup of a raw clip polygon: (i) one pass dropping vertices
 // within tol (max-norm) of the previously kept one, vertex 0 always kept and
 // the last kept one dropped if within tol of vertex 0; (ii) repeated sweeps in
 // index order removing any vertex with |cross(next-prev, v-prev)| <=
 // tol * maxnorm(next-prev), until a sweep removes nothing or n < 3.
-template <bool LAB>
-__device__ __forceinline__ int cleanup(const LdsPoly<LAB>& P, int b, int n, double tol) {
+__device__ __forceinline__ int cleanup(const LdsPoly& P, int n, double tol) {
   if (n == 0) return 0;
+  const int bs = P.bs;
   int m = 1;
-  double lu = P.u[P.at(b, 0)], lv = P.v[P.at(b, 0)];
+  double lu = P.u[0], lv = P.v[0];
   for (int i = 1; i < n; ++i) {
-    const double cu = P.u[P.at(b, i)], cv = P.v[P.at(b, i)];
+    const double cu = P.u[i * bs], cv = P.v[i * bs];
     if (linf(cu - lu, cv - lv) > tol) {
-      if (m != i) poly_move(P, b, m, i);
+      if (m != i) poly_move(P, m, i);
       ++m;
       lu = cu;
       lv = cv;
     }
   }
-  if (m > 1 && linf(lu - P.u[P.at(b, 0)], lv - P.v[P.at(b, 0)]) <= tol) --m;
+  if (m > 1 && linf(lu - P.u[0], lv - P.v[0]) <= tol) --m;
   n = m;
   bool changed = true;
   while (changed && n >= 3) {
     changed = false;
     int i = 0;
     while (i < n && n >= 3) {
-      const int ia = (i + n - 1) % n, ib = (i + 1) % n;
-      const double au = P.u[P.at(b, ia)], av = P.v[P.at(b, ia)];
-      const double bu = P.u[P.at(b, ib)] - au, bv = P.v[P.at(b, ib)] - av;
-      const double cr = bu * (P.v[P.at(b, i)] - av) - bv * (P.u[P.at(b, i)] - au);
+      const int ia = i == 0 ? n - 1 : i - 1, ib = i + 1 == n ? 0 : i + 1;
+      const double au = P.u[ia * bs], av = P.v[ia * bs];
+      const double bu = P.u[ib * bs] - au, bv = P.v[ib * bs] - av;
+      const double cr = bu * (P.v[i * bs] - av) - bv * (P.u[i * bs] - au);
       if (fabs(cr) <= tol * linf(bu, bv)) {
-        for (int j = i; j + 1 < n; ++j) poly_move(P, b, j, j + 1);
+        for (int j = i; j + 1 < n; ++j) poly_move(P, j, j + 1);
         --n;
         changed = true;
       } else {
@@ -347,26 +333,49 @@ __device__ __forceinline__ int cleanup(const LdsPoly<LAB>& P, int b, int n, doub
   return n;
 }
 
-template <bool LAB>
-__device__ __forceinline__ double poly_fan_area(const LdsPoly<LAB>& P, int b, int n) {
-  const double u0 = P.u[P.at(b, 0)], v0 = P.v[P.at(b, 0)];
-  double a = 0.0;
-  for (int i = 1; i + 1 < n; ++i) {
-    const double u1 = P.u[P.at(b, i)], v1 = P.v[P.at(b, i)];
-    const double u2 = P.u[P.at(b, i + 1)], v2 = P.v[P.at(b, i + 1)];
-    a = a + ((u1 - u0) * (v2 - v0) - (v1 - v0) * (u2 - u0));
+// Whether the cleanup would leave the polygon q (n vertices) as it is: its
+// tests on neighbouring vertices, all of them failing (then each vertex's
+// previously kept one is its predecessor, and the first sweep changes
+// nothing).
+__device__ __forceinline__ bool is_clean(const RegPoly& q, int n, double tol) {
+  bool ok = true;
+#pragma unroll
+  for (int i = 0; i < CAP0; ++i) {
+    if (i < n) {
+      const bool wrap = i + 1 == n;
+      const int in = i + 1 < CAP0 ? i + 1 : 0, ip = i > 0 ? i - 1 : 0;
+      // predecessor of vertex 0: the last vertex
+      double au = q.u[ip], av = q.v[ip];
+      if (i == 0) {
+#pragma unroll
+        for (int k = 1; k < CAP0; ++k) {
+          au = k + 1 == n ? q.u[k] : au;
+          av = k + 1 == n ? q.v[k] : av;
+        }
+        if (n > 1) ok = ok && !(linf(au - q.u[0], av - q.v[0]) <= tol);
+      } else {
+        ok = ok && linf(q.u[i] - au, q.v[i] - av) > tol;
+      }
+      const double bu = (wrap ? q.u[0] : q.u[in]) - au, bv = (wrap ? q.v[0] : q.v[in]) - av;
+      const double cr = bu * (q.v[i] - av) - bv * (q.u[i] - au);
+      ok = ok && !(fabs(cr) <= tol * linf(bu, bv));
+    }
   }
+  return ok;
+}
+
+__device__ __forceinline__ double poly_fan_area(const RegPoly& q, int n) {
+  double a = 0.0;
+#pragma unroll
+  for (int i = 1; i + 1 < CAP0; ++i)
+    if (i + 1 < n)
+      a = a + ((q.u[i] - q.u[0]) * (q.v[i + 1] - q.v[0]) - (q.v[i] - q.v[0]) * (q.u[i + 1] - q.u[0]));
   return 0.5 * a;
 }
 
 // Status bits of one pair evaluation.
 enum : int { PS_DEGEN_SLAVE = 1, PS_DEGEN_MASTER = 2, PS_OVERFLOW = 4, PS_LOST = 8 };
 
-// Projection, orientation, clip and cleanup of one candidate.  On return:
-// S, Mn = projected slave / master nodes (node order), hs, hm = heights,
-// Mo = master polygon walked counter-clockwise (flip: Mo = (M0, M3, M2, M1),
-// i.e. Mo[l] = Mn[(4 - l) % 4]; otherwise Mo = Mn),
-// polygon in buffer `res` with `n` vertices (0: not a pair).
 // Slave-only part of the pair geometry: projected slave nodes, their area and
 // the longest projected edge (max-norm), from the slave frame f.
 __device__ __forceinline__ void slave_setup(const double Xs[4][3], const double f[12], V2 S[4], double hs[4],
@@ -420,43 +429,37 @@ __device__ __forceinline__ bool pair_screen(const V2 S[4], double As, const doub
   return true;
 }
 
-// Clip and cleanup of a screened candidate; the polygon ends in buffer
-// `res` with the returned vertex count (0: not a pair).
-template <bool LAB>
+// Clip and cleanup of a screened candidate; the polygon ends in q with the
+// returned vertex count (0: not a pair).
 __device__ __forceinline__ int pair_clip_screened(const V2 S[4], double As, double hmax, const V2 Mn[4], bool flip,
-                                                  double eps_d, double eps_a, const LdsPoly<LAB>& P, int& res,
+                                                  double eps_d, double eps_a, const LdsPoly& P, RegPoly& q,
                                                   int& status) {
   const V2 Mo[4] = {Mn[0], flip ? Mn[3] : Mn[1], Mn[2], flip ? Mn[1] : Mn[3]};
   bool ovf;
-  res = 0;
-  int n = clip_polygon<LAB>(S, Mo, P, res, ovf);
+  int n = clip_polygon(S, Mo, P, ovf);
   if (ovf) { status = PS_OVERFLOW; return 0; }
-  n = cleanup<LAB>(P, res, n, eps_d * hmax);
+  q.load(P, n);
+  const double tol = eps_d * hmax;
+  if (!is_clean(q, n, tol)) {
+    n = cleanup(P, n, tol);
+    q.load(P, n);
+  }
   if (n < 3) return 0;
-  const double Ap = poly_fan_area<LAB>(P, res, n);
+  const double Ap = poly_fan_area(q, n);
   if (!(Ap > eps_a * As)) return 0;
   return n;
 }
 
-// Master part: projection of the master nodes onto the slave plane,
-// orientation, clip and cleanup, given the slave setup.
-template <bool LAB>
-__device__ __forceinline__ int pair_clip(const V2 S[4], double As, double hmax, const double Xm[4][3],
-                                         const double f[12], double eps_d, double eps_a, V2 Mn[4], double hm[4],
-                                         bool& flip, const LdsPoly<LAB>& P, int& res, int& status) {
-  res = 0;
-  if (!pair_screen(S, As, Xm, f, eps_a, Mn, hm, flip, status)) return 0;
-  return pair_clip_screened<LAB>(S, As, hmax, Mn, flip, eps_d, eps_a, P, res, status);
-}
-
-template <bool LAB>
+// Projection, screening, clip and cleanup of one pair given its slave frame
+// (flip: the master polygon is walked as (M0, M3, M2, M1)).
 __device__ __forceinline__ int pair_geometry(const double Xs[4][3], const double Xm[4][3], const double f[12],
-                                             double eps_d, double eps_a, V2 S[4], V2 Mn[4], double hs[4],
-                                             double hm[4], bool& flip, const LdsPoly<LAB>& P, int& res,
+                                             double eps_d, double eps_a, bool& flip, const LdsPoly& P, RegPoly& q,
                                              int& status) {
-  double As, hmax;
+  V2 S[4], Mn[4];
+  double hs[4], hm[4], As, hmax;
   slave_setup(Xs, f, S, hs, As, hmax);
-  return pair_clip<LAB>(S, As, hmax, Xm, f, eps_d, eps_a, Mn, hm, flip, P, res, status);
+  if (!pair_screen(S, As, Xm, f, eps_a, Mn, hm, flip, status)) return 0;
+  return pair_clip_screened(S, As, hmax, Mn, flip, eps_d, eps_a, P, q, status);
 }
 
 // Precomputed slave data for the candidate pass, structure-of-arrays

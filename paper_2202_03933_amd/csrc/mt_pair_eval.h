@@ -61,16 +61,17 @@ __device__ __forceinline__ GPoly gpoly(const PolyBuf& b, int64_t p) {
 }
 __device__ __forceinline__ uint8_t gpoly_nf(const PolyBuf& b, int64_t p) { return b.nf[b.at(p)]; }
 
-// Copies a clip polygon (n vertices in LDS buffer res) and its provenance to
-// entry idx of a polygon buffer.
-__device__ __forceinline__ void poly_store(const LdsPoly<true>& P, int res, int n, bool flip, const PolyBuf& out,
-                                           int64_t idx) {
+// Writes a clip polygon (n vertices) and its provenance to entry idx of a
+// polygon buffer.
+__device__ __forceinline__ void poly_store(const RegPoly& q, int n, bool flip, const PolyBuf& out, int64_t idx) {
   out.nf[idx] = (uint8_t)(n | (flip ? 0x80 : 0));
-  for (int i = 0; i < n; ++i) {
-    out.u[(int64_t)i * out.stride + idx] = P.u[P.at(res, i)];
-    out.v[(int64_t)i * out.stride + idx] = P.v[P.at(res, i)];
-    out.lab[(int64_t)i * out.stride + idx] = P.vl[P.at(res, i)];
-  }
+#pragma unroll
+  for (int i = 0; i < CAP0; ++i)
+    if (i < n) {
+      out.u[(int64_t)i * out.stride + idx] = q.u[i];
+      out.v[(int64_t)i * out.stride + idx] = q.v[i];
+      out.lab[(int64_t)i * out.stride + idx] = (uint8_t)q.lab[i];
+    }
 }
 
 // Frame, projection, orientation, clip and cleanup of pair p; stores the
@@ -78,16 +79,15 @@ __device__ __forceinline__ void poly_store(const LdsPoly<true>& P, int res, int 
 // PS_LOST when the polygon is no longer a segment at these coordinates (the
 // pair then contributes nothing).
 __device__ __forceinline__ int store_pair_polygon(const double Xs[4][3], const double Xm[4][3], const double* ns,
-                                                   const KParams& kp, const LdsPoly<true>& P, const PolyBuf& out,
+                                                   const KParams& kp, const LdsPoly& P, const PolyBuf& out,
                                                    int64_t p) {
   double f[12];
   slave_frame_p(Xs, ns, f);
-  V2 S[4], Mn[4];
-  double hs[4], hm[4];
-  int res, st;
+  RegPoly q;
+  int st;
   bool flip;
-  const int n = pair_geometry<true>(Xs, Xm, f, kp.eps_d, kp.eps_a, S, Mn, hs, hm, flip, P, res, st);
-  poly_store(P, res, n, flip, out, out.at(p));
+  const int n = pair_geometry(Xs, Xm, f, kp.eps_d, kp.eps_a, flip, P, q, st);
+  poly_store(q, n, flip, out, out.at(p));
   return st | (n >= 3 ? 0 : PS_LOST);
 }
 

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(BSC) void k_clip_screened(const double* __restrict_
                                                         uint8_t* __restrict__ nv_out, int32_t* __restrict__ flag2,
                                                         PolyBuf out, Counters* cnt) {
   __shared__ double su[CAPT * BSC], sv[CAPT * BSC];
-  __shared__ uint8_t sl[CAPT * BSC], se[CAPT * BSC];
+  __shared__ uint16_t sl[CAPT * BSC];
   const int64_t n_maybe = *n_dev;
   const int64_t tile = dyn_tile(blockIdx.x, n_maybe, BSC);
   if (tile < 0) return;
@@ -85,16 +85,21 @@ __global__ __launch_bounds__(BSC) void k_clip_screened(const double* __restrict_
         Xm[(2 * k + 1) / 3][(2 * k + 1) % 3] = t.y;
       }
     }
+    // (the screening has decided; its projection again, not its tests)
     V2 Mn[4];
-    double hm[4];
-    int st, res;
-    bool flip;
-    pair_screen(S, As, Xm, f, kp.eps_a, Mn, hm, flip, st);
-    const LdsPoly<true> P{su + threadIdx.x, sv + threadIdx.x, sl + threadIdx.x, se + threadIdx.x, BSC};
-    const int n = pair_clip_screened<true>(S, As, hmax, Mn, flip, kp.eps_d, kp.eps_a, P, res, st);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      double h;
+      project(Xm[k], f, Mn[k], h);
+    }
+    const bool flip = quad_fan_area(Mn) < 0.0;
+    int st = 0;
+    const LdsPoly P{su + threadIdx.x, sv + threadIdx.x, sl + threadIdx.x, BSC};
+    RegPoly q;
+    const int n = pair_clip_screened(S, As, hmax, Mn, flip, kp.eps_d, kp.eps_a, P, q, st);
     nv_out[c] = (uint8_t)n;
     flag2[i] = n >= 3 ? 1 : 0;
-    poly_store(P, res, n, flip, out, i);
+    poly_store(q, n, flip, out, i);
     if (st & PS_OVERFLOW) atomicAdd(&cnt->overflow, 1ull);
   }
 }
@@ -158,7 +163,7 @@ __global__ __launch_bounds__(BSC) void k_pair_poly(MeshPtrs S, MeshPtrs M, KPara
                                                     const int32_t* __restrict__ pair_m,
                                                     const int32_t* __restrict__ n_dev, PolyBuf out, Counters* cnt) {
   __shared__ double su[CAPT * BSC], sv[CAPT * BSC];
-  __shared__ uint8_t sl[CAPT * BSC], se[CAPT * BSC];
+  __shared__ uint16_t sl[CAPT * BSC];
   const int64_t n_pairs = *n_dev;
   const int64_t tile = dyn_tile(blockIdx.x, n_pairs, BSC);
   if (tile < 0) return;
@@ -168,7 +173,7 @@ __global__ __launch_bounds__(BSC) void k_pair_poly(MeshPtrs S, MeshPtrs M, KPara
   const int s = pair_s[p];
   load_nodes(S.x, S.y, S.z, load_conn(S.conn, s), Xs);
   load_nodes(M.x, M.y, M.z, load_conn(M.conn, pair_m[p]), Xm);
-  const LdsPoly<true> P{su + threadIdx.x, sv + threadIdx.x, sl + threadIdx.x, se + threadIdx.x, BSC};
+  const LdsPoly P{su + threadIdx.x, sv + threadIdx.x, sl + threadIdx.x, BSC};
   const int st = store_pair_polygon(Xs, Xm, elem_nrm(S, s), kp, P, out, p);
   if (st) atomicAdd(&cnt->degen_poly, 1ull);
 }
