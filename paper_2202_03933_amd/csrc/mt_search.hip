@@ -238,7 +238,7 @@ __device__ __forceinline__ int cell_coord(double c, double lo, double inv_beta, 
 // ---- box prefilter ------------------------------------------------------------
 // The candidate test compares (slave lo - delta) with master hi and master lo
 // with (slave hi + delta) on each axis.  Master box bounds are stored as
-// quantisation levels (20 bits each, one 16-byte record per master): level q
+// quantisation levels (21 bits each, one 16-byte record per master): level q
 // of axis d stands for B(q) = qo + q qu, computed the same way wherever it is
 // used, so B is non-decreasing in q, and a master bound x is stored as the
 // largest q with B(q) <= x (then B(q) <= x < B(q + 1)).  For each slave the
@@ -246,16 +246,9 @@ __device__ __forceinline__ int cell_coord(double c, double lo, double inv_beta, 
 // delta; a test is then decided by integer comparisons when the levels
 // separate the values, and by the exact FP64 test otherwise, so the
 // candidate list is the one of the exact test.
-//
-// The three axes' levels sit in one 64-bit word, each in 21 bits with the
-// top one free: with that guard bit set in the minuend, one subtraction
-// compares all three axes (a field's guard survives when its minuend is not
-// the smaller), about 28 instructions a test against 45 with the fields
-// taken apart; the walk is bound by VALU issue.
-constexpr int QBITS = 20;
-constexpr int QSTRIDE = 21;
+constexpr int QBITS = 21;
 constexpr int64_t QMAX = (int64_t(1) << QBITS) - 1;
-constexpr uint64_t QGUARD = (uint64_t(1) << QBITS) * (1 + (uint64_t(1) << QSTRIDE) + (uint64_t(1) << (2 * QSTRIDE)));
+constexpr uint64_t QMASK = (uint64_t(1) << QBITS) - 1;
 constexpr uint64_t QEXACT = uint64_t(1) << 63;  // record flag: exact test only
 
 __device__ __forceinline__ double qlevel(const Grid& g, int d, int64_t q) { return g.qo[d] + (double)q * g.qu[d]; }
@@ -267,7 +260,7 @@ __device__ int64_t q_max_le(const Grid& g, int d, double x, bool strict) {
     const double b = qlevel(g, d, q);
     return strict ? b < x : b <= x;
   };
-  const double f = floor((x - g.qo[d]) * g.iqu[d]);  // (a power of two: the quotient's bits)
+  const double f = floor((x - g.qo[d]) / g.qu[d]);
   int64_t q = (int64_t)fmin(fmax(f, -1.0), (double)(QMAX + 1));
   for (int it = 0; it < 4; ++it) {
     if (q >= 0 && !ok(q)) {
@@ -289,42 +282,28 @@ __device__ int64_t q_max_le(const Grid& g, int d, double x, bool strict) {
   return lo;
 }
 
-// Per-slave thresholds of the prefilter, packed like the records: on axis d
-// a master with levels (ql, qh) fails when qh < ea or ql > ec, and passes
-// when qh >= lp and ql <= cp; anything else goes to the exact test.  With la
-// and ea the largest levels below and not above a, ec the largest not above
-// c: lp = la + 1, cp = ec - 1.  A slave whose thresholds do not fit the
-// fields (a bound off the quantised range or not finite) takes the exact
-// test throughout.
+// Per-slave thresholds of the prefilter: on axis d a master with levels
+// (ql, qh) fails when qh < ea or ql > ecf, passes when qh > la and ql < ecp;
+// anything else goes to the exact test.
 struct QSlave {
-  uint64_t ea, ec, lp, cp;
-  bool exact;
+  int32_t la[3], ea[3], ecp[3], ecf[3];
 };
 
 __device__ __forceinline__ QSlave q_slave(const Grid& g, const double lo[3], const double hi[3], double delta) {
-  QSlave t{0, 0, 0, 0, false};
+  QSlave t;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const double a = lo[d] - delta, c = hi[d] + delta;  // as in the exact test
-    if (!(isfinite(a) && isfinite(c))) {
-      t.exact = true;
-      continue;
+    if (isfinite(a) && isfinite(c)) {
+      t.la[d] = (int32_t)q_max_le(g, d, a, true);
+      t.ea[d] = (int32_t)q_max_le(g, d, a, false);
+      t.ecp[d] = t.ecf[d] = (int32_t)q_max_le(g, d, c, false);
+    } else {  // never decided by the levels
+      t.la[d] = (int32_t)QMAX + 1;
+      t.ea[d] = -1;
+      t.ecp[d] = -1;
+      t.ecf[d] = (int32_t)QMAX + 1;
     }
-    const int64_t ea = q_max_le(g, d, a, false), ec = q_max_le(g, d, c, false);
-    // the largest level below a: ea, or where ea lies on a the one before it
-    // (searched for when the levels there coincide)
-    int64_t la = ea;
-    if (ea >= 0 && !(qlevel(g, d, ea) < a))
-      la = ea == 0 || qlevel(g, d, ea - 1) < a ? ea - 1 : q_max_le(g, d, a, true);
-    if (ea < 0 || ec < 1 || ea > QMAX || ec > QMAX || la + 1 > QMAX) {
-      t.exact = true;
-      continue;
-    }
-    const int sh = QSTRIDE * d;
-    t.ea |= (uint64_t)ea << sh;
-    t.ec |= (uint64_t)ec << sh;
-    t.lp |= (uint64_t)(la + 1) << sh;
-    t.cp |= (uint64_t)(ec - 1) << sh;
   }
   return t;
 }
@@ -374,7 +353,6 @@ __device__ Grid grid_from(const PrepReduce& red, double delta, double bin_size, 
     int e = 0;
     (void)frexp(2.0 * L[d] / (double)QMAX, &e);
     g.qu[d] = L[d] > 0.0 && isfinite(L[d]) ? ldexp(1.0, e) : 1.0;
-    g.iqu[d] = 1.0 / g.qu[d];
   }
   // padded so that rounding in the box centres cannot move a centre across
   g.reach = (delta + 0.5 * emax) * (1.0 + 1e-9) + 1e-9 * beta_min;
@@ -434,7 +412,7 @@ __global__ __launch_bounds__(BS) void k_cell_place(const uint32_t* __restrict__ 
       exact = true;
       q = 0;
     }
-    w[j / 3] |= (uint64_t)q << (QSTRIDE * d);
+    w[j / 3] |= (uint64_t)q << (QBITS * d);
   }
   if (exact) w[1] |= QEXACT;
   reinterpret_cast<ulonglong2*>(qbox)[i] = make_ulonglong2(w[0], w[1]);
@@ -471,12 +449,17 @@ __device__ __forceinline__ bool touch(const SlaveBox& s, const double* __restric
 __device__ __forceinline__ bool touch_q(const SlaveBox& s, const QSlave& t, const double* __restrict__ sbox,
                                         const uint64_t* __restrict__ qbox, int i, double delta) {
   const ulonglong2 rec = reinterpret_cast<const ulonglong2*>(qbox)[i];
-  const uint64_t ql = rec.x, qh = rec.y;  // (qh with the exact flag: that decides first)
-  const uint64_t pass = ((qh | QGUARD) - t.lp) & ((t.cp | QGUARD) - ql) & QGUARD;
-  const uint64_t meet = ((qh | QGUARD) - t.ea) & ((t.ec | QGUARD) - ql) & QGUARD;
-  if (!(t.exact || (qh & QEXACT))) {
-    if (pass == QGUARD) return true;
-    if (meet != QGUARD) return false;
+  bool fail = false, pass = (rec.y & QEXACT) == 0;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int32_t ql = (int32_t)((rec.x >> (QBITS * d)) & QMASK);
+    const int32_t qh = (int32_t)((rec.y >> (QBITS * d)) & QMASK);
+    fail = fail || qh < t.ea[d] || ql > t.ecf[d];
+    pass = pass && qh > t.la[d] && ql < t.ecp[d];
+  }
+  if ((rec.y & QEXACT) == 0) {
+    if (fail) return false;
+    if (pass) return true;
   }
   return touch(s, sbox, i, delta);
 }
@@ -592,11 +575,10 @@ __device__ __forceinline__ void load_master_data(const double* __restrict__ md, 
   }
 }
 
-// Screening of the candidates of a slave element against its plane data.
-// nv_out is the candidates' vertex count, NV_CLIP where the clip will write
-// it (the candidate is screened in), 0 otherwise.
-constexpr uint8_t NV_CLIP = 255;
-
+// Screening of one candidate (master m of slave s, output slot ci) against
+// the slave plane data: projection of the master nodes, degeneracy checks and
+// the separating-line quick exit decide flag[ci] (1: to be clipped;
+// otherwise the vertex count is 0).
 struct SlavePlane {
   double f[12], As;
   V2 S[4];
@@ -617,44 +599,10 @@ struct ScreenOut {
   unsigned degen_s, degen_m;
 };
 
-// Bounding box of a projected quad.
-struct Box2 {
-  double lu, hu, lv, hv;
-};
-__device__ __forceinline__ Box2 box2(const V2 q[4]) {
-  return Box2{fmin(fmin(q[0].u, q[1].u), fmin(q[2].u, q[3].u)), fmax(fmax(q[0].u, q[1].u), fmax(q[2].u, q[3].u)),
-              fmin(fmin(q[0].v, q[1].v), fmin(q[2].v, q[3].v)), fmax(fmax(q[0].v, q[1].v), fmax(q[2].v, q[3].v))};
-}
-
-// First part of the screening, for every candidate (master m of slave s,
-// output slot ci): the projection, the degeneracy checks and the boxes of
-// the two projected quads (disjoint: no overlap).  Returns whether the
-// separating lines are still to be tried.
-__device__ __forceinline__ bool screen_box(const SlavePlane& P, const Box2& bs, int s, int m, int64_t ci,
-                                           const double* __restrict__ md, double eps_a,
-                                           int32_t* __restrict__ cand_s, int32_t* __restrict__ cand_m,
-                                           uint8_t* __restrict__ nv_out, ScreenOut& so) {
-  double Xm[4][3];
-  load_master_data(md, m, Xm);
-  V2 Mn[4];
-  double hm;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) project(Xm[k], P.f, Mn[k], hm);
-  const bool bad_s = !(P.As > 0.0);
-  const bool bad_m = !bad_s && fabs(quad_fan_area(Mn)) <= eps_a * P.As;
-  so.degen_s += bad_s ? 1u : 0u;
-  so.degen_m += bad_m ? 1u : 0u;
-  const Box2 bm = box2(Mn);
-  const bool apart = bm.lu > bs.hu || bm.hu < bs.lu || bm.lv > bs.hv || bm.hv < bs.lv;
-  nv_out[ci] = 0;
-  cand_m[ci] = m;
-  cand_s[ci] = s;
-  return !(bad_s || bad_m || apart);
-}
-
-// Second part, for those left: the separating-line test.
-__device__ __forceinline__ bool screen_lines(const SlavePlane& P, int m, int64_t ci, const double* __restrict__ md,
-                                             double eps_a, uint8_t* __restrict__ nv_out) {
+__device__ __forceinline__ bool screen_one(const SlavePlane& P, int s, int m, int64_t ci,
+                                           const double* __restrict__ md, double eps_a, int32_t* __restrict__ cand_s,
+                                           int32_t* __restrict__ cand_m, uint8_t* __restrict__ nv_out,
+                                           int32_t* __restrict__ flag, ScreenOut& so) {
   double Xm[4][3];
   load_master_data(md, m, Xm);
   V2 Mn[4];
@@ -662,7 +610,12 @@ __device__ __forceinline__ bool screen_lines(const SlavePlane& P, int m, int64_t
   int st;
   bool flip;
   const bool clip = pair_screen(P.S, P.As, Xm, P.f, eps_a, Mn, hm, flip, st);
-  if (clip) nv_out[ci] = NV_CLIP;
+  flag[ci] = clip ? 1 : 0;
+  if (!clip) nv_out[ci] = 0;
+  so.degen_s += (st & PS_DEGEN_SLAVE) ? 1u : 0u;
+  so.degen_m += (st & PS_DEGEN_MASTER) ? 1u : 0u;
+  cand_m[ci] = m;
+  cand_s[ci] = s;
   return clip;
 }
 
@@ -678,29 +631,12 @@ __device__ __forceinline__ void count_degenerate(const ScreenOut& so, Counters* 
 // of the list (the masters of one slave are distinct), screens it and writes
 // it there.  No lane reads what another lane wrote; the group's number of
 // screened-in candidates (to scr_cnt[s]) is summed by lane shuffles.
-//
-// Bound by VALU issue (14 candidates per slave, of which about 4 overlap its
-// box in the plane and 3 its quad): a wavefront runs every candidate through
-// the cheap box test first and only those left, about 3 a lane instead of
-// 8, through the separating lines.  Wavy 1024 x 1024 / 777 x 777: 0.29 ms
-// with every candidate through the lines and 16 ranks counted for any list,
-// FILL_MS ms now.
-template <int N>
-__device__ __forceinline__ void list_ranks(const int32_t* __restrict__ tmp, int32_t n_s, int s, int c, const int* own,
-                                           int* rank) {
-  for (int k = 0; k < c; ++k) {
-    const int x = tmp[(int64_t)k * n_s + s];
-#pragma unroll
-    for (int q = 0; q < N; ++q) rank[q] += x < own[q] ? 1 : 0;
-  }
-}
-
 __global__ __launch_bounds__(BS) void k_cand_fill(int32_t n_s, const int32_t* __restrict__ tmp,
                                                    const int32_t* __restrict__ off, int32_t* __restrict__ cand_s,
                                                    int32_t* __restrict__ cand_m, const double* __restrict__ sd,
                                                    const double* __restrict__ md, double eps_a,
-                                                   uint8_t* __restrict__ nv_out, int32_t* __restrict__ scr_cnt,
-                                                   Counters* cnt, int64_t cap) {
+                                                   uint8_t* __restrict__ nv_out, int32_t* __restrict__ flag,
+                                                   int32_t* __restrict__ scr_cnt, Counters* cnt, int64_t cap) {
   const int64_t t = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * BS + threadIdx.x;
   const int s = (int)(t / G), r = (int)(t % G);
   if (s >= n_s) return;  // whole groups leave together
@@ -720,33 +656,17 @@ __global__ __launch_bounds__(BS) void k_cand_fill(int32_t n_s, const int32_t* __
       own[q] = k < c ? tmp[(int64_t)k * n_s + s] : 0x7fffffff;
       rank[q] = 0;
     }
-    if (c <= CTMP / 2)
-      list_ranks<OWN / 2>(tmp, n_s, s, c, own, rank);
-    else
-      list_ranks<OWN>(tmp, n_s, s, c, own, rank);
+    for (int k = 0; k < c; ++k) {
+      const int x = tmp[(int64_t)k * n_s + s];
+#pragma unroll
+      for (int q = 0; q < OWN; ++q) rank[q] += x < own[q] ? 1 : 0;
+    }
     SlavePlane P;
     load_plane(sd, n_s, s, P);
-    const Box2 bs = box2(P.S);
     ScreenOut so{0u, 0u};
-    unsigned left = 0;
-#pragma unroll
-    for (int q = 0; q < OWN; ++q)
-      if (r + q * G < c &&
-          screen_box(P, bs, s, own[q], (int64_t)base + rank[q], md, eps_a, cand_s, cand_m, nv_out, so))
-        left |= 1u << q;
+    for (int q = 0; q < OWN && r + q * G < c; ++q)
+      nscr += screen_one(P, s, own[q], (int64_t)base + rank[q], md, eps_a, cand_s, cand_m, nv_out, flag, so) ? 1 : 0;
     count_degenerate(so, cnt);
-    while (left) {
-      const int q = __builtin_ctz(left);
-      left &= left - 1;
-      // (static indices: the q-th of the registers)
-      int m = own[0], k = rank[0];
-#pragma unroll
-      for (int i = 1; i < OWN; ++i) {
-        m = q == i ? own[i] : m;
-        k = q == i ? rank[i] : k;
-      }
-      nscr += screen_lines(P, m, (int64_t)base + k, md, eps_a, nv_out) ? 1 : 0;
-    }
   }
   // all G lanes of the group are active here
 #pragma unroll
@@ -765,7 +685,7 @@ __device__ __forceinline__ void fill_long(int s, int32_t n_s, int base, int c, i
                                           const Grid& g, double delta, int32_t* __restrict__ cand_s,
                                           int32_t* __restrict__ cand_m, const double* __restrict__ sd,
                                           const double* __restrict__ md, double eps_a, uint8_t* __restrict__ nv_out,
-                                          ScreenOut& so, int& nscr) {
+                                          int32_t* __restrict__ flag, ScreenOut& so, int& nscr) {
   walk_cells(load_box(box_s, n_s, s), sbox, mvals, cell_start, g, delta, v, vs, c);
   for (int i = 1; i < c; ++i) {
     const int x = v[i * vs];
@@ -778,13 +698,8 @@ __device__ __forceinline__ void fill_long(int s, int32_t n_s, int base, int c, i
   }
   SlavePlane P;
   load_plane(sd, n_s, s, P);
-  const Box2 bs = box2(P.S);
-  for (int i = 0; i < c; ++i) {
-    const int m = v[i * vs];
-    const int64_t ci = (int64_t)base + i;
-    if (screen_box(P, bs, s, m, ci, md, eps_a, cand_s, cand_m, nv_out, so))
-      nscr += screen_lines(P, m, ci, md, eps_a, nv_out) ? 1 : 0;
-  }
+  for (int i = 0; i < c; ++i)
+    nscr += screen_one(P, s, v[i * vs], (int64_t)base + i, md, eps_a, cand_s, cand_m, nv_out, flag, so) ? 1 : 0;
 }
 
 __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict__ box_s, int32_t n_s,
@@ -795,7 +710,7 @@ __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict_
                                                         const int32_t* __restrict__ off, int32_t* __restrict__ cand_s,
                                                         int32_t* __restrict__ cand_m, const double* __restrict__ sd,
                                                         const double* __restrict__ md, double eps_a,
-                                                        uint8_t* __restrict__ nv_out,
+                                                        uint8_t* __restrict__ nv_out, int32_t* __restrict__ flag,
                                                         int32_t* __restrict__ scr_cnt, Counters* cnt,
                                                         int64_t cap) {
   __shared__ int32_t lds[CCAP * BS];
@@ -813,10 +728,10 @@ __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict_
   int nscr = 0;
   if (c <= CCAP)
     fill_long(s, n_s, base, c, lds + threadIdx.x, BS, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd,
-              md, eps_a, nv_out, so, nscr);
+              md, eps_a, nv_out, flag, so, nscr);
   else
     fill_long(s, n_s, base, c, cand_m + base, 1, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd, md,
-              eps_a, nv_out, so, nscr);
+              eps_a, nv_out, flag, so, nscr);
   count_degenerate(so, cnt);
   scr_cnt[s] = nscr;
 }
@@ -875,14 +790,14 @@ hipError_t launch_cand_count(const double* box_s, int32_t n_s, const double* sbo
 hipError_t launch_cand_fill(const double* box_s, int32_t n_s, const double* sbox, const uint32_t* mvals,
                             const int32_t* cell_start, const Grid* g, double delta, const int32_t* tmp, const int32_t* off,
                             int32_t* cand_s, int32_t* cand_m, const double* sd, const double* md, double eps_a,
-                            uint8_t* nv, int32_t* scr_cnt, Counters* cnt, int64_t cap,
+                            uint8_t* nv, int32_t* flag, int32_t* scr_cnt, Counters* cnt, int64_t cap,
                             hipStream_t s) {
   if (n_s == 0) return hipSuccess;
-  k_cand_fill<<<group_blocks(n_s), BS, 0, s>>>(n_s, tmp, off, cand_s, cand_m, sd, md, eps_a, nv, scr_cnt, cnt,
+  k_cand_fill<<<group_blocks(n_s), BS, 0, s>>>(n_s, tmp, off, cand_s, cand_m, sd, md, eps_a, nv, flag, scr_cnt, cnt,
                                                cap);
   k_cand_fill_long<<<xcd_grid((unsigned)((n_s + BS - 1) / BS)), BS, 0, s>>>(box_s, n_s, sbox, mvals, cell_start, g, delta,
                                                                             off, cand_s, cand_m, sd, md, eps_a, nv,
-                                                                            scr_cnt, cnt, cap);
+                                                                            flag, scr_cnt, cnt, cap);
   return hipGetLastError();
 }
 
