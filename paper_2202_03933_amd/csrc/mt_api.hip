@@ -140,7 +140,6 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   A.take(c->cand_s, 4 * C);
   A.take(c->cand_m, 4 * C);
   A.take(c->cand_nv, C);
-  A.take(c->cand_flag, 4 * C);
   A.take(c->scr_cnt, 4 * (ns + 1));
   A.take(c->scr_off, 4 * (ns + 1));
   A.take(c->maybe_list, 4 * SC);
@@ -663,7 +662,7 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
                             c->cell_start.as<int32_t>(), g, c->params.delta, c->cand_tmp.as<int32_t>(),
                             c->cand_off.as<int32_t>(), c->cand_s.as<int32_t>(), c->cand_m.as<int32_t>(),
                             c->sdata.as<double>(), c->mdata.as<double>(), kp.eps_a, c->cand_nv.as<uint8_t>(),
-                            c->cand_flag.as<int32_t>(), c->scr_cnt.as<int32_t>(), cnt, cap.candidates, st));
+                            c->scr_cnt.as<int32_t>(), cnt, cap.candidates, st));
   }
   const int64_t SC = cap.screened;
   c->mpoly_stride = SC;
@@ -673,7 +672,7 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
     PhaseTimer t(c, MT_T_COMPACT, st);
     MT_HIP(scan_exclusive(c->scr_cnt.as<int32_t>(), c->scr_off.as<int32_t>(), ns, c->scan_tmp, st, 0,
                           ScanStage{ScanStage::SCREENED, SC, dst}));
-    MT_HIP(launch_maybe_list(c->cand_flag.as<int32_t>(), c->cand_off.as<int32_t>(), c->scr_off.as<int32_t>(), ns,
+    MT_HIP(launch_maybe_list(c->cand_nv.as<uint8_t>(), c->cand_off.as<int32_t>(), c->scr_off.as<int32_t>(), ns,
                              cap.candidates, SC, c->maybe_list.as<int32_t>(), st));
   }
   {

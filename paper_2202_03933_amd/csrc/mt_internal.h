@@ -202,8 +202,7 @@ struct mt_ctx {
   mt::Buf cand_tmp;        // [CTMP][n_s_el] candidates kept by the count pass
   mt::Buf cand_off;        // [n_s_el + 1]
   mt::Buf cand_s, cand_m;  // [candidate capacity]
-  mt::Buf cand_nv;         // uint8 [candidate capacity]
-  mt::Buf cand_flag;       // int32 [candidate capacity] 1 = screened in (to be clipped)
+  mt::Buf cand_nv;         // uint8 [candidate capacity] vertex count; 255: screened in, the clip writes it
   mt::Buf scr_cnt;         // int32 [n_s + 1] screened-in candidates per slave element
   mt::Buf scr_off;         // int32 [n_s + 1] exclusive scan of scr_cnt
   // screened candidates (index i < DevState::n_screened)
@@ -318,20 +317,21 @@ hipError_t launch_cand_count(const double* box_s, int32_t n_s, const double* sbo
                              const uint32_t* mvals, const int32_t* cell_start, const Grid* g, double delta,
                              int32_t* count,
                              int32_t* tmp, hipStream_t s);
-// Candidates of slave s go to [off[s], off[s + 1]) of cand_s / cand_m / nv /
-// flag, whose length is cap: a slave whose range ends beyond cap writes
+// Candidates of slave s go to [off[s], off[s + 1]) of cand_s / cand_m / nv
+// (vertex count, or 255 where the clip is to write it), whose length is cap: a
+// slave whose range ends beyond cap writes
 // nothing and gets scr_cnt[s] = 0 (the stage totals flag the excess).
 hipError_t launch_cand_fill(const double* box_s, int32_t n_s, const double* sbox, const uint32_t* mvals,
                             const int32_t* cell_start, const Grid* g, double delta, const int32_t* tmp,
                             const int32_t* off, int32_t* cand_s, int32_t* cand_m, const double* sd, const double* md, double eps_a,
-                            uint8_t* nv, int32_t* flag, int32_t* scr_cnt, Counters* cnt, int64_t cap,
+                            uint8_t* nv, int32_t* scr_cnt, Counters* cnt, int64_t cap,
                             hipStream_t s);
 int cand_tmp_per_slave();
 
 // ---- pairs (mt_pairs.hip) ----------------------------------------------------
 // Histogram of clip vertex counts nv[0..n) added to hist[17].
 hipError_t launch_nv_hist(const uint8_t* nv, int64_t n, unsigned long long* hist, hipStream_t s);
-hipError_t launch_maybe_list(const int32_t* flag, const int32_t* cand_off, const int32_t* scr_off, int32_t n_s,
+hipError_t launch_maybe_list(const uint8_t* nv, const int32_t* cand_off, const int32_t* scr_off, int32_t n_s,
                              int64_t cap_cand, int64_t cap, int32_t* mlist, hipStream_t s);
 hipError_t launch_clip_screened(const double* mdata, const double* sdata, int32_t n_s, const KParams& kp,
                                 const int32_t* cand_s, const int32_t* cand_m, const int32_t* mlist,

@@ -42,7 +42,7 @@ __device__ __forceinline__ void load_slave_data(const double* __restrict__ sd, i
 // candidates from mlist[scr_off[s]] on, in order; a slave whose candidates
 // were not stored (beyond their capacity) has none, and nothing is written
 // at or past the capacity of the list.
-__global__ __launch_bounds__(BS) void k_maybe_list(const int32_t* __restrict__ flag, const int32_t* __restrict__ cand_off,
+__global__ __launch_bounds__(BS) void k_maybe_list(const uint8_t* __restrict__ nv, const int32_t* __restrict__ cand_off,
                                                     const int32_t* __restrict__ scr_off, int32_t n_s,
                                                     int64_t cap_cand, int64_t cap, int32_t* __restrict__ mlist) {
   const int s = blockIdx.x * BS + threadIdx.x;
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(BS) void k_maybe_list(const int32_t* __restrict__ f
   if (c0 < 0 || (int64_t)c1 > cap_cand) return;
   int64_t o = scr_off[s];
   for (int c = c0; c < c1 && o < cap; ++c)
-    if (flag[c]) mlist[o++] = c;
+    if (nv[c]) mlist[o++] = c;
 }
 
 // Clip and cleanup of every screened candidate (LDS clip buffers with
@@ -222,10 +222,10 @@ hipError_t launch_nv_hist(const uint8_t* nv, int64_t n, unsigned long long* hist
   return hipGetLastError();
 }
 
-hipError_t launch_maybe_list(const int32_t* flag, const int32_t* cand_off, const int32_t* scr_off, int32_t n_s,
+hipError_t launch_maybe_list(const uint8_t* nv, const int32_t* cand_off, const int32_t* scr_off, int32_t n_s,
                              int64_t cap_cand, int64_t cap, int32_t* mlist, hipStream_t s) {
   if (n_s == 0) return hipSuccess;
-  k_maybe_list<<<(unsigned)((n_s + BS - 1) / BS), BS, 0, s>>>(flag, cand_off, scr_off, n_s, cap_cand, cap, mlist);
+  k_maybe_list<<<(unsigned)((n_s + BS - 1) / BS), BS, 0, s>>>(nv, cand_off, scr_off, n_s, cap_cand, cap, mlist);
   return hipGetLastError();
 }
 

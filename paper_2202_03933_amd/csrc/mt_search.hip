@@ -577,8 +577,10 @@ __device__ __forceinline__ void load_master_data(const double* __restrict__ md, 
 
 // Screening of one candidate (master m of slave s, output slot ci) against
 // the slave plane data: projection of the master nodes, degeneracy checks and
-// the separating-line quick exit decide flag[ci] (1: to be clipped;
-// otherwise the vertex count is 0).
+// the separating-line quick exit decide its vertex count nv_out[ci]: NV_CLIP
+// where it is to be clipped (the clip overwrites it), otherwise 0.
+constexpr uint8_t NV_CLIP = 255;
+
 struct SlavePlane {
   double f[12], As;
   V2 S[4];
@@ -602,7 +604,7 @@ struct ScreenOut {
 __device__ __forceinline__ bool screen_one(const SlavePlane& P, int s, int m, int64_t ci,
                                            const double* __restrict__ md, double eps_a, int32_t* __restrict__ cand_s,
                                            int32_t* __restrict__ cand_m, uint8_t* __restrict__ nv_out,
-                                           int32_t* __restrict__ flag, ScreenOut& so) {
+                                           ScreenOut& so) {
   double Xm[4][3];
   load_master_data(md, m, Xm);
   V2 Mn[4];
@@ -610,8 +612,7 @@ __device__ __forceinline__ bool screen_one(const SlavePlane& P, int s, int m, in
   int st;
   bool flip;
   const bool clip = pair_screen(P.S, P.As, Xm, P.f, eps_a, Mn, hm, flip, st);
-  flag[ci] = clip ? 1 : 0;
-  if (!clip) nv_out[ci] = 0;
+  nv_out[ci] = clip ? NV_CLIP : 0;
   so.degen_s += (st & PS_DEGEN_SLAVE) ? 1u : 0u;
   so.degen_m += (st & PS_DEGEN_MASTER) ? 1u : 0u;
   cand_m[ci] = m;
@@ -631,11 +632,18 @@ __device__ __forceinline__ void count_degenerate(const ScreenOut& so, Counters* 
 // of the list (the masters of one slave are distinct), screens it and writes
 // it there.  No lane reads what another lane wrote; the group's number of
 // screened-in candidates (to scr_cnt[s]) is summed by lane shuffles.
+//
+// About half the time is VALU issue, the rest latency at 4 wavefronts per
+// SIMD (the masters' records staged through LDS by the whole wavefront, a
+// third of the cache accesses: no faster).  The screening marks the vertex
+// count and keeps no array of its own.  Wavy 1024 x 1024 / 777 x 777: 0.28 ms
+// and 0.040 ms for the list of the screened-in with a 4-byte flag per
+// candidate, 0.25 and 0.018 ms now.
 __global__ __launch_bounds__(BS) void k_cand_fill(int32_t n_s, const int32_t* __restrict__ tmp,
                                                    const int32_t* __restrict__ off, int32_t* __restrict__ cand_s,
                                                    int32_t* __restrict__ cand_m, const double* __restrict__ sd,
                                                    const double* __restrict__ md, double eps_a,
-                                                   uint8_t* __restrict__ nv_out, int32_t* __restrict__ flag,
+                                                   uint8_t* __restrict__ nv_out,
                                                    int32_t* __restrict__ scr_cnt, Counters* cnt, int64_t cap) {
   const int64_t t = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * BS + threadIdx.x;
   const int s = (int)(t / G), r = (int)(t % G);
@@ -665,7 +673,7 @@ __global__ __launch_bounds__(BS) void k_cand_fill(int32_t n_s, const int32_t* __
     load_plane(sd, n_s, s, P);
     ScreenOut so{0u, 0u};
     for (int q = 0; q < OWN && r + q * G < c; ++q)
-      nscr += screen_one(P, s, own[q], (int64_t)base + rank[q], md, eps_a, cand_s, cand_m, nv_out, flag, so) ? 1 : 0;
+      nscr += screen_one(P, s, own[q], (int64_t)base + rank[q], md, eps_a, cand_s, cand_m, nv_out, so) ? 1 : 0;
     count_degenerate(so, cnt);
   }
   // all G lanes of the group are active here
@@ -685,7 +693,7 @@ __device__ __forceinline__ void fill_long(int s, int32_t n_s, int base, int c, i
                                           const Grid& g, double delta, int32_t* __restrict__ cand_s,
                                           int32_t* __restrict__ cand_m, const double* __restrict__ sd,
                                           const double* __restrict__ md, double eps_a, uint8_t* __restrict__ nv_out,
-                                          int32_t* __restrict__ flag, ScreenOut& so, int& nscr) {
+                                          ScreenOut& so, int& nscr) {
   walk_cells(load_box(box_s, n_s, s), sbox, mvals, cell_start, g, delta, v, vs, c);
   for (int i = 1; i < c; ++i) {
     const int x = v[i * vs];
@@ -699,7 +707,7 @@ __device__ __forceinline__ void fill_long(int s, int32_t n_s, int base, int c, i
   SlavePlane P;
   load_plane(sd, n_s, s, P);
   for (int i = 0; i < c; ++i)
-    nscr += screen_one(P, s, v[i * vs], (int64_t)base + i, md, eps_a, cand_s, cand_m, nv_out, flag, so) ? 1 : 0;
+    nscr += screen_one(P, s, v[i * vs], (int64_t)base + i, md, eps_a, cand_s, cand_m, nv_out, so) ? 1 : 0;
 }
 
 __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict__ box_s, int32_t n_s,
@@ -710,7 +718,7 @@ __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict_
                                                         const int32_t* __restrict__ off, int32_t* __restrict__ cand_s,
                                                         int32_t* __restrict__ cand_m, const double* __restrict__ sd,
                                                         const double* __restrict__ md, double eps_a,
-                                                        uint8_t* __restrict__ nv_out, int32_t* __restrict__ flag,
+                                                        uint8_t* __restrict__ nv_out,
                                                         int32_t* __restrict__ scr_cnt, Counters* cnt,
                                                         int64_t cap) {
   __shared__ int32_t lds[CCAP * BS];
@@ -728,10 +736,10 @@ __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict_
   int nscr = 0;
   if (c <= CCAP)
     fill_long(s, n_s, base, c, lds + threadIdx.x, BS, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd,
-              md, eps_a, nv_out, flag, so, nscr);
+              md, eps_a, nv_out, so, nscr);
   else
     fill_long(s, n_s, base, c, cand_m + base, 1, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd, md,
-              eps_a, nv_out, flag, so, nscr);
+              eps_a, nv_out, so, nscr);
   count_degenerate(so, cnt);
   scr_cnt[s] = nscr;
 }
@@ -790,14 +798,14 @@ hipError_t launch_cand_count(const double* box_s, int32_t n_s, const double* sbo
 hipError_t launch_cand_fill(const double* box_s, int32_t n_s, const double* sbox, const uint32_t* mvals,
                             const int32_t* cell_start, const Grid* g, double delta, const int32_t* tmp, const int32_t* off,
                             int32_t* cand_s, int32_t* cand_m, const double* sd, const double* md, double eps_a,
-                            uint8_t* nv, int32_t* flag, int32_t* scr_cnt, Counters* cnt, int64_t cap,
+                            uint8_t* nv, int32_t* scr_cnt, Counters* cnt, int64_t cap,
                             hipStream_t s) {
   if (n_s == 0) return hipSuccess;
-  k_cand_fill<<<group_blocks(n_s), BS, 0, s>>>(n_s, tmp, off, cand_s, cand_m, sd, md, eps_a, nv, flag, scr_cnt, cnt,
+  k_cand_fill<<<group_blocks(n_s), BS, 0, s>>>(n_s, tmp, off, cand_s, cand_m, sd, md, eps_a, nv, scr_cnt, cnt,
                                                cap);
   k_cand_fill_long<<<xcd_grid((unsigned)((n_s + BS - 1) / BS)), BS, 0, s>>>(box_s, n_s, sbox, mvals, cell_start, g, delta,
                                                                             off, cand_s, cand_m, sd, md, eps_a, nv,
-                                                                            flag, scr_cnt, cnt, cap);
+                                                                            scr_cnt, cnt, cap);
   return hipGetLastError();
 }
 
