@@ -166,6 +166,7 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   A.take(c->M_col, 64 * P);
   A.take(c->posD, 64 * ns);
   A.take(c->posM, 64 * P);
+  A.take(c->erow, 32 * ns);
   if (nodal) {
     A.take(c->nrm_node, 32 * nsn);
     A.take(c->nrm_el, 32 * ns);
@@ -407,8 +408,8 @@ int enqueue_backward(mt_ctx* c, const double* W_D, const double* W_M, const doub
     PhaseTimer t(c, MT_T_PAIR_BWD, st);
     const KParams kp = kparams(c->params);
     MT_HIP(launch_pair_bwd(S, M, kp, c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(), c->pair_off.as<int32_t>(),
-                           dev_n_pairs(c), P, poly_buf(c), c->mp_pos.as<int32_t>(), c->posD.as<int32_t>(),
-                           c->posM.as<int32_t>(), W_D, W_M, w_g, c->blk.as<double>(), fwd_sums(c),
+                           dev_n_pairs(c), P, poly_buf(c), c->mp_pos.as<int32_t>(),
+                           c->erow.as<int32_t>(), c->posD.as<int32_t>(), c->posM.as<int32_t>(), W_D, W_M, w_g, c->blk.as<double>(), fwd_sums(c),
                            c->gpair.as<double>(), bwd_sums(c), c->counters.as<Counters>(), st));
   }
   PhaseTimer t(c, MT_T_GRAD_REDUCE, st);
@@ -862,7 +863,7 @@ int mt::csr_pattern(mt_ctx* c, int64_t* nnz_D, int64_t* nnz_M, hipStream_t st, b
     MT_HIP(launch_pattern_positions(c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(), np_dev, P, S.conn, M.conn,
                                     S.n_el, c->pair_off.as<int32_t>(), c->D_rowptr.as<int32_t>(),
                                     c->D_col.as<int32_t>(), c->M_rowptr.as<int32_t>(), c->M_col.as<int32_t>(),
-                                    c->posD.as<int32_t>(), c->posM.as<int32_t>(), st));
+                                    c->posD.as<int32_t>(), c->posM.as<int32_t>(), c->erow.as<int32_t>(), st));
     if (aux) {
       // on the second internal stream: the index's short atomic and sort
       // kernels run beside the forward instead of after it

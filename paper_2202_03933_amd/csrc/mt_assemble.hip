@@ -290,12 +290,12 @@ __device__ __forceinline__ void lower_bound4(P v, int u, const int key[4], int p
   }
 }
 
-// CSR positions of the local blocks, one lane per pair (M) or slave element
-// with pairs (D), for the four local nodes j in turn: for M, of the four
-// master nodes of pair p in the row of slave node j of its element
-// (posM[(4 j + l) * pstride + p]); for D, of the four nodes of element e in
-// the row of its node j (posD[(4 j + k) * n_el + e]; elements without pairs
-// are skipped, nothing reads their entries).  The rows a workgroup's lanes
+// Places of the local block entries in their CSR rows (store_pos4), one lane
+// per pair (M) or slave element with pairs (D), for the four local nodes j
+// in turn: for M, of the four master nodes of pair p in the row of slave
+// node j of its element; for D, of the four nodes of element e in the row of
+// its node j, and the starts of the element's rows (erow; elements without
+// pairs are skipped, nothing reads their entries).  The rows a workgroup's lanes
 // need for one j are neighbours in a mesh numbered row by row, so the
 // workgroup stages the span of the column array from its smallest to its
 // largest row in LDS with coalesced loads and each lane searches its row
@@ -311,7 +311,8 @@ __device__ __forceinline__ void block_positions(unsigned block, int64_t n, int32
                                                 const int32_t* __restrict__ conn_s,
                                                 const int32_t* __restrict__ conn_m,
                                                 const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-                                                int32_t* __restrict__ pos, int64_t pstride) {
+                                                int32_t* __restrict__ pos, int64_t pstride,
+                                                const int32_t* __restrict__ rowptr_m, int32_t* __restrict__ erow) {
   // XCD-major tiles: neighbouring pairs (and the rows they stage) share an L2
   const int64_t tile = dyn_tile(block, n, BS);
   if (tile < 0) return;  // whole workgroups past the end
@@ -359,9 +360,20 @@ __device__ __forceinline__ void block_positions(unsigned block, int64_t n, int32
         lower_bound4(span + (r0 - c0), u, key, ix);
       else
         lower_bound4(col + r0, u, key, ix);
-#pragma unroll
-      for (int l = 0; l < 4; ++l) pos[(int64_t)(j * 4 + l) * pstride + i] = r0 + ix[l];
+      store_pos4(pos, pstride, i, j, u, ix);
     }
+  }
+  if (!MCOLS && act) {
+    int r[8];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int d0 = rowptr[key[j]], m0 = rowptr_m[key[j]];
+      r[j] = row_start(d0, rowptr[key[j] + 1] - d0);
+      r[4 + j] = row_start(m0, rowptr_m[key[j] + 1] - m0);
+    }
+    int4* dst = reinterpret_cast<int4*>(erow) + 2 * i;
+    dst[0] = make_int4(r[0], r[1], r[2], r[3]);
+    dst[1] = make_int4(r[4], r[5], r[6], r[7]);
   }
 }
 
@@ -377,15 +389,16 @@ __global__ __launch_bounds__(BS) void k_positions(unsigned d_blocks, int32_t n_s
                                                    const int32_t* __restrict__ D_col,
                                                    const int32_t* __restrict__ M_rowptr,
                                                    const int32_t* __restrict__ M_col, int32_t* __restrict__ posD,
-                                                   int32_t* __restrict__ posM, int64_t pstride) {
+                                                   int32_t* __restrict__ posM, int64_t pstride,
+                                                   int32_t* __restrict__ erow) {
   __shared__ int32_t span[POS_SPAN];
   __shared__ int32_t red[2][BS / 64];
   if (blockIdx.x < d_blocks)
     block_positions<false>(blockIdx.x, n_s_el, span, red, nullptr, nullptr, pair_off, conn_s, nullptr, D_rowptr,
-                           D_col, posD, n_s_el);
+                           D_col, posD, n_s_el, M_rowptr, erow);
   else
     block_positions<true>(blockIdx.x - d_blocks, *n_pairs, span, red, pair_s, pair_m, nullptr, conn_s, conn_m,
-                          M_rowptr, M_col, posM, pstride);
+                          M_rowptr, M_col, posM, pstride, nullptr, nullptr);
 }
 
 // One thread per slave node (row): the row is accumulated in a per-thread
@@ -628,11 +641,11 @@ hipError_t launch_pattern_positions(const int32_t* pair_s, const int32_t* pair_m
                                     int64_t cap, const int32_t* conn_s, const int32_t* conn_m, int32_t n_s_el,
                                     const int32_t* pair_off, const int32_t* D_rowptr, const int32_t* D_col,
                                     const int32_t* M_rowptr, const int32_t* M_col, int32_t* posD, int32_t* posM,
-                                    hipStream_t s) {
+                                    int32_t* erow, hipStream_t s) {
   const unsigned nd = xcd_grid(grid_of(n_s_el)), nm = xcd_grid(grid_of(cap));
   if (nd + nm == 0) return hipSuccess;
   k_positions<<<nd + nm, BS, 0, s>>>(nd, n_s_el, n_pairs, pair_s, pair_m, pair_off, conn_s, conn_m, D_rowptr, D_col,
-                                     M_rowptr, M_col, posD, posM, cap);
+                                     M_rowptr, M_col, posD, posM, cap, erow);
   return hipGetLastError();
 }
 

@@ -21,15 +21,14 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
 }
 
 // Upstream weights of pair p gathered through the position maps.
-__device__ __forceinline__ void gather_weights(int s, int64_t p, int4 csn, const int32_t* __restrict__ posD,
+__device__ __forceinline__ void gather_weights(int s, int64_t p, int4 csn, const int32_t* __restrict__ erow,
+                                               const int32_t* __restrict__ posD,
                                                int32_t n_s, const int32_t* __restrict__ posM, int64_t stride,
                                                const double* __restrict__ W_D, const double* __restrict__ W_M,
                                                const double* __restrict__ w_g, double WD[16], double WM[16],
                                                double wg[4]) {
-#pragma unroll
-  for (int k = 0; k < 16; ++k) WD[k] = W_D[posD[(int64_t)k * n_s + s]];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) WM[k] = W_M[posM[(int64_t)k * stride + p]];
+  load_weights(W_D, load_erow(erow, s, 0), posD, n_s, s, WD);
+  load_weights(W_M, load_erow(erow, s, 1), posM, stride, p, WM);
   wg[0] = w_g[csn.x];
   wg[1] = w_g[csn.y];
   wg[2] = w_g[csn.z];
@@ -40,14 +39,14 @@ __device__ __forceinline__ void gather_weights(int s, int64_t p, int4 csn, const
 // lane per slave element, after the sweep (elem_dual_adjoint).
 template <bool NODAL>
 __global__ __launch_bounds__(BSC) __attribute__((amdgpu_waves_per_eu(2))) void k_elem_dual_adj(
-    MeshPtrs S, const int32_t* __restrict__ pair_off, const int32_t* __restrict__ posD,
+    MeshPtrs S, const int32_t* __restrict__ pair_off, const int32_t* __restrict__ erow, const int32_t* __restrict__ posD,
     const int32_t* __restrict__ posM, int64_t stride, const double* __restrict__ W_D, const double* __restrict__ W_M,
     const double* __restrict__ w_g, const double* __restrict__ blk, ElemSums eblk, ElemSums egrad) {
   const int e = xcd_tile(blockIdx.x, gridDim.x) * BSC + threadIdx.x;
   if (e >= eblk.n_el) return;
   const int p0 = pair_off[e], p1 = pair_off[e + 1];
   if (p0 == p1) return;
-  elem_dual_adjoint<NODAL>(S, e, p0, p1, posD, posM, stride, W_D, W_M, w_g, blk, eblk, egrad);
+  elem_dual_adjoint<NODAL>(S, e, p0, p1, erow, posD, posM, stride, W_D, W_M, w_g, blk, eblk, egrad);
 }
 
 template <int NQ, bool DUAL, bool NODAL>
@@ -56,6 +55,7 @@ __global__ __launch_bounds__(BSC) __attribute__((amdgpu_waves_per_eu(2))) void k
                                                    const int32_t* __restrict__ pair_m,
                                                    const int32_t* __restrict__ n_dev, PolyBuf poly,
                                                    const int32_t* __restrict__ mpos,
+                                                   const int32_t* __restrict__ erow,
                                                    const int32_t* __restrict__ posD, const int32_t* __restrict__ posM,
                                                    const double* __restrict__ W_D, const double* __restrict__ W_M,
                                                    const double* __restrict__ w_g, double* __restrict__ gpair,
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(BSC) __attribute__((amdgpu_waves_per_eu(2))) void k
     prev = p > 0 ? pair_s[p - 1] : -1;
     const int4 csn = load_conn(S.conn, s);
     double WD[16], WM[16], wg[4];
-    gather_weights(s, p, csn, posD, n_s, posM, stride, W_D, W_M, w_g, WD, WM, wg);
+    gather_weights(s, p, csn, erow, posD, n_s, posM, stride, W_D, W_M, w_g, WD, WM, wg);
     double Xmb[4][3];
     pair_backward<NQ, DUAL, NODAL>(S, s, csn, M, load_conn(M.conn, pair_m[p]), gpoly(poly, p), gpoly_nf(poly, p), kp,
                                    st, WD, WM, wg, Xsb, Xmb, n0b, noconv);
@@ -93,7 +93,8 @@ __global__ __launch_bounds__(BSC) __attribute__((amdgpu_waves_per_eu(2))) void k
 
 hipError_t launch_pair_bwd(const DeviceMesh& S, const DeviceMesh& M, const KParams& kp, const int32_t* pair_s,
                            const int32_t* pair_m, const int32_t* pair_off, const int32_t* n_pairs, int64_t cap,
-                           const PolyBuf& poly, const int32_t* mpos, const int32_t* posD, const int32_t* posM,
+                           const PolyBuf& poly, const int32_t* mpos, const int32_t* erow,
+                           const int32_t* posD, const int32_t* posM,
                            const double* W_D, const double* W_M, const double* w_g, const double* blk,
                            const ElemSums& eblk, double* gpair, const ElemSums& egrad, Counters* cnt, hipStream_t s) {
   if (cap == 0) return hipSuccess;
@@ -105,12 +106,12 @@ hipError_t launch_pair_bwd(const DeviceMesh& S, const DeviceMesh& M, const KPara
                            : (nodal ? k_pair_bwd<3, false, true> : k_pair_bwd<3, false, false>))
                 : (kp.dual ? (nodal ? k_pair_bwd<7, true, true> : k_pair_bwd<7, true, false>)
                            : (nodal ? k_pair_bwd<7, false, true> : k_pair_bwd<7, false, false>));
-  hipLaunchKernelGGL(k, dim3(nb), dim3(BSC), 0, s, ms, S.n_el, mm, kp, pair_s, pair_m, n_pairs, poly, mpos, posD, posM,
+  hipLaunchKernelGGL(k, dim3(nb), dim3(BSC), 0, s, ms, S.n_el, mm, kp, pair_s, pair_m, n_pairs, poly, mpos, erow, posD, posM,
                      W_D, W_M, w_g, gpair, cap, egrad, cnt);
   if (kp.dual && S.n_el > 0) {
     auto* kd = nodal ? k_elem_dual_adj<true> : k_elem_dual_adj<false>;
-    hipLaunchKernelGGL(kd, dim3(xcd_grid((unsigned)((S.n_el + BSC - 1) / BSC))), dim3(BSC), 0, s, ms, pair_off, posD,
-                       posM, cap, W_D, W_M, w_g, blk, eblk, egrad);
+    hipLaunchKernelGGL(kd, dim3(xcd_grid((unsigned)((S.n_el + BSC - 1) / BSC))), dim3(BSC), 0, s, ms, pair_off, erow,
+                       posD, posM, cap, W_D, W_M, w_g, blk, eblk, egrad);
   }
   return hipGetLastError();
 }

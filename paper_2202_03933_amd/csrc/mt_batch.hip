@@ -40,6 +40,7 @@ struct BatchInst {
   const int32_t* M_rowptr;
   const int32_t* posD;
   const int32_t* posM;
+  const int32_t* erow;
   const int32_t* minc_off;
   const int32_t* minc_list;
   const int32_t* mstart;
@@ -159,10 +160,8 @@ __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(3))) void k
 // Upstream weights of pair p of instance I.
 __device__ __forceinline__ void batch_weights(const BatchInst& I, int s, int4 c, int64_t p, double WD[16],
                                               double WM[16], double wg[4]) {
-#pragma unroll
-  for (int k = 0; k < 16; ++k) WD[k] = I.W_D[I.posD[(int64_t)k * I.n_s_el + s]];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) WM[k] = I.W_M[I.posM[(int64_t)k * I.stride + p]];
+  load_weights(I.W_D, load_erow(I.erow, s, 0), I.posD, I.n_s_el, s, WD);
+  load_weights(I.W_M, load_erow(I.erow, s, 1), I.posM, I.stride, p, WM);
   wg[0] = I.w_g[c.x];
   wg[1] = I.w_g[c.y];
   wg[2] = I.w_g[c.z];
@@ -243,7 +242,7 @@ __global__ __launch_bounds__(ROWS_PER_ITEM) __attribute__((amdgpu_waves_per_eu(2
   const BatchInst& I = inst[w.inst];
   const int p0 = I.pair_off[e], p1 = I.pair_off[e + 1];
   if (p0 == p1) return;
-  elem_dual_adjoint<NODAL>(I.S, e, p0, p1, I.posD, I.posM, I.stride, I.W_D, I.W_M, I.w_g, I.blk, I.eblk, I.egrad);
+  elem_dual_adjoint<NODAL>(I.S, e, p0, p1, I.erow, I.posD, I.posM, I.stride, I.W_D, I.W_M, I.w_g, I.blk, I.eblk, I.egrad);
 }
 
 using PolyFn = void (*)(const BatchInst*, const WorkItem*, const int32_t*, int32_t*);
@@ -690,6 +689,7 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
     I.M_rowptr = c->M_rowptr.as<int32_t>();
     I.posD = c->posD.as<int32_t>();
     I.posM = c->posM.as<int32_t>();
+    I.erow = c->erow.as<int32_t>();
     I.minc_off = c->minc_off.as<int32_t>();
     I.minc_list = c->minc_list.as<int32_t>();
     I.mstart = c->mp_off.as<int32_t>();

@@ -145,6 +145,7 @@ __device__ __forceinline__ void dual_adjoint(const double Xs[4][3], const double
 // 0.18 ms per pair kernel before).
 template <bool NODAL>
 __device__ __forceinline__ void elem_dual_adjoint(const MeshPtrs& S, int e, int p0, int p1,
+                                                  const int32_t* __restrict__ erow,
                                                   const int32_t* __restrict__ posD,
                                                   const int32_t* __restrict__ posM, int64_t stride,
                                                   const double* __restrict__ W_D, const double* __restrict__ W_M,
@@ -155,29 +156,28 @@ __device__ __forceinline__ void elem_dual_adjoint(const MeshPtrs& S, int e, int 
   double G[16];
   {
     const double wg[4] = {w_g[c.x], w_g[c.y], w_g[c.z], w_g[c.w]};
-    double D[16], g[4];
+    double D[16], g[4], WD[16];
+    load_weights(W_D, load_erow(erow, e, 0), posD, eblk.n_el, e, WD);
     elem_sums<16>(eblk, 0, e, p0, p1, D);
     elem_sums<4>(eblk, 16, e, p0, p1, g);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      double w[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) w[k] = W_D[posD[(int64_t)(4 * j + k) * eblk.n_el + e]];
+      const double* w = WD + 4 * j;
 #pragma unroll
       for (int m = 0; m < 4; ++m)
         G[4 * j + m] =
             wg[j] * g[m] + w[0] * D[4 * m] + w[1] * D[4 * m + 1] + w[2] * D[4 * m + 2] + w[3] * D[4 * m + 3];
     }
   }
+  const int4 mrows = load_erow(erow, e, 1);
   for (int p = p0; p < p1; ++p) {
-    double M[16];
+    double M[16], WM[16];
+    load_weights(W_M, mrows, posM, stride, p, WM);
 #pragma unroll
     for (int k = 0; k < 16; ++k) M[k] = blk[(int64_t)k * stride + p];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      double w[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) w[k] = W_M[posM[(int64_t)(4 * j + k) * stride + p]];
+      const double* w = WM + 4 * j;
 #pragma unroll
       for (int m = 0; m < 4; ++m)
         G[4 * j + m] += w[0] * M[4 * m] + w[1] * M[4 * m + 1] + w[2] * M[4 * m + 2] + w[3] * M[4 * m + 3];

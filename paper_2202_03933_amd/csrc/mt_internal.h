@@ -223,8 +223,9 @@ struct mt_ctx {
   mt::Buf pat_elist;       // int32 [EL][n_s_el] those master nodes, sorted
   mt::Buf D_cnt, D_rowptr, D_col;  // D_col: [16 n_s_el] (bound of nnz(D))
   mt::Buf M_cnt, M_rowptr, M_col;  // M_col: [16 pair capacity] (bound of nnz(M))
-  mt::Buf posD;            // [16][n_s_el]
-  mt::Buf posM;            // [16][pair capacity]
+  mt::Buf posD;            // [16][n_s_el] places in the CSR rows (store_pos4)
+  mt::Buf posM;            // [16][pair capacity] likewise
+  mt::Buf erow;            // [n_s_el][8] starts of its D and M rows (load_erow)
   // clip polygons of the pairs (mt::PolyBuf); valid for the coordinates of
   // generation poly_gen (coord_gen counts coordinate and pair-list changes)
   mt::Buf pair_slot;       // int32 [pair capacity] entry of each pair's polygon in the mpoly buffers
@@ -371,13 +372,14 @@ hipError_t launch_pattern_rows(bool fill, const int32_t* inc_off, const int32_t*
                                const int32_t* conn_m, int32_t* D_cnt, int32_t* M_cnt, const int32_t* D_rowptr,
                                const int32_t* M_rowptr, int32_t* D_col, int32_t* M_col, int32_t* keep,
                                int32_t n_s_el, int32_t* ecnt, int32_t* elist, hipStream_t s);
-// CSR positions of every local block entry (posD[(4 j + k) * n_s_el + e],
-// posM[(4 j + l) * cap + p]) from the filled column arrays.
+// Places of every local block entry in its CSR row (store_pos4 with strides
+// n_s_el and cap), from the filled column arrays, and the starts of each
+// element's rows (load_erow).
 hipError_t launch_pattern_positions(const int32_t* pair_s, const int32_t* pair_m, const int32_t* n_pairs,
                                     int64_t cap, const int32_t* conn_s, const int32_t* conn_m, int32_t n_s_el,
                                     const int32_t* pair_off, const int32_t* D_rowptr, const int32_t* D_col,
                                     const int32_t* M_rowptr, const int32_t* M_col, int32_t* posD, int32_t* posM,
-                                    hipStream_t s);
+                                    int32_t* erow, hipStream_t s);
 hipError_t launch_elem_mlist(int32_t n_s_el, const int32_t* pair_off, const int32_t* pair_m, const int32_t* conn_m,
                              int32_t* ecnt, int32_t* elist, hipStream_t s);
 int pattern_keep_per_row();
@@ -406,7 +408,8 @@ hipError_t launch_master_index(const int32_t* pair_m, const int32_t* n_pairs, in
 // blocks (the gradient through the dual coefficients needs them).
 hipError_t launch_pair_bwd(const DeviceMesh& S, const DeviceMesh& M, const KParams& kp, const int32_t* pair_s,
                            const int32_t* pair_m, const int32_t* pair_off, const int32_t* n_pairs, int64_t cap,
-                           const PolyBuf& poly, const int32_t* mpos, const int32_t* posD, const int32_t* posM,
+                           const PolyBuf& poly, const int32_t* mpos, const int32_t* erow,
+                           const int32_t* posD, const int32_t* posM,
                            const double* W_D, const double* W_M, const double* w_g, const double* blk,
                            const ElemSums& eblk, double* gpair, const ElemSums& egrad, Counters* cnt, hipStream_t s);
 

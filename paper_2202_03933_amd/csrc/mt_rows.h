@@ -25,6 +25,72 @@ __device__ __forceinline__ void elem_sums(const ElemSums& E, int k0, int e, int 
     for (int k = 0; k < N; ++k) v[k] += E.v[(int64_t)(k0 + k) * E.stride + E.n_el + t];
 }
 
+// Places of the four entries of block row j of pair (or element) i within
+// their CSR row, of len columns: up to POS_PACKED columns as four bytes of
+// the word at pos[4 j * stride + i], else one word each at
+// pos[(4 j + l) * stride + i].  16 bytes a pair instead of 64 to write and
+// to read, one load instead of four: at wavy 1024 x 1024 / 777 x 777 the
+// positions 0.203 -> 0.173 ms, the assembly 0.316 -> 0.311, the reverse sweep
+// 0.569 -> 0.577 (its gathers wait as before, and unpack).
+constexpr int POS_PACKED = 256;
+
+__device__ __forceinline__ void store_pos4(int32_t* __restrict__ pos, int64_t stride, int64_t i, int j, int len,
+                                           const int ix[4]) {
+  if (len <= POS_PACKED) {
+    pos[(int64_t)(4 * j) * stride + i] = (int32_t)((uint32_t)ix[0] | (uint32_t)ix[1] << 8 | (uint32_t)ix[2] << 16 |
+                                                   (uint32_t)ix[3] << 24);
+  } else {
+#pragma unroll
+    for (int l = 0; l < 4; ++l) pos[(int64_t)(4 * j + l) * stride + i] = ix[l];
+  }
+}
+
+__device__ __forceinline__ void load_pos4(const int32_t* __restrict__ pos, int64_t stride, int64_t i, int j, int len,
+                                          int ix[4]) {
+  const uint32_t w = (uint32_t)pos[(int64_t)(4 * j) * stride + i];  // (both forms start here)
+#pragma unroll
+  for (int l = 0; l < 4; ++l) ix[l] = (int)(w >> (8 * l) & 255u);
+  if (len > POS_PACKED) {
+    ix[0] = (int)w;
+#pragma unroll
+    for (int l = 1; l < 4; ++l) ix[l] = pos[(int64_t)(4 * j + l) * stride + i];
+  }
+}
+
+// The starts of the CSR rows of a slave element's four nodes, D's at
+// erow[8 e ..] and M's at erow[8 e + 4 ..], with the sign bit set where the
+// row has more than POS_PACKED columns (elements with pairs only): what the
+// reverse sweep needs to turn places into positions, without the way over
+// the connectivity and the row pointers (0.591 ms that way, 0.577 so).
+__device__ __forceinline__ int row_start(int r0, int len) { return len <= POS_PACKED ? r0 : r0 | (int)0x80000000; }
+
+// Upstream weights of the 16 block entries, r[j] the marked start of row j:
+// W[4 j + l] = w[start of row j + place l].  One branch for the four rows,
+// behind all loads of places.
+__device__ __forceinline__ void load_weights(const double* __restrict__ w, int4 rows, const int32_t* __restrict__ pos,
+                                             int64_t stride, int64_t i, double W[16]) {
+  const int r[4] = {rows.x, rows.y, rows.z, rows.w};
+  uint32_t word[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) word[j] = (uint32_t)pos[(int64_t)(4 * j) * stride + i];
+  if ((r[0] | r[1] | r[2] | r[3]) >= 0) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) W[k] = w[r[k / 4] + (int)(word[k / 4] >> (8 * (k % 4)) & 255u)];
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      int ix[4];
+      load_pos4(pos, stride, i, j, r[j] < 0 ? POS_PACKED + 1 : 0, ix);
+#pragma unroll
+      for (int l = 0; l < 4; ++l) W[4 * j + l] = w[(r[j] & 0x7fffffff) + ix[l]];
+    }
+  }
+}
+
+__device__ __forceinline__ int4 load_erow(const int32_t* __restrict__ erow, int64_t e, int m) {
+  return reinterpret_cast<const int4*>(erow)[2 * e + m];
+}
+
 // The pairs that one node's row gathers, as one flat sequence k = 0 .. n-1:
 // the pairs of its incident elements (ascending), each element's pairs in
 // their order.  Up to four incident elements are held in registers, so the
@@ -91,8 +157,10 @@ __device__ __forceinline__ void assemble_row(int a, const int32_t* __restrict__ 
                                              const double* __restrict__ blk, int64_t stride, const ElemSums& E,
                                              double* __restrict__ D_val, double* __restrict__ M_val,
                                              double* __restrict__ gap) {
-  for (int i = D_rowptr[a]; i < D_rowptr[a + 1]; ++i) D_val[i] = 0.0;
-  for (int i = M_rowptr[a]; i < M_rowptr[a + 1]; ++i) M_val[i] = 0.0;
+  const int d0 = D_rowptr[a], nd = D_rowptr[a + 1] - d0;
+  const int m0 = M_rowptr[a], nm = M_rowptr[a + 1] - m0;
+  for (int i = 0; i < nd; ++i) D_val[d0 + i] = 0.0;
+  for (int i = 0; i < nm; ++i) M_val[m0 + i] = 0.0;
   double g = 0.0;
   for (int i = inc_off[a]; i < inc_off[a + 1]; ++i) {
     const int e = inc_list[i] >> 2, j = inc_list[i] & 3;
@@ -101,25 +169,28 @@ __device__ __forceinline__ void assemble_row(int a, const int32_t* __restrict__ 
     double vd[4], vg[1];
     elem_sums<4>(E, 4 * j, e, p0, p1, vd);
     elem_sums<1>(E, 16 + j, e, p0, p1, vg);
+    int ix[4];
+    load_pos4(posD, E.n_el, e, j, nd, ix);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) D_val[posD[(int64_t)(j * 4 + k) * E.n_el + e]] += vd[k];
+    for (int k = 0; k < 4; ++k) D_val[d0 + ix[k]] += vd[k];
     g += vg[0];
     for (int p = p0; p < p1; ++p) {
+      load_pos4(posM, stride, p, j, nm, ix);
 #pragma unroll
-      for (int l = 0; l < 4; ++l)
-        M_val[posM[(int64_t)(j * 4 + l) * stride + p]] += blk[(int64_t)(j * 4 + l) * stride + p];
+      for (int l = 0; l < 4; ++l) M_val[m0 + ix[l]] += blk[(int64_t)(j * 4 + l) * stride + p];
     }
   }
   gap[a] = g;
 }
 
 // One sweep over the incident elements of row a (ascending, then their
-// pairs), adding the D part (DP: entry q at acc[(q - d0) * astride], and the
-// gap, returned) and/or the M part (MP: entry q at acc[(q + moff) * astride]).
+// pairs), adding the D part (DP: column i of nd at acc[i * astride], and the
+// gap, returned) and/or the M part (MP: column i of nm at
+// acc[(i + moff) * astride]).
 template <bool DP, bool MP>
 __device__ __forceinline__ double row_sweep(int a, const int32_t* __restrict__ inc_off,
                                             const int32_t* __restrict__ inc_list,
-                                            const int32_t* __restrict__ pair_off, int d0, int moff,
+                                            const int32_t* __restrict__ pair_off, int nd, int nm, int moff,
                                             const int32_t* __restrict__ posD, const int32_t* __restrict__ posM,
                                             const double* __restrict__ blk, int64_t stride, const ElemSums& E,
                                             double* acc, int astride) {
@@ -130,8 +201,7 @@ __device__ __forceinline__ double row_sweep(int a, const int32_t* __restrict__ i
     if (p0 == p1) continue;
     if (DP) {
       int pd[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) pd[k] = posD[(int64_t)(j * 4 + k) * E.n_el + e] - d0;
+      load_pos4(posD, E.n_el, e, j, nd, pd);
       double vd[4], vg[1];
       elem_sums<4>(E, 4 * j, e, p0, p1, vd);
       elem_sums<1>(E, 16 + j, e, p0, p1, vg);
@@ -143,13 +213,11 @@ __device__ __forceinline__ double row_sweep(int a, const int32_t* __restrict__ i
       for (int p = p0; p < p1; ++p) {
         double vm[4];
         int pm[4];
+        load_pos4(posM, stride, p, j, nm, pm);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          vm[k] = blk[(int64_t)(j * 4 + k) * stride + p];
-          pm[k] = posM[(int64_t)(j * 4 + k) * stride + p] + moff;
-        }
+        for (int k = 0; k < 4; ++k) vm[k] = blk[(int64_t)(j * 4 + k) * stride + p];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc[pm[k] * astride] += vm[k];
+        for (int k = 0; k < 4; ++k) acc[(pm[k] + moff) * astride] += vm[k];
       }
     }
   }
@@ -179,15 +247,15 @@ __device__ __forceinline__ void assemble_row_acc(int a, const int32_t* __restric
   double g;
   if (nd + nm <= cap) {
     for (int i = 0; i < nd + nm; ++i) acc[i * astride] = 0.0;
-    g = row_sweep<true, true>(a, inc_off, inc_list, pair_off, d0, nd - m0, posD, posM, blk, stride, E, acc, astride);
+    g = row_sweep<true, true>(a, inc_off, inc_list, pair_off, nd, nm, nd, posD, posM, blk, stride, E, acc, astride);
     for (int i = 0; i < nd; ++i) D_val[d0 + i] = acc[i * astride];
     for (int i = 0; i < nm; ++i) M_val[m0 + i] = acc[(nd + i) * astride];
   } else if (nd <= cap && nm <= cap) {
     for (int i = 0; i < nd; ++i) acc[i * astride] = 0.0;
-    g = row_sweep<true, false>(a, inc_off, inc_list, pair_off, d0, 0, posD, posM, blk, stride, E, acc, astride);
+    g = row_sweep<true, false>(a, inc_off, inc_list, pair_off, nd, nm, 0, posD, posM, blk, stride, E, acc, astride);
     for (int i = 0; i < nd; ++i) D_val[d0 + i] = acc[i * astride];
     for (int i = 0; i < nm; ++i) acc[i * astride] = 0.0;
-    row_sweep<false, true>(a, inc_off, inc_list, pair_off, d0, -m0, posD, posM, blk, stride, E, acc, astride);
+    row_sweep<false, true>(a, inc_off, inc_list, pair_off, nd, nm, 0, posD, posM, blk, stride, E, acc, astride);
     for (int i = 0; i < nm; ++i) M_val[m0 + i] = acc[i * astride];
   } else {
     assemble_row(a, inc_off, inc_list, pair_off, D_rowptr, M_rowptr, posD, posM, blk, stride, E, D_val, M_val, gap);
