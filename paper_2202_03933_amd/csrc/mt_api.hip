@@ -120,8 +120,10 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   const size_t C = (size_t)cap.candidates, SC = (size_t)cap.screened, P = (size_t)cap.pairs, G = (size_t)cap.cells;
   const bool nodal = c->params.normals == MT_NORMALS_NODAL;
   const size_t scan = sizeof(int32_t) * (size_t)scan_tmp_elems(scan_max(c, cap));
-  A.take(c->counters, sizeof(Counters));
-  A.take(c->state, sizeof(DevState));
+  Buf status;
+  A.take(status, sizeof(DevStatus));
+  c->counters = Buf{status.p, sizeof(Counters)};
+  c->state = Buf{status.p ? static_cast<char*>(status.p) + offsetof(DevStatus, state) : nullptr, sizeof(DevState)};
   A.take(c->box_s, 48 * ns);
   A.take(c->box_m, 48 * nm);
   A.take(c->sdata, 8 * SD_N * ns);
@@ -232,6 +234,11 @@ hipError_t read_back(mt_ctx* c, std::initializer_list<ReadBack> items, hipStream
   return hipSuccess;
 }
 
+// The counters and the state: one copy.
+hipError_t read_status(mt_ctx* c, DevStatus* h, hipStream_t st) {
+  return read_back(c, {{h, c->counters.p, sizeof(*h)}}, st);
+}
+
 // Status of the device checks from the read-back state and counters.
 int device_status(const DevState& ds, const Counters& hc, bool with_noconv) {
   if (ds.flags & DS_NONFINITE) return fail(MT_EINVAL, "a coordinate is NaN or infinite");
@@ -281,12 +288,12 @@ int normals_for_coords(mt_ctx* c, hipStream_t st) {
 }
 
 // The counts of a build (and the nonzeros of its pattern) as read back.
-void set_counts(mt_ctx* c, const DevState& hs, const int32_t nnz[2]) {
+void set_counts(mt_ctx* c, const DevState& hs) {
   c->n_cand = hs.n_cand;
   c->n_maybe = hs.n_screened;
   c->n_pairs = hs.n_pairs;
-  c->nnz_D = nnz[0];
-  c->nnz_M = nnz[1];
+  c->nnz_D = c->have_pattern ? hs.nnz_D : 0;
+  c->nnz_M = c->have_pattern ? hs.nnz_M : 0;
   c->grid = hs.grid;
   c->counts_known = true;
 }
@@ -298,15 +305,8 @@ int mt::host_counts(mt_ctx* c) {
   if (c->counts_known || !c->have_pairs) return MT_OK;
   DeviceScope ds(c->device);
   DevState hs;
-  int32_t nnz[2] = {0, 0};
-  const int32_t n = c->side[0].n_nodes;
-  if (c->have_pattern) {
-    MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}, {&nnz[0], c->D_rowptr.as<int32_t>() + n, 4},
-                         {&nnz[1], c->M_rowptr.as<int32_t>() + n, 4}}, c->last_stream));
-  } else {
-    MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}}, c->last_stream));
-  }
-  set_counts(c, hs, nnz);
+  MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}}, c->last_stream));
+  set_counts(c, hs);
   return MT_OK;
 }
 
@@ -695,17 +695,12 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
   c->poly_gen = c->coord_gen;
   c->have_pairs = true;
   if (!n_cand_out && !n_pairs_out) return MT_OK;
-  DevState hs;
-  Counters hc;
-  MT_HIP(read_back(c, {{&hs, dst, sizeof(hs)}, {&hc, cnt, sizeof(hc)}}, st));
-  c->n_cand = hs.n_cand;
-  c->n_maybe = hs.n_screened;
-  c->n_pairs = hs.n_pairs;
-  c->grid = hs.grid;
-  c->counts_known = true;
+  DevStatus h;
+  MT_HIP(read_status(c, &h, st));
+  set_counts(c, h.state);
   if (n_cand_out) *n_cand_out = c->n_cand;
   if (n_pairs_out) *n_pairs_out = c->n_pairs;
-  return device_status(hs, hc, false);
+  return device_status(h.state, h.counters, false);
 }
 
 int mt_required_capacity(mt_ctx* c, mt_capacity* need) {
@@ -727,19 +722,10 @@ int mt_check(mt_ctx* c) {
   if (!c->have_pairs) return fail(MT_ESTATE, "mt_check: no build");
   if (int rc = ws_live(c)) return rc;
   DeviceScope ds(c->device);
-  DevState hs;
-  Counters hc;
-  int32_t nnz[2] = {0, 0};
-  const int32_t n = c->side[0].n_nodes;
-  if (c->have_pattern) {
-    MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}, {&hc, c->counters.p, sizeof(hc)},
-                         {&nnz[0], c->D_rowptr.as<int32_t>() + n, 4}, {&nnz[1], c->M_rowptr.as<int32_t>() + n, 4}},
-                     c->last_stream));
-  } else {
-    MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}, {&hc, c->counters.p, sizeof(hc)}}, c->last_stream));
-  }
-  set_counts(c, hs, nnz);  // the same wait serves later reads of the counts
-  return device_status(hs, hc, true);
+  DevStatus h;
+  MT_HIP(read_status(c, &h, c->last_stream));
+  set_counts(c, h.state);  // the same wait serves later reads of the counts
+  return device_status(h.state, h.counters, true);
 }
 
 int mt_get_counts(mt_ctx* c, int64_t* n_cand, int64_t* n_pairs, int64_t* nnz_D, int64_t* nnz_M) {
@@ -852,7 +838,8 @@ int mt::csr_pattern(mt_ctx* c, int64_t* nnz_D, int64_t* nnz_M, hipStream_t st, b
                                c->pat_keep.as<int32_t>(), S.n_el, c->pat_ecnt.as<int32_t>(),
                                c->pat_elist.as<int32_t>(), st));
     MT_HIP(scan_exclusive2(c->D_cnt.as<int32_t>(), c->D_rowptr.as<int32_t>(), c->M_cnt.as<int32_t>(),
-                           c->M_rowptr.as<int32_t>(), n, c->scan_tmp, st, aux ? SCAN_BLOCKS_BESIDE : 0));
+                           c->M_rowptr.as<int32_t>(), n, c->scan_tmp, st, aux ? SCAN_BLOCKS_BESIDE : 0,
+                           ScanStage{ScanStage::NNZ, 0, c->state.as<DevState>()}));
     // the column arrays are sized by the local block entries (16 per slave
     // element for D, 16 per pair for M); then the CSR position of every
     // local block entry, pair by pair
@@ -887,17 +874,9 @@ int mt::csr_pattern(mt_ctx* c, int64_t* nnz_D, int64_t* nnz_M, hipStream_t st, b
   c->have_pattern = true;
   ++c->pattern_gen;
   if (!nnz_D && !nnz_M) return MT_OK;
-  int32_t tot[2] = {0, 0};
   DevState hs;
-  MT_HIP(read_back(c, {{&tot[0], c->D_rowptr.as<int32_t>() + n, 4}, {&tot[1], c->M_rowptr.as<int32_t>() + n, 4},
-                       {&hs, c->state.p, sizeof(hs)}}, st));
-  c->nnz_D = tot[0];
-  c->nnz_M = tot[1];
-  c->n_cand = hs.n_cand;
-  c->n_maybe = hs.n_screened;
-  c->n_pairs = hs.n_pairs;
-  c->grid = hs.grid;
-  c->counts_known = true;
+  MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}}, st));
+  set_counts(c, hs);
   if (nnz_D) *nnz_D = c->nnz_D;
   if (nnz_M) *nnz_M = c->nnz_M;
   return MT_OK;
@@ -911,11 +890,12 @@ int mt_get_csr(mt_ctx* c, int32_t* D_rowptr, int32_t* D_col, int32_t* M_rowptr, 
   if (int rc = host_counts(c)) return rc;
   DeviceScope ds(c->device);
   hipStream_t st = (hipStream_t)stream;
-  const size_t nr = (size_t)c->side[0].n_nodes + 1;
-  if (D_rowptr) MT_HIP(hipMemcpyAsync(D_rowptr, c->D_rowptr.p, 4 * nr, hipMemcpyDeviceToDevice, st));
-  if (M_rowptr) MT_HIP(hipMemcpyAsync(M_rowptr, c->M_rowptr.p, 4 * nr, hipMemcpyDeviceToDevice, st));
-  if (D_col && c->nnz_D) MT_HIP(hipMemcpyAsync(D_col, c->D_col.p, 4 * (size_t)c->nnz_D, hipMemcpyDeviceToDevice, st));
-  if (M_col && c->nnz_M) MT_HIP(hipMemcpyAsync(M_col, c->M_col.p, 4 * (size_t)c->nnz_M, hipMemcpyDeviceToDevice, st));
+  const int64_t nr = (int64_t)c->side[0].n_nodes + 1;
+  MT_HIP(copy_i32(CopyList{{c->D_rowptr.as<int32_t>(), c->M_rowptr.as<int32_t>(), c->D_col.as<int32_t>(),
+                            c->M_col.as<int32_t>()},
+                           {D_rowptr, M_rowptr, D_col, M_col},
+                           {nr, nr, c->nnz_D, c->nnz_M}},
+                  st));
   return MT_OK;
 }
 

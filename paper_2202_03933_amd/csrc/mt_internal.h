@@ -102,7 +102,13 @@ struct DevState {
   int32_t need_screened;  // screened candidates among the kept candidates
   int32_t need_pairs;     // pairs among the kept screened candidates
   uint32_t flags;         // DS_* bits
-  int32_t pad[2];
+  int32_t nnz_D, nnz_M;   // nonzeros of the last pattern (written by the scans of its row lengths)
+};
+
+// What the host reads back, in one piece.
+struct DevStatus {
+  Counters counters;
+  DevState state;
 };
 
 // Clip polygons of the pairs, structure-of-arrays over the pair index p:
@@ -268,10 +274,12 @@ namespace mt {
 // stage, written to the device state clamped to the stage's capacity `cap`,
 // an excess flagged.
 struct ScanStage {
-  enum { CANDIDATES, SCREENED, PAIRS };
+  // NNZ: of the first array of a scan of two; the second's is the other one
+  enum { CANDIDATES, SCREENED, PAIRS, NNZ };
   int32_t stage = 0;
   int64_t cap = 0;
   DevState* st = nullptr;
+  bool second = false;
 };
 // Scratch (int32 elements) of a scan of up to n values.
 int64_t scan_tmp_elems(int64_t n);
@@ -283,13 +291,21 @@ hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, const Buf&
 // Two such scans of arrays of the same length (in into out, in2 into out2)
 // in the launches of one; the same scratch.
 hipError_t scan_exclusive2(const int32_t* in, int32_t* out, const int32_t* in2, int32_t* out2, int64_t n,
-                           const Buf& tmp, hipStream_t s, int64_t max_blocks = 0);
+                           const Buf& tmp, hipStream_t s, int64_t max_blocks = 0, const ScanStage& stage = ScanStage{});
 // Workgroup cap of scans that run beside the pair kernels.
 constexpr int64_t SCAN_BLOCKS_BESIDE = 256;
 // The same over a count the device holds (*n_dev <= cap): out[0..*n_dev],
 // out[*n_dev] = total; what lies behind is not written.
 hipError_t scan_exclusive_dev(const int32_t* in, int32_t* out, const int32_t* n_dev, int64_t cap, const Buf& tmp,
                               hipStream_t s, const ScanStage& stage = ScanStage{});
+// Copies of n[q] int32 from src[q] to dst[q] (device memory; dst null or n 0:
+// none), in one launch.
+struct CopyList {
+  const int32_t* src[4];
+  int32_t* dst[4];
+  int64_t n[4];
+};
+hipError_t copy_i32(const CopyList& list, hipStream_t s);
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 
 // ---- search (mt_search.hip) ------------------------------------------------

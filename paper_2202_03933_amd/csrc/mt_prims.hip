@@ -107,9 +107,14 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_sums(const int32_t* __restrict
 }
 
 // The total of a stage of the build into the device state, clamped to the
-// stage's capacity (the flag records an excess).
-__device__ void stage_total(const ScanStage& g, int64_t total) {
+// stage's capacity (the flag records an excess); the nonzeros of the pattern
+// as they are (second: of the scan's second array).
+__device__ void stage_total(const ScanStage& g, int64_t total, bool second) {
   DevState* st = g.st;
+  if (g.stage == ScanStage::NNZ) {
+    (second ? st->nnz_M : st->nnz_D) = (int32_t)total;
+    return;
+  }
   const bool over = total < 0 || total > g.cap;  // negative: the int32 scan overflowed (more than 2^31)
   const int32_t all = (int32_t)(total < 0 ? 0x7fffffff : total);
   const int32_t kept = (int32_t)(total < 0 ? 0 : (total < g.cap ? total : g.cap));
@@ -192,7 +197,7 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_scan(const int32_t* __restrict
   }
   if (w == end && threadIdx.x == 0) {
     if (live == n) out[n] = off;  // (else written above: no value lies behind the live ones)
-    if (stage.st) stage_total(stage, off);
+    if (stage.st) stage_total(stage, off, (blockIdx.y != 0) != stage.second);
   }
 }
 
@@ -212,8 +217,10 @@ hipError_t scan_impl(const int32_t* in, int32_t* out, int64_t n, const int32_t* 
   if (in2) addr |= reinterpret_cast<uintptr_t>(in2) | reinterpret_cast<uintptr_t>(out2);
   const bool vec = (addr & 15) == 0;
   if (in2 && blocks > SCAN_DIRECT) {
-    hipError_t e = scan_impl(in, out, n, n_dev, tmp, s, nullptr, nullptr, max_blocks);
-    return e != hipSuccess ? e : scan_impl(in2, out2, n, nullptr, tmp, s, nullptr, nullptr, max_blocks);
+    hipError_t e = scan_impl(in, out, n, n_dev, tmp, s, nullptr, nullptr, max_blocks, stage);
+    ScanStage other = stage;
+    other.second = true;
+    return e != hipSuccess ? e : scan_impl(in2, out2, n, nullptr, tmp, s, nullptr, nullptr, max_blocks, other);
   }
   const dim3 grid((unsigned)blocks, in2 ? 2u : 1u);
   if (blocks <= SCAN_SELF && per == 1) {
@@ -262,7 +269,34 @@ __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
 }
+
+// Several copies in one launch, a row of workgroups each: four runtime copies
+// are four launches of about 2 us one after the other, and as many calls.
+__global__ __launch_bounds__(256) void k_copy_i32(CopyList L) {
+  const int q = blockIdx.y;
+  const int32_t* __restrict__ src = L.src[q];
+  int32_t* __restrict__ dst = L.dst[q];
+  if (!dst) return;
+  const int64_t n = L.n[q], t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  int64_t done = 0;
+  if (((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0) {
+    done = n & ~int64_t(3);
+    for (int64_t i = t; i < n / 4; i += step)
+      reinterpret_cast<int4*>(dst)[i] = reinterpret_cast<const int4*>(src)[i];
+  }
+  for (int64_t i = done + t; i < n; i += step) dst[i] = src[i];
+}
 }  // namespace
+
+hipError_t copy_i32(const CopyList& list, hipStream_t s) {
+  int64_t most = 0;
+  for (int q = 0; q < 4; ++q)
+    if (list.dst[q]) most = std::max(most, list.n[q]);
+  if (most == 0) return hipSuccess;
+  const int64_t blocks = std::min<int64_t>((most + 1023) / 1024, FILL_BLOCKS);
+  k_copy_i32<<<dim3((unsigned)blocks, 4), 256, 0, s>>>(list);
+  return hipGetLastError();
+}
 
 hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, const Buf& tmp, hipStream_t s,
                           int64_t max_blocks, const ScanStage& stage) {
@@ -271,9 +305,9 @@ hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, const Buf&
 }
 
 hipError_t scan_exclusive2(const int32_t* in, int32_t* out, const int32_t* in2, int32_t* out2, int64_t n,
-                           const Buf& tmp, hipStream_t s, int64_t max_blocks) {
+                           const Buf& tmp, hipStream_t s, int64_t max_blocks, const ScanStage& stage) {
   if ((int64_t)(tmp.bytes / sizeof(int32_t)) < scan_tmp_elems(n)) return hipErrorInvalidValue;
-  return scan_impl(in, out, n, nullptr, tmp.as<int32_t>(), s, in2, out2, max_blocks);
+  return scan_impl(in, out, n, nullptr, tmp.as<int32_t>(), s, in2, out2, max_blocks, stage);
 }
 
 hipError_t scan_exclusive_dev(const int32_t* in, int32_t* out, const int32_t* n_dev, int64_t cap, const Buf& tmp,
