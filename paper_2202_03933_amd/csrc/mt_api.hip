@@ -657,13 +657,12 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
     MT_HIP(launch_cand_count(c->box_s.as<double>(), ns, c->sbox.as<double>(), c->qbox.as<uint64_t>(),
                              c->vals.as<uint32_t>(), c->cell_start.as<int32_t>(), g, c->params.delta,
                              c->cand_cnt.as<int32_t>(), c->cand_tmp.as<int32_t>(), st));
-    MT_HIP(scan_exclusive(c->cand_cnt.as<int32_t>(), c->cand_off.as<int32_t>(), ns, c->scan_tmp, st, 0,
-                          ScanStage{ScanStage::CANDIDATES, cap.candidates, dst}));
     MT_HIP(launch_cand_fill(c->box_s.as<double>(), ns, c->sbox.as<double>(), c->vals.as<uint32_t>(),
-                            c->cell_start.as<int32_t>(), g, c->params.delta, c->cand_tmp.as<int32_t>(),
-                            c->cand_off.as<int32_t>(), c->cand_s.as<int32_t>(), c->cand_m.as<int32_t>(),
-                            c->sdata.as<double>(), c->mdata.as<double>(), kp.eps_a, c->cand_nv.as<uint8_t>(),
-                            c->scr_cnt.as<int32_t>(), cnt, cap.candidates, st));
+                            c->cell_start.as<int32_t>(), g, c->params.delta, c->cand_cnt.as<int32_t>(),
+                            c->cand_tmp.as<int32_t>(), c->cand_off.as<int32_t>(), c->scan_tmp,
+                            c->cand_s.as<int32_t>(), c->cand_m.as<int32_t>(), c->sdata.as<double>(),
+                            c->mdata.as<double>(), kp.eps_a, c->cand_nv.as<uint8_t>(), c->scr_cnt.as<int32_t>(), cnt,
+                            ScanStage{ScanStage::CANDIDATES, cap.candidates, dst}, st));
   }
   const int64_t SC = cap.screened;
   c->mpoly_stride = SC;
@@ -671,10 +670,9 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
                       c->mpoly_nf.as<uint8_t>(), SC, nullptr};
   {
     PhaseTimer t(c, MT_T_COMPACT, st);
-    MT_HIP(scan_exclusive(c->scr_cnt.as<int32_t>(), c->scr_off.as<int32_t>(), ns, c->scan_tmp, st, 0,
-                          ScanStage{ScanStage::SCREENED, SC, dst}));
-    MT_HIP(launch_maybe_list(c->cand_nv.as<uint8_t>(), c->cand_off.as<int32_t>(), c->scr_off.as<int32_t>(), ns,
-                             cap.candidates, SC, c->maybe_list.as<int32_t>(), st));
+    MT_HIP(launch_maybe_list(c->cand_nv.as<uint8_t>(), c->cand_off.as<int32_t>(), c->scr_cnt.as<int32_t>(),
+                             c->scr_off.as<int32_t>(), ns, cap.candidates, c->scan_tmp, c->maybe_list.as<int32_t>(),
+                             ScanStage{ScanStage::SCREENED, SC, dst}, st));
   }
   {
     PhaseTimer t(c, MT_T_CLIP, st);
@@ -832,21 +830,16 @@ int mt::csr_pattern(mt_ctx* c, int64_t* nnz_D, int64_t* nnz_M, hipStream_t st, b
       MT_HIP(launch_pair_fwd(S, M, kparams(c->params), c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(), np_dev, P,
                              poly_buf(c), c->blk.as<double>(), fwd_sums(c), c->counters.as<Counters>(), c->aux));
     }
-    MT_HIP(launch_pattern_rows(false, c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), n,
-                               c->pair_off.as<int32_t>(), c->pair_m.as<int32_t>(), S.conn, M.conn,
-                               c->D_cnt.as<int32_t>(), c->M_cnt.as<int32_t>(), nullptr, nullptr, nullptr, nullptr,
-                               c->pat_keep.as<int32_t>(), S.n_el, c->pat_ecnt.as<int32_t>(),
-                               c->pat_elist.as<int32_t>(), st));
-    MT_HIP(scan_exclusive2(c->D_cnt.as<int32_t>(), c->D_rowptr.as<int32_t>(), c->M_cnt.as<int32_t>(),
-                           c->M_rowptr.as<int32_t>(), n, c->scan_tmp, st, aux ? SCAN_BLOCKS_BESIDE : 0,
-                           ScanStage{ScanStage::NNZ, 0, c->state.as<DevState>()}));
     // the column arrays are sized by the local block entries (16 per slave
-    // element for D, 16 per pair for M); then the CSR position of every
-    // local block entry, pair by pair
-    MT_HIP(launch_pattern_rows(true, c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), n,
-                               c->pair_off.as<int32_t>(), c->pair_m.as<int32_t>(), S.conn, M.conn, nullptr, nullptr,
-                               c->D_rowptr.as<int32_t>(), c->M_rowptr.as<int32_t>(), c->D_col.as<int32_t>(),
-                               c->M_col.as<int32_t>(), c->pat_keep.as<int32_t>(), S.n_el, nullptr, nullptr, st));
+    // element for D, 16 per pair for M); then the places of the local block
+    // entries in them, pair by pair
+    MT_HIP(launch_pattern_rows(c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), n, c->pair_off.as<int32_t>(),
+                               c->pair_m.as<int32_t>(), S.conn, M.conn, c->D_cnt.as<int32_t>(),
+                               c->M_cnt.as<int32_t>(), c->D_rowptr.as<int32_t>(), c->M_rowptr.as<int32_t>(),
+                               c->D_col.as<int32_t>(), c->M_col.as<int32_t>(), c->pat_keep.as<int32_t>(), S.n_el,
+                               c->pat_ecnt.as<int32_t>(), c->pat_elist.as<int32_t>(), c->scan_tmp,
+                               aux ? SCAN_BLOCKS_BESIDE : 0,
+                               ScanStage{ScanStage::NNZ, 0, c->state.as<DevState>()}, st));
     MT_HIP(launch_pattern_positions(c->pair_s.as<int32_t>(), c->pair_m.as<int32_t>(), np_dev, P, S.conn, M.conn,
                                     S.n_el, c->pair_off.as<int32_t>(), c->D_rowptr.as<int32_t>(),
                                     c->D_col.as<int32_t>(), c->M_rowptr.as<int32_t>(), c->M_col.as<int32_t>(),

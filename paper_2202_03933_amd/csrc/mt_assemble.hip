@@ -7,6 +7,7 @@
 #include "mt_geometry.h"
 #include "mt_internal.h"
 #include "mt_rows.h"
+#include "mt_scan.h"
 
 namespace mt {
 
@@ -210,8 +211,7 @@ __device__ __forceinline__ void pattern_row(int a, int32_t n, int32_t* lds, cons
                                             const int32_t* __restrict__ pair_m,
                                             const int32_t* __restrict__ conn_s,
                                             const int32_t* __restrict__ conn_m, int32_t* cnt,
-                                            const int32_t* __restrict__ rowptr, int32_t* colv, int32_t* keep,
-                                            int kcap) {
+                                            int32_t* col, int32_t* keep, int kcap) {
   const int u = row_columns<MCOLS>(a, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, lds, PB, PCAP);
   if (u >= 0) {
     if (!FILL) {
@@ -219,59 +219,93 @@ __device__ __forceinline__ void pattern_row(int a, int32_t n, int32_t* lds, cons
       if (u <= kcap)
         for (int i = 0; i < u; ++i) keep[(int64_t)i * n] = lds[i * PB];
     } else {
-      int32_t* col = colv + rowptr[a];
       for (int i = 0; i < u; ++i) col[i] = lds[i * PB];
     }
   } else if (!FILL) {
     cnt[a] = row_columns_scan<MCOLS>(a, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, nullptr);
   } else {
-    row_columns_scan<MCOLS>(a, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, colv + rowptr[a]);
+    row_columns_scan<MCOLS>(a, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, col);
   }
 }
 
 // Kept rows of the fill pass: copied from the lane-interleaved scratch.
-__device__ __forceinline__ void kept_row(int a, int32_t n, int u, const int32_t* __restrict__ keep,
-                                         const int32_t* __restrict__ rowptr, int32_t* colv) {
-  int32_t* col = colv + rowptr[a];
+__device__ __forceinline__ void kept_row(int a, int32_t n, int u, const int32_t* __restrict__ keep, int32_t* col) {
   for (int i = 0; i < u; ++i) col[i] = keep[(int64_t)i * n + a];
 }
 
-template <bool FILL>
-__global__ __launch_bounds__(PB) void k_pattern_rows(const int32_t* __restrict__ inc_off,
-                                                      const int32_t* __restrict__ inc_list, int32_t n,
-                                                      const int32_t* __restrict__ pair_off,
-                                                      const int32_t* __restrict__ pair_m,
-                                                      const int32_t* __restrict__ conn_s,
-                                                      const int32_t* __restrict__ conn_m, int32_t* D_cnt,
-                                                      int32_t* M_cnt,
-                                                      const int32_t* __restrict__ D_rowptr,
-                                                      const int32_t* __restrict__ M_rowptr, int32_t* D_col,
-                                                      int32_t* M_col, int32_t* keepD, int32_t* keepM, int32_t n_el,
-                                                      const int32_t* __restrict__ ecnt,
-                                                      const int32_t* __restrict__ elist) {
+// Count pass.
+__global__ __launch_bounds__(PB) void k_pattern_count(const int32_t* __restrict__ inc_off,
+                                                       const int32_t* __restrict__ inc_list, int32_t n,
+                                                       const int32_t* __restrict__ pair_off,
+                                                       const int32_t* __restrict__ pair_m,
+                                                       const int32_t* __restrict__ conn_s,
+                                                       const int32_t* __restrict__ conn_m, int32_t* D_cnt,
+                                                       int32_t* M_cnt, int32_t* keepD, int32_t* keepM, int32_t n_el,
+                                                       const int32_t* __restrict__ ecnt,
+                                                       const int32_t* __restrict__ elist) {
   __shared__ int32_t lds[PCAP * PB];
   const int a = xcd_tile(blockIdx.x, gridDim.x) * PB + threadIdx.x;
   if (a >= n) return;
   int32_t* seg = lds + threadIdx.x;
-  // D row
-  if (FILL && D_rowptr[a + 1] - D_rowptr[a] <= KD)
-    kept_row(a, n, D_rowptr[a + 1] - D_rowptr[a], keepD, D_rowptr, D_col);
+  pattern_row<false, false>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, D_cnt, nullptr, keepD + a,
+                            KD);
+  // M row: merge of the element lists where they exist
+  const int u = merge_mrow(a, n, inc_off, inc_list, n_el, ecnt, elist, keepM + a, KM);
+  if (u >= 0)
+    M_cnt[a] = u;
   else
-    pattern_row<FILL, false>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, D_cnt, D_rowptr, D_col,
-                             keepD + a, KD);
-  // M row (count pass: merge of the element lists when they exist)
-  if (!FILL && ecnt) {
-    const int u = merge_mrow(a, n, inc_off, inc_list, n_el, ecnt, elist, keepM + a, KM);
-    if (u >= 0) {
-      M_cnt[a] = u;
-      return;
+    pattern_row<false, true>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, M_cnt, nullptr,
+                             keepM + a, KM);
+}
+
+// Fill pass; SELF (up to SELF_OFFSETS rows): the row pointers from the counts
+// in the same launch.
+template <bool SELF>
+__global__ __launch_bounds__(PB) void k_pattern_fill(const int32_t* __restrict__ inc_off,
+                                                      const int32_t* __restrict__ inc_list, int32_t n,
+                                                      const int32_t* __restrict__ pair_off,
+                                                      const int32_t* __restrict__ pair_m,
+                                                      const int32_t* __restrict__ conn_s,
+                                                      const int32_t* __restrict__ conn_m,
+                                                      const int32_t* __restrict__ D_cnt,
+                                                      const int32_t* __restrict__ M_cnt, int32_t* D_rowptr,
+                                                      int32_t* M_rowptr, int32_t* D_col, int32_t* M_col,
+                                                      const int32_t* __restrict__ keepD,
+                                                      const int32_t* __restrict__ keepM, ScanStage stage) {
+  __shared__ int32_t lds[PCAP * PB];
+  const int a0 = xcd_tile(blockIdx.x, gridDim.x) * PB, a = a0 + threadIdx.x;
+  if (a0 >= n) return;  // the whole workgroup
+  int d0 = 0, m0 = 0, nd = 0, nm = 0;
+  if (a < n) {
+    nd = SELF ? D_cnt[a] : D_rowptr[a + 1] - (d0 = D_rowptr[a]);
+    nm = SELF ? M_cnt[a] : M_rowptr[a + 1] - (m0 = M_rowptr[a]);
+  }
+  if (SELF) {
+    d0 = self_offset<PB>(D_cnt, a0, nd);
+    m0 = self_offset<PB>(M_cnt, a0, nm);
+  }
+  if (a >= n) return;
+  if (SELF) {
+    D_rowptr[a] = d0;
+    M_rowptr[a] = m0;
+    if (a == n - 1) {
+      D_rowptr[n] = d0 + nd;
+      M_rowptr[n] = m0 + nm;
+      stage_total(stage, d0 + nd, false);
+      stage_total(stage, m0 + nm, true);
     }
   }
-  if (FILL && M_rowptr[a + 1] - M_rowptr[a] <= KM)
-    kept_row(a, n, M_rowptr[a + 1] - M_rowptr[a], keepM, M_rowptr, M_col);
+  int32_t* seg = lds + threadIdx.x;
+  if (nd <= KD)
+    kept_row(a, n, nd, keepD, D_col + d0);
   else
-    pattern_row<FILL, true>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, M_cnt, M_rowptr, M_col,
-                            keepM + a, KM);
+    pattern_row<true, false>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, nullptr, D_col + d0,
+                             nullptr, KD);
+  if (nm <= KM)
+    kept_row(a, n, nm, keepM, M_col + m0);
+  else
+    pattern_row<true, true>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, nullptr, M_col + m0,
+                            nullptr, KM);
 }
 
 // Positions of four keys that all occur in the sorted row v[0..u): a
@@ -618,22 +652,26 @@ hipError_t launch_inc_sort(const int32_t* off, int32_t n_nodes, int32_t* list, h
   return hipGetLastError();
 }
 
-hipError_t launch_pattern_rows(bool fill, const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
+hipError_t launch_pattern_rows(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
                                const int32_t* pair_off, const int32_t* pair_m, const int32_t* conn_s,
-                               const int32_t* conn_m, int32_t* D_cnt, int32_t* M_cnt, const int32_t* D_rowptr,
-                               const int32_t* M_rowptr, int32_t* D_col, int32_t* M_col, int32_t* keep,
-                               int32_t n_s_el, int32_t* ecnt, int32_t* elist, hipStream_t s) {
-  if (n_nodes == 0) return hipSuccess;
+                               const int32_t* conn_m, int32_t* D_cnt, int32_t* M_cnt, int32_t* D_rowptr,
+                               int32_t* M_rowptr, int32_t* D_col, int32_t* M_col, int32_t* keep, int32_t n_s_el,
+                               const int32_t* ecnt, const int32_t* elist, const Buf& scan_tmp, int64_t scan_blocks,
+                               const ScanStage& stage, hipStream_t s) {
   const unsigned g = xcd_grid((unsigned)((n_nodes + PB - 1) / PB));
   int32_t* keepD = keep;
   int32_t* keepM = keep + (int64_t)KD * n_nodes;
-  if (fill)
-    k_pattern_rows<true><<<g, PB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, pair_m, conn_s, conn_m, D_cnt, M_cnt,
-                                          D_rowptr, M_rowptr, D_col, M_col, keepD, keepM, n_s_el, nullptr, nullptr);
-  else
-    k_pattern_rows<false><<<g, PB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, pair_m, conn_s, conn_m, D_cnt,
-                                           M_cnt, D_rowptr, M_rowptr, D_col, M_col, keepD, keepM, n_s_el, ecnt,
-                                           elist);
+  const bool self = n_nodes > 0 && n_nodes <= SELF_OFFSETS;
+  if (n_nodes > 0)
+    k_pattern_count<<<g, PB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, pair_m, conn_s, conn_m, D_cnt, M_cnt,
+                                     keepD, keepM, n_s_el, ecnt, elist);
+  if (!self) {
+    const hipError_t e = scan_exclusive2(D_cnt, D_rowptr, M_cnt, M_rowptr, n_nodes, scan_tmp, s, scan_blocks, stage);
+    if (e != hipSuccess || n_nodes == 0) return e;
+  }
+  auto* k = self ? k_pattern_fill<true> : k_pattern_fill<false>;
+  k<<<g, PB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, pair_m, conn_s, conn_m, D_cnt, M_cnt, D_rowptr, M_rowptr,
+                     D_col, M_col, keepD, keepM, stage);
   return hipGetLastError();
 }
 

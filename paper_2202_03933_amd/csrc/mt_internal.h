@@ -334,22 +334,26 @@ hipError_t launch_cand_count(const double* box_s, int32_t n_s, const double* sbo
                              const uint32_t* mvals, const int32_t* cell_start, const Grid* g, double delta,
                              int32_t* count,
                              int32_t* tmp, hipStream_t s);
-// Candidates of slave s go to [off[s], off[s + 1]) of cand_s / cand_m / nv
-// (vertex count, or 255 where the clip is to write it), whose length is cap: a
-// slave whose range ends beyond cap writes
-// nothing and gets scr_cnt[s] = 0 (the stage totals flag the excess).
+// Offsets of the counts into off (their total to the stage), and the
+// candidates: those of slave s go to [off[s], off[s + 1]) of cand_s / cand_m /
+// nv (vertex count, or 255 where the clip is to write it), whose length is
+// stage.cap: a slave whose range ends beyond it writes nothing and gets
+// scr_cnt[s] = 0 (the stage totals flag the excess).
 hipError_t launch_cand_fill(const double* box_s, int32_t n_s, const double* sbox, const uint32_t* mvals,
-                            const int32_t* cell_start, const Grid* g, double delta, const int32_t* tmp,
-                            const int32_t* off, int32_t* cand_s, int32_t* cand_m, const double* sd, const double* md, double eps_a,
-                            uint8_t* nv, int32_t* scr_cnt, Counters* cnt, int64_t cap,
-                            hipStream_t s);
+                            const int32_t* cell_start, const Grid* g, double delta, const int32_t* count,
+                            const int32_t* tmp, int32_t* off, const Buf& scan_tmp, int32_t* cand_s, int32_t* cand_m,
+                            const double* sd, const double* md, double eps_a, uint8_t* nv, int32_t* scr_cnt,
+                            Counters* cnt, const ScanStage& stage, hipStream_t s);
 int cand_tmp_per_slave();
 
 // ---- pairs (mt_pairs.hip) ----------------------------------------------------
 // Histogram of clip vertex counts nv[0..n) added to hist[17].
 hipError_t launch_nv_hist(const uint8_t* nv, int64_t n, unsigned long long* hist, hipStream_t s);
-hipError_t launch_maybe_list(const uint8_t* nv, const int32_t* cand_off, const int32_t* scr_off, int32_t n_s,
-                             int64_t cap_cand, int64_t cap, int32_t* mlist, hipStream_t s);
+// Offsets of scr_cnt into scr_off (their total to the stage) and the list of
+// the screened-in candidates, of length stage.cap.
+hipError_t launch_maybe_list(const uint8_t* nv, const int32_t* cand_off, const int32_t* scr_cnt, int32_t* scr_off,
+                             int32_t n_s, int64_t cap_cand, const Buf& scan_tmp, int32_t* mlist,
+                             const ScanStage& stage, hipStream_t s);
 hipError_t launch_clip_screened(const double* mdata, const double* sdata, int32_t n_s, const KParams& kp,
                                 const int32_t* cand_s, const int32_t* cand_m, const int32_t* mlist,
                                 const int32_t* n_maybe, int64_t cap, uint8_t* nv, int32_t* flag2, const PolyBuf& out,
@@ -383,11 +387,15 @@ hipError_t launch_inc_count(const int32_t* conn, int32_t n_el, int32_t* cnt, hip
 hipError_t launch_inc_fill(const int32_t* conn, int32_t n_el, const int32_t* off, int32_t* cur,
                            int32_t* list, hipStream_t s);
 hipError_t launch_inc_sort(const int32_t* off, int32_t n_nodes, int32_t* list, hipStream_t s);
-hipError_t launch_pattern_rows(bool fill, const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
+// The row patterns: counts, row pointers (the totals to the stage) and sorted
+// columns; the scan between the passes with at most scan_blocks workgroups a
+// launch (0: any).
+hipError_t launch_pattern_rows(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
                                const int32_t* pair_off, const int32_t* pair_m, const int32_t* conn_s,
-                               const int32_t* conn_m, int32_t* D_cnt, int32_t* M_cnt, const int32_t* D_rowptr,
-                               const int32_t* M_rowptr, int32_t* D_col, int32_t* M_col, int32_t* keep,
-                               int32_t n_s_el, int32_t* ecnt, int32_t* elist, hipStream_t s);
+                               const int32_t* conn_m, int32_t* D_cnt, int32_t* M_cnt, int32_t* D_rowptr,
+                               int32_t* M_rowptr, int32_t* D_col, int32_t* M_col, int32_t* keep, int32_t n_s_el,
+                               const int32_t* ecnt, const int32_t* elist, const Buf& scan_tmp, int64_t scan_blocks,
+                               const ScanStage& stage, hipStream_t s);
 // Places of every local block entry in its CSR row (store_pos4 with strides
 // n_s_el and cap), from the filled column arrays, and the starts of each
 // element's rows (load_erow).

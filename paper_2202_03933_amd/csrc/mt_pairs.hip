@@ -9,6 +9,7 @@
 #include <algorithm>
 
 #include "mt_pair_eval.h"
+#include "mt_scan.h"
 
 namespace mt {
 
@@ -42,16 +43,38 @@ __device__ __forceinline__ void load_slave_data(const double* __restrict__ sd, i
 // candidates from mlist[scr_off[s]] on, in order; a slave whose candidates
 // were not stored (beyond their capacity) has none, and nothing is written
 // at or past the capacity of the list.
+__device__ __forceinline__ void maybe_of_slave(int s, const uint8_t* __restrict__ nv,
+                                               const int32_t* __restrict__ cand_off, int64_t o, int64_t cap_cand,
+                                               int64_t cap, int32_t* __restrict__ mlist) {
+  const int c0 = cand_off[s], c1 = cand_off[s + 1];
+  if (c0 < 0 || (int64_t)c1 > cap_cand) return;
+  for (int c = c0; c < c1 && o < cap; ++c)
+    if (nv[c]) mlist[o++] = c;
+}
+
 __global__ __launch_bounds__(BS) void k_maybe_list(const uint8_t* __restrict__ nv, const int32_t* __restrict__ cand_off,
                                                     const int32_t* __restrict__ scr_off, int32_t n_s,
                                                     int64_t cap_cand, int64_t cap, int32_t* __restrict__ mlist) {
   const int s = blockIdx.x * BS + threadIdx.x;
+  if (s < n_s) maybe_of_slave(s, nv, cand_off, scr_off[s], cap_cand, cap, mlist);
+}
+
+// The offsets with it, for up to SELF_OFFSETS slave elements.
+__global__ __launch_bounds__(BS) void k_maybe_list_self(const uint8_t* __restrict__ nv,
+                                                         const int32_t* __restrict__ cand_off,
+                                                         const int32_t* __restrict__ scr_cnt,
+                                                         int32_t* __restrict__ scr_off, int32_t n_s, int64_t cap_cand,
+                                                         int32_t* __restrict__ mlist, ScanStage stage) {
+  const int s0 = blockIdx.x * BS, s = s0 + threadIdx.x;
+  const int x = s < n_s ? scr_cnt[s] : 0;
+  const int o = self_offset<BS>(scr_cnt, s0, x);
   if (s >= n_s) return;
-  const int c0 = cand_off[s], c1 = cand_off[s + 1];
-  if (c0 < 0 || (int64_t)c1 > cap_cand) return;
-  int64_t o = scr_off[s];
-  for (int c = c0; c < c1 && o < cap; ++c)
-    if (nv[c]) mlist[o++] = c;
+  scr_off[s] = o;
+  if (s == n_s - 1) {
+    scr_off[n_s] = o + x;
+    stage_total(stage, o + x, false);
+  }
+  maybe_of_slave(s, nv, cand_off, o, cap_cand, stage.cap, mlist);
 }
 
 // Clip and cleanup of every screened candidate (LDS clip buffers with
@@ -222,10 +245,17 @@ hipError_t launch_nv_hist(const uint8_t* nv, int64_t n, unsigned long long* hist
   return hipGetLastError();
 }
 
-hipError_t launch_maybe_list(const uint8_t* nv, const int32_t* cand_off, const int32_t* scr_off, int32_t n_s,
-                             int64_t cap_cand, int64_t cap, int32_t* mlist, hipStream_t s) {
-  if (n_s == 0) return hipSuccess;
-  k_maybe_list<<<(unsigned)((n_s + BS - 1) / BS), BS, 0, s>>>(nv, cand_off, scr_off, n_s, cap_cand, cap, mlist);
+hipError_t launch_maybe_list(const uint8_t* nv, const int32_t* cand_off, const int32_t* scr_cnt, int32_t* scr_off,
+                             int32_t n_s, int64_t cap_cand, const Buf& scan_tmp, int32_t* mlist,
+                             const ScanStage& stage, hipStream_t s) {
+  const unsigned nb = (unsigned)((n_s + BS - 1) / BS);
+  if (n_s > 0 && n_s <= SELF_OFFSETS) {
+    k_maybe_list_self<<<nb, BS, 0, s>>>(nv, cand_off, scr_cnt, scr_off, n_s, cap_cand, mlist, stage);
+    return hipGetLastError();
+  }
+  hipError_t e = scan_exclusive(scr_cnt, scr_off, n_s, scan_tmp, s, 0, stage);
+  if (e != hipSuccess || n_s == 0) return e;
+  k_maybe_list<<<nb, BS, 0, s>>>(nv, cand_off, scr_off, n_s, cap_cand, stage.cap, mlist);
   return hipGetLastError();
 }
 

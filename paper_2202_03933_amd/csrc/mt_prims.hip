@@ -1,6 +1,6 @@
 // Device-wide primitives: exclusive scan and fill, written for 64-wide
 // wavefronts.
-#include "mt_internal.h"
+#include "mt_scan.h"
 
 namespace mt {
 
@@ -9,39 +9,6 @@ namespace {
 constexpr int SCAN_BS = 256;
 constexpr int SCAN_IPT = 8;
 constexpr int SCAN_TILE = SCAN_BS * SCAN_IPT;
-
-__device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
-
-// Inclusive scan of one value per lane across a wavefront.
-template <class T>
-__device__ __forceinline__ T wave_inclusive(T x) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    T y = __shfl_up(x, d, 64);
-    if (lane_id() >= d) x += y;
-  }
-  return x;
-}
-
-// Exclusive scan across the block of one value per thread; returns the
-// exclusive prefix and writes the block total to *total.
-template <class T>
-__device__ __forceinline__ T block_exclusive(T x, T* total) {
-  __shared__ T wsum[SCAN_BS / 64];
-  const int w = threadIdx.x >> 6;
-  T inc = wave_inclusive(x);
-  if (lane_id() == 63) wsum[w] = inc;
-  __syncthreads();
-  T off = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < SCAN_BS / 64; ++i) {
-    if (i < w) off += wsum[i];
-    tot += wsum[i];
-  }
-  __syncthreads();
-  *total = tot;
-  return off + inc - x;
-}
 
 // n_dev (optional): a count the device holds, at most n; entries from it on
 // count as zero, and the outputs behind out[*n_dev] are left alone.
@@ -102,34 +69,8 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_sums(const int32_t* __restrict
     for (int i = 0; i < SCAN_IPT; ++i) s += v[i];
   }
   int32_t tot;
-  block_exclusive(s, &tot);
+  block_exclusive<SCAN_BS>(s, &tot);
   if (threadIdx.x == 0) sums[blockIdx.x] = tot;
-}
-
-// The total of a stage of the build into the device state, clamped to the
-// stage's capacity (the flag records an excess); the nonzeros of the pattern
-// as they are (second: of the scan's second array).
-__device__ void stage_total(const ScanStage& g, int64_t total, bool second) {
-  DevState* st = g.st;
-  if (g.stage == ScanStage::NNZ) {
-    (second ? st->nnz_M : st->nnz_D) = (int32_t)total;
-    return;
-  }
-  const bool over = total < 0 || total > g.cap;  // negative: the int32 scan overflowed (more than 2^31)
-  const int32_t all = (int32_t)(total < 0 ? 0x7fffffff : total);
-  const int32_t kept = (int32_t)(total < 0 ? 0 : (total < g.cap ? total : g.cap));
-  if (g.stage == ScanStage::CANDIDATES) {
-    st->n_cand = all;
-    if (over) st->flags |= DS_CAP_CAND;
-  } else if (g.stage == ScanStage::SCREENED) {
-    st->need_screened = all;
-    st->n_screened = kept;
-    if (over) st->flags |= DS_CAP_SCREENED;
-  } else {
-    st->need_pairs = all;
-    st->n_pairs = kept;
-    if (over) st->flags |= DS_CAP_PAIRS;
-  }
 }
 
 // out[i] = offset of the workgroup + exclusive prefix of in within its
@@ -157,7 +98,7 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_scan(const int32_t* __restrict
   if (OFF == OFF_SUMS) {
     int32_t part = 0;
     for (int64_t i = threadIdx.x; i < w; i += SCAN_BS) part += offs[i];
-    block_exclusive(part, &off);
+    block_exclusive<SCAN_BS>(part, &off);
   } else if (OFF == OFF_SELF) {
     int32_t part = 0;
     for (int64_t t = 0; t < w * per; ++t) {
@@ -166,7 +107,7 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_scan(const int32_t* __restrict
 #pragma unroll
       for (int i = 0; i < SCAN_IPT; ++i) part += v[i];
     }
-    block_exclusive(part, &off);
+    block_exclusive<SCAN_BS>(part, &off);
   } else if (offs) {
     off = offs[w];
   }
@@ -178,7 +119,7 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_scan(const int32_t* __restrict
 #pragma unroll
     for (int i = 0; i < SCAN_IPT; ++i) s += v[i];
     int32_t tot;
-    int32_t run = block_exclusive(s, &tot) + off;
+    int32_t run = block_exclusive<SCAN_BS>(s, &tot) + off;
     int32_t o[SCAN_IPT];
 #pragma unroll
     for (int i = 0; i < SCAN_IPT; ++i) {

@@ -1,0 +1,95 @@
+// Scans within a workgroup, and a consumer's own offsets from the counts
+// before it.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "mt_internal.h"
+
+namespace mt {
+
+// Inclusive scan of one value per lane across a wavefront.
+template <class T>
+__device__ __forceinline__ T wave_inclusive(T x) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    T y = __shfl_up(x, d, 64);
+    if ((int)(threadIdx.x & 63) >= d) x += y;
+  }
+  return x;
+}
+
+// Exclusive scan across the workgroup (N threads) of one value per thread;
+// returns the exclusive prefix and writes the total to *total.
+template <int N, class T>
+__device__ __forceinline__ T block_exclusive(T x, T* total) {
+  __shared__ T wsum[N / 64];
+  const int w = threadIdx.x >> 6;
+  T inc = wave_inclusive(x);
+  if ((threadIdx.x & 63) == 63) wsum[w] = inc;
+  __syncthreads();
+  T off = 0, tot = 0;
+#pragma unroll
+  for (int i = 0; i < N / 64; ++i) {
+    if (i < w) off += wsum[i];
+    tot += wsum[i];
+  }
+  __syncthreads();
+  *total = tot;
+  return off + inc - x;
+}
+
+// Offset of each thread's value x (of N threads, cnt[0 .. first) before
+// them; cnt 16-byte aligned, first a multiple of 4): the workgroup adds up
+// the counts before its own, so that no launch need scan them first.  The
+// whole workgroup calls it.
+template <int N>
+__device__ __forceinline__ int32_t self_offset(const int32_t* __restrict__ cnt, int32_t first, int32_t x) {
+  int32_t part = 0;
+  for (int32_t i = 4 * (int32_t)threadIdx.x; i < first; i += 4 * N) {
+    const int4 v = *reinterpret_cast<const int4*>(cnt + i);
+    part += v.x + v.y + v.z + v.w;
+  }
+  int32_t before, own;
+  block_exclusive<N>(part, &before);
+  const int32_t off = block_exclusive<N>(x, &own);
+  return before + off;
+}
+
+// Up to this many counts the kernel that uses their offsets finds them itself
+// (self_offset): every workgroup reads the counts before its own from L2,
+// where the scan costs a launch and the gap before it.  Whole step, wavy,
+// without read-back, scan -> own offsets: 4K slave elements 218 -> 186 us,
+// 10K 233 -> 226, 16K 248 -> 247, 20K 250 -> 249, 33K 270 -> 282, 66K
+// 331 -> 382.
+constexpr int64_t SELF_OFFSETS = 20480;
+
+// The total of a stage of the build into the device state, clamped to the
+// stage's capacity (the flag records an excess); the nonzeros of the pattern
+// as they are (second: of the scan's second array).
+__device__ __forceinline__ void stage_total(const ScanStage& g, int64_t total, bool second) {
+  DevState* st = g.st;
+  if (g.stage == ScanStage::NNZ) {
+    (second ? st->nnz_M : st->nnz_D) = (int32_t)total;
+    return;
+  }
+  const bool over = total < 0 || total > g.cap;  // negative: the int32 scan overflowed (more than 2^31)
+  const int32_t all = (int32_t)(total < 0 ? 0x7fffffff : total);
+  const int32_t kept = (int32_t)(total < 0 ? 0 : (total < g.cap ? total : g.cap));
+  if (g.stage == ScanStage::CANDIDATES) {
+    st->n_cand = all;
+    if (over) st->flags |= DS_CAP_CAND;
+  } else if (g.stage == ScanStage::SCREENED) {
+    st->need_screened = all;
+    st->n_screened = kept;
+    if (over) st->flags |= DS_CAP_SCREENED;
+  } else {
+    st->need_pairs = all;
+    st->n_pairs = kept;
+    if (over) st->flags |= DS_CAP_PAIRS;
+  }
+}
+
+}  // namespace mt

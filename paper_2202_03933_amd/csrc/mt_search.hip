@@ -7,7 +7,7 @@
 #include <cstring>
 
 #include "mt_geometry.h"
-#include "mt_internal.h"
+#include "mt_scan.h"
 
 namespace mt {
 
@@ -639,18 +639,11 @@ __device__ __forceinline__ void count_degenerate(const ScreenOut& so, Counters* 
 // count and keeps no array of its own.  Wavy 1024 x 1024 / 777 x 777: 0.28 ms
 // and 0.040 ms for the list of the screened-in with a 4-byte flag per
 // candidate, 0.25 and 0.018 ms now.
-__global__ __launch_bounds__(BS) void k_cand_fill(int32_t n_s, const int32_t* __restrict__ tmp,
-                                                   const int32_t* __restrict__ off, int32_t* __restrict__ cand_s,
-                                                   int32_t* __restrict__ cand_m, const double* __restrict__ sd,
-                                                   const double* __restrict__ md, double eps_a,
-                                                   uint8_t* __restrict__ nv_out,
-                                                   int32_t* __restrict__ scr_cnt, Counters* cnt, int64_t cap) {
-  const int64_t t = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * BS + threadIdx.x;
-  const int s = (int)(t / G), r = (int)(t % G);
-  if (s >= n_s) return;  // whole groups leave together
-  const int base = off[s];
-  const int c = off[s + 1] - base;
-  if (c > CTMP) return;  // k_cand_fill_long
+__device__ __forceinline__ void fill_short(int s, int r, int32_t n_s, int base, int c,
+                                           const int32_t* __restrict__ tmp, int32_t* __restrict__ cand_s,
+                                           int32_t* __restrict__ cand_m, const double* __restrict__ sd,
+                                           const double* __restrict__ md, double eps_a, uint8_t* __restrict__ nv_out,
+                                           int32_t* __restrict__ scr_cnt, Counters* cnt, int64_t cap) {
   if (base < 0 || (int64_t)base + c > cap) {  // output too short: the host sizes it, runs the pass again
     if (r == 0) scr_cnt[s] = 0;
     return;
@@ -710,6 +703,34 @@ __device__ __forceinline__ void fill_long(int s, int32_t n_s, int base, int c, i
     nscr += screen_one(P, s, v[i * vs], (int64_t)base + i, md, eps_a, cand_s, cand_m, nv_out, so) ? 1 : 0;
 }
 
+// One slave of the long fill: its place [base, base + c) in the output.
+template <int LANES>
+__device__ __forceinline__ void fill_long_slave(int s, int32_t n_s, int base, int c, int64_t cap, int32_t* lds,
+                                                const double* __restrict__ box_s, const double* __restrict__ sbox,
+                                                const uint32_t* __restrict__ mvals,
+                                                const int32_t* __restrict__ cell_start, const Grid* __restrict__ gp,
+                                                double delta, int32_t* __restrict__ cand_s,
+                                                int32_t* __restrict__ cand_m, const double* __restrict__ sd,
+                                                const double* __restrict__ md, double eps_a,
+                                                uint8_t* __restrict__ nv_out, int32_t* __restrict__ scr_cnt,
+                                                Counters* cnt) {
+  if (base < 0 || (int64_t)base + c > cap) {
+    scr_cnt[s] = 0;
+    return;
+  }
+  const Grid g = *gp;
+  ScreenOut so{0u, 0u};
+  int nscr = 0;
+  if (c <= CCAP)
+    fill_long(s, n_s, base, c, lds, LANES, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd, md, eps_a,
+              nv_out, so, nscr);
+  else
+    fill_long(s, n_s, base, c, cand_m + base, 1, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd, md,
+              eps_a, nv_out, so, nscr);
+  count_degenerate(so, cnt);
+  scr_cnt[s] = nscr;
+}
+
 __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict__ box_s, int32_t n_s,
                                                         const double* __restrict__ sbox,
                                                         const uint32_t* __restrict__ mvals,
@@ -724,24 +745,62 @@ __global__ __launch_bounds__(BS) void k_cand_fill_long(const double* __restrict_
   __shared__ int32_t lds[CCAP * BS];
   const int s = xcd_tile(blockIdx.x, gridDim.x) * BS + threadIdx.x;
   if (s >= n_s) return;
-  const int base = off[s];
-  const int c = off[s + 1] - base;
-  if (c <= CTMP) return;
-  if (base < 0 || (int64_t)base + c > cap) {
-    scr_cnt[s] = 0;
-    return;
+  const int base = off[s], c = off[s + 1] - base;
+  if (c > CTMP)
+    fill_long_slave<BS>(s, n_s, base, c, cap, lds + threadIdx.x, box_s, sbox, mvals, cell_start, gp, delta, cand_s,
+                        cand_m, sd, md, eps_a, nv_out, scr_cnt, cnt);
+}
+
+__global__ __launch_bounds__(BS) void k_cand_fill(int32_t n_s, const int32_t* __restrict__ tmp,
+                                                   const int32_t* __restrict__ off, int32_t* __restrict__ cand_s,
+                                                   int32_t* __restrict__ cand_m, const double* __restrict__ sd,
+                                                   const double* __restrict__ md, double eps_a,
+                                                   uint8_t* __restrict__ nv_out,
+                                                   int32_t* __restrict__ scr_cnt, Counters* cnt, int64_t cap) {
+  const int64_t t = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * BS + threadIdx.x;
+  const int s = (int)(t / G), r = (int)(t % G);
+  if (s >= n_s) return;  // whole groups leave together
+  const int base = off[s], c = off[s + 1] - base;
+  if (c <= CTMP)  // (else k_cand_fill_long)
+    fill_short(s, r, n_s, base, c, tmp, cand_s, cand_m, sd, md, eps_a, nv_out, scr_cnt, cnt, cap);
+}
+
+// Both fills and the offsets in one launch, for up to SELF_OFFSETS slave
+// elements: each workgroup finds its own offsets from the counts and leaves
+// them in off; the first lane of a group takes a long list.
+__global__ __launch_bounds__(BS) void k_cand_fill_self(const double* __restrict__ box_s, int32_t n_s,
+                                                        const double* __restrict__ sbox,
+                                                        const uint32_t* __restrict__ mvals,
+                                                        const int32_t* __restrict__ cell_start,
+                                                        const Grid* __restrict__ gp, double delta,
+                                                        const int32_t* __restrict__ count,
+                                                        const int32_t* __restrict__ tmp, int32_t* __restrict__ off,
+                                                        int32_t* __restrict__ cand_s, int32_t* __restrict__ cand_m,
+                                                        const double* __restrict__ sd, const double* __restrict__ md,
+                                                        double eps_a, uint8_t* __restrict__ nv_out,
+                                                        int32_t* __restrict__ scr_cnt, Counters* cnt,
+                                                        ScanStage stage) {
+  __shared__ int32_t lds[CCAP * (BS / G)];
+  const int s0 = xcd_tile(blockIdx.x, gridDim.x) * (BS / G);
+  if (s0 >= n_s) return;  // the whole workgroup
+  const int s = s0 + (int)threadIdx.x / G, r = (int)threadIdx.x % G;
+  const int c = s < n_s ? count[s] : 0;
+  int base = self_offset<BS>(count, s0, r == 0 ? c : 0);
+  if (r > 0) base = (int)((uint32_t)base - (uint32_t)c);
+  if (s >= n_s) return;  // whole groups leave together
+  if (r == 0) {
+    off[s] = base;
+    if (s == n_s - 1) {
+      const int total = (int)((uint32_t)base + (uint32_t)c);
+      off[n_s] = total;
+      stage_total(stage, total, false);
+    }
   }
-  const Grid g = *gp;
-  ScreenOut so{0u, 0u};
-  int nscr = 0;
-  if (c <= CCAP)
-    fill_long(s, n_s, base, c, lds + threadIdx.x, BS, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd,
-              md, eps_a, nv_out, so, nscr);
-  else
-    fill_long(s, n_s, base, c, cand_m + base, 1, box_s, sbox, mvals, cell_start, g, delta, cand_s, cand_m, sd, md,
-              eps_a, nv_out, so, nscr);
-  count_degenerate(so, cnt);
-  scr_cnt[s] = nscr;
+  if (c <= CTMP)
+    fill_short(s, r, n_s, base, c, tmp, cand_s, cand_m, sd, md, eps_a, nv_out, scr_cnt, cnt, stage.cap);
+  else if (r == 0)
+    fill_long_slave<BS / G>(s, n_s, base, c, stage.cap, lds + threadIdx.x / G, box_s, sbox, mvals, cell_start, gp,
+                            delta, cand_s, cand_m, sd, md, eps_a, nv_out, scr_cnt, cnt);
 }
 
 }  // namespace
@@ -796,16 +855,22 @@ hipError_t launch_cand_count(const double* box_s, int32_t n_s, const double* sbo
 }
 
 hipError_t launch_cand_fill(const double* box_s, int32_t n_s, const double* sbox, const uint32_t* mvals,
-                            const int32_t* cell_start, const Grid* g, double delta, const int32_t* tmp, const int32_t* off,
-                            int32_t* cand_s, int32_t* cand_m, const double* sd, const double* md, double eps_a,
-                            uint8_t* nv, int32_t* scr_cnt, Counters* cnt, int64_t cap,
-                            hipStream_t s) {
-  if (n_s == 0) return hipSuccess;
+                            const int32_t* cell_start, const Grid* g, double delta, const int32_t* count,
+                            const int32_t* tmp, int32_t* off, const Buf& scan_tmp, int32_t* cand_s, int32_t* cand_m,
+                            const double* sd, const double* md, double eps_a, uint8_t* nv, int32_t* scr_cnt,
+                            Counters* cnt, const ScanStage& stage, hipStream_t s) {
+  if (n_s > 0 && n_s <= SELF_OFFSETS) {
+    k_cand_fill_self<<<group_blocks(n_s), BS, 0, s>>>(box_s, n_s, sbox, mvals, cell_start, g, delta, count, tmp, off,
+                                                      cand_s, cand_m, sd, md, eps_a, nv, scr_cnt, cnt, stage);
+    return hipGetLastError();
+  }
+  hipError_t e = scan_exclusive(count, off, n_s, scan_tmp, s, 0, stage);
+  if (e != hipSuccess || n_s == 0) return e;
   k_cand_fill<<<group_blocks(n_s), BS, 0, s>>>(n_s, tmp, off, cand_s, cand_m, sd, md, eps_a, nv, scr_cnt, cnt,
-                                               cap);
+                                               stage.cap);
   k_cand_fill_long<<<xcd_grid((unsigned)((n_s + BS - 1) / BS)), BS, 0, s>>>(box_s, n_s, sbox, mvals, cell_start, g, delta,
                                                                             off, cand_s, cand_m, sd, md, eps_a, nv,
-                                                                            scr_cnt, cnt, cap);
+                                                                            scr_cnt, cnt, stage.cap);
   return hipGetLastError();
 }
 

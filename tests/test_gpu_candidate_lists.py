@@ -38,7 +38,7 @@ def strips(counts):
 def test_lists(counts):
     from paper_2202_03933_amd import MortarInterface, default_params
     itf = strips(counts)
-    print(f"[gpu] {itf.name}", flush=True)
+    print(f"[gpu] {itf.name[:80]}", flush=True)
     it = MortarInterface(itf.slave.X, itf.slave.conn, itf.master.X, itf.master.conn,
                          params=default_params(delta=itf.delta), device="cuda:0").setup()
     cs, cm = oracle.search(itf.slave, itf.master, itf.delta)
