@@ -100,12 +100,12 @@ __global__ __launch_bounds__(SCAN_BS) void k_tile_scan(const int32_t* __restrict
     for (int64_t i = threadIdx.x; i < w; i += SCAN_BS) part += offs[i];
     block_exclusive<SCAN_BS>(part, &off);
   } else if (OFF == OFF_SELF) {
+    // (w <= end: the tiles before this one hold live values only)
     int32_t part = 0;
-    for (int64_t t = 0; t < w * per; ++t) {
-      int32_t v[SCAN_IPT];
-      load_slot<VEC>(in, t * SCAN_TILE + (int64_t)threadIdx.x * SCAN_IPT, live, v);
-#pragma unroll
-      for (int i = 0; i < SCAN_IPT; ++i) part += v[i];
+    if (VEC) {
+      part = sum_before<SCAN_BS>(in, (int32_t)(w * SCAN_TILE));
+    } else {
+      for (int64_t i = threadIdx.x; i < w * SCAN_TILE; i += SCAN_BS) part += in[i];
     }
     block_exclusive<SCAN_BS>(part, &off);
   } else if (offs) {

@@ -41,18 +41,35 @@ __device__ __forceinline__ T block_exclusive(T x, T* total) {
   return off + inc - x;
 }
 
+// This thread's share of the sum of cnt[0 .. first) (16-byte aligned, first a
+// multiple of 4) over a workgroup of N threads: 8 loads in flight (one at a
+// time, whole steps of 20K to 66K slave elements took 4 to 12 us longer).
+template <int N>
+__device__ __forceinline__ int32_t sum_before(const int32_t* __restrict__ cnt, int32_t first) {
+  constexpr int U = 8;
+  int32_t part = 0;
+  for (int32_t i = 4 * (int32_t)threadIdx.x; i < first; i += 4 * N * U) {
+    int4 v[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int32_t k = i + 4 * N * q;
+      v[q] = make_int4(0, 0, 0, 0);
+      if (k < first) v[q] = *reinterpret_cast<const int4*>(cnt + k);
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) part += v[q].x + v[q].y + v[q].z + v[q].w;
+  }
+  return part;
+}
+
 // Offset of each thread's value x (of N threads, cnt[0 .. first) before
 // them; cnt 16-byte aligned, first a multiple of 4): the workgroup adds up
 // the counts before its own, so that no launch need scan them first.  The
 // whole workgroup calls it.
 template <int N>
 __device__ __forceinline__ int32_t self_offset(const int32_t* __restrict__ cnt, int32_t first, int32_t x) {
-  int32_t part = 0;
-  for (int32_t i = 4 * (int32_t)threadIdx.x; i < first; i += 4 * N) {
-    const int4 v = *reinterpret_cast<const int4*>(cnt + i);
-    part += v.x + v.y + v.z + v.w;
-  }
   int32_t before, own;
+  const int32_t part = sum_before<N>(cnt, first);
   block_exclusive<N>(part, &before);
   const int32_t off = block_exclusive<N>(x, &own);
   return before + off;
@@ -61,10 +78,10 @@ __device__ __forceinline__ int32_t self_offset(const int32_t* __restrict__ cnt, 
 // Up to this many counts the kernel that uses their offsets finds them itself
 // (self_offset): every workgroup reads the counts before its own from L2,
 // where the scan costs a launch and the gap before it.  Whole step, wavy,
-// without read-back, scan -> own offsets: 4K slave elements 218 -> 186 us,
-// 10K 233 -> 226, 16K 248 -> 247, 20K 250 -> 249, 33K 270 -> 282, 66K
-// 331 -> 382.
-constexpr int64_t SELF_OFFSETS = 20480;
+// without read-back, scan -> own offsets: 4K slave elements 213 -> 192 us,
+// 10K 229 -> 214, 16K 245 -> 230, 33K 264 -> 253, 66K 320 -> 317, 90K
+// 362 -> 369, 161K 515 -> 588.
+constexpr int64_t SELF_OFFSETS = 67584;
 
 // The total of a stage of the build into the device state, clamped to the
 // stage's capacity (the flag records an excess); the nonzeros of the pattern
