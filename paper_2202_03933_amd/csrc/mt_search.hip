@@ -466,9 +466,14 @@ __device__ __forceinline__ bool touch_q(const SlaveBox& s, const QSlave& t, cons
 
 constexpr int CCAP = 48;  // per-thread LDS segment of the long-list fill (masters)
 constexpr int CTMP = 32;  // candidates per slave kept by the count pass
-constexpr int G = 2;      // lanes per slave element in the count and fill passes
-static_assert(64 % G == 0 && BS % G == 0, "groups must not straddle a wave");
-constexpr int OWN = CTMP / G;  // candidates per lane in the grouped fill
+// lanes per slave element (template argument G) in the count and fill passes;
+// groups do not straddle a wavefront
+constexpr int LANES_MANY = 2, LANES_FEW = 8;
+// Up to this many slave elements 8 lanes each: two would leave SIMDs idle, and
+// the passes' time is one lane's serial walk.  Whole step, wavy, without
+// read-back, 2 -> 8 lanes: 16K slave elements 232 -> 224 us, 33K 254 -> 250,
+// 66K 318 -> 331 (4 lanes 225, 250, 318; 16 lanes 227, 262, 364).
+constexpr int32_t FEW_SLAVES = 32768;
 
 // The 27 cells around the slave centre's cell, restricted to those that can
 // hold the centre of a touching master (within g.reach of the box).
@@ -517,6 +522,7 @@ __device__ __forceinline__ int walk_cells(const SlaveBox& b, const double* __res
 // masters lo + r, lo + r + G, ...): the group's hits of one step are ranked
 // by a wave ballot, so v receives the same candidates in the same order as
 // the one-lane walk, and the boxes a group reads in one step are adjacent.
+template <int G>
 __device__ __forceinline__ int walk_cells_group(const SlaveBox& b, const double* __restrict__ sbox,
                                                 const uint64_t* __restrict__ qbox,
                                                 const uint32_t* __restrict__ mvals, const int32_t* __restrict__ cell_start,
@@ -548,6 +554,7 @@ __device__ __forceinline__ int walk_cells_group(const SlaveBox& b, const double*
 
 // Count pass, G lanes per slave: the number of candidates, and the first
 // CTMP of them (walk order) in the lane-interleaved scratch tmp[k * n_s + s].
+template <int G>
 __global__ __launch_bounds__(BS) void k_cand_count(const double* __restrict__ box_s, int32_t n_s,
                                                     const double* __restrict__ sbox,
                                                     const uint64_t* __restrict__ qbox,
@@ -560,7 +567,7 @@ __global__ __launch_bounds__(BS) void k_cand_count(const double* __restrict__ bo
   if (s >= n_s) return;  // whole groups leave together
   const Grid g = *gp;
   const SlaveBox b = load_box(box_s, n_s, s);
-  const int c = walk_cells_group(b, sbox, qbox, mvals, cell_start, g, delta, tmp + s, n_s, CTMP, r,
+  const int c = walk_cells_group<G>(b, sbox, qbox, mvals, cell_start, g, delta, tmp + s, n_s, CTMP, r,
                                  (int)(__lane_id() & ~(G - 1)));
   if (r == 0) count[s] = c;
 }
@@ -639,6 +646,7 @@ __device__ __forceinline__ void count_degenerate(const ScreenOut& so, Counters* 
 // count and keeps no array of its own.  Wavy 1024 x 1024 / 777 x 777: 0.28 ms
 // and 0.040 ms for the list of the screened-in with a 4-byte flag per
 // candidate, 0.25 and 0.018 ms now.
+template <int G>
 __device__ __forceinline__ void fill_short(int s, int r, int32_t n_s, int base, int c,
                                            const int32_t* __restrict__ tmp, int32_t* __restrict__ cand_s,
                                            int32_t* __restrict__ cand_m, const double* __restrict__ sd,
@@ -650,6 +658,7 @@ __device__ __forceinline__ void fill_short(int s, int r, int32_t n_s, int base, 
   }
   int nscr = 0;
   if (r < c) {
+    constexpr int OWN = CTMP / G;  // candidates per lane
     int own[OWN], rank[OWN];
 #pragma unroll
     for (int q = 0; q < OWN; ++q) {
@@ -757,17 +766,19 @@ __global__ __launch_bounds__(BS) void k_cand_fill(int32_t n_s, const int32_t* __
                                                    const double* __restrict__ md, double eps_a,
                                                    uint8_t* __restrict__ nv_out,
                                                    int32_t* __restrict__ scr_cnt, Counters* cnt, int64_t cap) {
+  constexpr int G = LANES_MANY;
   const int64_t t = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * BS + threadIdx.x;
   const int s = (int)(t / G), r = (int)(t % G);
   if (s >= n_s) return;  // whole groups leave together
   const int base = off[s], c = off[s + 1] - base;
   if (c <= CTMP)  // (else k_cand_fill_long)
-    fill_short(s, r, n_s, base, c, tmp, cand_s, cand_m, sd, md, eps_a, nv_out, scr_cnt, cnt, cap);
+    fill_short<G>(s, r, n_s, base, c, tmp, cand_s, cand_m, sd, md, eps_a, nv_out, scr_cnt, cnt, cap);
 }
 
 // Both fills and the offsets in one launch, for up to SELF_OFFSETS slave
 // elements: each workgroup finds its own offsets from the counts and leaves
 // them in off; the first lane of a group takes a long list.
+template <int G>
 __global__ __launch_bounds__(BS) void k_cand_fill_self(const double* __restrict__ box_s, int32_t n_s,
                                                         const double* __restrict__ sbox,
                                                         const uint32_t* __restrict__ mvals,
@@ -797,7 +808,7 @@ __global__ __launch_bounds__(BS) void k_cand_fill_self(const double* __restrict_
     }
   }
   if (c <= CTMP)
-    fill_short(s, r, n_s, base, c, tmp, cand_s, cand_m, sd, md, eps_a, nv_out, scr_cnt, cnt, stage.cap);
+    fill_short<G>(s, r, n_s, base, c, tmp, cand_s, cand_m, sd, md, eps_a, nv_out, scr_cnt, cnt, stage.cap);
   else if (r == 0)
     fill_long_slave<BS / G>(s, n_s, base, c, stage.cap, lds + threadIdx.x / G, box_s, sbox, mvals, cell_start, gp,
                             delta, cand_s, cand_m, sd, md, eps_a, nv_out, scr_cnt, cnt);
@@ -843,14 +854,16 @@ hipError_t launch_cell_place(const uint32_t* cell, const uint32_t* rank, int32_t
 
 // Grids of the candidate passes: XCD-aware (each XCD's L2 serves a
 // contiguous eighth of the slave elements, whose masters are neighbours).
-unsigned group_blocks(int32_t n_s) { return xcd_grid((unsigned)(((int64_t)n_s * G + BS - 1) / BS)); }
+unsigned group_blocks(int32_t n_s, int lanes) { return xcd_grid((unsigned)(((int64_t)n_s * lanes + BS - 1) / BS)); }
 
 hipError_t launch_cand_count(const double* box_s, int32_t n_s, const double* sbox, const uint64_t* qbox,
                              const uint32_t* mvals,
                              const int32_t* cell_start, const Grid* g, double delta, int32_t* count, int32_t* tmp,
                              hipStream_t s) {
   if (n_s == 0) return hipSuccess;
-  k_cand_count<<<group_blocks(n_s), BS, 0, s>>>(box_s, n_s, sbox, qbox, mvals, cell_start, g, delta, count, tmp);
+  const bool few = n_s <= FEW_SLAVES;
+  (few ? k_cand_count<LANES_FEW> : k_cand_count<LANES_MANY>)<<<group_blocks(n_s, few ? LANES_FEW : LANES_MANY), BS, 0, s>>>(
+      box_s, n_s, sbox, qbox, mvals, cell_start, g, delta, count, tmp);
   return hipGetLastError();
 }
 
@@ -860,13 +873,16 @@ hipError_t launch_cand_fill(const double* box_s, int32_t n_s, const double* sbox
                             const double* sd, const double* md, double eps_a, uint8_t* nv, int32_t* scr_cnt,
                             Counters* cnt, const ScanStage& stage, hipStream_t s) {
   if (n_s > 0 && n_s <= SELF_OFFSETS) {
-    k_cand_fill_self<<<group_blocks(n_s), BS, 0, s>>>(box_s, n_s, sbox, mvals, cell_start, g, delta, count, tmp, off,
-                                                      cand_s, cand_m, sd, md, eps_a, nv, scr_cnt, cnt, stage);
+    const bool few = n_s <= FEW_SLAVES;
+    auto* k = few ? k_cand_fill_self<LANES_FEW> : k_cand_fill_self<LANES_MANY>;
+    k<<<group_blocks(n_s, few ? LANES_FEW : LANES_MANY), BS, 0, s>>>(box_s, n_s, sbox, mvals, cell_start, g, delta,
+                                                                     count, tmp, off, cand_s, cand_m, sd, md, eps_a,
+                                                                     nv, scr_cnt, cnt, stage);
     return hipGetLastError();
   }
   hipError_t e = scan_exclusive(count, off, n_s, scan_tmp, s, 0, stage);
   if (e != hipSuccess || n_s == 0) return e;
-  k_cand_fill<<<group_blocks(n_s), BS, 0, s>>>(n_s, tmp, off, cand_s, cand_m, sd, md, eps_a, nv, scr_cnt, cnt,
+  k_cand_fill<<<group_blocks(n_s, LANES_MANY), BS, 0, s>>>(n_s, tmp, off, cand_s, cand_m, sd, md, eps_a, nv, scr_cnt, cnt,
                                                stage.cap);
   k_cand_fill_long<<<xcd_grid((unsigned)((n_s + BS - 1) / BS)), BS, 0, s>>>(box_s, n_s, sbox, mvals, cell_start, g, delta,
                                                                             off, cand_s, cand_m, sd, md, eps_a, nv,

@@ -1,5 +1,6 @@
 """Search and row pattern on both sides of the size up to which the kernels
-find their own offsets (67,584 slave elements or nodes) and at a third of it, with lists longer
+find their own offsets (67,584 slave elements or nodes) at a third of it, and at
+the size up to which a slave element has eight lanes (32,768), with lists longer
 than the short fill holds on either side, against the oracle bit for bit."""
 
 import numpy as np
@@ -16,12 +17,12 @@ LONG = (33, 2, 49, 48, 32, 1, 40)
 # elements / nodes: 20,480 / 20,769; 20,193 / 20,480; 20,481 / 27,312; 13,652 / 20,481;
 # 67,584 / 68,105; 67,065 / 67,584; 67,585 / 69,552; 65,620 / 67,585
 @pytest.mark.parametrize("nx,ny", [(160, 128), (159, 127), (6827, 3), (6826, 2), (264, 256), (263, 255), (1931, 35),
-                                   (1930, 34)])
+                                   (1930, 34), (256, 128), (10923, 3)])
 def test_sizes(nx, ny):
     check_search(nx, ny, 0.0)
 
 
-@pytest.mark.parametrize("n", [20480, 20481, 67584, 67585])
+@pytest.mark.parametrize("n", [20480, 20481, 32768, 32769, 67584, 67585])
 def test_long_lists(n):
     rng = np.random.default_rng(n)
     counts = np.ones(n, dtype=int)
