@@ -233,7 +233,10 @@ __device__ __forceinline__ void kept_row(int a, int32_t n, int u, const int32_t*
   for (int i = 0; i < u; ++i) col[i] = keep[(int64_t)i * n + a];
 }
 
-// Count pass.
+// Count pass: D rows by the workgroups with blockIdx.y = 0, M rows by the
+// others, as in the fill pass: one thread for both rows ran their chains of
+// dependent loads in turn (64 x 64 / 49 x 49: 16 -> 10 us and 11 -> 8 us; no
+// slower at 1024 x 1024 / 777 x 777, 83 and 81 us).
 __global__ __launch_bounds__(PB) void k_pattern_count(const int32_t* __restrict__ inc_off,
                                                        const int32_t* __restrict__ inc_list, int32_t n,
                                                        const int32_t* __restrict__ pair_off,
@@ -247,8 +250,11 @@ __global__ __launch_bounds__(PB) void k_pattern_count(const int32_t* __restrict_
   const int a = xcd_tile(blockIdx.x, gridDim.x) * PB + threadIdx.x;
   if (a >= n) return;
   int32_t* seg = lds + threadIdx.x;
-  pattern_row<false, false>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, D_cnt, nullptr, keepD + a,
-                            KD);
+  if (blockIdx.y == 0) {
+    pattern_row<false, false>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, D_cnt, nullptr,
+                              keepD + a, KD);
+    return;
+  }
   // M row: merge of the element lists where they exist
   const int u = merge_mrow(a, n, inc_off, inc_list, n_el, ecnt, elist, keepM + a, KM);
   if (u >= 0)
@@ -275,37 +281,30 @@ __global__ __launch_bounds__(PB) void k_pattern_fill(const int32_t* __restrict__
   __shared__ int32_t lds[PCAP * PB];
   const int a0 = xcd_tile(blockIdx.x, gridDim.x) * PB, a = a0 + threadIdx.x;
   if (a0 >= n) return;  // the whole workgroup
-  int d0 = 0, m0 = 0, nd = 0, nm = 0;
-  if (a < n) {
-    nd = SELF ? D_cnt[a] : D_rowptr[a + 1] - (d0 = D_rowptr[a]);
-    nm = SELF ? M_cnt[a] : M_rowptr[a + 1] - (m0 = M_rowptr[a]);
-  }
-  if (SELF) {
-    d0 = self_offset<PB>(D_cnt, a0, nd);
-    m0 = self_offset<PB>(M_cnt, a0, nm);
-  }
+  // this workgroup's side
+  const bool mside = blockIdx.y != 0;
+  const int32_t* cnt = mside ? M_cnt : D_cnt;
+  int32_t* rowptr = mside ? M_rowptr : D_rowptr;
+  int r0 = 0, u = 0;
+  if (a < n) u = SELF ? cnt[a] : rowptr[a + 1] - (r0 = rowptr[a]);
+  if (SELF) r0 = self_offset<PB>(cnt, a0, u);
   if (a >= n) return;
   if (SELF) {
-    D_rowptr[a] = d0;
-    M_rowptr[a] = m0;
+    rowptr[a] = r0;
     if (a == n - 1) {
-      D_rowptr[n] = d0 + nd;
-      M_rowptr[n] = m0 + nm;
-      stage_total(stage, d0 + nd, false);
-      stage_total(stage, m0 + nm, true);
+      rowptr[n] = r0 + u;
+      stage_total(stage, r0 + u, mside);
     }
   }
   int32_t* seg = lds + threadIdx.x;
-  if (nd <= KD)
-    kept_row(a, n, nd, keepD, D_col + d0);
+  int32_t* col = (mside ? M_col : D_col) + r0;
+  if (u <= (mside ? KM : KD))
+    kept_row(a, n, u, mside ? keepM : keepD, col);
+  else if (mside)
+    pattern_row<true, true>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, nullptr, col, nullptr, KM);
   else
-    pattern_row<true, false>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, nullptr, D_col + d0,
-                             nullptr, KD);
-  if (nm <= KM)
-    kept_row(a, n, nm, keepM, M_col + m0);
-  else
-    pattern_row<true, true>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, nullptr, M_col + m0,
-                            nullptr, KM);
+    pattern_row<true, false>(a, n, seg, inc_off, inc_list, pair_off, pair_m, conn_s, conn_m, nullptr, col, nullptr,
+                             KD);
 }
 
 // Positions of four keys that all occur in the sorted row v[0..u): a
@@ -336,8 +335,14 @@ __device__ __forceinline__ void lower_bound4(P v, int u, const int key[4], int p
 // there; a span longer than POS_SPAN is searched in global memory.  Lanes
 // write consecutive entries.
 constexpr int POS_SPAN = 4096;
+// Up to this many slave elements the four block rows go to four workgroups
+// (EACH), which read the connectivity again but do not search one after the
+// other.  Whole step, wavy, without read-back, one workgroup -> four: 16K
+// slave elements 203 -> 191 us, 33K 239 -> 234, 66K 307 -> 304, 90K and 161K
+// 0.5 % less, 262K 740 -> 749.
+constexpr int32_t POS_EACH = 163840;
 
-template <bool MCOLS>
+template <bool MCOLS, bool EACH>
 __device__ __forceinline__ void block_positions(unsigned block, int64_t n, int32_t* span, int32_t (*red)[BS / 64],
                                                 const int32_t* __restrict__ pair_s,
                                                 const int32_t* __restrict__ pair_m,
@@ -362,7 +367,7 @@ __device__ __forceinline__ void block_positions(unsigned block, int64_t n, int32
   const int key[4] = {key4.x, key4.y, key4.z, key4.w};
   const int w = threadIdx.x >> 6;
 #pragma unroll 1
-  for (int j = 0; j < 4; ++j) {
+  for (int j = EACH ? (int)blockIdx.y : 0; j < (EACH ? (int)blockIdx.y + 1 : 4); ++j) {
     const int a = j == 0 ? cs.x : j == 1 ? cs.y : j == 2 ? cs.z : cs.w;
     int lo = act ? a : 0x7fffffff, hi = act ? a : -1;
 #pragma unroll
@@ -397,7 +402,7 @@ __device__ __forceinline__ void block_positions(unsigned block, int64_t n, int32
       store_pos4(pos, pstride, i, j, u, ix);
     }
   }
-  if (!MCOLS && act) {
+  if (!MCOLS && act && (!EACH || blockIdx.y == 0)) {
     int r[8];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -413,6 +418,7 @@ __device__ __forceinline__ void block_positions(unsigned block, int64_t n, int32
 
 // Both in one launch: the first d_blocks workgroups (a multiple of 8) take
 // D, the others M.
+template <bool EACH>
 __global__ __launch_bounds__(BS) void k_positions(unsigned d_blocks, int32_t n_s_el, const int32_t* __restrict__ n_pairs,
                                                    const int32_t* __restrict__ pair_s,
                                                    const int32_t* __restrict__ pair_m,
@@ -428,10 +434,10 @@ __global__ __launch_bounds__(BS) void k_positions(unsigned d_blocks, int32_t n_s
   __shared__ int32_t span[POS_SPAN];
   __shared__ int32_t red[2][BS / 64];
   if (blockIdx.x < d_blocks)
-    block_positions<false>(blockIdx.x, n_s_el, span, red, nullptr, nullptr, pair_off, conn_s, nullptr, D_rowptr,
+    block_positions<false, EACH>(blockIdx.x, n_s_el, span, red, nullptr, nullptr, pair_off, conn_s, nullptr, D_rowptr,
                            D_col, posD, n_s_el, M_rowptr, erow);
   else
-    block_positions<true>(blockIdx.x - d_blocks, *n_pairs, span, red, pair_s, pair_m, nullptr, conn_s, conn_m,
+    block_positions<true, EACH>(blockIdx.x - d_blocks, *n_pairs, span, red, pair_s, pair_m, nullptr, conn_s, conn_m,
                           M_rowptr, M_col, posM, pstride, nullptr, nullptr);
 }
 
@@ -663,14 +669,14 @@ hipError_t launch_pattern_rows(const int32_t* inc_off, const int32_t* inc_list, 
   int32_t* keepM = keep + (int64_t)KD * n_nodes;
   const bool self = n_nodes > 0 && n_nodes <= SELF_OFFSETS;
   if (n_nodes > 0)
-    k_pattern_count<<<g, PB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, pair_m, conn_s, conn_m, D_cnt, M_cnt,
+    k_pattern_count<<<dim3(g, 2), PB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, pair_m, conn_s, conn_m, D_cnt, M_cnt,
                                      keepD, keepM, n_s_el, ecnt, elist);
   if (!self) {
     const hipError_t e = scan_exclusive2(D_cnt, D_rowptr, M_cnt, M_rowptr, n_nodes, scan_tmp, s, scan_blocks, stage);
     if (e != hipSuccess || n_nodes == 0) return e;
   }
   auto* k = self ? k_pattern_fill<true> : k_pattern_fill<false>;
-  k<<<g, PB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, pair_m, conn_s, conn_m, D_cnt, M_cnt, D_rowptr, M_rowptr,
+  k<<<dim3(g, 2), PB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off, pair_m, conn_s, conn_m, D_cnt, M_cnt, D_rowptr, M_rowptr,
                      D_col, M_col, keepD, keepM, stage);
   return hipGetLastError();
 }
@@ -682,7 +688,8 @@ hipError_t launch_pattern_positions(const int32_t* pair_s, const int32_t* pair_m
                                     int32_t* erow, hipStream_t s) {
   const unsigned nd = xcd_grid(grid_of(n_s_el)), nm = xcd_grid(grid_of(cap));
   if (nd + nm == 0) return hipSuccess;
-  k_positions<<<nd + nm, BS, 0, s>>>(nd, n_s_el, n_pairs, pair_s, pair_m, pair_off, conn_s, conn_m, D_rowptr, D_col,
+  const bool each = n_s_el <= POS_EACH;
+  (each ? k_positions<true> : k_positions<false>)<<<dim3(nd + nm, each ? 4 : 1), BS, 0, s>>>(nd, n_s_el, n_pairs, pair_s, pair_m, pair_off, conn_s, conn_m, D_rowptr, D_col,
                                      M_rowptr, M_col, posD, posM, cap, erow);
   return hipGetLastError();
 }

@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
 LONG = (33, 2, 49, 48, 32, 1, 40)
 
 
-# elements / nodes: 20,480 / 20,769; 20,193 / 20,480; 20,481 / 27,312; 13,652 / 20,481;
-# 67,584 / 68,105; 67,065 / 67,584; 67,585 / 69,552; 65,620 / 67,585
-@pytest.mark.parametrize("nx,ny", [(160, 128), (159, 127), (6827, 3), (6826, 2), (264, 256), (263, 255), (1931, 35),
-                                   (1930, 34), (256, 128), (10923, 3)])
+# elements / nodes: 20,480 / 20,769; 20,193 / 20,480; 20,608; 32,768; 32,896;
+# 67,584 / 68,105; 67,065 / 67,584; 67,840
+@pytest.mark.parametrize("nx,ny", [(160, 128), (159, 127), (161, 128), (256, 128), (257, 128), (264, 256), (263, 255),
+                                   (265, 256)])
 def test_sizes(nx, ny):
     check_search(nx, ny, 0.0)
 
