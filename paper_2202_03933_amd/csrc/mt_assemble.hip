@@ -441,10 +441,16 @@ __global__ __launch_bounds__(BS) void k_positions(unsigned d_blocks, int32_t n_s
                           M_rowptr, M_col, posM, pstride, nullptr, nullptr);
 }
 
-// One thread per slave node (row): the row is accumulated in a per-thread
-// LDS segment (lane-interleaved) in a fixed order and written once.
-constexpr int AB = 128;   // block of the assembly kernel
-constexpr int ACAP = 32;  // per-thread accumulator entries (D + M of one row)
+// One thread per row of D (blockIdx.y = 0, with the gap) or M, accumulated in
+// a per-thread LDS segment (lane-interleaved) in a fixed order and written
+// once.  The bytes (blocks, places, values: 1.1 GB at 1024 x 1024 /
+// 777 x 777, 0.23 ms at the rate of a copy) bound large steps, the chain of
+// dependent loads small ones.  One thread for both rows, 32 entries each:
+// 0.310 ms there; D and M apart, ROW_ACC entries each: 0.269 ms, and the whole
+// step of 181 x 181 / 141 x 141 236 -> 228 us.  (Where the masters are 1.6
+// times finer and rows of 27 to 32 columns take two sweeps, 512 x 512 /
+// 821 x 821, the whole step is 2.26 ms instead of 2.23.)
+constexpr int AB = 128;  // block of the assembly kernel
 
 __global__ __launch_bounds__(AB) void k_assemble(const int32_t* __restrict__ inc_off,
                                                   const int32_t* __restrict__ inc_list, int32_t n,
@@ -455,11 +461,15 @@ __global__ __launch_bounds__(AB) void k_assemble(const int32_t* __restrict__ inc
                                                   const int32_t* __restrict__ posM, const double* __restrict__ blk,
                                                   int64_t stride, ElemSums eblk, double* __restrict__ D_val,
                                                   double* __restrict__ M_val, double* __restrict__ gap) {
-  __shared__ double acc[ACAP * AB];
+  __shared__ double acc[ROW_ACC * AB];
   const int a = xcd_tile(blockIdx.x, gridDim.x) * AB + threadIdx.x;
   if (a >= n) return;
-  assemble_row_acc(a, inc_off, inc_list, pair_off, D_rowptr, M_rowptr, posD, posM, blk, stride, eblk, D_val, M_val,
-                   gap, acc + threadIdx.x, AB, ACAP);
+  if (blockIdx.y == 0)
+    assemble_row<false>(a, inc_off, inc_list, pair_off, D_rowptr, posD, blk, stride, eblk, D_val, gap,
+                        acc + threadIdx.x, AB, ROW_ACC);
+  else
+    assemble_row<true>(a, inc_off, inc_list, pair_off, M_rowptr, posM, blk, stride, eblk, M_val, gap,
+                       acc + threadIdx.x, AB, ROW_ACC);
 }
 
 // Nodal gradients of both sides in one launch: the first s_blocks workgroups
@@ -709,9 +719,8 @@ hipError_t launch_assemble(const int32_t* inc_off, const int32_t* inc_list, int3
                            const int32_t* posM, const double* blk, int64_t stride, const ElemSums& eblk,
                            double* D_val, double* M_val, double* gap, hipStream_t s) {
   if (n_nodes == 0) return hipSuccess;
-  k_assemble<<<xcd_grid((unsigned)((n_nodes + AB - 1) / AB)), AB, 0, s>>>(inc_off, inc_list, n_nodes, pair_off,
-                                                                          D_rowptr, M_rowptr, posD, posM, blk, stride,
-                                                                          eblk, D_val, M_val, gap);
+  k_assemble<<<dim3(xcd_grid((unsigned)((n_nodes + AB - 1) / AB)), 2), AB, 0, s>>>(
+      inc_off, inc_list, n_nodes, pair_off, D_rowptr, M_rowptr, posD, posM, blk, stride, eblk, D_val, M_val, gap);
   return hipGetLastError();
 }
 

@@ -206,17 +206,20 @@ __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(2))) void k
 }
 
 // Row phases: one block per item of ROWS_PER_ITEM rows of one instance.
-constexpr int BATCH_ACAP = 32;  // per-thread row accumulator of the batched assembly
-
+// (D rows and gaps by the workgroups with blockIdx.y = 0, M rows by the others.)
 __global__ __launch_bounds__(ROWS_PER_ITEM) void k_batch_assemble(const BatchInst* __restrict__ inst,
                                                                    const WorkItem* __restrict__ items) {
-  __shared__ double acc[BATCH_ACAP * ROWS_PER_ITEM];
+  __shared__ double acc[ROW_ACC * ROWS_PER_ITEM];
   const WorkItem w = items[blockIdx.x];
   const int a = w.begin + threadIdx.x;
   if (a >= w.end) return;
   const BatchInst& I = inst[w.inst];
-  assemble_row_acc(a, I.inc_off, I.inc_list, I.pair_off, I.D_rowptr, I.M_rowptr, I.posD, I.posM, I.blk, I.stride,
-                   I.eblk, I.D_val, I.M_val, I.gap, acc + threadIdx.x, ROWS_PER_ITEM, BATCH_ACAP);
+  if (blockIdx.y == 0)
+    assemble_row<false>(a, I.inc_off, I.inc_list, I.pair_off, I.D_rowptr, I.posD, I.blk, I.stride, I.eblk, I.D_val,
+                        I.gap, acc + threadIdx.x, ROWS_PER_ITEM, ROW_ACC);
+  else
+    assemble_row<true>(a, I.inc_off, I.inc_list, I.pair_off, I.M_rowptr, I.posM, I.blk, I.stride, I.eblk, I.M_val,
+                       I.gap, acc + threadIdx.x, ROWS_PER_ITEM, ROW_ACC);
 }
 
 __global__ __launch_bounds__(ROWS_PER_ITEM) void k_batch_grad_rows(const BatchInst* __restrict__ inst,
@@ -436,7 +439,7 @@ int launch_fwd_all(mt_batch* b, hipStream_t st) {
   int rc = launch_fwd(b, st);
   if (rc) return rc;
   if (b->n_ritems_s) {
-    k_batch_assemble<<<b->n_ritems_s, ROWS_PER_ITEM, 0, st>>>(b->d_inst.as<BatchInst>(), b->d_ritems_s.as<WorkItem>());
+    k_batch_assemble<<<dim3((unsigned)b->n_ritems_s, 2), ROWS_PER_ITEM, 0, st>>>(b->d_inst.as<BatchInst>(), b->d_ritems_s.as<WorkItem>());
     B_HIP(hipGetLastError());
   }
   return MT_OK;

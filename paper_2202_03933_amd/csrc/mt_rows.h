@@ -146,123 +146,90 @@ __device__ __forceinline__ int run_at(const RowRuns& R, int k, int& j) {
 // pairs whose loads the gradient gathers issue together
 constexpr int ROW_BATCH = 8;
 
-// Row a of D, M and the gap from the slave elements' D blocks and gaps and
-// the pairs' M blocks blk[c * stride + p].
-__device__ __forceinline__ void assemble_row(int a, const int32_t* __restrict__ inc_off,
-                                             const int32_t* __restrict__ inc_list,
-                                             const int32_t* __restrict__ pair_off,
-                                             const int32_t* __restrict__ D_rowptr,
-                                             const int32_t* __restrict__ M_rowptr,
-                                             const int32_t* __restrict__ posD, const int32_t* __restrict__ posM,
-                                             const double* __restrict__ blk, int64_t stride, const ElemSums& E,
-                                             double* __restrict__ D_val, double* __restrict__ M_val,
-                                             double* __restrict__ gap) {
-  const int d0 = D_rowptr[a], nd = D_rowptr[a + 1] - d0;
-  const int m0 = M_rowptr[a], nm = M_rowptr[a + 1] - m0;
-  for (int i = 0; i < nd; ++i) D_val[d0 + i] = 0.0;
-  for (int i = 0; i < nm; ++i) M_val[m0 + i] = 0.0;
-  double g = 0.0;
-  for (int i = inc_off[a]; i < inc_off[a + 1]; ++i) {
-    const int e = inc_list[i] >> 2, j = inc_list[i] & 3;
-    const int p0 = pair_off[e], p1 = pair_off[e + 1];
-    if (p0 == p1) continue;
-    double vd[4], vg[1];
-    elem_sums<4>(E, 4 * j, e, p0, p1, vd);
-    elem_sums<1>(E, 16 + j, e, p0, p1, vg);
-    int ix[4];
-    load_pos4(posD, E.n_el, e, j, nd, ix);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) D_val[d0 + ix[k]] += vd[k];
-    g += vg[0];
-    for (int p = p0; p < p1; ++p) {
-      load_pos4(posM, stride, p, j, nm, ix);
-#pragma unroll
-      for (int l = 0; l < 4; ++l) M_val[m0 + ix[l]] += blk[(int64_t)(j * 4 + l) * stride + p];
-    }
-  }
-  gap[a] = g;
-}
-
 // One sweep over the incident elements of row a (ascending, then their
-// pairs), adding the D part (DP: column i of nd at acc[i * astride], and the
-// gap, returned) and/or the M part (MP: column i of nm at
-// acc[(i + moff) * astride]).
-template <bool DP, bool MP>
+// pairs), len columns long, for its D part (MP false; the gap is returned) or
+// its M part (from the pairs' blocks blk[c * stride + p]): add(column, value)
+// for every contribution, in order.
+template <bool MP, class F>
 __device__ __forceinline__ double row_sweep(int a, const int32_t* __restrict__ inc_off,
                                             const int32_t* __restrict__ inc_list,
-                                            const int32_t* __restrict__ pair_off, int nd, int nm, int moff,
-                                            const int32_t* __restrict__ posD, const int32_t* __restrict__ posM,
-                                            const double* __restrict__ blk, int64_t stride, const ElemSums& E,
-                                            double* acc, int astride) {
+                                            const int32_t* __restrict__ pair_off, int len,
+                                            const int32_t* __restrict__ pos, const double* __restrict__ blk,
+                                            int64_t stride, const ElemSums& E, F add) {
   double g = 0.0;
   for (int i = inc_off[a]; i < inc_off[a + 1]; ++i) {
     const int e = inc_list[i] >> 2, j = inc_list[i] & 3;
     const int p0 = pair_off[e], p1 = pair_off[e + 1];
     if (p0 == p1) continue;
-    if (DP) {
-      int pd[4];
-      load_pos4(posD, E.n_el, e, j, nd, pd);
-      double vd[4], vg[1];
-      elem_sums<4>(E, 4 * j, e, p0, p1, vd);
+    int ix[4];
+    double v[4];
+    if (!MP) {
+      double vg[1];
+      load_pos4(pos, E.n_el, e, j, len, ix);
+      elem_sums<4>(E, 4 * j, e, p0, p1, v);
       elem_sums<1>(E, 16 + j, e, p0, p1, vg);
       g += vg[0];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) acc[pd[k] * astride] += vd[k];
-    }
-    if (MP) {
+      for (int k = 0; k < 4; ++k) add(ix[k], v[k]);
+    } else {
       for (int p = p0; p < p1; ++p) {
-        double vm[4];
-        int pm[4];
-        load_pos4(posM, stride, p, j, nm, pm);
+        load_pos4(pos, stride, p, j, len, ix);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) vm[k] = blk[(int64_t)(j * 4 + k) * stride + p];
+        for (int k = 0; k < 4; ++k) v[k] = blk[(int64_t)(j * 4 + k) * stride + p];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc[(pm[k] + moff) * astride] += vm[k];
+        for (int k = 0; k < 4; ++k) add(ix[k], v[k]);
       }
     }
   }
   return g;
 }
 
-// Same as assemble_row, accumulating the row in a per-thread scratch segment
-// of cap entries, acc[i * astride], and writing it once: D and M entries
-// together in one sweep when they fit, else in two sweeps (D with the gap,
-// then M) when each part fits; longer rows fall back to assemble_row.  Every
-// entry receives its contributions in the same order in all three forms.
+// Row a of D with the gap (MP false) or of M, accumulated in a per-thread
+// segment of cap entries, acc[i * astride], and written once; a row of up to
+// ROW_WINDOWS segments in as many sweeps, a longer one in global memory.
+// Every entry receives its contributions in the same order in all forms.
 // (Issuing the loads of several pairs together, as the gradient gathers
 // below do, measured slower here: the row's LDS updates, not its loads, set
 // the pace.)
-__device__ __forceinline__ void assemble_row_acc(int a, const int32_t* __restrict__ inc_off,
-                                                 const int32_t* __restrict__ inc_list,
-                                                 const int32_t* __restrict__ pair_off,
-                                                 const int32_t* __restrict__ D_rowptr,
-                                                 const int32_t* __restrict__ M_rowptr,
-                                                 const int32_t* __restrict__ posD, const int32_t* __restrict__ posM,
-                                                 const double* __restrict__ blk, int64_t stride, const ElemSums& E,
-                                                 double* __restrict__ D_val, double* __restrict__ M_val,
-                                                 double* __restrict__ gap, double* acc, int astride, int cap) {
-  const int d0 = D_rowptr[a], d1 = D_rowptr[a + 1];
-  const int m0 = M_rowptr[a], m1 = M_rowptr[a + 1];
-  const int nd = d1 - d0, nm = m1 - m0;
-  double g;
-  if (nd + nm <= cap) {
-    for (int i = 0; i < nd + nm; ++i) acc[i * astride] = 0.0;
-    g = row_sweep<true, true>(a, inc_off, inc_list, pair_off, nd, nm, nd, posD, posM, blk, stride, E, acc, astride);
-    for (int i = 0; i < nd; ++i) D_val[d0 + i] = acc[i * astride];
-    for (int i = 0; i < nm; ++i) M_val[m0 + i] = acc[(nd + i) * astride];
-  } else if (nd <= cap && nm <= cap) {
-    for (int i = 0; i < nd; ++i) acc[i * astride] = 0.0;
-    g = row_sweep<true, false>(a, inc_off, inc_list, pair_off, nd, nm, 0, posD, posM, blk, stride, E, acc, astride);
-    for (int i = 0; i < nd; ++i) D_val[d0 + i] = acc[i * astride];
-    for (int i = 0; i < nm; ++i) acc[i * astride] = 0.0;
-    row_sweep<false, true>(a, inc_off, inc_list, pair_off, nd, nm, 0, posD, posM, blk, stride, E, acc, astride);
-    for (int i = 0; i < nm; ++i) M_val[m0 + i] = acc[i * astride];
+constexpr int ROW_WINDOWS = 4;
+
+template <bool MP>
+__device__ __forceinline__ void assemble_row(int a, const int32_t* __restrict__ inc_off,
+                                             const int32_t* __restrict__ inc_list,
+                                             const int32_t* __restrict__ pair_off,
+                                             const int32_t* __restrict__ rowptr, const int32_t* __restrict__ pos,
+                                             const double* __restrict__ blk, int64_t stride, const ElemSums& E,
+                                             double* __restrict__ val, double* __restrict__ gap, double* acc,
+                                             int astride, int cap) {
+  const int r0 = rowptr[a], u = rowptr[a + 1] - r0;
+  val += r0;
+  double g = 0.0;
+  if (u <= cap) {
+    for (int i = 0; i < u; ++i) acc[i * astride] = 0.0;
+    g = row_sweep<MP>(a, inc_off, inc_list, pair_off, u, pos, blk, stride, E,
+                      [&](int i, double v) { acc[i * astride] += v; });
+    for (int i = 0; i < u; ++i) val[i] = acc[i * astride];
+  } else if (u <= ROW_WINDOWS * cap) {
+    for (int w = 0; w < u; w += cap) {
+      const int n = min(cap, u - w);
+      for (int i = 0; i < n; ++i) acc[i * astride] = 0.0;
+      g = row_sweep<MP>(a, inc_off, inc_list, pair_off, u, pos, blk, stride, E, [&](int i, double v) {
+        if (i >= w && i < w + n) acc[(i - w) * astride] += v;
+      });
+      for (int i = 0; i < n; ++i) val[w + i] = acc[i * astride];
+    }
   } else {
-    assemble_row(a, inc_off, inc_list, pair_off, D_rowptr, M_rowptr, posD, posM, blk, stride, E, D_val, M_val, gap);
-    return;
+    for (int i = 0; i < u; ++i) val[i] = 0.0;
+    g = row_sweep<MP>(a, inc_off, inc_list, pair_off, u, pos, blk, stride, E,
+                      [&](int i, double v) { val[i] += v; });
   }
-  gap[a] = g;
+  if (!MP) gap[a] = g;
 }
+
+// Accumulator entries per thread of the assembly kernels: M rows of 5 x 5
+// master nodes fit, and LDS leaves room for 12 wavefronts on a CU (32 entries:
+// 10).
+constexpr int ROW_ACC = 26;
 
 // Sum over the flat pair sequence of R of the three components
 // gpair[(3 j + d) * stride + p], d = 0, 1, 2, in sequence order.
