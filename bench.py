@@ -421,7 +421,7 @@ def recorded_counters(name):
 
 ALL_SOURCES = ["mt_prims.hip", "mt_search.hip", "mt_pairs.hip", "mt_assemble.hip", "mt_backward.hip",
                "mt_elements.hip", "mt_normals.hip", "mt_batch.hip", "mt_api.hip", "mt_geometry.h",
-               "mt_pair_eval.h", "mt_dual.h", "mt_rows.h", "mt_internal.h"]
+               "mt_pair_eval.h", "mt_dual.h", "mt_rows.h", "mt_scan.h", "mt_internal.h"]
 FP64_SUMMARY = "wavy1024_fp64_counters.md"  # executed FP64 VALU instructions of every kernel of the step
 # mt_batch.hip holds its kernels first and the host code that drives them after
 # this line; the batched kernels are identified by the part before it
@@ -440,8 +440,8 @@ def algorithmic_bytes(n_sn, n_mn, n_se, n_me, n_cand, n_pairs, nnz_D, nnz_M):
     """Algorithmic HBM bytes of each phase: what the method must move, not
     what the kernels' staging adds.
       search:   nodes once (24 B/node), connectivity once (16 B/element), the
-                master bin sort (4 passes, key+value read and written, 16 B
-                per master per pass), candidate list written and read
+                masters' cells and places in them (8 B per master written and
+                read), candidate list written and read
                 (2 x 8 B per candidate), pair list written (8 B per pair);
       pattern:  pair list (8 B) and each pair's master connectivity (16 B)
                 read, slave connectivity (16 B/element) read, CSR column
@@ -455,7 +455,7 @@ def algorithmic_bytes(n_sn, n_mn, n_se, n_me, n_cand, n_pairs, nnz_D, nnz_M):
     conn = 16 * (n_se + n_me)
     csr_idx = 4 * (nnz_D + nnz_M) + 8 * (n_sn + 1)
     vals = 8 * (nnz_D + nnz_M + n_sn)
-    search = nodes + conn + 4 * 16 * n_me + 16 * n_cand + 8 * n_pairs
+    search = nodes + conn + 16 * n_me + 16 * n_cand + 8 * n_pairs
     pattern = 8 * n_pairs + 16 * n_pairs + 16 * n_se + csr_idx
     fwd = nodes + conn + 8 * n_pairs + csr_idx + vals
     bwd = nodes + conn + 8 * n_pairs + csr_idx + vals + 24 * (n_sn + n_mn)
@@ -729,9 +729,10 @@ def main():
                                  "frac": ach / FP64_VECTOR_PEAK_TFLOPS, "flops_per_unit": fl,
                                  "unit_kind": "slave element", "units_per_launch": e["slave_elements"]}
             # per slave element its connectivity, nodes and pair range
-            # (16 + 96 + 8 B), per pair its master index, connectivity and
-            # nodes (4 + 16 + 96 B) read and its 36 block values (288 B) written
-            by = e["slave_elements"] * 120 + e["n_pairs"] * 404
+            # (16 + 96 + 8 B) read and its 20 summed values (160 B) written,
+            # per pair its master index, connectivity and nodes
+            # (4 + 16 + 96 B) read and its 16 block values (128 B) written
+            by = e["slave_elements"] * 280 + e["n_pairs"] * 244
             e["roofline_hbm"] = dict(hbm_entry(by, e["k_elem_fwd_ms"]), kernel="k_elem_fwd")
     if cpu:
         one, alln = cpu["one_core"], cpu["all_cores"]

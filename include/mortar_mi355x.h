@@ -198,8 +198,8 @@ int mt_workspace_size(mt_ctx* ctx, const mt_capacity* cap, size_t* bytes);
  *  2. Cartesian bins over the nodes' bounding box expanded by the minimal
  *     bin size beta_min = max(longest slave edge, largest element box extent
  *     + delta, params.bin_size) (the paper's rule without a motion term,
- *     raised so that 27 bins are complete); master elements sorted by bin
- *     with a radix sort, bin ranges by segmented scan;
+ *     raised so that 27 bins are complete); master elements ordered by
+ *     bin (counts, scan, placement);
  *  3. candidates: (s, m) whose boxes overlap after enlarging the slave box by
  *     delta, found in the 27 bins around s, sorted by (s, m);
  *  4. each candidate is projected onto the slave auxiliary plane and
@@ -360,7 +360,7 @@ int mt_get_stats(mt_ctx* ctx, mt_stats* st);
  * Sec. "Numerical experiments") as per-launch HIP events: when enabled, every
  * phase below is bracketed by two events recorded on the call's stream. */
 #define MT_T_PREP 0        /* element bounding boxes, grid reductions, per-element data */
-#define MT_T_BIN_SORT 1    /* master bin keys, radix sort, bin ranges */
+#define MT_T_BIN_SORT 1    /* masters per bin, their scan, placement */
 #define MT_T_CAND 2        /* candidate count, scan, fill with screening (projection, separating line) */
 #define MT_T_CLIP 3        /* clip and cleanup of the screened candidates (one kernel) */
 #define MT_T_COMPACT 4     /* scans, screened-candidate list, pair-list compaction */

@@ -30,8 +30,9 @@ __device__ __forceinline__ void elem_sums(const ElemSums& E, int k0, int e, int 
 // the word at pos[4 j * stride + i], else one word each at
 // pos[(4 j + l) * stride + i].  16 bytes a pair instead of 64 to write and
 // to read, one load instead of four: at wavy 1024 x 1024 / 777 x 777 the
-// positions 0.203 -> 0.173 ms, the assembly 0.316 -> 0.311, the reverse sweep
-// 0.569 -> 0.577 (its gathers wait as before, and unpack).
+// positions 0.203 -> 0.173 ms, the assembly 0.316 -> 0.311 (0.269 since D and M
+// rows are apart), the reverse sweep 0.569 -> 0.577 (its gathers wait as
+// before, and unpack).
 constexpr int POS_PACKED = 256;
 
 __device__ __forceinline__ void store_pos4(int32_t* __restrict__ pos, int64_t stride, int64_t i, int j, int len,
