@@ -346,9 +346,11 @@ int mt_integrate_backward(mt_ctx* ctx, double* D_val, double* M_val, double* gap
 
 /* Counts of the last build and pattern (host; NULL skips, nonzeros 0 before
  * a pattern): candidates found, pairs kept, nonzeros of D and M.
- * Synchronises the stream of the last call only when they have not been read
- * back since (by mt_build_pairs or mt_csr_pattern with count pointers,
- * mt_check, or a getter).  Errors: MT_ESTATE (no build). */
+ * Right after mt_check the counts that it read (no further wait); else it
+ * synchronises the stream of the last call only when they have not been read
+ * back since (by mt_build_pairs or mt_csr_pattern with count pointers, or a
+ * getter).  A replayed graph of the caller's counts anew: mt_check first.
+ * Errors: MT_ESTATE (no build). */
 int mt_get_counts(mt_ctx* ctx, int64_t* n_cand, int64_t* n_pairs, int64_t* nnz_D, int64_t* nnz_M);
 
 /* Copy the counters of the last calls into *st (host).  Synchronises the

@@ -287,15 +287,19 @@ int normals_for_coords(mt_ctx* c, hipStream_t st) {
   return MT_OK;
 }
 
-// The counts of a build (and the nonzeros of its pattern) as read back.
-void set_counts(mt_ctx* c, const DevState& hs) {
+// The counts of a build (and the nonzeros of its pattern) as read back:
+// known to every later call, or (mt_check) only to the next mt_get_counts.
+// A graph of the caller's that is replayed after a check counts anew without
+// a call here, so the getters must not take the check's counts for theirs.
+void set_counts(mt_ctx* c, const DevState& hs, bool known) {
   c->n_cand = hs.n_cand;
   c->n_maybe = hs.n_screened;
   c->n_pairs = hs.n_pairs;
   c->nnz_D = c->have_pattern ? hs.nnz_D : 0;
   c->nnz_M = c->have_pattern ? hs.nnz_M : 0;
   c->grid = hs.grid;
-  c->counts_known = true;
+  c->counts_known = c->counts_known || known;
+  c->counts_checked = !known;
 }
 
 }  // namespace
@@ -306,7 +310,7 @@ int mt::host_counts(mt_ctx* c) {
   DeviceScope ds(c->device);
   DevState hs;
   MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}}, c->last_stream));
-  set_counts(c, hs);
+  set_counts(c, hs, true);
   return MT_OK;
 }
 
@@ -551,6 +555,7 @@ int mt_update_coordinates(mt_ctx* c, int side, const double* x, const double* y,
   if (m.n_nodes > 0 && (!x || !y || !z)) return fail(MT_EINVAL, "mt_update_coordinates: null array");
   m.x = x; m.y = y; m.z = z;
   ++c->coord_gen;
+  c->counts_checked = false;
   return MT_OK;
 }
 
@@ -590,7 +595,7 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
   hipStream_t st = (hipStream_t)stream;
   c->last_stream = st;
   c->have_pairs = c->have_pattern = c->have_master_index = false;
-  c->counts_known = false;
+  c->counts_known = c->counts_checked = false;
   ++c->coord_gen;
   c->side[0].nrm = nullptr;
   const DeviceMesh& S = c->side[0];
@@ -695,7 +700,7 @@ int mt_build_pairs(mt_ctx* c, const mt_capacity* cap_in, void* ws, size_t ws_byt
   if (!n_cand_out && !n_pairs_out) return MT_OK;
   DevStatus h;
   MT_HIP(read_status(c, &h, st));
-  set_counts(c, h.state);
+  set_counts(c, h.state, true);
   if (n_cand_out) *n_cand_out = c->n_cand;
   if (n_pairs_out) *n_pairs_out = c->n_pairs;
   return device_status(h.state, h.counters, false);
@@ -722,13 +727,19 @@ int mt_check(mt_ctx* c) {
   DeviceScope ds(c->device);
   DevStatus h;
   MT_HIP(read_status(c, &h, c->last_stream));
-  set_counts(c, h.state);  // the same wait serves later reads of the counts
+  set_counts(c, h.state, false);
   return device_status(h.state, h.counters, true);
 }
 
 int mt_get_counts(mt_ctx* c, int64_t* n_cand, int64_t* n_pairs, int64_t* nnz_D, int64_t* nnz_M) {
   if (!c) return fail(MT_EINVAL, "mt_get_counts: null");
   if (!c->have_pairs) return fail(MT_ESTATE, "mt_get_counts: no build");
+  if (int rc = ws_live(c)) return rc;
+  if (c->counts_checked) {
+    // those that the check before this call read back, without another wait
+    c->counts_known = true;
+    c->counts_checked = false;
+  }
   if (int rc = host_counts(c)) return rc;
   if (n_cand) *n_cand = c->n_cand;
   if (n_pairs) *n_pairs = c->n_pairs;
@@ -788,7 +799,7 @@ int mt::csr_pattern(mt_ctx* c, int64_t* nnz_D, int64_t* nnz_M, hipStream_t st, b
   if (16 * (int64_t)S.n_el >= (int64_t(1) << 31) || 16 * P >= (int64_t(1) << 31))
     return fail(MT_ECAPACITY, "mt_csr_pattern: more than 2^31 block entries");
   c->have_pattern = false;
-  c->counts_known = false;
+  c->counts_known = c->counts_checked = false;
   const int32_t* np_dev = dev_n_pairs(c);
   PhaseTimer timer(c, MT_T_PATTERN, st);
   if (!c->have_inc[0]) {
@@ -869,7 +880,7 @@ int mt::csr_pattern(mt_ctx* c, int64_t* nnz_D, int64_t* nnz_M, hipStream_t st, b
   if (!nnz_D && !nnz_M) return MT_OK;
   DevState hs;
   MT_HIP(read_back(c, {{&hs, c->state.p, sizeof(hs)}}, st));
-  set_counts(c, hs);
+  set_counts(c, hs, true);
   if (nnz_D) *nnz_D = c->nnz_D;
   if (nnz_M) *nnz_M = c->nnz_M;
   return MT_OK;
@@ -1101,7 +1112,7 @@ void mt::search_replayed(mt_ctx* c, hipStream_t st) {
   // mt_build_pairs (same workspace binding, no read-back)
   c->last_stream = st;
   c->have_master_index = false;
-  c->counts_known = false;
+  c->counts_known = c->counts_checked = false;
   ++c->coord_gen;
   DeviceMesh& S = c->side[0];
   if (c->params.normals == MT_NORMALS_NODAL) {  // recomputed by the graph

@@ -186,6 +186,7 @@ struct mt_ctx {
   bool have_master_index = false;
   bool have_inc[2] = {false, false};  // node incidence of each side (depends on connectivity only)
   bool counts_known = false;  // n_cand .. nnz_M read back since the last build / pattern
+  bool counts_checked = false;  // .. by an mt_check, for the next mt_get_counts alone
   int64_t n_cand = 0, n_maybe = 0, n_pairs = 0, nnz_D = 0, nnz_M = 0;
   mt::Grid grid{};
 
