@@ -426,9 +426,10 @@ int mt_batch_workspace_size(mt_batch* b, size_t* bytes);
 /* Build the work queue and per-instance tables in the caller's workspace
  * `ws` of ws_bytes >= mt_batch_workspace_size bytes (256-byte aligned; kept
  * until the next mt_batch_build or mt_batch_destroy).  `tuning` may be
- * NULL.  Synchronises.  Errors: MT_EINVAL (instances differ in rule, basis
- * or normal field; bad workspace), MT_ECAPACITY (workspace too small),
- * MT_EUNSUPPORTED (an instance set to element-based integration). */
+ * NULL.  Synchronises the device (calls of this batch still running on any
+ * stream read the tables it writes).  Errors: MT_EINVAL (instances differ in
+ * rule, basis or normal field; bad workspace), MT_ECAPACITY (workspace too
+ * small), MT_EUNSUPPORTED (an instance set to element-based integration). */
 int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t ws_bytes, void* stream);
 /* Forward for every instance: D_val[i], M_val[i], gap[i] are host arrays of
  * K device pointers (outputs as for mt_integrate).  use_graph != 0 captures

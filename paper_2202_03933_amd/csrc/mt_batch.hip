@@ -723,7 +723,9 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
   b->n_ritems_s = (int)rs.size();
   b->n_ritems_sm = (int)rsm.size();
   b->n_eitems = (int)es.size();
-  B_HIP(hipStreamSynchronize(st));
+  // the tables below may still be read by a forward or backward of this batch
+  // on any stream, also one replayed from a graph of the caller's
+  B_HIP(hipDeviceSynchronize());
   if (!rs.empty()) B_HIP(hipMemcpy(b->d_ritems_s.p, rs.data(), sizeof(WorkItem) * rs.size(), hipMemcpyHostToDevice));
   if (!rsm.empty())
     B_HIP(hipMemcpy(b->d_ritems_sm.p, rsm.data(), sizeof(WorkItem) * rsm.size(), hipMemcpyHostToDevice));
