@@ -659,7 +659,9 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
   if (t.bucket <= 0) t.bucket = 4 * 64;
   // whole tiles: the sums per slave element run tile by tile whatever the
   // item, so the values do not depend on the tuning
-  t.bucket = (std::max(t.bucket, MIN_BUCKET) + TILE_PAIRS - 1) / TILE_PAIRS * TILE_PAIRS;
+  constexpr int MAX_BUCKET = INT32_MAX / TILE_PAIRS * TILE_PAIRS;
+  t.bucket = std::min(std::max(t.bucket, MIN_BUCKET), MAX_BUCKET);
+  t.bucket = (t.bucket + TILE_PAIRS - 1) / TILE_PAIRS * TILE_PAIRS;
   b->tune = t;
 
   b->h_inst.assign(b->ctxs.size(), BatchInst{});
