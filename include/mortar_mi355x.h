@@ -467,8 +467,8 @@ int mt_batch_backward(mt_batch* b, const double* const* W_D, const double* const
  * again.  Coordinates moved in place
  * are read by the replay.  In the graph no instance's pattern uses the
  * instance's internal streams, so the pairs-by-master index is built by the
- * first backward after it.  Errors: MT_EINVAL (use_graph on the null
- * stream), MT_ESTATE (an instance with no workspace of its own bound: never
+ * mt_batch_build or backward after it.  Errors: MT_EINVAL (use_graph on the
+ * null stream), MT_ESTATE (an instance with no workspace of its own bound: never
  * built, or built by mt_build_pairs_static), MT_EHIP (capture or
  * instantiation failed; the instances then hold no pair list), errors of the
  * per-instance calls. */

@@ -669,8 +669,12 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
   std::vector<WorkItem> rs, rsm, es;
   for (size_t i = 0; i < b->ctxs.size(); ++i) {
     mt_ctx* c = b->ctxs[i];
-    if (b->nodal) {
-      int rc2 = ensure_normals(c, st);
+    {
+      // the index here and not in the first backward, which may be recorded
+      // in a graph: its launches would replay each time, and a recording that
+      // is dropped would leave the context without what it counts as built
+      int rc2 = ensure_master_index(c, st);
+      if (!rc2 && b->nodal) rc2 = ensure_normals(c, st);
       if (rc2) return rc2;
     }
     const DeviceMesh& S = c->side[0];
@@ -794,18 +798,6 @@ int mt_batch_backward(mt_batch* b, const double* const* W_D, const double* const
     b->h_inst[i].gXm = gXm[i];
   }
   int rc = sync_instances(b, st);
-  // the pairs-by-master index of every instance that has none yet (its pattern
-  // was built without the internal streams), outside any graph of this call
-  // (recorded in a capture of the caller's, it is there once that replays
-  // and not before: not taken as built)
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  B_HIP(hipStreamIsCapturing(st, &cap));
-  for (size_t i = 0; i < b->ctxs.size() && rc == MT_OK; ++i) {
-    mt_ctx* c = b->ctxs[i];
-    if (c->have_master_index) continue;
-    rc = ensure_master_index(c, st);
-    if (cap != hipStreamCaptureStatusNone) c->have_master_index = false;
-  }
   if (rc) return rc;
   rc = upload_inst(b, st);
   if (rc) return rc;

@@ -484,7 +484,7 @@ int ws_live(mt_ctx* c);
 // mt_build_pairs into the bound workspace and capacities, then mt_csr_pattern,
 // without read-back (and without phase timers) on stream st; without `fork`
 // every kernel on st (none on the context's internal streams; the
-// pairs-by-master index is then built by the first backward).
+// pairs-by-master index is then built by mt_batch_build or a backward).
 int search_no_wait(mt_ctx* c, hipStream_t st, bool fork = true);
 // The host side of search_no_wait(c, st, false) for a replay of a graph
 // captured from it: the flags and generations that call sets.
