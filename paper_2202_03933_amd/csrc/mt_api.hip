@@ -394,8 +394,8 @@ int enqueue_assemble(mt_ctx* c, double* D_val, double* M_val, double* gap, hipSt
   PhaseTimer t(c, MT_T_ASSEMBLE, st);
   MT_HIP(launch_assemble(c->inc_off.as<int32_t>(), c->inc_list.as<int32_t>(), S.n_nodes, c->pair_off.as<int32_t>(),
                          c->D_rowptr.as<int32_t>(), c->M_rowptr.as<int32_t>(), c->posD.as<int32_t>(),
-                         c->posM.as<int32_t>(), c->blk.as<double>(), c->cap.pairs, fwd_sums(c), D_val, M_val, gap,
-                         st));
+                         c->posM.as<int32_t>(), c->blk.as<double>(), c->cap.pairs, fwd_sums(c), c->side[1].n_el, D_val,
+                         M_val, gap, st));
   return MT_OK;
 }
 

@@ -447,11 +447,10 @@ __global__ __launch_bounds__(BS) void k_positions(unsigned d_blocks, int32_t n_s
 // 777 x 777, 0.23 ms at the rate of a copy) bound large steps, the chain of
 // dependent loads small ones.  One thread for both rows, 32 entries each:
 // 0.310 ms there; D and M apart, ROW_ACC entries each: 0.269 ms, and the whole
-// step of 181 x 181 / 141 x 141 236 -> 228 us.  (Where the masters are 1.6
-// times finer and rows of 27 to 32 columns take two sweeps, 512 x 512 /
-// 821 x 821, the whole step is 2.26 ms instead of 2.23.)
+// step of 181 x 181 / 141 x 141 236 -> 228 us.  ACC: ROW_ACC or ROW_ACC_FINE.
 constexpr int AB = 128;  // block of the assembly kernel
 
+template <int ACC>
 __global__ __launch_bounds__(AB) void k_assemble(const int32_t* __restrict__ inc_off,
                                                   const int32_t* __restrict__ inc_list, int32_t n,
                                                   const int32_t* __restrict__ pair_off,
@@ -461,15 +460,15 @@ __global__ __launch_bounds__(AB) void k_assemble(const int32_t* __restrict__ inc
                                                   const int32_t* __restrict__ posM, const double* __restrict__ blk,
                                                   int64_t stride, ElemSums eblk, double* __restrict__ D_val,
                                                   double* __restrict__ M_val, double* __restrict__ gap) {
-  __shared__ double acc[ROW_ACC * AB];
+  __shared__ double acc[ACC * AB];
   const int a = xcd_tile(blockIdx.x, gridDim.x) * AB + threadIdx.x;
   if (a >= n) return;
   if (blockIdx.y == 0)
     assemble_row<false>(a, inc_off, inc_list, pair_off, D_rowptr, posD, blk, stride, eblk, D_val, gap,
-                        acc + threadIdx.x, AB, ROW_ACC);
+                        acc + threadIdx.x, AB, ACC);
   else
     assemble_row<true>(a, inc_off, inc_list, pair_off, M_rowptr, posM, blk, stride, eblk, M_val, gap,
-                       acc + threadIdx.x, AB, ROW_ACC);
+                       acc + threadIdx.x, AB, ACC);
 }
 
 // Nodal gradients of both sides in one launch: the first s_blocks workgroups
@@ -717,9 +716,10 @@ int pattern_elem_list() { return EL; }
 hipError_t launch_assemble(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes, const int32_t* pair_off,
                            const int32_t* D_rowptr, const int32_t* M_rowptr, const int32_t* posD,
                            const int32_t* posM, const double* blk, int64_t stride, const ElemSums& eblk,
-                           double* D_val, double* M_val, double* gap, hipStream_t s) {
+                           int32_t n_m_el, double* D_val, double* M_val, double* gap, hipStream_t s) {
   if (n_nodes == 0) return hipSuccess;
-  k_assemble<<<dim3(xcd_grid((unsigned)((n_nodes + AB - 1) / AB)), 2), AB, 0, s>>>(
+  auto* k = fine_masters(eblk.n_el, n_m_el) ? k_assemble<ROW_ACC_FINE> : k_assemble<ROW_ACC>;
+  k<<<dim3(xcd_grid((unsigned)((n_nodes + AB - 1) / AB)), 2), AB, 0, s>>>(
       inc_off, inc_list, n_nodes, pair_off, D_rowptr, M_rowptr, posD, posM, blk, stride, eblk, D_val, M_val, gap);
   return hipGetLastError();
 }

@@ -207,19 +207,20 @@ __global__ __launch_bounds__(BSZ) __attribute__((amdgpu_waves_per_eu(2))) void k
 
 // Row phases: one block per item of ROWS_PER_ITEM rows of one instance.
 // (D rows and gaps by the workgroups with blockIdx.y = 0, M rows by the others.)
+template <int ACC>
 __global__ __launch_bounds__(ROWS_PER_ITEM) void k_batch_assemble(const BatchInst* __restrict__ inst,
                                                                    const WorkItem* __restrict__ items) {
-  __shared__ double acc[ROW_ACC * ROWS_PER_ITEM];
+  __shared__ double acc[ACC * ROWS_PER_ITEM];
   const WorkItem w = items[blockIdx.x];
   const int a = w.begin + threadIdx.x;
   if (a >= w.end) return;
   const BatchInst& I = inst[w.inst];
   if (blockIdx.y == 0)
     assemble_row<false>(a, I.inc_off, I.inc_list, I.pair_off, I.D_rowptr, I.posD, I.blk, I.stride, I.eblk, I.D_val,
-                        I.gap, acc + threadIdx.x, ROWS_PER_ITEM, ROW_ACC);
+                        I.gap, acc + threadIdx.x, ROWS_PER_ITEM, ACC);
   else
     assemble_row<true>(a, I.inc_off, I.inc_list, I.pair_off, I.M_rowptr, I.posM, I.blk, I.stride, I.eblk, I.M_val,
-                       I.gap, acc + threadIdx.x, ROWS_PER_ITEM, ROW_ACC);
+                       I.gap, acc + threadIdx.x, ROWS_PER_ITEM, ACC);
 }
 
 __global__ __launch_bounds__(ROWS_PER_ITEM) void k_batch_grad_rows(const BatchInst* __restrict__ inst,
@@ -304,6 +305,7 @@ struct mt_batch {
   int nq = 7;
   bool dual = false;
   bool nodal = false;
+  bool fine = false;  // fine_masters of all instances together
   std::vector<mt::BatchInst> h_inst;
   std::vector<int64_t> pattern_gen;  // each instance's pattern generation at mt_batch_build
   mt::BatchInst* pinned = nullptr;
@@ -439,7 +441,8 @@ int launch_fwd_all(mt_batch* b, hipStream_t st) {
   int rc = launch_fwd(b, st);
   if (rc) return rc;
   if (b->n_ritems_s) {
-    k_batch_assemble<<<dim3((unsigned)b->n_ritems_s, 2), ROWS_PER_ITEM, 0, st>>>(b->d_inst.as<BatchInst>(), b->d_ritems_s.as<WorkItem>());
+    auto* k = b->fine ? k_batch_assemble<ROW_ACC_FINE> : k_batch_assemble<ROW_ACC>;
+    k<<<dim3((unsigned)b->n_ritems_s, 2), ROWS_PER_ITEM, 0, st>>>(b->d_inst.as<BatchInst>(), b->d_ritems_s.as<WorkItem>());
     B_HIP(hipGetLastError());
   }
   return MT_OK;
@@ -667,6 +670,7 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
   b->h_inst.assign(b->ctxs.size(), BatchInst{});
   b->pattern_gen.assign(b->ctxs.size(), 0);
   std::vector<WorkItem> rs, rsm, es;
+  int64_t n_s_el = 0, n_m_el = 0;
   for (size_t i = 0; i < b->ctxs.size(); ++i) {
     mt_ctx* c = b->ctxs[i];
     {
@@ -679,6 +683,8 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
     }
     const DeviceMesh& S = c->side[0];
     const DeviceMesh& M = c->side[1];
+    n_s_el += S.n_el;
+    n_m_el += M.n_el;
     BatchInst& I = b->h_inst[i];
     b->pattern_gen[i] = c->pattern_gen;
     I.S = MeshPtrs{S.x, S.y, S.z, S.conn, S.nrm};
@@ -726,6 +732,7 @@ int mt_batch_build(mt_batch* b, const mt_batch_tuning* tuning, void* ws, size_t 
       for (int r = 0; r < S.n_el; r += ROWS_PER_ITEM)
         es.push_back({(int32_t)i, r, std::min(S.n_el, r + ROWS_PER_ITEM), 0});
   }
+  b->fine = fine_masters(n_s_el, n_m_el);
   b->n_ritems_s = (int)rs.size();
   b->n_ritems_sm = (int)rsm.size();
   b->n_eitems = (int)es.size();

@@ -412,7 +412,8 @@ int pattern_elem_list();
 hipError_t launch_assemble(const int32_t* inc_off, const int32_t* inc_list, int32_t n_nodes,
                            const int32_t* pair_off, const int32_t* D_rowptr, const int32_t* M_rowptr,
                            const int32_t* posD, const int32_t* posM, const double* blk, int64_t blk_stride,
-                           const ElemSums& eblk, double* D_val, double* M_val, double* gap, hipStream_t s);
+                           const ElemSums& eblk, int32_t n_m_el, double* D_val, double* M_val, double* gap,
+                           hipStream_t s);
 // Nodal gradients from the staged components; the pairs of master
 // element m are the positions mstart[m] .. mstart[m + 1].
 hipError_t launch_grad_nodes(const int32_t* inc_off, const int32_t* inc_list, int32_t n_s_nodes,

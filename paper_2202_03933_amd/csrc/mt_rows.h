@@ -228,9 +228,16 @@ __device__ __forceinline__ void assemble_row(int a, const int32_t* __restrict__ 
 }
 
 // Accumulator entries per thread of the assembly kernels: M rows of 5 x 5
-// master nodes fit, and LDS leaves room for 12 wavefronts on a CU (32 entries:
-// 10).
+// master nodes fit, and LDS leaves room for 12 wavefronts on a CU; where the
+// masters are finer, rows of 6 x 6 (8 wavefronts).  Assembly alone, wavy,
+// 26 -> 36 entries, by the ratio of elements per side: 0.76 270 -> 295 us
+// (1024 slave elements a side), 1.0 39.7 -> 42.1, 1.2 57.9 -> 58.5, 1.3 67.6
+// -> 66.7, 1.4 75.7 -> 74.7, 1.5 101 -> 84, 1.6 154 -> 94, 2.0 313 -> 156
+// (400 a side; with 32 entries 102, 136 and 276 at the last three): the line
+// at 1.26 in this ratio, 1.6 in the elements.
 constexpr int ROW_ACC = 26;
+constexpr int ROW_ACC_FINE = 36;
+inline bool fine_masters(int64_t n_s_el, int64_t n_m_el) { return 10 * n_m_el > 16 * n_s_el; }
 
 // Sum over the flat pair sequence of R of the three components
 // gpair[(3 j + d) * stride + p], d = 0, 1, 2, in sequence order.
