@@ -293,7 +293,6 @@ int normals_for_coords(mt_ctx* c, hipStream_t st) {
 // a call here, so the getters must not take the check's counts for theirs.
 void set_counts(mt_ctx* c, const DevState& hs, bool known) {
   c->n_cand = hs.n_cand;
-  c->n_maybe = hs.n_screened;
   c->n_pairs = hs.n_pairs;
   c->nnz_D = c->have_pattern ? hs.nnz_D : 0;
   c->nnz_M = c->have_pattern ? hs.nnz_M : 0;

@@ -121,16 +121,8 @@ __device__ __forceinline__ void dual_adjoint(const double Xs[4][3], const double
         vb[k] += jb10 * d1[k] + jb11 * d2[k];
       }
     }
-  double nb[8][3];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    nb[k][0] = ub[k];
-    nb[k][1] = vb[k];
-    nb[k][2] = 0.0;
-    nb[4 + k][0] = nb[4 + k][1] = nb[4 + k][2] = 0.0;
-  }
-  double gsb[4][3], gmb[4][3];
-  projection_adjoint(Xs, Xs, ns, nb, gsb, gmb, n0b);
+  double gsb[4][3];
+  projection_adjoint(Xs, ns, ub, vb, gsb, n0b);
 #pragma unroll
   for (int k = 0; k < 4; ++k)
 #pragma unroll

@@ -69,8 +69,6 @@ struct PrepReduce {
   unsigned long long edge_bits;   // longest slave element edge
   unsigned long long lo_key[3];   // node bounding box, order-preserving keys
   unsigned long long hi_key[3];
-  int32_t bad_index;              // connectivity out of range
-  int32_t pad;
 };
 
 // Device counters of the pair pipeline (hist: filled on demand from the
@@ -187,7 +185,7 @@ struct mt_ctx {
   bool have_inc[2] = {false, false};  // node incidence of each side (depends on connectivity only)
   bool counts_known = false;  // n_cand .. nnz_M read back since the last build / pattern
   bool counts_checked = false;  // .. by an mt_check, for the next mt_get_counts alone
-  int64_t n_cand = 0, n_maybe = 0, n_pairs = 0, nnz_D = 0, nnz_M = 0;
+  int64_t n_cand = 0, n_pairs = 0, nnz_D = 0, nnz_M = 0;
   mt::Grid grid{};
 
   // element preparation
@@ -296,7 +294,8 @@ hipError_t scan_exclusive2(const int32_t* in, int32_t* out, const int32_t* in2, 
 // Workgroup cap of scans that run beside the pair kernels.
 constexpr int64_t SCAN_BLOCKS_BESIDE = 256;
 // The same over a count the device holds (*n_dev <= cap): out[0..*n_dev],
-// out[*n_dev] = total; what lies behind is not written.
+// out[*n_dev] = total; what lies behind is undefined (the last tile may write
+// on to out[cap - 1]).
 hipError_t scan_exclusive_dev(const int32_t* in, int32_t* out, const int32_t* n_dev, int64_t cap, const Buf& tmp,
                               hipStream_t s, const ScanStage& stage = ScanStage{});
 // Copies of n[q] int32 from src[q] to dst[q] (device memory; dst null or n 0:

@@ -4,7 +4,9 @@
 //
 // The clip polygon of a pair is computed once (k_pair_poly, in LDS) and
 // stored structure-of-arrays in HBM with each vertex's provenance; the
-// integration and its reverse mode read it from there and need no LDS.
+// integration and its reverse mode read it from there, and use LDS only for
+// what they need again after the quadrature (Stash) and for the sums per
+// slave element.
 //
 // Quadrature works in the monomial basis m(xi) = (1, xi1, xi2, xi1 xi2) of
 // the bilinear element: N(xi) = C m(xi) with C = H / 4,
@@ -165,10 +167,9 @@ __device__ __forceinline__ double rcp_nr(double d) {
   return r;
 }
 
-// Map coefficients (c, e1, e2, f) of a projected quad and the reciprocal
-// determinant of its Jacobian at xi = 0.
+// Map coefficients (c, e1, e2, f) of a projected quad.
 struct QMap {
-  double cu, cv, e1u, e1v, e2u, e2v, fu, fv, r0;
+  double cu, cv, e1u, e1v, e2u, e2v, fu, fv;
 };
 
 __device__ __forceinline__ QMap qmap(const V2 X[4]) {
@@ -182,7 +183,6 @@ __device__ __forceinline__ QMap qmap(const V2 X[4]) {
   m.e2v = 0.25 * ((X[2].v - X[1].v) + (X[3].v - X[0].v));
   m.fu = 0.25 * ((X[0].u - X[1].u) + (X[2].u - X[3].u));
   m.fv = 0.25 * ((X[0].v - X[1].v) + (X[2].v - X[3].v));
-  m.r0 = rcp_nr(m.e1u * m.e2v - m.e2u * m.e1v);
   return m;
 }
 
@@ -808,36 +808,29 @@ __device__ __forceinline__ void vertex_adjoint(uint8_t lab, double X, double Y, 
   cbm[7] += xb12 * pb[1];
 }
 
-// Adjoint of the projection (u, v, h) = ((X - x0).t1, (X - x0).t2,
-// (X - x0).n0) of the 8 nodes (slave 0..3, master 4..7) and of the slave
-// frame (x0, n0 = g1 x g2 / |g1 x g2|, t1 = g1 / |g1|, t2 = n0 x t1):
-// given nb[k] = (ubar, vbar, hbar) of node k, writes the coordinate
-// gradients Xsb (slave) and Xmb (master).  With the continuous normal field
-// (ns, the element's plane normal: n0 = ns, t1 = the part of g1 orthogonal to
-// n0, normalised) the gradient with respect to n0 is added to n0b instead.
-__device__ __forceinline__ void projection_adjoint(const double Xs[4][3], const double Xm[4][3], const double* ns,
-                                                   const double nb[8][3], double Xsb[4][3], double Xmb[4][3],
-                                                   double n0b_out[3]) {
+// Adjoint of the in-plane projection (u, v) = ((X - x0).t1, (X - x0).t2) of
+// the slave nodes and of the slave frame (x0, n0 = g1 x g2 / |g1 x g2|,
+// t1 = g1 / |g1|, t2 = n0 x t1): given ub, vb of the nodes, writes their
+// coordinate gradients Xsb.  With the continuous normal field (ns, the
+// element's plane normal: n0 = ns, t1 = the part of g1 orthogonal to n0,
+// normalised) the gradient with respect to n0 is added to n0b instead.
+__device__ __forceinline__ void projection_adjoint(const double Xs[4][3], const double* ns, const double ub[4],
+                                                   const double vb[4], double Xsb[4][3], double n0b_out[3]) {
 #pragma clang fp contract(fast)
   double f[12];
   slave_frame_p(Xs, ns, f);
   double x0b[3] = {0, 0, 0}, t1b[3] = {0, 0, 0}, t2b[3] = {0, 0, 0}, n0b[3] = {0, 0, 0};
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const double* X = k < 4 ? Xs[k] : Xm[k - 4];
-    const double ub = nb[k][0], vbb = nb[k][1], hb = nb[k][2];
-    double* Xb = k < 4 ? Xsb[k] : Xmb[k - 4];
+  for (int k = 0; k < 4; ++k)
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      const double dd = X[d] - f[d];
-      const double gg = ub * f[6 + d] + vbb * f[9 + d] + hb * f[3 + d];
-      Xb[d] = gg;
+      const double dd = Xs[k][d] - f[d];
+      const double gg = ub[k] * f[6 + d] + vb[k] * f[9 + d];
+      Xsb[k][d] = gg;
       x0b[d] -= gg;
-      t1b[d] += ub * dd;
-      t2b[d] += vbb * dd;
-      n0b[d] += hb * dd;
+      t1b[d] += ub[k] * dd;
+      t2b[d] += vb[k] * dd;
     }
-  }
   // t2 = n0 x t1
   const double* n0 = f + 3;
   const double* t1 = f + 6;

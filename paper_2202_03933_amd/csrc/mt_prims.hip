@@ -11,7 +11,8 @@ constexpr int SCAN_IPT = 8;
 constexpr int SCAN_TILE = SCAN_BS * SCAN_IPT;
 
 // n_dev (optional): a count the device holds, at most n; entries from it on
-// count as zero, and the outputs behind out[*n_dev] are left alone.
+// count as zero, and the outputs behind out[*n_dev] are undefined (the tile
+// that holds it is written whole, up to out[n - 1]).
 template <class T>
 __device__ __forceinline__ int64_t live_count(int64_t n, const int32_t* n_dev) {
   if (!n_dev) return n;

@@ -37,15 +37,6 @@ __device__ __forceinline__ T wave_max(T x) {
   }
   return x;
 }
-template <class T>
-__device__ __forceinline__ T wave_min(T x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const T y = __shfl_xor(x, d, 64);
-    x = x < y ? x : y;
-  }
-  return x;
-}
 
 // Element preparation: bounding boxes, the grid reductions (largest box
 // extent, longest slave edge, bounding box of all element boxes), for slave
