@@ -198,9 +198,15 @@ __device__ __forceinline__ QMap qmap(const V2 X[4]) {
 // det J = J0 D.  (b1 + D) / 2 and (b2 + D) / 2 are the determinants at
 // (0, xi2) and (xi1, 0) over J0, so on a convex quad nothing cancels.
 // The vectors are kept times 2 / J0: t1, t2 come out doubled.
+//
+// On a convex quad (the determinants at its corners, J0 (1 +- al +- be), have
+// the sign of J0) the root with that sign is the only one in the element.
+// Where a corner is reentrant the map folds inside the element, both roots
+// can lie in it, and the one meant is the one that Newton's method reaches
+// from the centre: a2 is then NaN, and no test lets the closed form through.
 struct IMap {
   double cu, cv, e1u, e1v, e2u, e2v, fu, fv;  // c; 2 e1 / J0, 2 e2 / J0, 2 f / J0
-  double a2;                                  // 2 al
+  double a2;                                  // 2 al (convex_a2)
   double j0;                                  // J0
 };
 
@@ -208,6 +214,13 @@ struct IMap {
 struct SMap {
   double e1u, e1v, e2u, e2v, fu, fv, a2, j0;
 };
+
+// 2 al from e1, e2 as they are and f times 2 / J0.
+__device__ __forceinline__ double convex_a2(double e1u, double e1v, double e2u, double e2v, double fu, double fv) {
+#pragma clang fp contract(fast)
+  const double a2 = e1u * fv - e1v * fu, b2 = e2u * fv - e2v * fu;
+  return fabs(a2) + fabs(b2) < 2.0 ? a2 : __builtin_nan("");
+}
 
 // Node k of a quad from its scaled map.
 __device__ __forceinline__ V2 map_node(const IMap& m, int k) {
@@ -256,7 +269,8 @@ template <class Map>
 __device__ __forceinline__ void inverse_newton(const Map& m, const IPoint& p, double tol, int maxit, double& x1,
                                                double& x2, double& rd, unsigned& noconv) {
 #pragma clang fp contract(fast)
-  const double al = 0.5 * m.a2, be = 0.25 * m.j0 * (m.e2u * m.fv - m.e2v * m.fu);
+  const double h = 0.25 * m.j0;
+  const double al = h * (m.e1u * m.fv - m.e1v * m.fu), be = h * (m.e2u * m.fv - m.e2v * m.fu);
   const double t1 = 0.5 * p.t1, t2 = 0.5 * p.t2;
   x1 = t1;
   x2 = t2;
@@ -304,13 +318,14 @@ constexpr double INV_MIN = 0x1p-10;
 // Inverse bilinear maps of point p on the slave quad (a) and the master quad
 // (b), and rda, rdb = J0 / det J there.  Closed form when kp.direct (a
 // tolerance no tighter than its rounding error and at least the default
-// number of steps allowed): 54 FP64 instructions and three estimates for
+// number of steps allowed) and both quads are convex: 54 FP64 instructions and three estimates for
 // both maps, where Newton's interleaved loop took about 35 per map and step
 // and a wavefront as many steps as its slowest lane.  Wavy 1024 x 1024 /
 // 777 x 777 (3.24M pairs, alone): forward 0.60 -> 0.38 ms, reverse sweep
 // 0.95 -> 0.76 ms; 64 batched interfaces (13M pairs): forward and backward
-// 9.35 -> 6.79 ms.  Newton's method for tighter settings and for points near
-// a fold of the map.  Maps that do not converge are counted in noconv.
+// 9.35 -> 6.79 ms.  Newton's method for tighter settings, other quads and
+// points near a fold of the map.  Maps that do not converge are counted in
+// noconv.
 __device__ __forceinline__ void inverse2(const SMap& A, const IMap& B, double pu, double pv, const KParams& kp,
                                          double& a1, double& a2, double& b1, double& b2, double& rda, double& rdb,
                                          unsigned& noconv) {
@@ -447,7 +462,7 @@ __device__ __forceinline__ void pair_setup(const double Xs[4][3], const double X
     ms.e2v = e2v * r;
     ms.fu = fu * r;
     ms.fv = fv * r;
-    ms.a2 = e1u * ms.fv - e1v * ms.fu;
+    ms.a2 = convex_a2(e1u, e1v, e2u, e2v, ms.fu, ms.fv);
   }
   ou = dot3(C[0], R[0]);
   ov = dot3(C[0], R[1]);
@@ -470,7 +485,7 @@ __device__ __forceinline__ void pair_setup(const double Xs[4][3], const double X
   mm.e2v = v[2] * r;
   mm.fu = u[3] * r;
   mm.fv = v[3] * r;
-  mm.a2 = u[1] * mm.fv - v[1] * mm.fu;
+  mm.a2 = convex_a2(u[1], v[1], u[2], v[2], mm.fu, mm.fv);
 }
 
 // Values a lane needs again after the quadrature, kept in LDS meanwhile
