@@ -124,9 +124,27 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   A.take(status, sizeof(DevStatus));
   c->counters = Buf{status.p, sizeof(Counters)};
   c->state = Buf{status.p ? static_cast<char*>(status.p) + offsetof(DevStatus, state) : nullptr, sizeof(DevState)};
+  // scratch of one call each, in one place: of the search, of the pattern and
+  // of the reverse sweep (no call leaves anything there for a later one)
+  const size_t sums = 8 * (size_t)elem_sums_stride((int64_t)ns, (int64_t)P);
+  const size_t at = A.off;
+  size_t end = 0;
+  auto over = [&A, &end, at] {
+    end = std::max(end, A.off);
+    A.off = at;
+  };
   A.take(c->box_s, 48 * ns);
-  A.take(c->box_m, 48 * nm);
   A.take(c->sdata, 8 * SD_N * ns);
+  A.take(c->cand_tmp, 4 * (size_t)cand_tmp_per_slave() * ns);
+  over();
+  A.take(c->pat_keep, 4 * (size_t)pattern_keep_per_row() * nsn);
+  A.take(c->pat_ecnt, 4 * ns);
+  A.take(c->pat_elist, 4 * (size_t)pattern_elem_list() * ns);
+  over();
+  A.take(c->egrad, (nodal ? BWD_SUMS_NODAL : BWD_SUMS) * sums);
+  over();
+  A.off = end;
+  A.take(c->box_m, 48 * nm);
   A.take(c->mdata, 96 * nm);
   A.take(c->prep_part, 72 * (size_t)(prep_blocks(S.n_el) + prep_blocks(M.n_el)));
   for (Buf* b : {&c->mcell, &c->mrank, &c->vals}) A.take(*b, 4 * nm);
@@ -135,10 +153,9 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   A.take(c->sbox, 48 * nm);
   A.take(c->qbox, 16 * nm);
   A.take(c->scan_tmp, scan);
-  A.take(c->aux_scan, scan);
+  A.take(c->aux_scan, sizeof(int32_t) * (size_t)scan_tmp_elems((int64_t)nm));  // (the pairs-by-master index)
   A.take(c->cand_cnt, 4 * (ns + 1));
   A.take(c->cand_off, 4 * (ns + 1));
-  A.take(c->cand_tmp, 4 * (size_t)cand_tmp_per_slave() * ns);
   A.take(c->cand_s, 4 * C);
   A.take(c->cand_m, 4 * C);
   A.take(c->cand_nv, C);
@@ -160,9 +177,6 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   A.take(c->inc_list, 16 * ns);
   for (Buf* b : {&c->minc_cnt, &c->minc_off, &c->minc_cur}) A.take(*b, 4 * (nmn + 1));
   A.take(c->minc_list, 16 * nm);
-  A.take(c->pat_keep, 4 * (size_t)pattern_keep_per_row() * nsn);
-  A.take(c->pat_ecnt, 4 * ns);
-  A.take(c->pat_elist, 4 * (size_t)pattern_elem_list() * ns);
   for (Buf* b : {&c->D_cnt, &c->M_cnt, &c->D_rowptr, &c->M_rowptr}) A.take(*b, 4 * (nsn + 1));
   A.take(c->D_col, 64 * ns);
   A.take(c->M_col, 64 * P);
@@ -178,11 +192,9 @@ void layout(mt_ctx* c, const mt_capacity& cap, Arena& A) {
   } else {
     for (Buf* b : {&c->nrm_node, &c->nrm_el, &c->nrm_sb, &c->nrm_ub, &c->nrm_cg}) *b = Buf{};
   }
-  const size_t sums = 8 * (size_t)elem_sums_stride((int64_t)ns, (int64_t)P);
   A.take(c->blk, 128 * P);
   A.take(c->eblk, FWD_SUMS * sums);
   A.take(c->gpair, 96 * P);
-  A.take(c->egrad, (nodal ? BWD_SUMS_NODAL : BWD_SUMS) * sums);
   A.take(c->mp_cnt, 8 * (nm + 1));
   A.take(c->mp_off, 4 * (nm + 1));
   A.take(c->mp_vals, 4 * P);
